@@ -66,6 +66,7 @@ enum : int32_t {
   ST_SINGULAR = 2,    // cross-covariance of rank < 2
   ST_SCALE = 4,       // pose scale outside [1e-6, 1e6]
   ST_DEGENERATE = 8,  // a cloud with zero variance
+  ST_STALLED = 16,    // the one-launch iteration loop gave up waiting (its blocks were not resident together)
 };
 
 // Row slot layout of the per-block wrench partials.
@@ -225,38 +226,182 @@ SGR_HDI bool kabsch_rot(const double C[9], double R[9], double* Vwarm = nullptr)
   return true;
 }
 
-// ------------------------------------------------------------- reductions
-__device__ inline double wave_sum(double x) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-  return x;
+// Reciprocal and reciprocal square root of a positive double: about 28 bits
+// on the device (the hardware estimates), full precision on the host.
+SGR_HDI double rough_rcp(double x) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return __builtin_amdgcn_rcp(x);
+#else
+  return 1.0 / x;
+#endif
+}
+SGR_HDI double rough_rsqrt(double x) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return __builtin_amdgcn_rsq(x);
+#else
+  return 1.0 / sqrt(x);
+#endif
 }
 
-__device__ inline float wave_sum_f(float x) {
+// Kabsch rotation of a well-conditioned C with positive determinant: then R
+// = V U^T is the transpose of the orthogonal polar factor of C, the limit of
+// Newton's iteration X <- (g X + X^-T / g) / 2 from X = C, with the scaling
+// g = (|X^-1| / |X|)^(1/2) in its first two steps (Higham, SIAM J. Sci. Stat.
+// Comput. 7, 1986).  X^-T is the cofactor matrix over the determinant, so a
+// step is about 45 operations and one reciprocal; the Jacobi SVD of
+// kabsch_rot is a chain of some thirty dependent divisions and square roots
+// (update_kernel: 7.7 us with it, 4.9 us so, on one thread).  C's own scale
+// and the value of g need no accuracy.  From the second step on no singular
+// value is below 1, so det - 1 bounds each one's distance from 1, and the
+// step taken at det - 1 < 1e-8 leaves its square, below the rounding of a
+// double.  Returns false, leaving R unset, when the determinant of C scaled
+// to Frobenius norm sqrt(3) is below 1/64 (a flat, singular or reflected C)
+// or not finite: the caller then takes kabsch_rot.
+SGR_HDI bool polar_rot(const double C[9], double R[9]) {
+  double n2 = 0.0;
+  for (int e = 0; e < 9; ++e) n2 += C[e] * C[e];
+  if (!(n2 > 1e-200 && n2 < 1e200)) return false;
+  const double sc = 1.7320508075688772 * rough_rsqrt(n2);
+  double X[9];
+  for (int e = 0; e < 9; ++e) X[e] = C[e] * sc;
+  for (int it = 0; it < 16; ++it) {
+    const double K[9] = {X[4] * X[8] - X[5] * X[7], X[5] * X[6] - X[3] * X[8], X[3] * X[7] - X[4] * X[6],
+                         X[2] * X[7] - X[1] * X[8], X[0] * X[8] - X[2] * X[6], X[1] * X[6] - X[0] * X[7],
+                         X[1] * X[5] - X[2] * X[4], X[2] * X[3] - X[0] * X[5], X[0] * X[4] - X[1] * X[3]};
+    const double det = X[0] * K[0] + X[1] * K[1] + X[2] * K[2];
+    if (it == 0 && !(det >= 1.0 / 64.0)) return false;
+    double rd = rough_rcp(det);
+    rd = rd + rd * (1.0 - det * rd);
+    rd = rd + rd * (1.0 - det * rd);
+    double a = 0.5, h = 0.5 * rd;
+    if (it < 2) {
+      double x2 = 0.0, k2 = 0.0;
+      for (int e = 0; e < 9; ++e) {
+        x2 += X[e] * X[e];
+        k2 += K[e] * K[e];
+      }
+      const double q = k2 * rd * rd * rough_rcp(x2);  // (|X^-1| / |X|)^2 = g^4
+      const double g2 = q * rough_rsqrt(q);
+      const double gi = rough_rsqrt(g2);
+      a = 0.5 * g2 * gi;
+      h = h * gi;
+    }
+    for (int e = 0; e < 9; ++e) X[e] = a * X[e] + h * K[e];
+    if (it > 1 && det - 1.0 < 1e-8) {
+      for (int r = 0; r < 3; ++r)
+        for (int c = 0; c < 3; ++c) R[3 * r + c] = X[3 * c + r];
+      return true;
+    }
+  }
+  return false;
+}
+
+// ------------------------------------------------------------- reductions
+__device__ inline double join_double(unsigned lo, unsigned hi) {
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// x of the lane whose number differs in bit OFF (2^k), by moves inside the
+// vector unit (a shuffle goes through LDS: its latency, six times in a row, was
+// most of a block sum).
+template <int OFF>
+__device__ inline unsigned xor_lane_u(unsigned x) {
+  if constexpr (OFF == 32 || OFF == 16) {
+    // swap(x, x): .x holds the lower lanes of each pair in both, .y the upper
+    const auto r = OFF == 32 ? __builtin_amdgcn_permlane32_swap(x, x, false, false)
+                             : __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    return (__lane_id() & OFF) ? r[0] : r[1];
+  } else if constexpr (OFF == 8) {
+    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xf, 0xf, true);  // row rotate by 8
+  } else if constexpr (OFF == 4) {
+    // lanes 0-3 of each eight take lane + 4, lanes 4-7 lane - 4
+    const int up = __builtin_amdgcn_update_dpp(0, (int)x, 0x104, 0xf, 0x5, false);
+    return (unsigned)__builtin_amdgcn_update_dpp(up, (int)x, 0x114, 0xf, 0xa, false);
+  } else {
+    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, OFF == 2 ? 0x4E : 0xB1, 0xf, 0xf, true);  // in fours
+  }
+}
+template <int OFF>
+__device__ inline double xor_lane(double x) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+  return join_double(xor_lane_u<OFF>((unsigned)b), xor_lane_u<OFF>((unsigned)(b >> 32)));
+}
+
+// Two values against the partner lane in bit OFF: lanes with the bit clear
+// get a + partner's a, the others b + partner's b.
+template <int OFF>
+__device__ inline double halve_pair(double a, double b) {
+  const unsigned long long x = (unsigned long long)__double_as_longlong(a);
+  const unsigned long long y = (unsigned long long)__double_as_longlong(b);
+  if constexpr (OFF == 32) {
+    const auto l = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+    return join_double(l[0], h[0]) + join_double(l[1], h[1]);
+  } else if constexpr (OFF == 16) {
+    const auto l = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+    return join_double(l[0], h[0]) + join_double(l[1], h[1]);
+  } else {
+    const bool up = (__lane_id() & OFF) != 0;
+    return (up ? b : a) + xor_lane<OFF>(up ? a : b);
+  }
+}
+
+template <int OFF, int W, int P>
+__device__ inline void wave_sum_steps(double (&v)[P]) {
+  if constexpr (OFF >= 1) {
+    if constexpr (W >= 1) {
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-  return x;
+      for (int i = 0; i < W; ++i) v[i] = halve_pair<OFF>(v[i], v[i + W]);
+    } else {
+      v[0] += xor_lane<OFF>(v[0]);
+    }
+    wave_sum_steps<OFF / 2, W / 2, P>(v);
+  }
+}
+
+// Sums each of v[0..P) (P a power of two up to 64) over the wave: on return
+// lane l holds the sum of component l / (64 / P) in v[0].  Each of the first
+// log2 P steps halves the number of values a lane carries, so 16 values cost
+// 17 exchanges instead of 96.  The additions pair lanes in bits 32, 16, 8, 4,
+// 2, 1 in that order, whatever P.
+template <int P>
+__device__ inline void wave_sum_many(double (&v)[P]) {
+  wave_sum_steps<32, P / 2, P>(v);
+}
+
+__device__ inline double wave_sum(double x) {
+  double v[1] = {x};
+  wave_sum_many<1>(v);
+  return v[0];
+}
+
+// The value lane l (the same in every lane) holds, in every lane.
+__device__ inline double lane_value(double x, int l) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+  return join_double(__builtin_amdgcn_readlane((unsigned)b, l), __builtin_amdgcn_readlane((unsigned)(b >> 32), l));
 }
 
 // Sum NV doubles over a block of BT threads (BT a multiple of 64) in a fixed
-// order; the result is valid in thread 0.  `lds` needs NV * BT/64 doubles.
+// order; the result is valid in wave 0.  `lds` needs NV * BT/64 doubles.
 template <int NV, int BT>
 __device__ inline void block_sum(double (&v)[NV], double* lds) {
+  static_assert(NV <= 32, "one lane group per component");
+  constexpr int P = NV <= 1 ? 1 : (NV <= 2 ? 2 : (NV <= 4 ? 4 : (NV <= 8 ? 8 : (NV <= 16 ? 16 : 32))));
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  double p[P];
 #pragma unroll
-  for (int k = 0; k < NV; ++k) v[k] = wave_sum(v[k]);
-  if (lane == 0) {
-#pragma unroll
-    for (int k = 0; k < NV; ++k) lds[w * NV + k] = v[k];
-  }
+  for (int k = 0; k < P; ++k) p[k] = k < NV ? v[k < NV ? k : 0] : 0.0;
+  wave_sum_many<P>(p);
+  const int comp = lane / (64 / P);
+  if (lane % (64 / P) == 0 && comp < NV) lds[w * NV + comp] = p[0];
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (threadIdx.x < 64) {
+    double s = 0.0;
+    if (threadIdx.x < NV)
+      for (int ww = 0; ww < BT / 64; ++ww) s += lds[ww * NV + threadIdx.x];
 #pragma unroll
-    for (int k = 0; k < NV; ++k) {
-      double s = 0.0;
-      for (int ww = 0; ww < BT / 64; ++ww) s += lds[ww * NV + k];
-      v[k] = s;
-    }
+    for (int k = 0; k < NV; ++k) v[k] = lane_value(s, k);
   }
   __syncthreads();
 }

@@ -64,14 +64,16 @@ __device__ inline void sum_partials(const double* __restrict__ wpart, int n, dou
 // that both sets of loads are in flight together, then applies the update
 // (update_apply).  Every field of the constant block it reads is loaded into
 // registers first, and the three it changes (status, warm-start vectors,
-// previous translation) are stored at the end: reading them in place would
-// order each later load behind those stores.  pose_in and pose_out may be
+// previous translation) are stored at the end (update_store): reading them in
+// place would order each later load behind those stores.  pose_in and pose_out may be
 // the same array (the pose is updated in place), so neither is declared
 // __restrict__; the pose is read into registers before anything is stored.
 struct UpdateIn {
   double G;
   double ybar0[3], SigY0[6], Vw[9], dprev[3];
-  double Mcount, dt2, lamX, lamY0, Mtot, momentum;
+  double Mcount, dt2, lamX, lamY0, momentum;
+  double dt2_m;  // dt2 / Mtot
+  double sq;     // the scale eq. 8 asks for, sqrt(lamX / lamY0)
   double P[13];
   int32_t status;
   bool cold;
@@ -83,136 +85,157 @@ __device__ inline void update_load(const Derived* __restrict__ dv, const double*
   u.cold = dv->cold_svd != 0;
   for (int e = 0; e < 3; ++e) u.ybar0[e] = dv->ybar0[e];
   for (int e = 0; e < 6; ++e) u.SigY0[e] = dv->SigY0[e];
-  // cold: the SVD starts from the identity, which is what it does without a
-  // warm start, to the bit
-  for (int e = 0; e < 9; ++e) u.Vw[e] = u.cold ? ((e % 4 == 0) ? 1.0 : 0.0) : dv->Vw[e];
+  for (int e = 0; e < 9; ++e) u.Vw[e] = dv->Vw[e];
   for (int e = 0; e < 3; ++e) u.dprev[e] = dv->dprev[e];
   u.Mcount = dv->Mcount;
   u.dt2 = dv->dt2;
   u.lamX = dv->lamX;
   u.lamY0 = dv->lamY0;
-  u.Mtot = dv->Mtot;
+  u.dt2_m = dv->dt2 / dv->Mtot;
+  u.sq = sqrt(dv->lamX / dv->lamY0);
   u.momentum = dv->momentum;
   for (int e = 0; e < 13; ++e) u.P[e] = pose_in[e];
   u.status = dv->status;
 }
 
-// The update itself (one thread).
-__device__ inline void update_apply(const double W[13], const UpdateIn& u, double* pose_out,
-                                    Derived* __restrict__ dv, int do_update, double* __restrict__ wrench_out,
-                                    double* __restrict__ stats_row) {
-  const double G = u.G;
-  const bool cold = u.cold;
-  double ybar0[3], SigY0[6], Vw[9], dprev[3];
-  for (int e = 0; e < 3; ++e) ybar0[e] = u.ybar0[e];
-  for (int e = 0; e < 6; ++e) SigY0[e] = u.SigY0[e];
-  for (int e = 0; e < 9; ++e) Vw[e] = u.Vw[e];
-  for (int e = 0; e < 3; ++e) dprev[e] = u.dprev[e];
-  const double Mcount = u.Mcount, dt2 = u.dt2, lamX = u.lamX, lamY0 = u.lamY0, Mtot = u.Mtot, momentum = u.momentum;
+__device__ __attribute__((noinline)) bool kabsch_call(const double* C, double* R, double* Vw) {
+  double c[9], r[9], v[9];
+  for (int e = 0; e < 9; ++e) c[e] = C[e], v[e] = Vw[e];
+  const bool ok = kabsch_rot(c, r, v);
+  for (int e = 0; e < 9; ++e) R[e] = r[e], Vw[e] = v[e];
+  return ok;
+}
+
+// The update itself: advances the state u (pose, warm-start vectors,
+// previous translation, status) by one iteration with the wrench W and
+// returns the scale factor c.  Nothing changes once the status is set.
+// OUTLINE: the SVD of a C that polar_rot does not take stays a call (the
+// loop kernel, whose registers hold the points).
+template <bool OUTLINE = false>
+__device__ inline double update_core(const double W[13], UpdateIn& u) {
+  double c = 1.0;
+  if (u.status != 0) return c;
+  const double s = u.P[0];
+  const double* R = u.P + 1;
+  const double* tv = u.P + 10;
+  const double* ybar0 = u.ybar0;
+  const double* SigY0 = u.SigY0;
+  bool ok = true;
+  for (int e = 0; e < 12; ++e) ok &= isfinite(W[e]);
+  // ybar = s R ybar0 + t ; Sigma_Y = s^2 R Sigma_Y0 R^T
+  double yb[3];
+  for (int r = 0; r < 3; ++r)
+    yb[r] = s * (R[3 * r] * ybar0[0] + R[3 * r + 1] * ybar0[1] + R[3 * r + 2] * ybar0[2]) + tv[r];
+  const double S0[9] = {SigY0[0], SigY0[3], SigY0[4], SigY0[3], SigY0[1],
+                        SigY0[5], SigY0[4], SigY0[5], SigY0[2]};
+  double RS[9];
+  for (int r = 0; r < 3; ++r)
+    for (int q = 0; q < 3; ++q) RS[3 * r + q] = R[3 * r] * S0[q] + R[3 * r + 1] * S0[3 + q] + R[3 * r + 2] * S0[6 + q];
+  double C[9];
+  for (int r = 0; r < 3; ++r)
+    for (int q = 0; q < 3; ++q) {
+      const double sig = s * s * (RS[3 * r] * R[3 * q] + RS[3 * r + 1] * R[3 * q + 1] + RS[3 * r + 2] * R[3 * q + 2]);
+      C[3 * r + q] = u.Mcount * sig + u.dt2 * W[WR_K + 3 * r + q];
+    }
+  for (int e = 0; e < 9; ++e) ok &= isfinite(C[e]);
+  double Rk[9];
+  if (!ok) {
+    u.status |= ST_NONFINITE;
+    return c;
+  }
+  // cold (the unrolled registration): always the SVD, from the identity,
+  // which is what it does without a warm start, to the bit
+  if (u.cold || !polar_rot(C, Rk)) {
+    double Vw[9];
+    for (int e = 0; e < 9; ++e) Vw[e] = u.cold ? ((e % 4 == 0) ? 1.0 : 0.0) : u.Vw[e];
+    bool rot;
+    if constexpr (OUTLINE)
+      rot = kabsch_call(C, Rk, Vw);
+    else
+      rot = kabsch_rot(C, Rk, Vw);
+    if (!u.cold)
+      for (int e = 0; e < 9; ++e) u.Vw[e] = Vw[e];
+    if (!rot) {
+      u.status |= ST_SINGULAR;
+      return c;
+    }
+  }
+  c = u.cold ? sqrt(u.lamX / (s * s * u.lamY0)) : u.sq / s;
+  double d[3];
+  for (int r = 0; r < 3; ++r) d[r] = u.dt2_m * W[WR_F + r];
+  // velocity state: the share momentum of the previous translation
+  if (u.momentum != 0.0)
+    for (int r = 0; r < 3; ++r) d[r] += u.momentum * u.dprev[r];
+  // column form: y' = c Rk^T (y - ybar) + ybar + d
+  double Rn[9];
+  for (int r = 0; r < 3; ++r)
+    for (int q = 0; q < 3; ++q) Rn[3 * r + q] = Rk[r] * R[q] + Rk[3 + r] * R[3 + q] + Rk[6 + r] * R[6 + q];
+  // one Newton-Schulz step towards the nearest rotation: Rn (3I - Rn^T Rn)/2
+  double RtR[9];
+  for (int r = 0; r < 3; ++r)
+    for (int q = 0; q < 3; ++q) RtR[3 * r + q] = Rn[r] * Rn[q] + Rn[3 + r] * Rn[3 + q] + Rn[6 + r] * Rn[6 + q];
+  double Ro[9];
+  for (int r = 0; r < 3; ++r)
+    for (int q = 0; q < 3; ++q) {
+      double acc = 0.0;
+      for (int k = 0; k < 3; ++k) acc += Rn[3 * r + k] * ((k == q ? 3.0 : 0.0) - RtR[3 * k + q]);
+      Ro[3 * r + q] = 0.5 * acc;
+    }
+  double tn[3];
+  for (int r = 0; r < 3; ++r) {
+    const double dv0 = tv[0] - yb[0], dv1 = tv[1] - yb[1], dv2 = tv[2] - yb[2];
+    tn[r] = c * (Rk[r] * dv0 + Rk[3 + r] * dv1 + Rk[6 + r] * dv2) + yb[r] + d[r];
+  }
+  const double sn = c * s;
+  bool fin = isfinite(sn);
+  for (int e = 0; e < 9; ++e) fin &= isfinite(Ro[e]);
+  for (int e = 0; e < 3; ++e) fin &= isfinite(tn[e]);
+  if (!fin) {
+    u.status |= ST_NONFINITE;
+  } else if (!(sn > 1e-6 && sn < 1e6)) {
+    u.status |= ST_SCALE;
+  } else {
+    u.P[0] = sn;
+    for (int e = 0; e < 9; ++e) u.P[1 + e] = Ro[e];
+    for (int e = 0; e < 3; ++e) u.P[10 + e] = tn[e];
+    for (int e = 0; e < 3; ++e) u.dprev[e] = d[e];
+  }
+  return c;
+}
+
+// The state an update changes, back into the constant block.
+__device__ inline void update_store(const UpdateIn& u, Derived* __restrict__ dv) {
+  dv->status = u.status;
+  if (!u.cold)
+    for (int e = 0; e < 9; ++e) dv->Vw[e] = u.Vw[e];
+  for (int e = 0; e < 3; ++e) dv->dprev[e] = u.dprev[e];
+}
+
+__device__ inline void stats_write(const double W[13], const UpdateIn& u, double G, double c,
+                                   double* __restrict__ row) {
+  row[ST_G] = G;
+  for (int e = 0; e < 12; ++e) row[ST_F + e] = W[e];
+  row[ST_U] = W[WR_U];
+  for (int e = 0; e < 13; ++e) row[ST_POSE + e] = u.P[e];
+  row[ST_C] = c;
+  row[ST_STATUS] = (double)u.status;
+  for (int e = ST_STATUS + 1; e < STATS_STRIDE; ++e) row[e] = 0.0;
+}
+
+__device__ inline void update_apply(const double W[13], UpdateIn& u, double* pose_out, Derived* __restrict__ dv,
+                                    int do_update, double* __restrict__ wrench_out, double* __restrict__ stats_row) {
   if (wrench_out) {
     for (int e = 0; e < 13; ++e) wrench_out[e] = W[e];
   }
-  double P[13];
-  for (int e = 0; e < 13; ++e) P[e] = u.P[e];
-  double Pn[13];
-  for (int e = 0; e < 13; ++e) Pn[e] = P[e];
   double c = 1.0;
-  int32_t st = u.status;
-  if (do_update && st == 0) {
-    const double s = P[0];
-    const double* R = P + 1;
-    const double* tv = P + 10;
-    bool ok = true;
-    for (int e = 0; e < 12; ++e) ok &= isfinite(W[e]);
-    // ybar = s R ybar0 + t ; Sigma_Y = s^2 R Sigma_Y0 R^T
-    double yb[3];
-    for (int r = 0; r < 3; ++r)
-      yb[r] = s * (R[3 * r] * ybar0[0] + R[3 * r + 1] * ybar0[1] + R[3 * r + 2] * ybar0[2]) + tv[r];
-    const double S0[9] = {SigY0[0], SigY0[3], SigY0[4], SigY0[3], SigY0[1],
-                          SigY0[5], SigY0[4], SigY0[5], SigY0[2]};
-    double RS[9];
-    for (int r = 0; r < 3; ++r)
-      for (int q = 0; q < 3; ++q) RS[3 * r + q] = R[3 * r] * S0[q] + R[3 * r + 1] * S0[3 + q] + R[3 * r + 2] * S0[6 + q];
-    double C[9];
-    for (int r = 0; r < 3; ++r)
-      for (int q = 0; q < 3; ++q) {
-        const double sig = s * s * (RS[3 * r] * R[3 * q] + RS[3 * r + 1] * R[3 * q + 1] + RS[3 * r + 2] * R[3 * q + 2]);
-        C[3 * r + q] = Mcount * sig + dt2 * W[WR_K + 3 * r + q];
-      }
-    for (int e = 0; e < 9; ++e) ok &= isfinite(C[e]);
-    double Rk[9];
-    if (!ok) {
-      st |= ST_NONFINITE;
-    } else if (!kabsch_rot(C, Rk, Vw)) {
-      st |= ST_SINGULAR;
-    } else {
-      c = sqrt(lamX / (s * s * lamY0));
-      double d[3];
-      const double dt2_m = dt2 / Mtot;
-      for (int r = 0; r < 3; ++r) d[r] = dt2_m * W[WR_F + r];
-      // velocity state: the share momentum of the previous translation
-      if (momentum != 0.0)
-        for (int r = 0; r < 3; ++r) d[r] += momentum * dprev[r];
-      // column form: y' = c Rk^T (y - ybar) + ybar + d
-      double Rn[9];
-      for (int r = 0; r < 3; ++r)
-        for (int q = 0; q < 3; ++q) Rn[3 * r + q] = Rk[r] * R[q] + Rk[3 + r] * R[3 + q] + Rk[6 + r] * R[6 + q];
-      // one Newton-Schulz step towards the nearest rotation: Rn (3I - Rn^T Rn)/2
-      double RtR[9];
-      for (int r = 0; r < 3; ++r)
-        for (int q = 0; q < 3; ++q) RtR[3 * r + q] = Rn[r] * Rn[q] + Rn[3 + r] * Rn[3 + q] + Rn[6 + r] * Rn[6 + q];
-      double Ro[9];
-      for (int r = 0; r < 3; ++r)
-        for (int q = 0; q < 3; ++q) {
-          double acc = 0.0;
-          for (int k = 0; k < 3; ++k) acc += Rn[3 * r + k] * ((k == q ? 3.0 : 0.0) - RtR[3 * k + q]);
-          Ro[3 * r + q] = 0.5 * acc;
-        }
-      double tn[3];
-      for (int r = 0; r < 3; ++r) {
-        const double dv0 = tv[0] - yb[0], dv1 = tv[1] - yb[1], dv2 = tv[2] - yb[2];
-        tn[r] = c * (Rk[r] * dv0 + Rk[3 + r] * dv1 + Rk[6 + r] * dv2) + yb[r] + d[r];
-      }
-      const double sn = c * s;
-      bool fin = isfinite(sn);
-      for (int e = 0; e < 9; ++e) fin &= isfinite(Ro[e]);
-      for (int e = 0; e < 3; ++e) fin &= isfinite(tn[e]);
-      if (!fin) {
-        st |= ST_NONFINITE;
-      } else if (!(sn > 1e-6 && sn < 1e6)) {
-        st |= ST_SCALE;
-      } else {
-        Pn[0] = sn;
-        for (int e = 0; e < 9; ++e) Pn[1 + e] = Ro[e];
-        for (int e = 0; e < 3; ++e) Pn[10 + e] = tn[e];
-        for (int e = 0; e < 3; ++e) dprev[e] = d[e];
-      }
-    }
-    dv->status = st;
-    if (!cold)
-      for (int e = 0; e < 9; ++e) dv->Vw[e] = Vw[e];
-    for (int e = 0; e < 3; ++e) dv->dprev[e] = dprev[e];
+  if (do_update && u.status == 0) {
+    c = update_core(W, u);
+    update_store(u, dv);
   }
   if (pose_out) {
-    for (int e = 0; e < 13; ++e) pose_out[e] = Pn[e];
+    for (int e = 0; e < 13; ++e) pose_out[e] = u.P[e];
   }
-  if (stats_row) {
-    stats_row[ST_G] = G;
-    for (int e = 0; e < 12; ++e) stats_row[ST_F + e] = W[e];
-    stats_row[ST_U] = W[WR_U];
-    for (int e = 0; e < 13; ++e) stats_row[ST_POSE + e] = Pn[e];
-    stats_row[ST_C] = c;
-    stats_row[ST_STATUS] = (double)st;
-    for (int e = ST_STATUS + 1; e < STATS_STRIDE; ++e) stats_row[e] = 0.0;
-  }
-}
-
-__device__ inline void pose_update(const double W[13], const double* pose_in, double* pose_out,
-                                   Derived* __restrict__ dv, int t, double G_fixed, int do_update,
-                                   double* __restrict__ wrench_out, double* __restrict__ stats_row) {
-  UpdateIn u;
-  update_load(dv, pose_in, t, G_fixed, u);
-  update_apply(W, u, pose_out, dv, do_update, wrench_out, stats_row);
+  if (stats_row) stats_write(W, u, u.G, c, stats_row);
 }
 
 }  // namespace sgr
