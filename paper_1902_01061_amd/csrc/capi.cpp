@@ -5,6 +5,7 @@
 
 #include <cmath>
 #include <cstdio>
+#include <cstdlib>
 #include <algorithm>
 #include <cstring>
 #include <mutex>
@@ -48,6 +49,7 @@ struct sgr_ctx {
   std::vector<GraphCache> gcp;  // pyramidal schedule, one per level
   GraphCache gcv;  // vector descriptors
   TileTable tiles;
+  int loop_spins = 2000000;  // polls before the one-launch loop gives up (about 2 s)
 };
 
 namespace {
@@ -253,6 +255,7 @@ void key_add(std::vector<uint8_t>& k, const T* p, size_t n) {
 // descriptors, set-up, then E iterations of (persistent force, update).
 struct BatchIn {
   int B;
+  bool use_loop = true;                  // flags bit 3: one launch for all iterations (false: after a stall)
   std::vector<const sgr_cloud*> tm, rf;  // per registration
   std::vector<int> tm_cloud, rf_cloud;   // index of each registration's clouds in `clouds`
   std::vector<const sgr_cloud*> clouds;  // distinct clouds (descriptors computed once each)
@@ -300,9 +303,11 @@ int run_batch(sgr_ctx* ctx, const BatchIn& in, const sgr_params* prm, double* po
   }
   for (int r = 0; r < B; ++r) ref_off[r] = ref_off[in.pack_of[r]];
   std::vector<RegDesc> regs(B);
+  // flags bit 3 (p = 1): pair sums once, then O(M) iterations
+  const bool pinv = (prm->flags & FLAG_PINV) != 0;
   std::vector<int4> items;
   int slot = 0;
-  for (int r = 0; r < B; ++r) {
+  for (int r = 0; r < B && !pinv; ++r) {
     const int nib = (int)((Ms[r] + ipb - 1) / ipb), nch = (int)((Ns[r] + chunk_len - 1) / chunk_len);
     regs[r].wslot0 = slot;
     regs[r].n_items = nib * nch;
@@ -317,17 +322,65 @@ int run_batch(sgr_ctx* ctx, const BatchIn& in, const sgr_params* prm, double* po
   };
   std::stable_sort(items.begin(), items.end(), [&](const int4& a, const int4& b) { return cost(a) > cost(b); });
   const int n_items = (int)items.size();
-  // flags bit 3 (p = 1): pair sums once, then one wrench slot per block of
-  // 256 template points in every iteration, described by regs_p
-  const bool pinv = (prm->flags & FLAG_PINV) != 0;
-  std::vector<int2> tblk;
-  std::vector<int> pslot0(B, 0), pslots(B, 0);
-  if (pinv)
+  // With the pair sums, registrations of the same two clouds (the starts of a
+  // sweep) share the first one's template and sums.
+  int n_own = B;
+  std::vector<int> src(B);
+  std::vector<int2> tblk, lblk;   // per-iteration kernels; blocks of the loop launch
+  std::vector<int> pslot0(B, 0), pslots(B, 0), lnb(B, 0), nch(B, 1);
+  std::vector<int4> sitems;       // pair-sum items
+  int ppt = 0, sum_chunk = 0;
+  bool loop = pinv && in.use_loop, chunked = false;
+  size_t xwords = 0;
+  int64_t s_rows = 0, part_rows = 0;
+  if (pinv) {
+    n_own = 0;
+    int64_t pairs = 0, points = 0;
     for (int r = 0; r < B; ++r) {
+      const int o = in.pack_of[r];
+      src[r] = in.tm_cloud[r] == in.tm_cloud[o] ? o : r;
+      if (src[r] == r) {
+        n_own = r + 1;  // the owners come first
+        pairs += Ms[r] * Ns[r];
+        s_rows += Ms[r];
+      }
+      points += Ms[r];
       pslot0[r] = (int)tblk.size();
       pslots[r] = pinv_blocks((int)Ms[r]);
       for (int b = 0; b < pslots[r]; ++b) tblk.push_back(make_int2(r, b));
     }
+    // chunks for about 3000 items (a dozen per CU, so that the decreasing
+    // order evens out the end of the launch) of at least 5e5 pairs (a block's
+    // start and end cost a few us): whole tiles of 256 reference points
+    const int64_t rows = psum_batch_points();
+    const int64_t per = std::max<int64_t>(pairs / 3000, 500000) / rows;
+    sum_chunk = (int)std::max<int64_t>(512, (per + 255) / 256 * 256);
+    for (int r = 0; r < n_own; ++r) {
+      nch[r] = (int)((Ns[r] + sum_chunk - 1) / sum_chunk);
+      chunked |= nch[r] > 1;
+      if (nch[r] > 1) part_rows += nch[r] * Ms[r];
+      for (int b = 0; b < (int)((Ms[r] + rows - 1) / rows); ++b)
+        for (int c = 0; c < nch[r]; ++c) sitems.push_back(make_int4(r, b, c, 0));
+    }
+    auto scost = [&](const int4& it) {
+      return std::min<int64_t>(rows, Ms[it.x] - it.y * rows) * std::min<int64_t>(sum_chunk, Ns[it.x] - (int64_t)it.z * sum_chunk);
+    };
+    std::stable_sort(sitems.begin(), sitems.end(), [&](const int4& a, const int4& b) { return scost(a) > scost(b); });
+    ppt = loop_points(points, B);
+    for (int r = 0; r < B; ++r) {
+      lnb[r] = loop_blocks((int)Ms[r], ppt);
+      loop = loop && lnb[r] > 0;
+    }
+    // the largest first
+    std::vector<int> order(B);
+    for (int r = 0; r < B; ++r) order[r] = r;
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return Ms[a] > Ms[b]; });
+    if (loop)
+      for (int r : order) {
+        for (int b = 0; b < lnb[r]; ++b) lblk.push_back(make_int2(r, b));
+        xwords += loop_words(lnb[r]);
+      }
+  }
   const int n_tblk = (int)tblk.size();
   const int n_slots = std::max(n_items, n_tblk);
 
@@ -348,15 +401,23 @@ int run_batch(sgr_ctx* ctx, const BatchIn& in, const sgr_params* prm, double* po
   cv.take<double>(B);
   int64_t perm_total = 0;
   for (int r = 0; r < B; ++r) perm_total += Ms[r];
-  cv.take<int>(perm_total);
+  cv.take<int>(pinv ? 0 : perm_total);
   cv.take<float4>(perm_total);
   cv.take<float2>(perm_total);
   cv.take<int>(B + 1);
-  cv.take<char>(sort_perm_workspace(perm_total, B));
+  cv.take<char>(pinv ? 0 : sort_perm_workspace(perm_total, B));
+  const size_t sync_ints = 64 + 2 * xwords;  // the loop's ticket, then its exchange words
   if (pinv) {
     cv.take<int2>(n_tblk);
     cv.take<RegDesc>(B);
-    cv.take<double>((size_t)perm_total * 5);
+    cv.take<double>((size_t)s_rows * 5);
+    cv.take<double>((size_t)part_rows * 5);
+    cv.take<PsumReg>(B);
+    cv.take<int4>(sitems.size());
+    cv.take<LoopReg>(B);
+    cv.take<int2>(lblk.size());
+    cv.take<int>(sync_ints);
+    cv.take<double>((size_t)B * 13);
   }
   std::vector<int> cl_n(ncl);
   for (int c = 0; c < ncl; ++c) cl_n[c] = (int)in.clouds[c]->n;
@@ -377,14 +438,21 @@ int run_batch(sgr_ctx* ctx, const BatchIn& in, const sgr_params* prm, double* po
   float* d_lw = w.take<float>(ref_total);
   double* d_wpart = w.take<double>((size_t)n_slots * WR_STRIDE);
   double* d_energy = w.take<double>(B);
-  int* d_perm = w.take<int>(perm_total);
+  int* d_perm = w.take<int>(pinv ? 0 : perm_total);
   float4* d_tm4 = w.take<float4>(perm_total);
   float2* d_tmx = w.take<float2>(perm_total);
   int* d_poff = w.take<int>(B + 1);
-  char* d_sws = w.take<char>(sort_perm_workspace(perm_total, B));
+  char* d_sws = w.take<char>(pinv ? 0 : sort_perm_workspace(perm_total, B));
   int2* d_tblk = pinv ? w.take<int2>(n_tblk) : nullptr;
   RegDesc* d_regs_p = pinv ? w.take<RegDesc>(B) : nullptr;
-  double* d_S = pinv ? w.take<double>((size_t)perm_total * 5) : nullptr;
+  double* d_S = pinv ? w.take<double>((size_t)s_rows * 5) : nullptr;
+  double* d_part = pinv ? w.take<double>((size_t)part_rows * 5) : nullptr;
+  PsumReg* d_sums = pinv ? w.take<PsumReg>(B) : nullptr;
+  int4* d_sitems = pinv ? w.take<int4>(sitems.size()) : nullptr;
+  LoopReg* d_lregs = pinv ? w.take<LoopReg>(B) : nullptr;
+  int2* d_lblk = pinv ? w.take<int2>(lblk.size()) : nullptr;
+  int* d_sync = pinv ? w.take<int>(sync_ints) : nullptr;
+  double* d_pose0 = pinv ? w.take<double>((size_t)B * 13) : nullptr;
   char* d_gws = w.take<char>(gws_bytes);
 
   for (int c = 0; c < ncl; ++c)
@@ -405,9 +473,10 @@ int run_batch(sgr_ctx* ctx, const BatchIn& in, const sgr_params* prm, double* po
   }
   std::vector<int> poff(B + 1, 0);
   for (int r = 0; r < B; ++r) {
-    regs[r].perm = d_perm + poff[r];
-    regs[r].tm4 = d_tm4 + poff[r];
-    regs[r].tmx = d_tmx + poff[r];
+    const int o = pinv ? poff[src[r]] : poff[r];
+    regs[r].perm = pinv ? nullptr : d_perm + o;
+    regs[r].tm4 = d_tm4 + o;
+    regs[r].tmx = d_tmx + o;
     poff[r + 1] = poff[r] + (int)Ms[r];
   }
   HIPCHK(hipMemcpyAsync(d_cds, cds.data(), sizeof(CloudDesc) * ncl, hipMemcpyHostToDevice, st));
@@ -415,17 +484,40 @@ int run_batch(sgr_ctx* ctx, const BatchIn& in, const sgr_params* prm, double* po
   HIPCHK(hipMemcpyAsync(d_prep, preps.data(), sizeof(PrepDesc) * B, hipMemcpyHostToDevice, st));
   HIPCHK(hipMemcpyAsync(d_b2r, blk2reg.data(), sizeof(int) * blk2reg.size(), hipMemcpyHostToDevice, st));
   HIPCHK(hipMemcpyAsync(d_regs, regs.data(), sizeof(RegDesc) * B, hipMemcpyHostToDevice, st));
-  HIPCHK(hipMemcpyAsync(d_items, items.data(), sizeof(int4) * n_items, hipMemcpyHostToDevice, st));
+  if (n_items > 0) HIPCHK(hipMemcpyAsync(d_items, items.data(), sizeof(int4) * n_items, hipMemcpyHostToDevice, st));
   HIPCHK(hipMemcpyAsync(d_poff, poff.data(), sizeof(int) * (B + 1), hipMemcpyHostToDevice, st));
   std::vector<RegDesc> regs_p;
+  std::vector<PsumReg> sums(pinv ? B : 0);
+  std::vector<LoopReg> lregs(loop ? B : 0);
   if (pinv) {
     regs_p = regs;
+    size_t so = 0, po = 0, xo = 0;
     for (int r = 0; r < B; ++r) {
       regs_p[r].wslot0 = pslot0[r];
       regs_p[r].n_items = pslots[r];
+      if (src[r] == r) {
+        sums[r] = PsumReg{regs[r].tm4, d_S + so * 5, d_part + po * 5, ref_off[r], (int)Ms[r], (int)Ns[r], nch[r], 0};
+        so += Ms[r];
+        if (nch[r] > 1) po += (size_t)nch[r] * Ms[r];
+      } else {
+        sums[r] = sums[src[r]];
+      }
+      if (loop) {
+        lregs[r] = LoopReg{regs[r].tm4, regs[r].tmx, sums[r].S, poses + 13 * (size_t)r, d_pose0 + 13 * (size_t)r,
+                           d_dv + r, stats ? stats + (size_t)r * prm->E * STATS_STRIDE : nullptr, d_energy + r,
+                           reinterpret_cast<unsigned long long*>(d_sync + 64) + xo, (int)Ms[r], lnb[r]};
+        xo += loop_words(lnb[r]);
+      }
     }
-    HIPCHK(hipMemcpyAsync(d_tblk, tblk.data(), sizeof(int2) * n_tblk, hipMemcpyHostToDevice, st));
-    HIPCHK(hipMemcpyAsync(d_regs_p, regs_p.data(), sizeof(RegDesc) * B, hipMemcpyHostToDevice, st));
+    HIPCHK(hipMemcpyAsync(d_sums, sums.data(), sizeof(PsumReg) * B, hipMemcpyHostToDevice, st));
+    HIPCHK(hipMemcpyAsync(d_sitems, sitems.data(), sizeof(int4) * sitems.size(), hipMemcpyHostToDevice, st));
+    if (loop) {
+      HIPCHK(hipMemcpyAsync(d_lregs, lregs.data(), sizeof(LoopReg) * B, hipMemcpyHostToDevice, st));
+      HIPCHK(hipMemcpyAsync(d_lblk, lblk.data(), sizeof(int2) * lblk.size(), hipMemcpyHostToDevice, st));
+    } else {
+      HIPCHK(hipMemcpyAsync(d_tblk, tblk.data(), sizeof(int2) * n_tblk, hipMemcpyHostToDevice, st));
+      HIPCHK(hipMemcpyAsync(d_regs_p, regs_p.data(), sizeof(RegDesc) * B, hipMemcpyHostToDevice, st));
+    }
   }
 
   // descriptors of every cloud: the exact grid search for all clouds at
@@ -448,10 +540,12 @@ int run_batch(sgr_ctx* ctx, const BatchIn& in, const sgr_params* prm, double* po
   HIPCHK(launch_pack_batch(d_prep, d_b2r, (int)blk2reg.size(), d_dv, d_ref4, d_lw, st));
   {
     const int max_M = (int)*std::max_element(Ms.begin(), Ms.end());
-    HIPCHK(launch_sort_perm_batch(d_regs, B, d_poff, perm_total, max_M, d_perm, d_sws, st));
-    HIPCHK(launch_pack_tmpl_batch(d_regs, B, max_M, d_dv, st));
+    // the pair sums do not depend on the visiting order: no sort for them
+    if (!pinv) HIPCHK(launch_sort_perm_batch(d_regs, B, d_poff, perm_total, max_M, d_perm, d_sws, st));
+    HIPCHK(launch_pack_tmpl_batch(d_regs, n_own, max_M, d_dv, st));
   }
-  if (pinv) HIPCHK(launch_psum_batch(d_regs, d_tblk, n_tblk, d_poff, d_ref4, d_lw, d_S, st));
+  if (pinv)
+    HIPCHK(launch_psum_batch(d_sums, n_own, d_sitems, (int)sitems.size(), sum_chunk, chunked, d_ref4, d_lw, st));
   if (R0_multistart) HIPCHK(launch_init_multistart(R0_multistart, B, d_mom + 10 * in.tm_cloud[0], poses, st));
 
   // One block per work item: the hardware hands the items out in the list's
@@ -460,11 +554,11 @@ int run_batch(sgr_ctx* ctx, const BatchIn& in, const sgr_params* prm, double* po
   // batch (1.43 s against 1.34 s; 4 blocks per CU, 1.55 s): with more blocks
   // than are resident, the second round starts only as whole item lists end.
   const int grid = n_items;
-  auto loop = [&](hipStream_t s) -> int {
+  auto iterations = [&](hipStream_t s) -> int {
     for (int t = 0; t < prm->E; ++t) {
       const bool wu = stats != nullptr || t == prm->E - 1;
       if (pinv) {
-        HIPCHK(launch_pinv_batch(d_regs_p, d_tblk, n_tblk, d_poff, d_S, poses, d_dv, t, wu, d_wpart, s));
+        HIPCHK(launch_pinv_batch(d_regs_p, d_tblk, n_tblk, d_sums, poses, d_dv, t, wu, d_wpart, s));
       } else {
         BatchArgs A{d_regs, d_items, n_items, d_ref4, d_lw, poses, d_dv, chunk_len, t, d_wpart};
         HIPCHK(launch_force_batch(A, R, pm, wu, grid, s));
@@ -474,24 +568,37 @@ int run_batch(sgr_ctx* ctx, const BatchIn& in, const sgr_params* prm, double* po
     }
     return SGR_OK;
   };
-  if ((prm->flags & 1) || prm->E < 2) {
-    if (int e = loop(st)) return e;
+  if (loop) {
+    HIPCHK(launch_fill_i(d_sync, (int)sync_ints, st));
+    HIPCHK(launch_pinv_loop_batch(d_lregs, d_lblk, (int)lblk.size(), ppt, d_sync, 0, prm->E, ctx->loop_spins, st));
+  } else if ((prm->flags & 1) || prm->E < 2) {
+    if (int e = iterations(st)) return e;
   } else {
     std::vector<uint8_t> key;
     key_add(key, &B, 1);
     key_add(key, prm, 1);
     key_add(key, items.data(), items.size());
     key_add(key, regs.data(), regs.size());
-    const void* ptrs[4] = {ctx->ws, poses, stats, R0_multistart};
-    key_add(key, ptrs, 4);
-    if (int e = run_graph(ctx, ctx->gcb, key, loop, st)) return e;
+    const void* ptrs[5] = {ctx->ws, poses, stats, R0_multistart, d_sums};
+    key_add(key, ptrs, 5);
+    if (int e = run_graph(ctx, ctx->gcb, key, iterations, st)) return e;
   }
   if (energy_out) HIPCHK(hipMemcpyAsync(energy_out, d_energy, sizeof(double) * B, hipMemcpyDeviceToDevice, st));
   if (best_out) HIPCHK(launch_argmin(d_energy, B, best_out, st));
   std::vector<Derived> dh(B);
   HIPCHK(hipMemcpyAsync(dh.data(), d_dv, sizeof(Derived) * B, hipMemcpyDeviceToHost, st));
   HIPCHK(hipStreamSynchronize(st));
-  int bad = 0, degen = 0;
+  int bad = 0, degen = 0, stalled = 0;
+  for (int r = 0; r < B; ++r) stalled += (dh[r].status & ST_STALLED) != 0;
+  if (stalled) {
+    // the loop's blocks were not resident together: from the initial poses
+    // again, with one launch per iteration
+    if (!R0_multistart)
+      HIPCHK(hipMemcpyAsync(poses, d_pose0, sizeof(double) * 13 * B, hipMemcpyDeviceToDevice, st));
+    BatchIn again = in;
+    again.use_loop = false;
+    return run_batch(ctx, again, prm, poses, R0_multistart, energy_out, stats, best_out, st);
+  }
   for (int r = 0; r < B; ++r) {
     bad += dh[r].status != 0;
     degen += (dh[r].status & ST_DEGENERATE) != 0;
@@ -518,6 +625,9 @@ struct SingleWs {
   double* ps_part;  // pose-independent pair sums (flags bit 3): per chunk, then reduced
   double* ps_S;
   int ps_chunks;
+  int* sync;         // the loop's ticket (64 ints), then its exchange words
+  double* pose0;     // poses before each level's loop
+  int loop_ppt, loop_nb;  // the one-launch loop's shape (0 blocks: not used)
   int* perm;
   char* sws;
   float4* tm4;
@@ -527,7 +637,9 @@ struct SingleWs {
 };
 
 // kmax: largest k of a nearest-neighbour search the call makes (0: none).
-int carve_single(sgr_ctx* ctx, int M, int N, const sgr_params* prm, int kmax, SingleWs& w, bool radius) {
+// use_loop: flags bit 3 may run its iterations in one launch.
+int carve_single(sgr_ctx* ctx, int M, int N, const sgr_params* prm, int kmax, SingleWs& w, bool radius,
+                 bool use_loop, int n_levels) {
   const int pm = pmode_of(prm->p);
   const bool pinv = (prm->flags & FLAG_PINV) != 0;
   w.T = ctx->tiles.pick(M, N, pm);
@@ -535,6 +647,8 @@ int carve_single(sgr_ctx* ctx, int M, int N, const sgr_params* prm, int kmax, Si
   w.nslot = std::max(force_shape(ctx, M, N, w.T, pm).slots, w.TM.nblk);
   if (pinv) w.nslot = std::max(w.nslot, pinv_blocks(M));
   w.ps_chunks = pinv ? pinv_chunks(M, N, ctx->n_cu) : 0;
+  w.loop_ppt = pinv ? loop_points(M, 1) : 0;
+  w.loop_nb = pinv && use_loop ? loop_blocks(M, w.loop_ppt) : 0;
   size_t gbytes = kmax > 0 ? std::max(grid_knn_workspace(N, kmax), grid_knn_workspace(M, kmax)) : 0;
   if (radius) gbytes = std::max({gbytes, radius_desc_workspace(N), radius_desc_workspace(M)});
   for (int pass = 0; pass < 2; ++pass) {
@@ -553,6 +667,8 @@ int carve_single(sgr_ctx* ctx, int M, int N, const sgr_params* prm, int kmax, Si
     w.tmx = c.take<float2>(M);
     w.ps_part = pinv ? c.take<double>((size_t)w.ps_chunks * M * 5) : nullptr;
     w.ps_S = pinv ? c.take<double>((size_t)M * 5) : nullptr;
+    w.sync = pinv ? c.take<int>(64 + 2 * loop_words(w.loop_nb)) : nullptr;
+    w.pose0 = pinv ? c.take<double>((size_t)13 * n_levels) : nullptr;
     if (!pass)
       if (int e = ensure_ws(ctx, c.off)) return e;
   }
@@ -561,13 +677,25 @@ int carve_single(sgr_ctx* ctx, int M, int N, const sgr_params* prm, int kmax, Si
 
 // Derived constants from the curvatures and moments already in w, then the
 // packed reference and the curvature-sorted packed template.
-int setup_single(const sgr_cloud* tmpl, const sgr_cloud* ref, const PrepParams& P, SingleWs& w, hipStream_t st) {
+// With pair sums (flags bit 3) the template stays in its own order.
+int setup_single(const sgr_cloud* tmpl, const sgr_cloud* ref, const PrepParams& P, bool want_s2, SingleWs& w,
+                 hipStream_t st) {
   const int M = (int)tmpl->n, N = (int)ref->n;
   HIPCHK(launch_prepare(w.aX, ref->m, N, w.aY, tmpl->m, M, w.mom, w.mom + 10, P, w.dv, st));
   HIPCHK(launch_pack_ref(ref->x, ref->y, ref->z, w.aX, ref->m, N, w.dv, w.ref4, w.lw, st));
-  HIPCHK(launch_sort_perm(w.aY, M, w.perm, w.sws, st));
-  HIPCHK(launch_pack_tmpl(tmpl->x, tmpl->y, tmpl->z, w.aY, tmpl->m, M, w.perm, w.dv, w.tm4, w.tmx, st));
-  if (w.ps_S) HIPCHK(launch_psum(w.tm4, M, w.ref4, w.lw, N, w.ps_chunks, w.ps_part, w.ps_S, st));
+  if (!w.ps_S) HIPCHK(launch_sort_perm(w.aY, M, w.perm, w.sws, st));
+  HIPCHK(launch_pack_tmpl(tmpl->x, tmpl->y, tmpl->z, w.aY, tmpl->m, M, w.ps_S ? nullptr : w.perm, w.dv, w.tm4, w.tmx,
+                          st));
+  if (w.ps_S) HIPCHK(launch_psum(w.tm4, M, w.ref4, w.lw, N, w.ps_chunks, want_s2, w.ps_part, w.ps_S, st));
+  return SGR_OK;
+}
+
+// All iterations of the pair sums in one launch; sync: 64 ints, then the
+// exchange words.
+int run_loop(sgr_ctx* ctx, LoopReg g, int ppt, int* sync, int t0, int t1, hipStream_t st) {
+  g.xch = reinterpret_cast<unsigned long long*>(sync + 64);
+  HIPCHK(launch_fill_i(sync, 64 + 2 * (int)loop_words(g.nb), st));
+  HIPCHK(launch_pinv_loop(g, ppt, sync, t0, t1, ctx->loop_spins, st));
   return SGR_OK;
 }
 
@@ -579,8 +707,12 @@ int setup_single(const sgr_cloud* tmpl, const sgr_cloud* ref, const PrepParams& 
 // its energy is the FP32 one.
 int run_single_loop(sgr_ctx* ctx, GraphCache& gc, const sgr_cloud* tmpl, const sgr_cloud* ref,
                     const sgr_params* prm, const SingleWs& w, sgr_pose* inout, double* stats, int t0, int t1,
-                    hipStream_t st) {
+                    int level, hipStream_t st) {
   const int M = (int)tmpl->n, N = (int)ref->n;
+  if (w.loop_nb > 0)
+    return run_loop(ctx, LoopReg{w.tm4, w.tmx, w.ps_S, (double*)inout, w.pose0 + 13 * (size_t)level, w.dv, stats,
+                                 nullptr, nullptr, M, w.loop_nb},
+                    w.loop_ppt, w.sync, t0, t1, st);
   const int pm = pmode_of(prm->p);
   auto loop = [&](hipStream_t s) -> int {
     for (int t = t0; t < t1; ++t) {
@@ -667,14 +799,20 @@ struct VecWs {
   float2* tmx = nullptr;
   double* ps_part = nullptr;
   double* ps_S = nullptr;
+  int* sync = nullptr;      // as in SingleWs
+  double* pose0 = nullptr;
+  int loop_ppt = 0, loop_nb = 0;
 };
 
-int carve_vec(sgr_ctx* ctx, int M, int N, int D, bool with_f, bool with_mom, VecWs& w, bool pinv = false) {
+int carve_vec(sgr_ctx* ctx, int M, int N, int D, bool with_f, bool with_mom, VecWs& w, bool pinv = false,
+              bool use_loop = false) {
   w.K = vforce_K(D);
   w.n_cu = ctx->n_cu;
   w.n_chunks = vforce_chunks(M, N, ctx->n_cu);
   w.slots = vforce_n_iblk(M) * w.n_chunks;
   // every template row may be a far row, with a wrench slot of its own
+  w.loop_ppt = pinv ? loop_points(M, 1) : 0;
+  w.loop_nb = pinv && use_loop ? loop_blocks(M, w.loop_ppt) : 0;
   const int wslots = pinv ? std::max(w.slots + M, pinv_blocks(M)) : w.slots + M;
   for (int pass = 0; pass < 2; ++pass) {
     Carve c{pass ? ctx->ws : nullptr};
@@ -696,6 +834,8 @@ int carve_vec(sgr_ctx* ctx, int M, int N, int D, bool with_f, bool with_mom, Vec
       w.tmx = c.take<float2>(M);
       w.ps_part = c.take<double>((size_t)w.n_chunks * M * 5);
       w.ps_S = c.take<double>((size_t)M * 5);
+      w.sync = c.take<int>(64 + 2 * loop_words(w.loop_nb));
+      w.pose0 = c.take<double>(13);
     }
     if (!pass)
       if (int e = ensure_ws(ctx, c.off)) return e;
@@ -905,6 +1045,7 @@ int sgr_create(sgr_ctx** out, int device) {
     return fail(SGR_EHIP, "stream creation failed");
   }
   c->tiles.init(c->n_cu);
+  if (const char* v = std::getenv("SGR_LOOP_SPINS")) c->loop_spins = std::max(1, std::atoi(v));
   if (int e = scratch_init(device)) {
     (void)hipStreamDestroy(c->cap);
     delete c;
@@ -1075,20 +1216,30 @@ int sgr_register(sgr_ctx* ctx, const sgr_cloud* tmpl, const sgr_cloud* ref, cons
   HIPCHK(hipSetDevice(ctx->device));
   hipStream_t st = (hipStream_t)stream;
   const int M = (int)tmpl->n, N = (int)ref->n;
-  SingleWs w;
-  if (int e = carve_single(ctx, M, N, prm, prm->k, w, false)) return e;
-  HIPCHK(launch_grid_knn(ref->x, ref->y, ref->z, N, prm->k, w.aX, nullptr, w.gws, st));
-  HIPCHK(launch_grid_knn(tmpl->x, tmpl->y, tmpl->z, M, prm->k, w.aY, nullptr, w.gws, st));
-  HIPCHK(launch_moments(ref->x, ref->y, ref->z, N, w.mom + 10, st));
-  HIPCHK(launch_moments(tmpl->x, tmpl->y, tmpl->z, M, w.mom, st));
-  if (int e = setup_single(tmpl, ref, prep_of(prm), w, st)) return e;
-  if (int e = run_single_loop(ctx, ctx->gc, tmpl, ref, prm, w, inout, stats, 0, prm->E, st)) return e;
-  int32_t status = 0;
-  HIPCHK(hipMemcpyAsync(&status, &w.dv->status, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-  HIPCHK(hipStreamSynchronize(st));
-  if (status & ST_DEGENERATE) return fail(SGR_EDEGENERATE, "degenerate input: zero variance or zero curvature spread");
-  if (status) return fail(SGR_ENUMERIC, "numeric failure in the update (status " + std::to_string(status) + ")");
-  return SGR_OK;
+  for (const bool use_loop : {true, false}) {
+    SingleWs w;
+    if (int e = carve_single(ctx, M, N, prm, prm->k, w, false, use_loop, 1)) return e;
+    HIPCHK(launch_grid_knn(ref->x, ref->y, ref->z, N, prm->k, w.aX, nullptr, w.gws, st));
+    HIPCHK(launch_grid_knn(tmpl->x, tmpl->y, tmpl->z, M, prm->k, w.aY, nullptr, w.gws, st));
+    HIPCHK(launch_moments(ref->x, ref->y, ref->z, N, w.mom + 10, st));
+    HIPCHK(launch_moments(tmpl->x, tmpl->y, tmpl->z, M, w.mom, st));
+    if (int e = setup_single(tmpl, ref, prep_of(prm), stats != nullptr, w, st)) return e;
+    if (int e = run_single_loop(ctx, ctx->gc, tmpl, ref, prm, w, inout, stats, 0, prm->E, 0, st)) return e;
+    int32_t status = 0;
+    HIPCHK(hipMemcpyAsync(&status, &w.dv->status, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+    HIPCHK(hipStreamSynchronize(st));
+    if (status & ST_STALLED) {
+      // the loop's blocks were not resident together: from the initial pose
+      // again, with one launch per iteration
+      HIPCHK(hipMemcpyAsync(inout, w.pose0, sizeof(sgr_pose), hipMemcpyDeviceToDevice, st));
+      continue;
+    }
+    if (status & ST_DEGENERATE)
+      return fail(SGR_EDEGENERATE, "degenerate input: zero variance or zero curvature spread");
+    if (status) return fail(SGR_ENUMERIC, "numeric failure in the update (status " + std::to_string(status) + ")");
+    return SGR_OK;
+  }
+  return fail(SGR_EHIP, "the iteration loop stalled");  // not reached: only the first pass can stall
 }
 
 int sgr_descriptors_radius(sgr_ctx* ctx, const sgr_cloud* c, float r2, float* a_out, int32_t* count_out,
@@ -1132,40 +1283,49 @@ int sgr_register_pyramid(sgr_ctx* ctx, const sgr_cloud* tmpl, const sgr_cloud* r
   HIPCHK(hipSetDevice(ctx->device));
   hipStream_t st = (hipStream_t)stream;
   const int M = (int)tmpl->n, N = (int)ref->n;
-  SingleWs w;
-  if (int e = carve_single(ctx, M, N, prm, kmax, w, radius)) return e;
-  if ((int)ctx->gcp.size() < n_levels) ctx->gcp.resize(n_levels);
-  HIPCHK(launch_moments(ref->x, ref->y, ref->z, N, w.mom + 10, st));
-  HIPCHK(launch_moments(tmpl->x, tmpl->y, tmpl->z, M, w.mom, st));
-  std::vector<int32_t> status(n_levels, 0);
-  int t0 = 0;
-  for (int l = 0; l < n_levels; ++l) {
-    const sgr_level& v = levels[l];
-    if (v.radius_scale > 0) {
-      const double s2 = v.radius_scale * v.radius_scale;
-      HIPCHK(launch_radius_desc(ref->x, ref->y, ref->z, N, w.mom + 10, s2, 0.f, w.aX, nullptr, w.gws, st));
-      HIPCHK(launch_radius_desc(tmpl->x, tmpl->y, tmpl->z, M, w.mom, s2, 0.f, w.aY, nullptr, w.gws, st));
-    } else {
-      HIPCHK(launch_grid_knn(ref->x, ref->y, ref->z, N, v.k, w.aX, nullptr, w.gws, st));
-      HIPCHK(launch_grid_knn(tmpl->x, tmpl->y, tmpl->z, M, v.k, w.aY, nullptr, w.gws, st));
+  for (const bool use_loop : {true, false}) {
+    SingleWs w;
+    if (int e = carve_single(ctx, M, N, prm, kmax, w, radius, use_loop, n_levels)) return e;
+    if ((int)ctx->gcp.size() < n_levels) ctx->gcp.resize(n_levels);
+    HIPCHK(launch_moments(ref->x, ref->y, ref->z, N, w.mom + 10, st));
+    HIPCHK(launch_moments(tmpl->x, tmpl->y, tmpl->z, M, w.mom, st));
+    std::vector<int32_t> status(n_levels, 0);
+    int t0 = 0;
+    for (int l = 0; l < n_levels; ++l) {
+      const sgr_level& v = levels[l];
+      if (v.radius_scale > 0) {
+        const double s2 = v.radius_scale * v.radius_scale;
+        HIPCHK(launch_radius_desc(ref->x, ref->y, ref->z, N, w.mom + 10, s2, 0.f, w.aX, nullptr, w.gws, st));
+        HIPCHK(launch_radius_desc(tmpl->x, tmpl->y, tmpl->z, M, w.mom, s2, 0.f, w.aY, nullptr, w.gws, st));
+      } else {
+        HIPCHK(launch_grid_knn(ref->x, ref->y, ref->z, N, v.k, w.aX, nullptr, w.gws, st));
+        HIPCHK(launch_grid_knn(tmpl->x, tmpl->y, tmpl->z, M, v.k, w.aY, nullptr, w.gws, st));
+      }
+      PrepParams P = prep_of(prm);
+      P.sigma_scale = v.sigma_scale;
+      if (int e = setup_single(tmpl, ref, P, stats != nullptr, w, st)) return e;
+      if (int e = run_single_loop(ctx, ctx->gcp[l], tmpl, ref, prm, w, inout, stats, t0, t0 + v.iters, l, st)) return e;
+      HIPCHK(hipMemcpyAsync(&status[l], &w.dv->status, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+      t0 += v.iters;
     }
-    PrepParams P = prep_of(prm);
-    P.sigma_scale = v.sigma_scale;
-    if (int e = setup_single(tmpl, ref, P, w, st)) return e;
-    if (int e = run_single_loop(ctx, ctx->gcp[l], tmpl, ref, prm, w, inout, stats, t0, t0 + v.iters, st)) return e;
-    HIPCHK(hipMemcpyAsync(&status[l], &w.dv->status, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    t0 += v.iters;
+    HIPCHK(hipStreamSynchronize(st));
+    int32_t any = 0;
+    for (int l = 0; l < n_levels; ++l) any |= status[l];
+    if (any & ST_STALLED) {
+      HIPCHK(hipMemcpyAsync(inout, w.pose0, sizeof(sgr_pose), hipMemcpyDeviceToDevice, st));
+      continue;
+    }
+    for (int l = 0; l < n_levels; ++l) {
+      if (status[l] & ST_DEGENERATE)
+        return fail(SGR_EDEGENERATE, "degenerate input at level " + std::to_string(l) +
+                                         ": zero variance or zero curvature spread");
+      if (status[l])
+        return fail(SGR_ENUMERIC, "numeric failure in the update at level " + std::to_string(l) + " (status " +
+                                      std::to_string(status[l]) + ")");
+    }
+    return SGR_OK;
   }
-  HIPCHK(hipStreamSynchronize(st));
-  for (int l = 0; l < n_levels; ++l) {
-    if (status[l] & ST_DEGENERATE)
-      return fail(SGR_EDEGENERATE, "degenerate input at level " + std::to_string(l) +
-                                       ": zero variance or zero curvature spread");
-    if (status[l])
-      return fail(SGR_ENUMERIC, "numeric failure in the update at level " + std::to_string(l) + " (status " +
-                                    std::to_string(status[l]) + ")");
-  }
-  return SGR_OK;
+  return fail(SGR_EHIP, "the iteration loop stalled");  // not reached: only the first pass can stall
 }
 
 int sgr_descriptors_hn(sgr_ctx* ctx, const sgr_cloud* c, int k, int D, float* h_out, sgr_stream_t stream) {
@@ -1226,53 +1386,65 @@ int sgr_register_vec(sgr_ctx* ctx, const sgr_cloud* tmpl, const float* a_t, cons
   hipStream_t st = (hipStream_t)stream;
   const int M = (int)tmpl->n, N = (int)ref->n;
   const bool pinv = (prm->flags & FLAG_PINV) != 0;
-  VecWs w;
-  if (int e = carve_vec(ctx, M, N, D, false, true, w, pinv)) return e;
-  HIPCHK(launch_moments(ref->x, ref->y, ref->z, N, w.mom + 10, st));
-  HIPCHK(launch_moments(tmpl->x, tmpl->y, tmpl->z, M, w.mom, st));
-  if (int e = setup_vec(tmpl, a_t, ref, a_r, D, w.mom, w.mom + 10, prm, w, st)) return e;
-  if (pinv) {
-    // the pair sums once: one pass of the vector kernel writing them per chunk
-    VForceArgs A = vargs(tmpl, ref, w, (const double*)inout, 0);
-    A.spart = w.ps_part;
-    HIPCHK(run_vforce(A, a_t, D, w, true, false, nullptr, st));
-    HIPCHK(launch_psum_reduce(w.ps_part, M, w.n_chunks, w.ps_S, st));
-    HIPCHK(launch_pack_plain(tmpl->x, tmpl->y, tmpl->z, tmpl->m, M, w.tm4, w.tmx, st));
-  }
-  auto loop = [&](hipStream_t s) -> int {
-    for (int t = 0; t < prm->E; ++t) {
-      const bool wu = stats != nullptr;  // U is read only from the stats
-      int used = w.slots;
-      if (pinv) {
-        HIPCHK(launch_pinv(w.tm4, w.tmx, w.ps_S, M, (const double*)inout, w.dv, t, wu, w.wpart, s));
-        used = pinv_blocks(M);
-      } else {
-        HIPCHK(run_vforce(vargs(tmpl, ref, w, (const double*)inout, t), a_t, D, w, wu, false, &used, s));
-      }
-      HIPCHK(launch_update(w.wpart, used, (const double*)inout, (double*)inout, w.dv, t, 0.0, 1, nullptr,
-                           stats ? stats + (size_t)t * STATS_STRIDE : nullptr, s));
+  for (const bool use_loop : {true, false}) {
+    VecWs w;
+    if (int e = carve_vec(ctx, M, N, D, false, true, w, pinv, use_loop)) return e;
+    HIPCHK(launch_moments(ref->x, ref->y, ref->z, N, w.mom + 10, st));
+    HIPCHK(launch_moments(tmpl->x, tmpl->y, tmpl->z, M, w.mom, st));
+    if (int e = setup_vec(tmpl, a_t, ref, a_r, D, w.mom, w.mom + 10, prm, w, st)) return e;
+    if (pinv) {
+      // the pair sums once: one pass of the vector kernel writing them per chunk
+      VForceArgs A = vargs(tmpl, ref, w, (const double*)inout, 0);
+      A.spart = w.ps_part;
+      HIPCHK(run_vforce(A, a_t, D, w, true, false, nullptr, st));
+      HIPCHK(launch_psum_reduce(w.ps_part, M, w.n_chunks, w.ps_S, st));
+      HIPCHK(launch_pack_plain(tmpl->x, tmpl->y, tmpl->z, tmpl->m, M, w.tm4, w.tmx, st));
     }
+    auto loop = [&](hipStream_t s) -> int {
+      for (int t = 0; t < prm->E; ++t) {
+        const bool wu = stats != nullptr;  // U is read only from the stats
+        int used = w.slots;
+        if (pinv) {
+          HIPCHK(launch_pinv(w.tm4, w.tmx, w.ps_S, M, (const double*)inout, w.dv, t, wu, w.wpart, s));
+          used = pinv_blocks(M);
+        } else {
+          HIPCHK(run_vforce(vargs(tmpl, ref, w, (const double*)inout, t), a_t, D, w, wu, false, &used, s));
+        }
+        HIPCHK(launch_update(w.wpart, used, (const double*)inout, (double*)inout, w.dv, t, 0.0, 1, nullptr,
+                             stats ? stats + (size_t)t * STATS_STRIDE : nullptr, s));
+      }
+      return SGR_OK;
+    };
+    if (w.loop_nb > 0) {
+      if (int e = run_loop(ctx, LoopReg{w.tm4, w.tmx, w.ps_S, (double*)inout, w.pose0, w.dv, stats, nullptr, nullptr, M,
+                                        w.loop_nb},
+                           w.loop_ppt, w.sync, 0, prm->E, st))
+        return e;
+    } else if ((prm->flags & FLAG_NO_GRAPH) || prm->E < 2) {
+      if (int e = loop(st)) return e;
+    } else {
+      std::vector<uint8_t> key;
+      const void* ptrs[12] = {tmpl->x, tmpl->y, tmpl->z, tmpl->m, ref->x, ref->y, ref->z, ref->m, inout, stats, a_t, a_r};
+      key_add(key, ptrs, 12);
+      const int64_t dims[5] = {M, N, D, w.half ? 1 : 0, w.n_far};
+      key_add(key, dims, 5);
+      key_add(key, prm, 1);
+      const void* wsp = ctx->ws;
+      key_add(key, &wsp, 1);
+      if (int e = run_graph(ctx, ctx->gcv, key, loop, st)) return e;
+    }
+    int32_t status = 0;
+    HIPCHK(hipMemcpyAsync(&status, &w.dv->status, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+    HIPCHK(hipStreamSynchronize(st));
+    if (status & ST_STALLED) {
+      HIPCHK(hipMemcpyAsync(inout, w.pose0, sizeof(sgr_pose), hipMemcpyDeviceToDevice, st));
+      continue;
+    }
+    if (status & ST_DEGENERATE) return fail(SGR_EDEGENERATE, "degenerate input: zero variance or zero descriptor spread");
+    if (status) return fail(SGR_ENUMERIC, "numeric failure in the update (status " + std::to_string(status) + ")");
     return SGR_OK;
-  };
-  if ((prm->flags & FLAG_NO_GRAPH) || prm->E < 2) {
-    if (int e = loop(st)) return e;
-  } else {
-    std::vector<uint8_t> key;
-    const void* ptrs[12] = {tmpl->x, tmpl->y, tmpl->z, tmpl->m, ref->x, ref->y, ref->z, ref->m, inout, stats, a_t, a_r};
-    key_add(key, ptrs, 12);
-    const int64_t dims[5] = {M, N, D, w.half ? 1 : 0, w.n_far};
-    key_add(key, dims, 5);
-    key_add(key, prm, 1);
-    const void* wsp = ctx->ws;
-    key_add(key, &wsp, 1);
-    if (int e = run_graph(ctx, ctx->gcv, key, loop, st)) return e;
   }
-  int32_t status = 0;
-  HIPCHK(hipMemcpyAsync(&status, &w.dv->status, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-  HIPCHK(hipStreamSynchronize(st));
-  if (status & ST_DEGENERATE) return fail(SGR_EDEGENERATE, "degenerate input: zero variance or zero descriptor spread");
-  if (status) return fail(SGR_ENUMERIC, "numeric failure in the update (status " + std::to_string(status) + ")");
-  return SGR_OK;
+  return fail(SGR_EHIP, "the iteration loop stalled");  // not reached: only the first pass can stall
 }
 
 int sgr_residual(sgr_ctx* ctx, const sgr_cloud* tmpl, const sgr_cloud* ref, const sgr_pose* pose, const int32_t* corr,

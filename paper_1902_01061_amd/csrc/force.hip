@@ -161,7 +161,7 @@ __device__ inline void pack_tmpl_body(const float* __restrict__ x, const float* 
                                       const Derived& D, float4* __restrict__ tm4, float2* __restrict__ tmx,
                                       int ip) {
   if (ip >= M) return;
-  const int i = perm[ip];
+  const int i = perm ? perm[ip] : ip;
   const float a = aY[i];
   tm4[ip] = make_float4(x[i], y[i], z[i], (float)(((double)a - D.abar) * D.bscale));
   tmx[ip] = make_float2(a, mY ? mY[i] : 1.f);

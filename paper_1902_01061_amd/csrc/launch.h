@@ -259,28 +259,68 @@ hipError_t launch_normal_hist(const float* x, const float* y, const float* z, in
                               void* ws, hipStream_t st);
 
 // Pose-independent pair sums of the p = 1 law: S[ip] = (sum_j c, sum_j c x_j
-// (3), sum_j c |x_j|^2) per template point in visiting order, c the pair
-// weight exp2(lw_j - (b_i - b_j)^2), from the packed template and reference;
-// part holds pinv_chunks(M, N, n_cu) * M * 5 doubles.  launch_pinv is the
-// per-iteration force from them: pinv_blocks(M) wrench partials in wpart
-// (the layout of the force kernel, for launch_update).
+// (3), sum_j c |x_j|^2) per template point, c the pair weight exp2(lw_j -
+// (b_i - b_j)^2), from the packed template and reference; part holds
+// pinv_chunks(M, N, n_cu) * M * 5 doubles.  want_s2 = false leaves the fifth
+// sum, which only the energy reads, 0.
 int pinv_chunks(int M, int N, int n_cu);
-int pinv_blocks(int M);
 hipError_t launch_psum(const float4* tm4, int M, const float4* ref4, const float* lw, int N, int n_chunks,
-                       double* part, double* S, hipStream_t st);
-hipError_t launch_pinv(const float4* tm4, const float2* tmx, const double* S, int M, const double* pose,
-                       const Derived* dv, int t, bool wu, double* wpart, hipStream_t st);
+                       bool want_s2, double* part, double* S, hipStream_t st);
 // S[i] = sum over n_chunks of part[chunk][i] (5 values per point, fixed order).
 hipError_t launch_psum_reduce(const double* part, int M, int n_chunks, double* S, hipStream_t st);
-// Template in its own order for launch_pinv: (x0, y0, z0, 0) and (0, m).
+// Template in its own order for these kernels: (x0, y0, z0, 0) and (0, m).
 hipError_t launch_pack_plain(const float* x, const float* y, const float* z, const float* mY, int M, float4* tm4,
                              float2* tmx, hipStream_t st);
-// Batched forms: tblk lists (registration, block of 256 template points);
-// registration r's sums sit at template offset poff[r] of S.  regs_p is
+// One registration's sums in a batch: template, packed reference at ref_off,
+// S [M][5], and with several chunks the partial sums part [n_chunks][M][5].
+struct PsumReg {
+  const float4* tm4;
+  double* S;
+  double* part;
+  int64_t ref_off;
+  int M, N;
+  int n_chunks;
+  int pad;
+};
+// items: (registration, block of psum_batch_points() template points, chunk,
+// -) in decreasing cost; chunk_len a multiple of 256; chunked: some
+// registration has more than one chunk.
+int psum_batch_points();
+hipError_t launch_psum_batch(const PsumReg* regs, int n_regs, const int4* items, int n_items, int chunk_len,
+                             bool chunked, const float4* ref4, const float* lw, hipStream_t st);
+// The iterations from the sums: all of them in one launch
+// (launch_pinv_loop; ppt points per thread, g.nb blocks, exchange words and
+// ticket zeroed by the caller), or one force launch per iteration, which
+// writes pinv_blocks(M) wrench partials in the force kernel's layout for
+// launch_update: for registrations of more points than the loop takes
+// (loop_blocks = 0) and after a stall (ST_STALLED).
+constexpr int LP_MAX_BLOCKS = 64;
+struct LoopReg {
+  const float4* tm4;
+  const float2* tmx;
+  const double* S;
+  double* pose;                // in place
+  double* pose0;               // receives the pose as it was
+  Derived* dv;
+  double* stats;               // [E][STATS_STRIDE] or nullptr
+  double* energy;              // energy of the last iteration, or nullptr
+  unsigned long long* xch;     // loop_words(nb) words
+  int M, nb;
+};
+int loop_points(int64_t M_total, int n_regs);
+int loop_blocks(int M, int ppt);
+size_t loop_words(int nb);
+hipError_t launch_pinv_loop(const LoopReg& g, int ppt, int* ticket, int t0, int t1, int spins, hipStream_t st);
+// blocks: (registration, block within it), blocks of one registration in
+// order and together.
+hipError_t launch_pinv_loop_batch(const LoopReg* regs, const int2* blocks, int n_blocks, int ppt, int* ticket, int t0,
+                                  int t1, int spins, hipStream_t st);
+int pinv_blocks(int M);
+hipError_t launch_pinv(const float4* tm4, const float2* tmx, const double* S, int M, const double* pose,
+                       const Derived* dv, int t, bool wu, double* wpart, hipStream_t st);
+// Batched: tblk lists (registration, block of 256 template points); regs_p is
 // regs with wslot0 / n_items describing one wrench slot per listed block.
-hipError_t launch_psum_batch(const RegDesc* regs, const int2* tblk, int n_tblk, const int* poff, const float4* ref4,
-                             const float* lw, double* S, hipStream_t st);
-hipError_t launch_pinv_batch(const RegDesc* regs_p, const int2* tblk, int n_tblk, const int* poff, const double* S,
+hipError_t launch_pinv_batch(const RegDesc* regs_p, const int2* tblk, int n_tblk, const PsumReg* sums,
                              const double* poses, const Derived* dvs, int t, bool wu, double* wpart, hipStream_t st);
 
 // Curvature of the radius neighbourhood of every point: members have float32
