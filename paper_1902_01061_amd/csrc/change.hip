@@ -53,7 +53,7 @@ __global__ __launch_bounds__(256) void change_flags_kernel(const float* __restri
   flags[i] = f;
 }
 
-size_t change_workspace(int M, int N) { return grid_knn_workspace(N, 1) + 3 * (((size_t)M * 4 + 255) & ~size_t(255)); }
+size_t change_workspace(int M, int N) { return grid_nn_workspace(N, M) + 3 * (((size_t)M * 4 + 255) & ~size_t(255)); }
 
 hipError_t launch_change(const float* yx, const float* yy, const float* yz, const float* aY, int M, const float* xx,
                          const float* xy, const float* xz, const float* aX, int N, const double* pose, float tau2,
@@ -65,7 +65,7 @@ hipError_t launch_change(const float* yx, const float* yy, const float* yz, cons
   float* qz = (float*)(p + 2 * qb);
   void* gws = p + 3 * qb;
   hipLaunchKernelGGL(posed_exact_kernel, dim3((M + 255) / 256), dim3(256), 0, st, yx, yy, yz, M, pose, qx, qy, qz);
-  if (hipError_t e = launch_grid_nn(xx, xy, xz, N, qx, qy, qz, M, tau2, nn, key, gws, st)) return e;
+  if (hipError_t e = launch_grid_nn(xx, xy, xz, N, qx, qy, qz, M, tau2, false, nn, key, gws, st)) return e;
   hipLaunchKernelGGL(change_flags_kernel, dim3((M + 255) / 256), dim3(256), 0, st, aY, aX, nn, key, M, tau2, shape_thr,
                      flags);
   return hipGetLastError();

@@ -3,21 +3,38 @@
 // every operation rounded, ties by index), followed by the FP64
 // neighbourhood covariance and curvature (Sec. III-A).
 //
-// 1. grid_setup: bounding box of the finite points and a cell size h with
-//    about two points per cell of the bounding volume (fewer cells than the
-//    allocated maximum), shrunk for surfaces after a first count;
-// 2. counting sort of the points by cell (cell counts, exclusive scan,
-//    scatter); the order inside a cell does not matter because candidates
-//    are ranked by the (distance, index) key;
-// 3. one query per lane, in cell order (neighbouring lanes search the same
-//    cells): shells of cells at Chebyshev radius 0, 1, 2, ... are scanned
-//    until the current k-th distance is below the distance from the query to
-//    the unsearched region (with a margin that covers the float32 rounding
-//    of cell assignment and of the key), so no closer point can be missed;
-//    a query still open after shell 1 is handed over with its list and
-//    resumed where it stopped (a wave per query; in a batch, a lane per
-//    query for shell 2, then a wave per query).
-#include <utility>
+// 1. The grid (grid_small_kernel: one block, cells in LDS; or the grid_*
+//    kernels for large clouds): the bounding box of the finite points, a trial
+//    cell of two points per cell of the box, the occupancy of the trial
+//    cells, and the final cell for about grid_occ(k) points per occupied cell;
+//    then a counting sort of the points by cell.  The order inside a cell
+//    does not matter because candidates are ranked by the (distance, index)
+//    key, and neither does the cell size.
+// 2. knn_kernel: 16 lanes per query, queries in cell order.  The points of
+//    the 27 cells around the query's are read row by row (the cells of a
+//    row are adjacent in the sorted array, so a row is one span), and those
+//    nearer than every unsearched cell go to the query's list in LDS; k of
+//    them are the answer.  Where the query's own cell already holds k points
+//    (the dense parts of a depth frame), it is searched first and its k-th
+//    key limits the rows and cells of the rest; where the 27 cells hold k
+//    points but not near enough, their k-th key limits a second ring.  The
+//    list is ranked by counting (every lane counts the keys below its own),
+//    which needs neither a sorting network nor a register list.
+// 3. knn_far_kernel: the queries left over.  One wave per outlier in empty
+//    space, which looks at growing rings of cells and then at the blocks of
+//    8 x 8 x 8 cells that hold points.
+//
+// What bounds it: the number of candidates (about 11 occupied cells of a
+// surface) and the latency of three dependent loads per query, which many
+// small queries per CU hide.  One lane per query, as before, kept a sorted
+// list in registers and left a 1 024-point cloud on four CUs and a
+// 36 000-point one on 141.  Both search kernels, before and now:
+//    1 024 points, k = 24:    94 us,   23 us
+//   36 000 points, k = 24:   425 us,   77 us
+//  307 200 points, k = 16: 1 561 us,  355 us
+// and the build of the last, 600 us and 52 us (its cell scan was one block's).
+#include <algorithm>
+#include <cmath>
 #include <vector>
 
 #include "common.h"
@@ -28,711 +45,1120 @@ namespace sgr {
 struct GridInfo {
   float lo[3];
   float h;
+  double inv_h;
   int dims[3];
   int ncells;
   double ext[3];  // bounding-box extents (for re-sizing the cells)
 };
 
+// Workspace and arrays of one cloud's search.
+struct GridJob {
+  const float* x;
+  const float* y;
+  const float* z;
+  float* a_out;     // curvatures, or nullptr
+  int n, max_cells;
+  float occ;        // wanted occupancy (mean over the points of their cell's count)
+  float reach;      // cells up to twice smaller than this are made as large (0: none)
+  GridInfo* gi;
+  int* cell_of;     // [n] (packed)
+  int* rank;        // [n] rank of the point within its cell
+  int* counts;      // [max_cells]
+  int* starts;      // [max_cells + 1]
+  int* part;        // per-block partials of the large build (GRID_PART ints)
+  float4* spts;     // points in cell order, w = index
+  int* scell;       // their cells' coordinates, packed (pack_cell)
+  float4* p4;       // points in their own order, (x, y, z, 0)
+  int32_t* nbr;     // neighbour lists
+  int* blocks;      // [0] number of blocks of BLK^3 cells that hold points, then those (pack_cell)
+};
+
+// One job by value (one cloud), or a table of jobs and a (cloud, block) list.
+struct GridArgs {
+  GridJob one;
+  const GridJob* jobs;
+  const int2* bmap;
+};
+
+// The job of this block and the block's number within it; pointers marked as
+// global memory (gptr).
+__device__ inline GridJob job_of(const GridArgs& A, int& block, int* cloud = nullptr) {
+  int c = 0;
+  block = blockIdx.x;
+  if (A.jobs) {
+    const int2 cb = A.bmap[blockIdx.x];
+    c = cb.x;
+    block = cb.y;
+  }
+  if (cloud) *cloud = c;
+  GridJob J = A.jobs ? A.jobs[c] : A.one;
+  J.x = gptr(J.x), J.y = gptr(J.y), J.z = gptr(J.z), J.a_out = gptr(J.a_out), J.gi = gptr(J.gi);
+  J.cell_of = gptr(J.cell_of), J.rank = gptr(J.rank), J.counts = gptr(J.counts), J.starts = gptr(J.starts);
+  J.part = gptr(J.part), J.spts = gptr(J.spts), J.scell = gptr(J.scell), J.p4 = gptr(J.p4), J.nbr = gptr(J.nbr);
+  J.blocks = gptr(J.blocks);
+  return J;
+}
+__device__ inline GridJob job_at(const GridArgs& A, int c) {
+  GridJob J = A.jobs ? A.jobs[c] : A.one;
+  J.gi = gptr(J.gi), J.starts = gptr(J.starts), J.spts = gptr(J.spts), J.scell = gptr(J.scell), J.nbr = gptr(J.nbr);
+  J.blocks = gptr(J.blocks);
+  return J;
+}
+
+// ------------------------------------------------------------------- grid
 // Cell counts per axis for cell size h, grown by 10 % steps until the grid
 // has at most max_cells cells.
 __device__ inline void grid_dims(GridInfo& G, double h, int max_cells) {
   int d[3];
-  for (int it = 0; it < 200; ++it) {
+  for (int it = 0; it < 400; ++it) {
+    const double ih = 1.0 / h;
     long long tot = 1;
     for (int a = 0; a < 3; ++a) {
-      d[a] = (int)fmin(1024.0, floor(G.ext[a] / h) + 1.0);
+      d[a] = (int)fmin(1024.0, floor(G.ext[a] * ih) + 1.0);
       tot *= d[a];
     }
     if (tot <= max_cells) break;
     h *= 1.1;
   }
   G.h = (float)h;
+  G.inv_h = 1.0 / (double)G.h;
   for (int a = 0; a < 3; ++a) G.dims[a] = d[a];
   G.ncells = d[0] * d[1] * d[2];
 }
 
-constexpr int GQ_BT = 256;
-constexpr int KNN_RCAP = 1;  // last shell the one-lane pass searches before handing a query over
-constexpr int SCAN_B = 1024;
-
-// Bodies of the grid kernels, shared by the one-cloud kernels and their
-// batched forms (a table of clouds, one launch per phase for all of them).
-__device__ inline void grid_setup_body(const float* __restrict__ X, const float* __restrict__ Y,
-                                       const float* __restrict__ Zc, int n, int max_cells, GridInfo* __restrict__ gi,
-                                       int* __restrict__ far, int* __restrict__ far2) {
-  // counts of the queries handed over by the one-lane pass (far) and, in a
-  // batch, by the pass that resumes them for one more shell (far2)
-  if (threadIdx.x == 0) {
-    far[0] = 0;
-    if (far2) far2[0] = 0;
-  }
-  __shared__ float red[16][6];
-  float v[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
-  // the bounding box of the finite points (an infinite coordinate would
-  // make the box infinite and the grid one row of cells)
-  for (int i = threadIdx.x; i < n; i += 1024) {
-    const float p[3] = {X[i], Y[i], Zc[i]};
-    if (!(isfinite(p[0]) && isfinite(p[1]) && isfinite(p[2]))) continue;
-    for (int a = 0; a < 3; ++a) {
-      v[a] = fminf(v[a], p[a]);
-      v[3 + a] = fmaxf(v[3 + a], p[a]);
-    }
-  }
-  for (int a = 0; a < 6; ++a) {
-    float m = v[a];
-    for (int off = 32; off > 0; off >>= 1) {
-      const float o = __shfl_xor(m, off, 64);
-      m = a < 3 ? fminf(m, o) : fmaxf(m, o);
-    }
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][a] = m;
-  }
-  __syncthreads();
-  if (threadIdx.x != 0) return;
-  for (int a = 0; a < 6; ++a)
-    for (int w = 1; w < 16; ++w) red[0][a] = a < 3 ? fminf(red[0][a], red[w][a]) : fmaxf(red[0][a], red[w][a]);
+// Trial grid from the box of the finite points (lo > hi: none): about two
+// points per cell of the bounding volume; flat or linear clouds fall back to
+// their non-degenerate extents.
+__device__ inline GridInfo grid_trial(const float box[6], int n, int max_cells) {
   GridInfo G;
   double e[3];
   for (int a = 0; a < 3; ++a) {
-    const bool any = red[0][a] <= red[0][3 + a];  // some finite point
-    G.lo[a] = any ? red[0][a] : 0.f;
-    e[a] = any ? (double)red[0][3 + a] - (double)red[0][a] : 0.0;
+    const bool any = box[a] <= box[3 + a];  // some finite point
+    G.lo[a] = any ? box[a] : 0.f;
+    e[a] = any ? (double)box[3 + a] - (double)box[a] : 0.0;
+    G.ext[a] = e[a];
   }
-  // cell size for about two points per cell of the bounding volume; flat or
-  // linear clouds fall back to their non-degenerate extents
-  double s[3] = {e[0], e[1], e[2]};
-  for (int i = 0; i < 2; ++i)
-    for (int j = 0; j < 2 - i; ++j)
-      if (s[j] < s[j + 1]) {
-        const double t = s[j];
-        s[j] = s[j + 1];
-        s[j + 1] = t;
-      }
-  // first guess: 2 points per cell of the bounding box (a volume); for
-  // surfaces grid_refine_kernel then shrinks the cells
+  const double hi = fmax(e[0], fmax(e[1], e[2])), lo = fmin(e[0], fmin(e[1], e[2]));
+  const double mid = fmax(fmin(e[0], e[1]), fmin(fmax(e[0], e[1]), e[2]));
   const double rho = 2.0;
-  for (int a = 0; a < 3; ++a) G.ext[a] = e[a];
   double h;
-  if (s[2] > 1e-6 * s[0])
-    h = cbrt(s[0] * s[1] * s[2] * rho / n);
-  else if (s[1] > 1e-6 * s[0])
-    h = sqrt(s[0] * s[1] * rho / n);
+  if (lo > 1e-6 * hi)
+    h = cbrt(hi * mid * lo * rho / n);
+  else if (mid > 1e-6 * hi)
+    h = sqrt(hi * mid * rho / n);
   else
-    h = s[0] * rho / n;
+    h = hi * rho / n;
   if (!(h > 0) || !isfinite(h)) h = 1.0;
   grid_dims(G, h, max_cells);
-  *gi = G;
+  return G;
 }
 
-__global__ __launch_bounds__(1024) void grid_setup_kernel(const float* __restrict__ X, const float* __restrict__ Y,
-                                                          const float* __restrict__ Zc, int n, int max_cells,
-                                                          GridInfo* __restrict__ gi, int* __restrict__ far) {
-  grid_setup_body(X, Y, Zc, n, max_cells, gi, far, nullptr);
+// Final cell size from the trial grid's occupancy mu, the mean over the
+// points of their cell's count.  Scans are surfaces, whose counts go with the
+// side squared; a cloud with fewer points per cell than wanted is taken as a
+// volume.
+// A search for points within `reach` settles every query in its 27 cells
+// when they are that large.
+__device__ inline void grid_resize(GridInfo& G, double mu, const GridJob& J) {
+  const double f = (double)J.occ / mu;
+  grid_dims(G, (double)G.h * (f < 1.0 ? sqrt(f) : cbrt(f)), J.max_cells);
+  if (G.h < J.reach && J.reach <= 2.f * G.h) grid_dims(G, (double)J.reach, J.max_cells);
 }
 
-// Second look at the cell size, from the first count: scans are surfaces
-// (often with dense clusters), whose occupied cells hold many more points
-// than the 2 per cell of a volume, and a query inside them meets hundreds of
-// candidates.  With mu the mean count of the occupied cells, the cell side
-// is scaled by sqrt(6 / mu) when mu > 6 (surface scaling: counts go with
-// the side squared), and left as it is for volume-like clouds.  The caller
-// counts again with the new grid.  (Measured on the scan clouds: queries in
-// their clusters dominate the search time at 2 points per cell.)
-__device__ inline void grid_refine_body(const int* __restrict__ counts, int n, int max_cells,
-                                        GridInfo* __restrict__ gi) {
-  __shared__ int red[16];
-  const GridInfo G0 = *gi;
-  int occ = 0;
-  for (int c = threadIdx.x; c < G0.ncells; c += 1024) occ += counts[c] > 0;
-  for (int off = 32; off > 0; off >>= 1) occ += __shfl_xor(occ, off, 64);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = occ;
-  __syncthreads();
-  if (threadIdx.x != 0) return;
-  occ = 0;
-  for (int w = 0; w < 16; ++w) occ += red[w];
-  const double mu = (double)n / (double)max(occ, 1);
-  if (!(mu > 6.0)) return;
-  GridInfo G = G0;
-  grid_dims(G, (double)G0.h * sqrt(6.0 / mu), max_cells);
-  *gi = G;
-}
-
-__global__ __launch_bounds__(1024) void grid_refine_kernel(const int* __restrict__ counts, int n, int max_cells,
-                                                           GridInfo* __restrict__ gi) {
-  grid_refine_body(counts, n, max_cells, gi);
-}
+// Wanted occupancy for k neighbours.  Counted over surfaces of even
+// density, a query of occupancy 0.45 k finds twice k points within the distance its 27 cells
+// cover, among five times k candidates, and one in fifty finds fewer than k;
+// at 0.3 k it is one in four, at 0.7 k the candidates are nine times k.
+inline float grid_occ(int k) { return std::max(2.0f, 0.5f * (float)k); }
 
 // Cell coordinates and cell faces are computed in FP64 so that rounding
 // cannot move a point across a face by more than a negligible fraction of a
 // cell, whatever the offset of the cloud from the origin.
-__device__ inline int cell_coord(float p, float lo, float h, int dim) {
-  const double u = floor(((double)p - (double)lo) / (double)h);
-  const int c = u < 0.0 ? 0 : (u >= (double)dim ? dim - 1 : (int)u);
-  return c;
+__device__ inline int cell_coord(float p, float lo, double inv_h, int dim) {
+  const double u = floor(((double)p - (double)lo) * inv_h);
+  return u < 0.0 ? 0 : (u >= (double)dim ? dim - 1 : (int)u);
 }
 
-__device__ inline void grid_count_point(const float* __restrict__ X, const float* __restrict__ Y,
-                                        const float* __restrict__ Zc, int n, const GridInfo* __restrict__ gi,
-                                        int* __restrict__ cell_of, int* __restrict__ counts, int i) {
-  if (i >= n) return;
-  const GridInfo& G = *gi;
-  const int cx = cell_coord(X[i], G.lo[0], G.h, G.dims[0]);
-  const int cy = cell_coord(Y[i], G.lo[1], G.h, G.dims[1]);
-  const int cz = cell_coord(Zc[i], G.lo[2], G.h, G.dims[2]);
-  const int c = (cz * G.dims[1] + cy) * G.dims[0] + cx;
-  cell_of[i] = c;
-  atomicAdd(&counts[c], 1);
+__device__ inline int cell_index(const GridInfo& G, const int c[3]) {
+  return (c[2] * G.dims[1] + c[1]) * G.dims[0] + c[0];
 }
-
-__global__ __launch_bounds__(256) void grid_count_kernel(const float* __restrict__ X, const float* __restrict__ Y,
-                                                         const float* __restrict__ Zc, int n,
-                                                         const GridInfo* __restrict__ gi, int* __restrict__ cell_of,
-                                                         int* __restrict__ counts) {
-  grid_count_point(X, Y, Zc, n, gi, cell_of, counts, blockIdx.x * 256 + threadIdx.x);
+__device__ inline void cell_of_point(const GridInfo& G, float x, float y, float z, int c[3]) {
+  c[0] = cell_coord(x, G.lo[0], G.inv_h, G.dims[0]);
+  c[1] = cell_coord(y, G.lo[1], G.inv_h, G.dims[1]);
+  c[2] = cell_coord(z, G.lo[2], G.inv_h, G.dims[2]);
 }
+__device__ inline int cell_index(const GridInfo& G, float x, float y, float z) {
+  int c[3];
+  cell_of_point(G, x, y, z, c);
+  return cell_index(G, c);
+}
+// At most 1024 cells per axis.
+__device__ inline int pack_cell(const int c[3]) { return c[0] | c[1] << 10 | c[2] << 20; }
 
-// Exclusive scan of counts[0, m) into starts[0, m], in three passes.
-__global__ __launch_bounds__(SCAN_B) void scan_local_kernel(const int* __restrict__ in, int m, int* __restrict__ out,
-                                                            int* __restrict__ bsum) {
-  __shared__ int s[SCAN_B];
-  const int i = blockIdx.x * SCAN_B + threadIdx.x;
-  const int v = i < m ? in[i] : 0;
-  s[threadIdx.x] = v;
+// Box of the finite points among the block's (points base + tid, stride):
+// an infinite coordinate would make the grid one row of cells.
+template <int BT>
+__device__ inline void box_of(const GridJob& J, int first, int stride, float box[6], float* lds) {
+  float v[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
+#pragma unroll 4
+  for (int i = first + threadIdx.x; i < J.n; i += stride) {
+    const float p[3] = {J.x[i], J.y[i], J.z[i]};
+    const bool fin = isfinite(p[0]) && isfinite(p[1]) && isfinite(p[2]);
+    for (int a = 0; a < 3; ++a) {
+      v[a] = fminf(v[a], fin ? p[a] : INFINITY);
+      v[3 + a] = fmaxf(v[3 + a], fin ? p[a] : -INFINITY);
+    }
+  }
+  for (int a = 0; a < 6; ++a) {
+    float m = a < 3 ? v[a] : -v[a];
+    m = fminf(m, __shfl_xor(m, 32, 64));
+    m = fminf(m, __shfl_xor(m, 16, 64));
+    m = fminf(m, __uint_as_float(xor_lane_u<8>(__float_as_uint(m))));
+    m = fminf(m, __uint_as_float(xor_lane_u<4>(__float_as_uint(m))));
+    m = fminf(m, __uint_as_float(xor_lane_u<2>(__float_as_uint(m))));
+    m = fminf(m, __uint_as_float(xor_lane_u<1>(__float_as_uint(m))));
+    if ((threadIdx.x & 63) == 0) lds[(threadIdx.x >> 6) * 6 + a] = m;
+  }
   __syncthreads();
-  for (int off = 1; off < SCAN_B; off <<= 1) {
-    const int t = threadIdx.x >= off ? s[threadIdx.x - off] : 0;
-    __syncthreads();
-    s[threadIdx.x] += t;
-    __syncthreads();
+  for (int a = 0; a < 6; ++a) {
+    float m = lds[a];
+    for (int w = 1; w < BT / 64; ++w) m = fminf(m, lds[w * 6 + a]);
+    box[a] = a < 3 ? m : -m;
   }
-  if (i < m) out[i] = s[threadIdx.x] - v;
-  if (threadIdx.x == SCAN_B - 1) bsum[blockIdx.x] = s[threadIdx.x];
+  __syncthreads();
 }
 
-__global__ __launch_bounds__(1024) void scan_blocks_kernel(int* __restrict__ bsum, int nb) {
-  // serial over block sums in one thread per 1024-chunk, nb is small
-  if (threadIdx.x != 0) return;
-  int acc = 0;
-  for (int b = 0; b < nb; ++b) {
-    const int v = bsum[b];
-    bsum[b] = acc;
-    acc += v;
-  }
-  bsum[nb] = acc;
-}
-
-__global__ __launch_bounds__(SCAN_B) void scan_add_kernel(int* __restrict__ out, int m, const int* __restrict__ bsum,
-                                                          int nb) {
-  const int i = blockIdx.x * SCAN_B + threadIdx.x;
-  if (i < m) out[i] += bsum[blockIdx.x];
-  if (blockIdx.x == 0 && threadIdx.x == 0) out[m] = bsum[nb];
-}
-
-// Also packs the point, in its own order, as p4[i] = (x, y, z, 0): one
-// 16-byte load per neighbour for the curvature instead of three.
-__device__ inline void grid_scatter_point(const float* __restrict__ X, const float* __restrict__ Y,
-                                          const float* __restrict__ Zc, int n, const int* __restrict__ cell_of,
-                                          const int* __restrict__ starts, int* __restrict__ cursor,
-                                          float4* __restrict__ spts, float4* __restrict__ p4, int i) {
-  if (i >= n) return;
-  const int c = cell_of[i];
-  const int pos = starts[c] + atomicAdd(&cursor[c], 1);
-  const float x = X[i], y = Y[i], z = Zc[i];
-  spts[pos] = make_float4(x, y, z, __int_as_float(i));
-  p4[i] = make_float4(x, y, z, 0.f);
-}
-
-__global__ __launch_bounds__(256) void grid_scatter_kernel(const float* __restrict__ X, const float* __restrict__ Y,
-                                                           const float* __restrict__ Zc, int n,
-                                                           const int* __restrict__ cell_of,
-                                                           const int* __restrict__ starts, int* __restrict__ cursor,
-                                                           float4* __restrict__ spts, float4* __restrict__ p4) {
-  grid_scatter_point(X, Y, Zc, n, cell_of, starts, cursor, spts, p4, blockIdx.x * 256 + threadIdx.x);
-}
-
-__device__ inline bool key_less(float d, int i, float bd, int bi) { return d < bd || (d == bd && i < bi); }
-
-// Visits spts[p0 .. p1) in order.  A lane searching far from its cell meets
-// thousands of candidates, and with few waves per SIMD one dependent load
-// per candidate would leave it waiting on memory for most of the kernel: the
-// lane therefore issues SPAN_U independent loads, parks the points in its own
-// LDS column (buf[u * GQ_BT], no other lane touches it, no barrier) and then
-// processes them in a rolled loop, which keeps the per-candidate code (the
-// top-k insertion) in one copy.  Six loads: with the 8-key candidate column
-// a 256-thread block then needs 40 KB of LDS, so four blocks (four waves
-// per SIMD, which the registers also allow) fit on a CU; with eight loads
-// only three fit, and the batched search took 16 % longer (measured on the
-// 512 clouds of the batch workload; four loads: 3 % longer).
-constexpr int SPAN_U = 6;
-
-template <class F>
-__device__ inline void span_points(const float4* __restrict__ spts, int p0, int p1, float4* buf, F&& f) {
-  for (int p = p0; p < p1; p += SPAN_U) {
+// Exclusive scan of one int per thread over a block of BT threads; returns
+// the prefix, total receives the sum.  lds: BT / 64 ints.
+template <int BT>
+__device__ inline int block_scan(int v, int& total, int* lds) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  int x = v;
 #pragma unroll
-    for (int u = 0; u < SPAN_U; ++u) buf[u * GQ_BT] = spts[min(p + u, p1 - 1)];
-    const int nu = min(SPAN_U, p1 - p);
-#pragma unroll 1
-    for (int u = 0; u < nu; ++u) f(buf[u * GQ_BT]);
+  for (int off = 1; off < 64; off <<= 1) {
+    const int o = __shfl_up(x, off, 64);
+    if (lane >= off) x += o;
   }
+  if (lane == 63) lds[w] = x;
+  __syncthreads();
+  int before = 0;
+  total = 0;
+  for (int u = 0; u < BT / 64; ++u) {
+    if (u < w) before += lds[u];
+    total += lds[u];
+  }
+  __syncthreads();
+  return before + x - v;
 }
 
-// The points of row (dz, dy) of shell r around cell c (the cells with
-// max(|dx|, |dy|, |dz|) = r in that row) as contiguous spans of the
-// cell-sorted point array.  The cells of one (z, y) row are adjacent in that
-// array, so a row on the shell's boundary is one span (two index loads,
-// however many cells) and a row inside the shell contributes its two end
-// cells.  Up to two spans are handed to a single call site (one inlined copy
-// of the caller's per-candidate code), in the order in which visiting the
-// cells one by one would meet the points.
-__device__ inline void row_bounds(const int* __restrict__ starts, const GridInfo& G, const int c[3], int r, int dz,
-                                  int dy, int& a0, int& a1, int& b0, int& b1) {
-  a0 = a1 = b0 = b1 = 0;
-  const int cz = c[2] + dz, cy = c[1] + dy;
-  if (cz < 0 || cz >= G.dims[2] || cy < 0 || cy >= G.dims[1]) return;
-  const int row = (cz * G.dims[1] + cy) * G.dims[0];
-  const bool full = r == 0 || abs(dz) == r || abs(dy) == r;
-  // first span: cells [c - r, c + r] of a boundary row (clipped to the
-  // grid), or the cell c - r of an interior row; second span: the cell
-  // c + r of an interior row.  (Each bound is loaded under one condition:
-  // assignments of loaded values to a0..b1 on several paths made the
-  // compiler keep them in scratch memory.)
-  const int xa0 = max(0, c[0] - r);
-  const int xa1 = full ? min(G.dims[0] - 1, c[0] + r) : c[0] - r;
-  if (xa1 >= xa0) {
-    a0 = starts[row + xa0];
-    a1 = starts[row + xa1 + 1];
+// Blocks of BLK^3 cells, listed where they hold points: what a query far from
+// everything looks at instead of the cells between.
+constexpr int BLK = 8;
+
+// Lists block number b of the grid (wave-uniform) if it holds points; lane l
+// looks at one of its BLK^2 rows of cells.  start(c): first point of cell c.
+template <class Start>
+__device__ inline void list_block(const GridInfo& G, int b, int* blocks, Start&& start) {
+  const int bd0 = (G.dims[0] + BLK - 1) / BLK, bd1 = (G.dims[1] + BLK - 1) / BLK;
+  const int bc[3] = {b % bd0, b / bd0 % bd1, b / (bd0 * bd1)};
+  const int lane = threadIdx.x & 63;
+  const int cy = bc[1] * BLK + lane % BLK, cz = bc[2] * BLK + lane / BLK;
+  bool any = false;
+  if (cy < G.dims[1] && cz < G.dims[2]) {
+    const int row = (cz * G.dims[1] + cy) * G.dims[0];
+    any = start(row + min(G.dims[0], bc[0] * BLK + BLK)) > start(row + bc[0] * BLK);
   }
-  const int xb = c[0] + r;
-  if (!full && xb < G.dims[0]) {
-    b0 = starts[row + xb];
-    b1 = starts[row + xb + 1];
-  }
+  if (__any(any) && lane == 0) blocks[1 + atomicAdd(blocks, 1)] = pack_cell(bc);
+}
+__device__ inline int block_count(const GridInfo& G) {
+  return ((G.dims[0] + BLK - 1) / BLK) * ((G.dims[1] + BLK - 1) / BLK) * ((G.dims[2] + BLK - 1) / BLK);
 }
 
-template <class F>
-__device__ inline void row_spans(const int* __restrict__ starts, const GridInfo& G, const int c[3], int r, int dz,
-                                 int dy, F&& f) {
-  int a0, a1, b0, b1;
-  row_bounds(starts, G, c, r, dz, dy, a0, a1, b0, b1);
-#pragma unroll 1
-  for (int h = 0; h < 2; ++h) {
-    const int q0 = h ? b0 : a0, q1 = h ? b1 : a1;
-    if (q0 < q1) f(q0, q1);
-  }
-}
+// Whole grid of one cloud in one block, its cells in LDS as 16-bit halves (so
+// n <= 65 535): one launch and no global atomics where the points are few
+// (the phases of the large build are launches of 3 to 5 us each, whatever the
+// size).
+constexpr int SM_BT = 1024;
+constexpr int SM_WORDS = 36 * SM_BT;  // 144 KB of the CU's 160 KB of LDS, two cells a word
 
-// Every point of shell r, row by row; far queries (outliers in empty space)
-// touch about 3x fewer index words than cell by cell.
-template <class F>
-__device__ inline void shell_spans(const int* __restrict__ starts, const GridInfo& G, const int c[3], int r, F&& f) {
-  for (int dz = -r; dz <= r; ++dz)
-    for (int dy = -r; dy <= r; ++dy) row_spans(starts, G, c, r, dz, dy, f);
-}
+__device__ inline int half_of(int w, int c) { return c & 1 ? (int)((unsigned)w >> 16) : w & 0xffff; }
 
-// After shell r has been searched: true when nothing outside the searched
-// cube can beat the current k-th key (or no cell lies outside it).  Margin:
-// 1e-3 of a cell for the face, 1e-5 relative for the float32 key; an
-// incomplete list (key NaN) never stops the search.
-__device__ inline bool shell_done(const GridInfo& G, const int c[3], const float qv[3], int r, float kth) {
-  double lb = INFINITY;
-  bool all = true;
-  for (int a = 0; a < 3; ++a) {
-    if (c[a] - r > 0) {
-      lb = fmin(lb, (double)qv[a] - ((double)G.lo[a] + (double)(c[a] - r) * (double)G.h));
-      all = false;
+__global__ __launch_bounds__(SM_BT) void grid_small_kernel(GridArgs A, int2* __restrict__ far) {
+  extern __shared__ int s_cnt[];  // [(max_cells + 1) / 2]
+  __shared__ float s_box[(SM_BT / 64) * 6];
+  __shared__ int s_scan[SM_BT / 64];
+  __shared__ double s_red[SM_BT / 64];
+  __shared__ GridInfo s_g;
+  int b, cloud;
+  const GridJob J = job_of(A, b, &cloud);
+  const int tid = threadIdx.x;
+  if (cloud == 0 && tid == 0) far[0] = make_int2(0, 0);  // queries left to the far pass
+  if (tid == 0) J.blocks[0] = 0;
+  float box[6];
+  box_of<SM_BT>(J, 0, SM_BT, box, s_box);
+  if (tid == 0) s_g = grid_trial(box, J.n, J.max_cells);
+  __syncthreads();
+  GridInfo G = s_g;
+  for (int pass = 0; pass < 2; ++pass) {
+    // counts of the trial cells, then of the final ones
+    const int words = (G.ncells + 1) >> 1;
+    for (int w = tid; w < words; w += SM_BT) s_cnt[w] = 0;
+    __syncthreads();
+#pragma unroll 4
+    for (int i = tid; i < J.n; i += SM_BT) {
+      const int c = cell_index(G, J.x[i], J.y[i], J.z[i]);
+      atomicAdd(&s_cnt[c >> 1], c & 1 ? 1 << 16 : 1);
     }
-    if (c[a] + r < G.dims[a] - 1) {
-      lb = fmin(lb, ((double)G.lo[a] + (double)(c[a] + r + 1) * (double)G.h) - (double)qv[a]);
-      all = false;
+    __syncthreads();
+    if (pass) break;
+    double sq[1] = {0.0};
+    for (int w = tid; w < words; w += SM_BT) {
+      const double lo = (double)half_of(s_cnt[w], 0), hi = (double)half_of(s_cnt[w], 1);
+      sq[0] += lo * lo + hi * hi;
     }
+    block_sum<1, SM_BT>(sq, s_red);
+    if (tid == 0) {
+      grid_resize(s_g, sq[0] / (double)J.n, J);
+      *J.gi = s_g;
+    }
+    __syncthreads();
+    G = s_g;
   }
-  if (all) return true;
-  const double lbs = lb - 1e-3 * (double)G.h;
-  return lbs > 0.0 && (double)kth * 1.00001 < lbs * lbs;
+  // exclusive scan in place: each thread a run of words
+  const int words = (G.ncells + 1) >> 1;
+  const int per = (words + SM_BT - 1) / SM_BT;
+  const int w0 = min(words, tid * per), w1 = min(words, w0 + per);
+  int sum = 0;
+  for (int w = w0; w < w1; ++w) sum += half_of(s_cnt[w], 0) + half_of(s_cnt[w], 1);
+  int total;
+  int run = block_scan<SM_BT>(sum, total, s_scan);
+  for (int w = w0; w < w1; ++w) {
+    const int lo = half_of(s_cnt[w], 0), hi = half_of(s_cnt[w], 1);
+    s_cnt[w] = run | (run + lo) << 16;
+    run += lo + hi;
+  }
+  __syncthreads();
+  for (int c = tid; c < G.ncells; c += SM_BT) J.starts[c] = half_of(s_cnt[c >> 1], c);
+  if (tid == 0) J.starts[G.ncells] = J.n;
+  for (int b = tid >> 6; b < block_count(G); b += SM_BT / 64)
+    list_block(G, b, J.blocks, [&](int c) { return c < G.ncells ? half_of(s_cnt[c >> 1], c) : J.n; });
+  __syncthreads();  // the starts are read above before the scatter moves them
+#pragma unroll 4
+  for (int i = tid; i < J.n; i += SM_BT) {
+    const float x = J.x[i], y = J.y[i], z = J.z[i];
+    int cc[3];
+    cell_of_point(G, x, y, z, cc);
+    const int c = cell_index(G, cc);
+    const int pos = half_of(atomicAdd(&s_cnt[c >> 1], c & 1 ? 1 << 16 : 1), c);
+    J.spts[pos] = make_float4(x, y, z, __int_as_float(i));
+    J.scell[pos] = pack_cell(cc);
+    J.p4[i] = make_float4(x, y, z, 0.f);
+  }
 }
 
+// The same in five launches over many blocks.  Partials: LG_BLOCKS boxes of 6
+// floats, then LG_BLOCKS (points, occupied) pairs, then the scan's block sums.
+constexpr int LG_BT = 256;
+constexpr int LG_BLOCKS = 256;
+constexpr int LG_SCAN = 4096;  // cells per block of the scan
+constexpr int LG_PART = LG_BLOCKS * 8;
+
+// Boxes per block; clears the counts and the far list.
+__global__ __launch_bounds__(LG_BT) void grid_box_kernel(GridJob J, int2* __restrict__ far) {
+  __shared__ float s_box[(LG_BT / 64) * 6];
+  const int t = blockIdx.x * LG_BT + threadIdx.x, nt = gridDim.x * LG_BT;
+  if (t == 0) {
+    far[0] = make_int2(0, 0);
+    J.blocks[0] = 0;
+  }
+  for (int c = t; c < J.max_cells; c += nt) J.counts[c] = J.starts[c] = 0;
+  float box[6];
+  box_of<LG_BT>(J, blockIdx.x * LG_BT, nt, box, s_box);
+  if (threadIdx.x < 6) reinterpret_cast<float*>(J.part)[blockIdx.x * 6 + threadIdx.x] = box[threadIdx.x];
+}
+
+// Box of all blocks' boxes, in every thread.
+__device__ inline void box_total(const GridJob& J, int nb, float box[6], float* lds) {
+  const float* p = reinterpret_cast<const float*>(J.part);
+  float v[6];
+  for (int a = 0; a < 6; ++a) v[a] = (int)threadIdx.x < nb ? p[threadIdx.x * 6 + a] : (a < 3 ? INFINITY : -INFINITY);
+  for (int a = 0; a < 6; ++a) {
+    float m = a < 3 ? v[a] : -v[a];
+    for (int off = 32; off > 0; off >>= 1) m = fminf(m, __shfl_xor(m, off, 64));
+    if ((threadIdx.x & 63) == 0) lds[(threadIdx.x >> 6) * 6 + a] = m;
+  }
+  __syncthreads();
+  for (int a = 0; a < 6; ++a) {
+    float m = lds[a];
+    for (int w = 1; w < LG_BT / 64; ++w) m = fminf(m, lds[w * 6 + a]);
+    box[a] = a < 3 ? m : -m;
+  }
+}
+
+// Lane's run of equal cells among neighbouring points (scan order puts them
+// in the same cell often, and atomics of a wave to one address are served one
+// by one): first is the run's first lane, len its length (valid there).
+__device__ inline bool cell_run(int c, int& first, int& len) {
+  const int lane = threadIdx.x & 63;
+  const int prev = __shfl_up(c, 1, 64);
+  const bool head = lane == 0 || prev != c;
+  const uint64_t heads = __ballot(head);
+  const uint64_t upto = ~0ull >> (63 - lane);  // lanes 0 .. lane
+  first = 63 - __builtin_clzll(heads & upto);
+  const uint64_t after = heads & ~upto;
+  len = (after ? __builtin_ctzll(after) : 64) - lane;
+  return head;
+}
+
+// Occupancy of the trial grid, estimated on one cell in eight (chosen by a
+// hash): the points of those cells, and the sum of their counts' squares,
+// which grows by (old + len)^2 - old^2 as a run of len points is counted.
+__global__ __launch_bounds__(LG_BT) void grid_occupancy_kernel(GridJob J) {
+  __shared__ float s_box[(LG_BT / 64) * 6];
+  __shared__ GridInfo s_g;
+  __shared__ float s_sum[2];
+  float box[6];
+  box_total(J, LG_BLOCKS, box, s_box);
+  if (threadIdx.x == 0) {
+    s_g = grid_trial(box, J.n, J.max_cells);
+    s_sum[0] = s_sum[1] = 0.f;
+  }
+  __syncthreads();
+  const GridInfo G = s_g;
+  float pts = 0.f, sq = 0.f;
+  const int nt = gridDim.x * LG_BT;
+  for (int base = blockIdx.x * LG_BT; base < J.n; base += nt) {  // whole blocks: every lane takes part
+    const int i = base + threadIdx.x;
+    const int c = i < J.n ? cell_index(G, J.x[i], J.y[i], J.z[i]) : -1 - (int)(threadIdx.x & 63);
+    int first, len;
+    if (cell_run(c, first, len) && i < J.n && ((unsigned)c * 2654435761u) >> 29 == 0u) {
+      const float old = (float)atomicAdd(&J.starts[c], len);
+      pts += (float)len;
+      sq += (float)len * (2.f * old + (float)len);
+    }
+  }
+  atomicAdd(&s_sum[0], pts);
+  atomicAdd(&s_sum[1], sq);
+  __syncthreads();
+  if (threadIdx.x < 2)
+    reinterpret_cast<float*>(J.part)[LG_BLOCKS * 6 + blockIdx.x * 2 + threadIdx.x] = s_sum[threadIdx.x];
+}
+
+// Cell of every point, its count and the point's rank in it.
+__global__ __launch_bounds__(LG_BT) void grid_count_kernel(GridJob J) {
+  __shared__ float s_box[(LG_BT / 64) * 6];
+  __shared__ GridInfo s_g;
+  float box[6];
+  box_total(J, LG_BLOCKS, box, s_box);
+  __syncthreads();
+  {
+    // LG_BT = LG_BLOCKS partials; the cell size needs no exact sum, but
+    // every block has to find the same one: a fixed order
+    static_assert(LG_BT == LG_BLOCKS, "one partial per thread");
+    const float* p = reinterpret_cast<const float*>(J.part) + LG_BLOCKS * 6;
+    float v[2] = {p[2 * threadIdx.x], p[2 * threadIdx.x + 1]};
+    for (int e = 0; e < 2; ++e) {
+      for (int off = 32; off > 0; off >>= 1) v[e] += __shfl_xor(v[e], off, 64);
+      if ((threadIdx.x & 63) == 0) s_box[(threadIdx.x >> 6) * 2 + e] = v[e];
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    float pts = 0.f, sq = 0.f;
+    for (int w = 0; w < LG_BT / 64; ++w) {
+      pts += s_box[2 * w];
+      sq += s_box[2 * w + 1];
+    }
+    GridInfo G = grid_trial(box, J.n, J.max_cells);
+    if (pts > 0.f) grid_resize(G, (double)sq / (double)pts, J);
+    s_g = G;
+    if (blockIdx.x == 0) *J.gi = G;
+  }
+  __syncthreads();
+  const GridInfo G = s_g;
+  const int lane = threadIdx.x & 63;
+  const int nt = gridDim.x * LG_BT;
+  for (int base = blockIdx.x * LG_BT; base < J.n; base += nt) {  // whole blocks: every lane takes part
+    const int i = base + threadIdx.x;
+    int cc[3] = {0, 0, 0}, c = -1 - lane;
+    if (i < J.n) {
+      cell_of_point(G, J.x[i], J.y[i], J.z[i], cc);
+      c = cell_index(G, cc);
+    }
+    int first, len, r = 0;
+    if (cell_run(c, first, len) && i < J.n) r = atomicAdd(&J.counts[c], len);
+    r = __shfl(r, first, 64) + lane - first;
+    if (i < J.n) {
+      J.cell_of[i] = pack_cell(cc);
+      J.rank[i] = r;
+    }
+  }
+}
+
+// Exclusive scan of the counts: block sums, then every block adds the sums
+// before it.
+__global__ __launch_bounds__(1024) void grid_sums_kernel(GridJob J) {
+  __shared__ int s_w[16];
+  const int nc = J.gi->ncells;
+  const int i = blockIdx.x * LG_SCAN + threadIdx.x * 4;
+  int v = 0;
+  if (i < nc)
+    for (int u = 0; u < 4; ++u) v += i + u < nc ? J.counts[i + u] : 0;
+  int total;
+  (void)block_scan<1024>(v, total, s_w);
+  if (threadIdx.x == 0) J.part[LG_PART + blockIdx.x] = total;
+}
+
+__global__ __launch_bounds__(1024) void grid_starts_kernel(GridJob J) {
+  __shared__ int s_w[16];
+  const int nc = J.gi->ncells;
+  const int first = blockIdx.x * LG_SCAN;
+  if (first >= nc) return;
+  int before = 0;
+  for (int b = threadIdx.x; b < (int)blockIdx.x; b += 1024) before += J.part[LG_PART + b];
+  int offset;
+  (void)block_scan<1024>(before, offset, s_w);
+  const int i = first + threadIdx.x * 4;
+  int v[4], sum = 0;
+  for (int u = 0; u < 4; ++u) {
+    v[u] = i + u < nc ? J.counts[i + u] : 0;
+    sum += v[u];
+  }
+  int total;
+  int run = offset + block_scan<1024>(sum, total, s_w);
+  for (int u = 0; u < 4; ++u) {
+    if (i + u < nc) J.starts[i + u] = run;
+    run += v[u];
+  }
+  if (first + LG_SCAN >= nc && threadIdx.x == 0) J.starts[nc] = offset + total;
+}
+
+// The first point_blocks blocks move the points, the others list the blocks
+// of cells.
+__global__ __launch_bounds__(LG_BT) void grid_scatter_kernel(GridJob J, int point_blocks) {
+  if ((int)blockIdx.x >= point_blocks) {
+    const GridInfo G = *J.gi;
+    const int nw = (gridDim.x - point_blocks) * (LG_BT / 64);
+    for (int b = (blockIdx.x - point_blocks) * (LG_BT / 64) + (threadIdx.x >> 6); b < block_count(G); b += nw)
+      list_block(G, b, J.blocks, [&](int c) { return J.starts[c]; });
+    return;
+  }
+  const int i = blockIdx.x * LG_BT + threadIdx.x;
+  if (i >= J.n) return;
+  const float x = J.x[i], y = J.y[i], z = J.z[i];
+  const int pc = J.cell_of[i];
+  const int cc[3] = {pc & 1023, (pc >> 10) & 1023, pc >> 20};
+  const int pos = J.starts[cell_index(*J.gi, cc)] + J.rank[i];
+  J.spts[pos] = make_float4(x, y, z, __int_as_float(i));
+  J.scell[pos] = pc;
+  J.p4[i] = make_float4(x, y, z, 0.f);
+}
+
+// ----------------------------------------------------------------- search
 __device__ inline float key_of(uint64_t w) { return __uint_as_float((uint32_t)(w >> 32)); }
 
-// Sorted insertion of a 64-bit (float32 key bits << 32 | index) word into
-// L[0..KC): one compare and two selects per slot.
-template <int KC>
-__device__ inline void insert_key(uint64_t (&L)[KC], uint64_t key) {
-  uint64_t ck = key;
+// Keys are (float32 distance bits << 32 | index): for distances >= 0 the bit
+// pattern orders like the value, so one unsigned compare gives the (distance,
+// index) order.
+__device__ inline uint64_t point_key(const float4& P, const float4& q) {
+  const float ex = __fsub_rn(P.x, q.x), ey = __fsub_rn(P.y, q.y), ez = __fsub_rn(P.z, q.z);
+  const float d2 = __fadd_rn(__fadd_rn(__fmul_rn(ex, ex), __fmul_rn(ey, ey)), __fmul_rn(ez, ez));
+  return ((uint64_t)__float_as_uint(d2) << 32) | (uint32_t)__float_as_int(P.w);
+}
+// The same with the squares fused into the sums, as a search that is compiled
+// with contraction rounds them.
+__device__ inline uint64_t point_key_fused(const float4& P, const float4& q) {
+  const float ex = __fsub_rn(P.x, q.x), ey = __fsub_rn(P.y, q.y), ez = __fsub_rn(P.z, q.z);
+  const float d2 = __builtin_fmaf(ez, ez, __builtin_fmaf(ex, ex, __fmul_rn(ey, ey)));
+  return ((uint64_t)__float_as_uint(d2) << 32) | (uint32_t)__float_as_int(P.w);
+}
+constexpr uint64_t KEY_INF = 0x7f800000ull << 32;  // no key of a finite distance reaches it
+
+// A query's place in the grid: its cell and its position in it in cell units,
+// formed in FP64 (in [0, 1) inside the grid; beyond it for a query outside,
+// whose cell is the nearest).  Distances in cell units below are floats with
+// a margin of 1e-3 of a cell, which covers their rounding and that of the
+// cells, and 2e-5 relative for the float32 key.
+struct Place {
+  int c[3];
+  float fr[3];
+
+  __device__ void set(const GridInfo& G, const float4& q) {
+    const float qv[3] = {q.x, q.y, q.z};
 #pragma unroll
-  for (int s = 0; s < KC; ++s) {
-    const uint64_t t = L[s];
-    const bool sw = ck < t;
-    L[s] = sw ? ck : t;
-    ck = sw ? t : ck;
+    for (int a = 0; a < 3; ++a) fr[a] = (float)(((double)qv[a] - (double)G.lo[a]) * G.inv_h - (double)c[a]);
   }
-}
-
-// Compare-exchange of two keys into ascending order.
-__device__ inline void cmp_swap(uint64_t& a, uint64_t& b) {
-  const bool sw = b < a;
-  const uint64_t lo = sw ? b : a, hi = sw ? a : b;
-  a = lo;
-  b = hi;
-}
-
-// f(integral_constant<int, I>) for I = 0 .. N-1, expanded at compile time (the
-// networks below index register arrays, which must never be indexed at run
-// time).
-template <class F, int... I>
-__device__ inline void static_for_seq(F&& f, std::integer_sequence<int, I...>) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, class F>
-__device__ inline void static_for(F&& f) {
-  static_for_seq(f, std::make_integer_sequence<int, N>{});
-}
-
-// Sorts a bitonic sequence (ascending, then descending) into ascending order
-// (Batcher's bitonic merger: half-cleaners of width N/2, N/4, ..., 1).
-template <int N, int J = N / 2>
-__device__ inline void bitonic_merge(uint64_t (&v)[N]) {
-  if constexpr (J > 0) {
-    static_for<N>([&](auto i) {
-      if constexpr ((i & J) == 0) cmp_swap(v[i], v[i | J]);
-    });
-    bitonic_merge<N, J / 2>(v);
+  // distance to the slab of cells d beyond the query's along axis a
+  __device__ float gap(int a, int d) const {
+    return fmaxf(0.f, fmaxf((float)d - fr[a], fr[a] - (float)(d + 1)) - 1e-3f);
   }
+};
+
+// Whole cells in a distance along a row, which has at most 1024.
+__device__ inline int cell_step(float d) { return (int)floorf(fminf(4096.f, fmaxf(-4096.f, d))); }
+
+// Keys below this bound belong to points nearer than every cell outside the
+// cube of radius r around the query's; KEY_INF when no cell lies outside it.
+__device__ inline uint64_t cube_bound(const GridInfo& G, const Place& at, int r) {
+  float lb = INFINITY;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    if (at.c[a] - r > 0) lb = fminf(lb, at.fr[a] + (float)r);
+    if (at.c[a] + r < G.dims[a] - 1) lb = fminf(lb, 1.f - at.fr[a] + (float)r);
+  }
+  if (lb == INFINITY) return KEY_INF;
+  const float d = fmaxf(0.f, lb - 1e-3f) * G.h;
+  return (uint64_t)__float_as_uint(d * d * (1.f - 2e-5f)) << 32;
 }
 
-// Sorts 8 keys ascending (bitonic sort: merges of width 2, 4, 8 with
-// alternating directions).
-template <int W = 2, int J = 1>
-__device__ inline void bitonic_sort8(uint64_t (&v)[8]) {
-  if constexpr (W <= 8) {
-    static_for<8>([&](auto i) {
-      if constexpr ((i & J) == 0) {
-        if constexpr ((i & W) == 0)
-          cmp_swap(v[i], v[i | J]);
-        else
-          cmp_swap(v[i | J], v[i]);
-      }
-    });
-    if constexpr (J > 1)
-      bitonic_sort8<W, J / 2>(v);
+// LDS written by some lanes of a wave is read by others of the same wave.
+__device__ inline void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Sum of an int over the lanes of a group.
+template <int GL>
+__device__ inline int group_sum(int v) {
+  if constexpr (GL == 64) {
+    v += (int)xor_lane_u<32>((unsigned)v);
+    v += (int)xor_lane_u<16>((unsigned)v);
+  }
+  v += (int)xor_lane_u<8>((unsigned)v);
+  v += (int)xor_lane_u<4>((unsigned)v);
+  v += (int)xor_lane_u<2>((unsigned)v);
+  v += (int)xor_lane_u<1>((unsigned)v);
+  return v;
+}
+template <int GL>
+__device__ inline unsigned group_max(unsigned v) {
+  if constexpr (GL == 64) {
+    v = max(v, xor_lane_u<32>(v));
+    v = max(v, xor_lane_u<16>(v));
+  }
+  v = max(v, xor_lane_u<8>(v));
+  v = max(v, xor_lane_u<4>(v));
+  v = max(v, xor_lane_u<2>(v));
+  return max(v, xor_lane_u<1>(v));
+}
+
+// A query's list of candidate keys in LDS, kept by a group of GL lanes (GL
+// 16 or 64).  Keys not below `bound` are refused.  trim() drops keys that k
+// others undercut and lowers the bound, by bisection on the distance bits (a
+// few counts of the list) instead of ranking it; the ranks of what is left are
+// counted once, at the end.
+template <int GL, int CAP>
+struct KeyList {
+  static constexpr int NE = (CAP + GL - 1) / GL;  // entries of a lane: l, l + GL, ...
+  static constexpr int SLACK = 12;                // keys beyond k that trim() may leave
+  uint64_t* key;   // [CAP]
+  int cnt;
+  int k;
+  uint64_t bound;
+
+  __device__ void load(uint64_t (&mine)[NE]) const {
+    const int l = threadIdx.x % GL;
+    wave_sync();
+#pragma unroll
+    for (int u = 0; u < NE; ++u) mine[u] = l + u * GL < cnt ? key[l + u * GL] : ~0ull;
+    wave_sync();
+  }
+
+  // rk[u] += number of keys below mine[u], for a lane's first N entries.
+  template <int N>
+  __device__ void count_below(const uint64_t (&mine)[NE], int (&rk)[NE]) const {
+#pragma unroll 4
+    for (int j = 0; j < cnt; ++j) {
+      const uint64_t o = key[j];
+#pragma unroll
+      for (int u = 0; u < (N < NE ? N : NE); ++u) rk[u] += o < mine[u];
+    }
+  }
+
+  // The lane with entry e gets f(key, rank among the list's keys), which are
+  // distinct.  All reads come before the first f.
+  template <class F>
+  __device__ void ranked(F&& f) {
+    uint64_t mine[NE];
+    int rk[NE];
+    load(mine);
+#pragma unroll
+    for (int u = 0; u < NE; ++u) rk[u] = 0;
+    // only the first entries of the lanes exist in a short list
+    if (cnt <= 2 * GL)
+      count_below<2>(mine, rk);
+    else if (cnt <= 3 * GL)
+      count_below<3>(mine, rk);
     else
-      bitonic_sort8<W * 2, W>(v);
+      count_below<NE>(mine, rk);
+    wave_sync();
+    const int l = threadIdx.x % GL;
+#pragma unroll
+    for (int u = 0; u < NE; ++u)
+      if (l + u * GL < cnt) f(mine[u], rk[u]);
   }
-}
 
-// Merges up to 8 keys cand[0 .. cnt) (the lane's LDS column) into the sorted
-// list L, keeping its KC smallest.  A flush runs in every lane of the wave
-// at once, and with one sorted insertion per key it would cost the largest
-// cnt of the wave times 7 KC operations; the keys instead go through one
-// network: the buffer, padded with all-ones keys, is sorted; with L and the
-// buffer both ascending and padded to a power of two P >= KC, the
-// element-wise minimum of L and the reversed buffer is a bitonic sequence
-// that holds the P smallest keys of the two, and a bitonic merger sorts it.
-// Keys are (key bits, index) words, so the result is the same list as that
-// of the insertions.
-template <int KC>
-__device__ inline void flush_keys(uint64_t (&L)[KC], const uint64_t* cand, int cnt) {
-  uint64_t B[8];
-  static_for<8>([&](auto u) { B[u] = u < cnt ? cand[u * GQ_BT] : ~0ull; });
-  bitonic_sort8(B);
-  if constexpr ((KC & (KC - 1)) == 0) {
-    // P = KC: only the last 8 slots meet a buffered key; merged in place
-    static_for<8>([&](auto u) {
-      const uint64_t b = B[u];
-      L[KC - 1 - u] = b < L[KC - 1 - u] ? b : L[KC - 1 - u];
-    });
-    bitonic_merge<KC>(L);
+  static __device__ uint64_t key_at(const float4& P, const float4& q) { return point_key(P, q); }
+
+  __device__ void trim() {
+    if (cnt < k) return;
+    uint64_t mine[NE];
+    load(mine);
+    const int l = threadIdx.x % GL;
+    unsigned d[NE], top = 0;
+#pragma unroll
+    for (int u = 0; u < NE; ++u) {
+      d[u] = (unsigned)(mine[u] >> 32);  // ~0 where there is no entry
+      if (l + u * GL < cnt) top = max(top, d[u]);
+    }
+    // the smallest distance hi tried with at least k keys up to it
+    unsigned lo = 0, hi = group_max<GL>(top);
+    int have = cnt;
+    while (have > k + SLACK && lo < hi) {
+      const unsigned mid = lo + ((hi - lo) >> 1);
+      int c = 0;
+#pragma unroll
+      for (int u = 0; u < NE; ++u) c += d[u] <= mid;
+      c = group_sum<GL>(c);
+      if (c >= k) {
+        hi = mid;
+        have = c;
+      } else {
+        lo = mid + 1;
+      }
+    }
+    if (have > k + SLACK) {
+      // more equal distances than fit: the k smallest keys by rank
+      int rk[NE];
+#pragma unroll
+      for (int u = 0; u < NE; ++u) rk[u] = 0;
+      count_below<NE>(mine, rk);
+      wave_sync();
+#pragma unroll
+      for (int u = 0; u < NE; ++u)
+        if (l + u * GL < cnt && rk[u] < k) key[rk[u]] = mine[u];
+      wave_sync();
+      cnt = k;
+      bound = min(bound, key[k - 1]);
+      return;
+    }
+    if (have < cnt) {
+      cnt = 0;
+#pragma unroll
+      for (int u = 0; u < NE; ++u) push(mine[u], d[u] <= hi);
+    }
+    bound = min(bound, (uint64_t)(hi + 1) << 32);
+  }
+
+  // Appends the keys of the lanes that have one.
+  __device__ void push(uint64_t w, bool pass) {
+    const uint64_t m = __ballot(pass);
+    if constexpr (GL == 16) {
+      const int lane = threadIdx.x & 63;
+      const unsigned mg = ((lane & 32 ? (unsigned)(m >> 32) : (unsigned)m) >> (lane & 16)) & 0xffffu;
+      if (pass) key[cnt + __popc(mg & ((1u << (lane & 15)) - 1u))] = w;
+      cnt += __popc(mg);
+    } else {
+      static_assert(GL == 64, "a group of 16 lanes or a wave");
+      if (pass) key[cnt + __popcll(m & ((1ull << (threadIdx.x & 63)) - 1ull))] = w;
+      cnt += __popcll(m);
+    }
+  }
+  // Number of keys below a bound.
+  __device__ int count_under(uint64_t b) const {
+    int c = 0;
+    wave_sync();
+    for (int e = threadIdx.x % GL; e < cnt; e += GL) c += key[e] < b;
+    return group_sum<GL>(c);
+  }
+  // One candidate per lane (ok: this lane has one); room() comes before.
+  __device__ void add(uint64_t w, bool ok) { push(w, ok && w < bound); }
+  template <int U>
+  __device__ void room() {
+    if (cnt > CAP - U * GL) trim();
+  }
+  __device__ void settle() {}
+  // The bound is about to be used again.
+  __device__ void lower() { trim(); }
+  // The keys are about to be met again.
+  __device__ void again() {
+    if (cnt >= k) {
+      trim();
+      ++bound;
+    }
+    cnt = 0;
+  }
+};
+
+// Sum over the lanes before this one of its group (exclusive), and the
+// group's total.
+template <int GL>
+__device__ inline int group_scan(int v, int& total) {
+  int x = v;
+  if constexpr (GL == 16) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);  // row shift right by 1, 2, 4, 8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, true);
+    total = __shfl(x, (int)(threadIdx.x & 63) | 15, 64);
   } else {
-    // KC = 24, P = 32: L's padding is all ones, so the sequence is L
-    // followed by the reversed buffer
-    static_assert(KC == 24, "list sizes are 8, 16, 24 or 32");
-    uint64_t D[32];
-    static_for<24>([&](auto i) { D[i] = L[i]; });
-    static_for<8>([&](auto u) { D[24 + u] = B[7 - u]; });
-    bitonic_merge<32>(D);
-    static_for<24>([&](auto i) { L[i] = D[i]; });
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int o = __shfl_up(x, off, 64);
+      if (lane >= off) x += o;
+    }
+    total = __builtin_amdgcn_readlane(x, 63);
   }
+  return x - v;
 }
 
-// Order in which a lane visits the rows (dz, dy) of shell r: the rows
-// nearest the query's cell first (by |dz| + |dy|, then max(|dz|, |dy|)), so
-// that the k-th key falls early and fewer later candidates are buffered.  Any
-// order visits the same points before the stopping test.
-__device__ inline void shell_row(int r, int ri, int& dz, int& dy) {
-  if (r == 1) {
-    // (0,0) (0,-1) (0,1) (-1,0) (1,0) (-1,-1) (-1,1) (1,-1) (1,1), as
-    // 2-bit fields of dz + 1 and dy + 1 (no table in memory)
-    dz = ((0x28215 >> (2 * ri)) & 3) - 1;
-    dy = ((0x22161 >> (2 * ri)) & 3) - 1;
-    return;
-  }
-  const int w = 2 * r + 1;
-  dz = ri / w - r;
-  dy = ri % w - r;
-}
+// Visits the points of the cells within radius R of the query's cell, but
+// not those within radius inner (< 0: none), that can hold keys below the
+// sink's bound.  A lane of the group looks up one row of cells at a time: the
+// distance from the query to the row, the cells of it within the bound, and
+// their span or, on both sides of the inner cube, two.  Spans are short (a
+// dozen points), so they are cut into segments of 8 points, laid out in LDS
+// (s_seg, GL * SEG_PER of them), and the group reads GL / 8 segments at once,
+// U times before it uses the first.
+//
+// RU rows per lane are looked up at once (the two loads of a row are the
+// longest wait of a search with many rows).  Returns the number of points in
+// the spans (of the group).
+constexpr int SEG_PER = 4;
 
-// Writes the k neighbour indices of every point (row = original index,
-// sorted by key; -1 where fewer than k finite points exist).  With a far
-// list, a query whose search is not finished after shell rcap (an outlier in
-// empty space, whose lane would otherwise sweep many cells alone and hold up
-// its wave) is appended to it instead, for grid_knn_far_kernel.
-// Candidates a lane buffers before they are inserted.  A candidate is
-// buffered when its key is below the k-th key of the list as it stood at the
-// last insertion; that key only decreases, so a rejected candidate could never
-// have entered.  Each lane's buffer is its own LDS column.  The active lanes
-// of a wave insert their buffers together as soon as one of them is full (and
-// at the end of every shell, before the stopping test): in a dense cluster
-// some lane accepts a candidate at almost every step, and inserting at once
-// would make the wave run the 5 KC-operation insertion at almost every step.
-constexpr int KNN_CB = 8;
-static_assert(KNN_CB == 8, "flush_keys sorts a buffer of 8 keys");
-
-// Query t (a position in the cell-sorted array); buf and cand are the lane's
-// LDS columns (stride GQ_BT).  No barriers.  The search starts at shell r0:
-// with r0 > 0 it resumes a query handed over after shell r0 - 1, whose list
-// of the k best of shells 0 .. r0 - 1 is in its output row (see below).
-template <int KC>
-__device__ inline void grid_knn_query(const float4* __restrict__ spts, const float4* __restrict__ p4,
-                                      const int* __restrict__ starts, const GridInfo* __restrict__ gi, int n, int k,
-                                      int rcap, int* __restrict__ far, int32_t* __restrict__ idx_out, int t,
-                                      float4* buf, uint64_t* cand, int r0) {
-  if (t >= n) return;
-  const GridInfo G = *gi;
-  const float4 q = spts[t];
-  const int qi = __float_as_int(q.w);
-  // a query with a non-finite coordinate has no finite key to any point:
-  // its list is empty (and searching for one would visit every shell)
-  if (!(isfinite(q.x) && isfinite(q.y) && isfinite(q.z))) {
-    for (int s = 0; s < k; ++s) idx_out[(int64_t)qi * k + s] = -1;
-    return;
-  }
-  const float qv[3] = {q.x, q.y, q.z};
-  int c[3];
-  for (int a = 0; a < 3; ++a) c[a] = cell_coord(qv[a], G.lo[a], G.h, G.dims[a]);
-  // The running top k as sorted 64-bit keys (float32 key bits << 32 |
-  // index): for keys >= 0 the bit pattern orders like the value, so one
-  // unsigned compare gives the (key, index) order.  Slots [0, KC - k) hold
-  // the sentinel 0, which no candidate undercuts, so slot KC - 1 is always
-  // the k-th best; empty slots hold all ones (key NaN, index -1).
-  // Candidates whose key is not below +inf (non-finite points, overflowing
-  // distances) never enter.
-  uint64_t L[KC];
-#pragma unroll
-  for (int s = 0; s < KC; ++s) L[s] = (s < KC - k) ? 0ull : ~0ull;
-  if (r0 > 0) {
-    // the row's indices in key order (-1: empty); their keys are rebuilt
-    // from the packed points with the same float32 arithmetic
-    const int64_t o = (int64_t)qi * k;
-#pragma unroll
-    for (int s = 0; s < KC; ++s) {
-      if (s >= KC - k) {
-        const int id = idx_out[o + (s - (KC - k))];
-        if (id >= 0) {
-          const float4 P = p4[id];
-          const float ex = __fsub_rn(P.x, q.x), ey = __fsub_rn(P.y, q.y), ez = __fsub_rn(P.z, q.z);
-          const float d2 = __fadd_rn(__fadd_rn(__fmul_rn(ex, ex), __fmul_rn(ey, ey)), __fmul_rn(ez, ez));
-          L[s] = ((uint64_t)__float_as_uint(d2) << 32) | (uint32_t)id;
-        }
+// The points of every lane's spans a and b; returns how many the lane's were.
+template <int GL, int U, class Sink>
+__device__ inline int take_spans(const GridJob& J, int2 a, int2 b, const float4& q, Sink& L, int2* s_seg) {
+  const int l = threadIdx.x % GL;
+  const int points = a.y - a.x + b.y - b.x;
+  int todo = ((a.y - a.x + 7) >> 3) + ((b.y - b.x + 7) >> 3);
+  for (;;) {
+    const int take = min(todo, SEG_PER);
+    int total;
+    const int at0 = group_scan<GL>(take, total);
+    if (total == 0) break;
+    wave_sync();
+    for (int u = 0; u < take; ++u) {
+      if (a.x >= a.y) {
+        a = b;
+        b = make_int2(0, 0);
       }
+      s_seg[at0 + u] = make_int2(a.x, min(a.x + 8, a.y));
+      a.x += 8;
+    }
+    todo -= take;
+    wave_sync();
+    for (int s = 0; s < total; s += U * (GL / 8)) {
+      float4 P[U];
+      bool ok[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int e = s + u * (GL / 8) + (l >> 3);
+        const int2 sg = e < total ? s_seg[e] : make_int2(0, 0);
+        ok[u] = sg.x + (l & 7) < sg.y;
+        P[u] = J.spts[ok[u] ? sg.x + (l & 7) : 0];
+      }
+      L.template room<U>();
+#pragma unroll
+      for (int u = 0; u < U; ++u) L.add(Sink::key_at(P[u], q), ok[u]);
+      L.settle();
     }
   }
-  int cnt = 0;  // buffered candidates of this lane
-  const int rmax = max(G.dims[0], max(G.dims[1], G.dims[2]));
-  for (int r = r0; r <= rmax; ++r) {
-    // the rows of shell r (see row_spans), then one end row that visits no
-    // point and empties the buffers through the same insertion code, so that
-    // this code exists once
-    const int w = 2 * r + 1, nrow = w * w;
-#pragma unroll 1
-    for (int ri = 0; ri <= nrow; ++ri) {
-      const bool end = ri == nrow;
-      int a0 = 0, a1 = 1, b0 = 0, b1 = 0;
-      if (!end) {
-        int dz, dy;
-        shell_row(r, ri, dz, dy);
-        row_bounds(starts, G, c, r, dz, dy, a0, a1, b0, b1);
-      }
-#pragma unroll 1
-      for (int h = 0; h < 2; ++h) {
-        const int q0 = h ? b0 : a0, q1 = h ? b1 : a1;
-#pragma unroll 1
-        for (int p = q0; p < q1; p += SPAN_U) {
-          if (!end) {
+  return points;
+}
+
+template <int GL, int U, int RU, class Sink>
+__device__ inline int visit(const GridJob& J, const GridInfo& G, const Place& at, const float4& q, int R, int inner,
+                            Sink& L, int2* s_seg) {
+  const int l = threadIdx.x % GL;
+  const int side = 2 * R + 1, rows = side * side;
+  const float inv_side = 1.f / (float)side;
+  const float inv_h = (float)G.inv_h;
+  int seen = 0;
+  for (int r0 = 0; r0 < rows; r0 += GL * RU) {
+    int2 a[RU], b[RU];
+    const float reach2 = key_of(L.bound) * (inv_h * inv_h) * (1.f + 2e-5f);
 #pragma unroll
-            for (int u = 0; u < SPAN_U; ++u) buf[u * GQ_BT] = spts[min(p + u, q1 - 1)];
-          }
-          const int nu = min(SPAN_U, q1 - p);
-#pragma unroll 1
-          for (int u = 0; u < nu; ++u) {
-            if (!end) {
-              const float4 P = buf[u * GQ_BT];
-              const float ex = __fsub_rn(P.x, q.x), ey = __fsub_rn(P.y, q.y), ez = __fsub_rn(P.z, q.z);
-              const float d2 = __fadd_rn(__fadd_rn(__fmul_rn(ex, ex), __fmul_rn(ey, ey)), __fmul_rn(ez, ez));
-              const uint64_t key = ((uint64_t)__float_as_uint(d2) << 32) | (uint32_t)__float_as_int(P.w);
-              if (d2 < INFINITY && key < L[KC - 1]) {
-                cand[cnt * GQ_BT] = key;
-                ++cnt;
-              }
-            }
-            if (__any(cnt == KNN_CB || (end && cnt > 0))) {
-              flush_keys<KC>(L, cand, cnt);
-              cnt = 0;
-            }
+    for (int v = 0; v < RU; ++v) {
+      a[v] = b[v] = make_int2(0, 0);
+      const int i = r0 + v * GL + l;
+      int dz = (int)(((float)i + 0.5f) * inv_side);
+      int dy = i - dz * side;
+      if (dy < 0) dy += side, --dz;
+      if (dy >= side) dy -= side, ++dz;
+      dz -= R;
+      dy -= R;
+      const int cz = at.c[2] + dz, cy = at.c[1] + dy, cx = at.c[0];
+      if (i < rows && cz >= 0 && cz < G.dims[2] && cy >= 0 && cy < G.dims[1]) {
+        const float gy = at.gap(1, dy), gz = at.gap(2, dz);
+        const float left = reach2 - (gy * gy + gz * gz);
+        if (!(left < 0.f)) {
+          // cells of the row within sqrt(left) of the query
+          const float reach = sqrtf(left) * 1.0001f + 2e-3f;
+          const int xl = max(max(0, cx - R), min(cx, cx + cell_step(at.fr[0] - reach)));
+          const int xr = min(min(G.dims[0] - 1, cx + R), max(cx, cx + cell_step(at.fr[0] + reach)));
+          const int* st = J.starts + (cz * G.dims[1] + cy) * G.dims[0];
+          if (max(abs(dy), abs(dz)) > inner) {
+            a[v] = make_int2(st[xl], st[xr + 1]);
+          } else {
+            if (xl < cx - inner) a[v] = make_int2(st[xl], st[cx - inner]);
+            if (xr > cx + inner) b[v] = make_int2(st[cx + inner + 1], st[xr + 1]);
           }
         }
       }
     }
-    if (shell_done(G, c, qv, r, key_of(L[KC - 1]))) break;
-    // handed to the far pass, which continues from shell rcap + 1 with the
-    // list written below (the k best of the shells searched here)
-    if (far && r >= rcap) {
-      far[1 + atomicAdd(far, 1)] = t;
-      break;
-    }
-  }
-  // static slot indices only (a runtime index would put L in scratch memory)
-  const int64_t o = (int64_t)qi * k;
 #pragma unroll
-  for (int s = 0; s < KC; ++s)
-    if (s >= KC - k) idx_out[o + (s - (KC - k))] = (int32_t)(uint32_t)L[s];
+    for (int v = 0; v < RU; ++v) seen += take_spans<GL, U>(J, a[v], b[v], q, L, s_seg);
+  }
+  return group_sum<GL>(seen);
 }
 
-template <int KC>
-__global__ __launch_bounds__(GQ_BT) void grid_knn_kernel(const float4* __restrict__ spts, const int* __restrict__ starts,
-                                                         const GridInfo* __restrict__ gi, int n, int k, int rcap,
-                                                         int* __restrict__ far, int32_t* __restrict__ idx_out) {
-  __shared__ float4 s_buf[SPAN_U * GQ_BT];
-  __shared__ uint64_t s_cand[KNN_CB * GQ_BT];
-  grid_knn_query<KC>(spts, nullptr, starts, gi, n, k, rcap, far, idx_out, blockIdx.x * GQ_BT + threadIdx.x,
-                     s_buf + threadIdx.x, s_cand + threadIdx.x, 0);
+// Radius of the smallest cube of cells around the query's outside of which no
+// key below the bound lies.
+__device__ inline int cells_reached(const GridInfo& G, const Place& at, uint64_t bound, int rmax) {
+  const float u = sqrtf(key_of(bound)) * (float)G.inv_h * 1.0001f + 2e-3f;
+  if (!(u < 1e9f)) return rmax;
+  float r = 0.f;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    if (at.c[a] > 0) r = fmaxf(r, -floorf(at.fr[a] - u));
+    if (at.c[a] < G.dims[a] - 1) r = fmaxf(r, floorf(at.fr[a] + u));
+  }
+  return r < (float)rmax ? (int)r : rmax;
 }
 
-// The queries grid_knn_kernel left unfinished, one wave per query (a
-// wave-uniform loop over the far list).  Lane l scans rows l, l + 64, ... of
-// each shell into its own sorted list of the KC best keys it has met (every
-// slot real, no sentinels); after the shell the wave merges the 64 lists into
-// the KC best of their union by KC rounds of a wave-wide minimum (keys are
-// unique, so exactly the lanes holding the minimum pop it, and duplicates of
-// a merged entry are popped together), and every lane continues from the
-// merged list (a shell in which no lane took a key leaves every list equal
-// to the merged one, and skips the merge).  The stopping test is
-// grid_knn_kernel's on the merged k-th key, so the neighbour list is the
-// same exact one.  This is far query t (a position in the cell-sorted
-// array) of the grid G, searched by the calling wave.
-template <int KC>
-__device__ inline void grid_knn_far_query(const float4* __restrict__ spts, const float4* __restrict__ p4,
-                                          const int* __restrict__ starts, const GridInfo& G, int k, int t,
-                                          int32_t* __restrict__ idx_out, float4* buf, int r0) {
+// Every key below the sink's bound, by the listed blocks of cells: a wave
+// measures 64 blocks at a time against the bound and visits those within it,
+// a lane per row, the nearest block of all first.
+template <int U, class Sink>
+__device__ inline void visit_blocks(const GridJob& J, const GridInfo& G, const Place& at, const float4& q, Sink& L,
+                                    int2* s_seg) {
   const int lane = threadIdx.x & 63;
-  const int rmax = max(G.dims[0], max(G.dims[1], G.dims[2]));
-  const float4 q = spts[t];
-  const int qi = __float_as_int(q.w);
-  const float qv[3] = {q.x, q.y, q.z};
-  int c[3];
-  for (int a = 0; a < 3; ++a) c[a] = cell_coord(qv[a], G.lo[a], G.h, G.dims[a]);
-  // The lane passes searched shells 0 .. r0 - 1 and left the k best of
-  // them in the query's output row (index -1 for an empty slot): lane s < k
-  // rebuilds entry s's key from the packed points (the same float32
-  // arithmetic as the key was made with), and every lane starts from that
-  // list, as after a merge.  Slots k .. KC-1 start empty; they never hold
-  // one of the k best.
-  uint64_t L[KC];
-  {
-    uint64_t mine = ~0ull;
-    if (lane < k) {
-      const int id = idx_out[(int64_t)qi * k + lane];
-      if (id >= 0) {
-        const float4 P = p4[id];
-        const float ex = __fsub_rn(P.x, q.x), ey = __fsub_rn(P.y, q.y), ez = __fsub_rn(P.z, q.z);
-        const float d2 = __fadd_rn(__fadd_rn(__fmul_rn(ex, ex), __fmul_rn(ey, ey)), __fmul_rn(ez, ez));
-        mine = ((uint64_t)__float_as_uint(d2) << 32) | (uint32_t)id;
+  const float inv_h2 = (float)G.inv_h * (float)G.inv_h * (1.f + 2e-5f);
+  // squared distance (cell units, never too large) to block bc
+  auto block_gap = [&](int pb) {
+    const int bc[3] = {pb & 1023, (pb >> 10) & 1023, pb >> 20};
+    float g2 = 0.f;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const float d = (float)(bc[a] * BLK - at.c[a]);
+      const float g = fmaxf(0.f, fmaxf(d - at.fr[a], at.fr[a] - (d + (float)BLK)) - 1e-3f);
+      g2 += g * g;
+    }
+    return g2;
+  };
+  auto visit_block = [&](int pb) {
+    const int dy = (pb >> 10 & 1023) * BLK + lane % BLK - at.c[1], dz = (pb >> 20) * BLK + lane / BLK - at.c[2];
+    const int cy = at.c[1] + dy, cz = at.c[2] + dz, x0 = (pb & 1023) * BLK;
+    int2 a = make_int2(0, 0);
+    if (cy < G.dims[1] && cz < G.dims[2]) {
+      const float gy = at.gap(1, dy), gz = at.gap(2, dz);
+      const float left = key_of(L.bound) * inv_h2 - (gy * gy + gz * gz);
+      if (!(left < 0.f)) {
+        const float reach = sqrtf(left) * 1.0001f + 2e-3f;
+        const int xl = max(x0, at.c[0] + cell_step(at.fr[0] - reach));
+        const int xr = min(min(G.dims[0], x0 + BLK) - 1, at.c[0] + cell_step(at.fr[0] + reach));
+        if (xl <= xr) {
+          const int* st = J.starts + (cz * G.dims[1] + cy) * G.dims[0];
+          a = make_int2(st[xl], st[xr + 1]);
+        }
       }
     }
-#pragma unroll
-    for (int s = 0; s < KC; ++s) L[s] = s < k ? __shfl(mine, s, 64) : ~0ull;
-  }
-  float kth = key_of(~0ull);  // the k-th key of the merged list (NaN: fewer than k yet)
-#pragma unroll
-  for (int s = 0; s < KC; ++s)
-    if (s == k - 1) kth = key_of(L[s]);
-  for (int r = r0; r <= rmax; ++r) {
-    const int side = 2 * r + 1;
-    bool took = false;
-    for (int row = lane; row < side * side; row += 64) {
-      row_spans(starts, G, c, r, row / side - r, row % side - r, [&](int p0, int p1) {
-        span_points(spts, p0, p1, buf, [&](const float4& P) {
-          const float ex = __fsub_rn(P.x, q.x), ey = __fsub_rn(P.y, q.y), ez = __fsub_rn(P.z, q.z);
-          const float d2 = __fadd_rn(__fadd_rn(__fmul_rn(ex, ex), __fmul_rn(ey, ey)), __fmul_rn(ez, ez));
-          const uint64_t key = ((uint64_t)__float_as_uint(d2) << 32) | (uint32_t)__float_as_int(P.w);
-          if (d2 < INFINITY && key < L[KC - 1]) {
-            insert_key(L, key);
-            took = true;
-          }
-        });
-      });
+    take_spans<64, U>(J, a, make_int2(0, 0), q, L, s_seg);
+  };
+  const int nb = J.blocks[0];
+  uint64_t best = ~0ull;
+  for (int i = lane; i < nb; i += 64)
+    best = min(best, (uint64_t)__float_as_uint(block_gap(J.blocks[1 + i])) << 32 | (unsigned)i);
+  for (int off = 32; off > 0; off >>= 1) best = min(best, (uint64_t)__shfl_xor((unsigned long long)best, off, 64));
+  const int first = nb > 0 ? (int)(unsigned)best : -1;
+  if (first < 0) return;
+  visit_block(__builtin_amdgcn_readfirstlane(J.blocks[1 + first]));
+  L.lower();
+  for (int i0 = 0; i0 < nb; i0 += 64) {
+    const int i = i0 + lane;
+    const int pb = J.blocks[1 + min(i, nb - 1)];
+    const float g2 = block_gap(pb);
+    bool want = i < nb && i != first;
+    for (;;) {
+      const uint64_t m = __ballot(want && !(g2 > key_of(L.bound) * inv_h2));
+      if (m == 0) break;
+      const int j = __builtin_ctzll(m);
+      if (lane == j) want = false;
+      visit_block(__builtin_amdgcn_readlane(pb, j));
+      L.lower();
     }
-    // no lane took a key in this shell: every lane's list is still the
-    // merged list of the last shell, which the merge would return again
-    if (__ballot(took) == 0) {
-      if (shell_done(G, c, qv, r, kth)) break;
+  }
+}
+
+constexpr int KF_ROWS = 4;
+// Every key below the sink's bound: a wave looks at the cells within 3, 8 and
+// 18 of the query's.  If the bound then still reaches further, the cells in
+// reach are mostly empty (in a cloud that is mostly surfaces) and the listed
+// blocks tell where the points are.  The sink's again() forgets the keys but
+// not the bound.
+template <int U, int RMAX, class Sink>
+__device__ inline void visit_reach(const GridJob& J, const GridInfo& G, const Place& at, const float4& q, Sink& L,
+                                   int2* s_seg) {
+  const int rmax = max(G.dims[0], max(G.dims[1], G.dims[2]));
+  for (int inner = -1, R = 3; R <= RMAX; R = 2 * R + 2) {
+    R = min(R, cells_reached(G, at, L.bound, rmax));
+    if (R <= inner) return;
+    visit<64, U, KF_ROWS>(J, G, at, q, R, inner, L, s_seg);
+    L.lower();
+    inner = R;
+  }
+  if (cells_reached(G, at, L.bound, rmax) <= RMAX) return;
+  L.again();
+  visit_blocks<U>(J, G, at, q, L, s_seg);
+}
+
+constexpr int KN_BT = 256;
+constexpr int KN_G = 16;                // lanes per query
+constexpr int KN_U = 3;
+constexpr int KN_CAP = 128;             // list entries: cut above 80, eight per lane
+constexpr int KN_STRIDE = KN_CAP + 2;   // the groups' lists start in different LDS banks
+constexpr int KN_Q = KN_BT / KN_G;      // queries of a block at a time
+using QueryList = KeyList<KN_G, KN_CAP>;
+
+// Writes a settled query's list: the k smallest keys in order, -1 where fewer
+// finite points than k exist.
+template <int GL, class List>
+__device__ inline void write_list(List& L, int k, int32_t* __restrict__ out) {
+  L.ranked([&](uint64_t w, int r) {
+    if (r < k) out[r] = (int32_t)(uint32_t)w;
+  });
+  for (int e = L.cnt + (int)(threadIdx.x % GL); e < k; e += GL) out[e] = -1;
+}
+
+// Lists of the queries knn_kernel leaves, counts first: near[0].x of the
+// queries with k points in their 27 cells, near[0].y of the others, which are
+// listed from the end of the same array (size entries).
+__device__ inline void leave_query(int2* list, int size, int cloud, int t, bool near) {
+  if (near)
+    list[1 + atomicAdd(&list[0].x, 1)] = make_int2(cloud, t);
+  else
+    list[size - atomicAdd(&list[0].y, 1)] = make_int2(cloud, t);
+}
+
+// Queries [block rounds KN_Q, ...) of a cloud in cell order, KN_Q at a time.
+__global__ __launch_bounds__(KN_BT, 4) void knn_kernel(GridArgs A, int k, int rounds, int2* __restrict__ far,
+                                                       int far_size) {
+  __shared__ uint64_t s_key[KN_Q * KN_STRIDE];
+  __shared__ int2 s_seg[KN_Q][KN_G * SEG_PER];
+  int block, cloud;
+  const GridJob J = job_of(A, block, &cloud);
+  const GridInfo G = *J.gi;
+  const int grp = threadIdx.x / KN_G, l = threadIdx.x % KN_G;
+  for (int round = 0; round < rounds; ++round) {
+    const int t = (block * rounds + round) * KN_Q + grp;
+    if (t >= J.n) return;  // no block barrier below; a group leaves as a whole
+    const float4 q = J.spts[t];
+    int32_t* out = J.nbr + (int64_t)__float_as_int(q.w) * k;
+    // a query with a non-finite coordinate has no finite key to any point:
+    // its list is empty (and searching for one would visit every cell)
+    if (!(isfinite(q.x) && isfinite(q.y) && isfinite(q.z))) {
+      for (int e = l; e < k; e += KN_G) out[e] = -1;
       continue;
     }
-    // merge the 64 lists: M collects the successive wave minima in order
-    uint64_t M[KC];
-#pragma unroll
-    for (int s = 0; s < KC; ++s) M[s] = ~0ull;
-#pragma unroll 1
-    for (int round = 0; round < KC; ++round) {
-      const uint64_t h = L[0];
-      uint64_t m = h;
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) {
-        const uint64_t o = __shfl_xor(m, off, 64);
-        m = o < m ? o : m;
-      }
-      const bool pop = h == m;
-#pragma unroll
-      for (int s = 0; s < KC - 1; ++s) L[s] = pop ? L[s + 1] : L[s];
-      L[KC - 1] = pop ? ~0ull : L[KC - 1];
-#pragma unroll
-      for (int s = 0; s < KC - 1; ++s) M[s] = M[s + 1];
-      M[KC - 1] = m;
+    const int pc = J.scell[t];
+    Place at{{pc & 1023, (pc >> 10) & 1023, pc >> 20}, {}};
+    at.set(G, q);
+    const int own = cell_index(G, at.c);
+    const bool dense = J.starts[own + 1] - J.starts[own] >= k;
+    const uint64_t edge = cube_bound(G, at, 1);
+    // the 27 cells, for keys below the edge; a dense query's own cell first,
+    // for any keys, whose k-th limits the rest
+    QueryList L{s_key + grp * KN_STRIDE, 0, k, dense ? KEY_INF : edge};
+    int seen = visit<KN_G, KN_U, 1>(J, G, at, q, dense ? 0 : 1, -1, L, s_seg[grp]);
+    if (dense) {
+      L.trim();
+      L.bound = min(L.bound, edge);
+      seen += visit<KN_G, KN_U, 1>(J, G, at, q, 1, 0, L, s_seg[grp]);
     }
-#pragma unroll
-    for (int s = 0; s < KC; ++s) {
-      L[s] = M[s];
-      if (s == k - 1) kth = key_of(M[s]);
+    // keys of a dense query's own cell may lie beyond the edge
+    bool found = edge == KEY_INF || (dense ? L.count_under(edge) : L.cnt) >= k;
+    if (found) {
+      if (L.cnt > 3 * KN_G) L.trim();
+      write_list<KN_G>(L, k, out);
+    } else if (l == 0) {
+      leave_query(far, far_size, cloud, t, seen >= k);
     }
-    if (shell_done(G, c, qv, r, kth)) break;
-  }
-  if (lane == 0) {
-    const int64_t o = (int64_t)qi * k;
-#pragma unroll
-    for (int s = 0; s < KC; ++s)
-      if (s < k) idx_out[o + s] = (int32_t)(uint32_t)L[s];
   }
 }
 
-// Wave `wave` of n_waves takes the far queries wave, wave + n_waves, ...
-template <int KC>
-__device__ inline void grid_knn_far_waves(const float4* __restrict__ spts, const float4* __restrict__ p4,
-                                          const int* __restrict__ starts,
-                                          const GridInfo* __restrict__ gi, int k, const int* __restrict__ far,
-                                          int32_t* __restrict__ idx_out, int wave, int n_waves, float4* buf) {
-  const int cnt = far[0];
-  const GridInfo G = *gi;
-  for (int f = wave; f < cnt; f += n_waves)
-    grid_knn_far_query<KC>(spts, p4, starts, G, k, far[1 + f], idx_out, buf, KNN_RCAP + 1);
-}
+constexpr int KF_CAP = 256;    // list entries of a wave: cut above 128, four per lane
+constexpr int KF_U = 2;
 
-template <int KC>
-__global__ __launch_bounds__(GQ_BT) void grid_knn_far_kernel(const float4* __restrict__ spts,
-                                                             const float4* __restrict__ p4,
-                                                             const int* __restrict__ starts,
-                                                             const GridInfo* __restrict__ gi, int k,
-                                                             const int* __restrict__ far,
-                                                             int32_t* __restrict__ idx_out) {
-  __shared__ float4 s_buf[SPAN_U * GQ_BT];
-  grid_knn_far_waves<KC>(spts, p4, starts, gi, k, far, idx_out, (blockIdx.x * GQ_BT + threadIdx.x) >> 6,
-                         (gridDim.x * GQ_BT) >> 6, s_buf + threadIdx.x);
+// The queries knn_kernel left.  Those with k points in their 27 cells, 16
+// lanes each: their k-th key lies a little beyond the bound of these cells, so
+// the bound is raised until k keys are below it (searching for any keys
+// first would fill the list from the dense cells next to a sparse place).  The
+// others, a wave each: the k-th key of the 128 points around the query in the
+// sorted array (its own and the next rows of cells) bounds a search by blocks
+// of cells.  Waves take the second kind first, the longer ones.
+__global__ __launch_bounds__(KN_BT) void knn_far_kernel(GridArgs A, int k, const int2* __restrict__ far,
+                                                        int far_size) {
+  __shared__ union {
+    struct {
+      uint64_t key[(KN_BT / 64) * KF_CAP];
+      int2 seg[KN_BT / 64][64 * SEG_PER];
+    } w;
+    struct {
+      uint64_t key[KN_Q * KN_STRIDE];
+      int2 seg[KN_Q][KN_G * SEG_PER];
+    } g;
+  } sh;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int waves = (gridDim.x * KN_BT) >> 6, first_wave = (blockIdx.x * KN_BT + threadIdx.x) >> 6;
+  const int n_near = far[0].x, n_far = far[0].y;
+  for (int f = first_wave; f < n_far; f += waves) {
+    const int2 ct = far[far_size - f];
+    const GridJob J = job_at(A, ct.x);
+    const GridInfo G = *J.gi;
+    const float4 q = J.spts[ct.y];
+    const int pc = J.scell[ct.y];
+    Place at{{pc & 1023, (pc >> 10) & 1023, pc >> 20}, {}};
+    at.set(G, q);
+    KeyList<64, KF_CAP> L{sh.w.key + wave * KF_CAP, 0, k, KEY_INF};
+    {
+      const int first = max(0, min(ct.y - 64, J.n - 128));
+      const float4 P0 = J.spts[min(first + lane, J.n - 1)], P1 = J.spts[min(first + 64 + lane, J.n - 1)];
+      L.add(point_key(P0, q), first + lane < J.n);
+      L.add(point_key(P1, q), first + 64 + lane < J.n);
+      L.again();
+    }
+    visit_reach<KF_U, 18>(J, G, at, q, L, sh.w.seg[wave]);
+    if (L.cnt > 3 * 64) L.trim();
+    write_list<64>(L, k, J.nbr + (int64_t)__float_as_int(q.w) * k);
+  }
+  __syncthreads();  // the lists of the other kind lie in the same LDS
+  const int grp = threadIdx.x / KN_G;
+  for (int f = blockIdx.x * KN_Q + grp; f < n_near; f += gridDim.x * KN_Q) {
+    const int2 ct = far[1 + f];
+    const GridJob J = job_at(A, ct.x);
+    const GridInfo G = *J.gi;
+    const float4 q = J.spts[ct.y];
+    const int pc = J.scell[ct.y];
+    Place at{{pc & 1023, (pc >> 10) & 1023, pc >> 20}, {}};
+    at.set(G, q);
+    const int rmax = max(G.dims[0], max(G.dims[1], G.dims[2]));
+    // fewer than k keys below the cube's bound: all keys below twice that
+    // distance squared, then five times, ...
+    QueryList L{sh.g.key + grp * KN_STRIDE, 0, k, 0};
+    float reach2 = 2.f * key_of(cube_bound(G, at, 1));
+    for (;;) {
+      L.cnt = 0;
+      L.bound = min(KEY_INF, (uint64_t)__float_as_uint(reach2) << 32);
+      const int R = cells_reached(G, at, L.bound, rmax);
+      const bool last = L.bound == KEY_INF;
+      visit<KN_G, KN_U, 2>(J, G, at, q, R, -1, L, sh.g.seg[grp]);
+      if (L.cnt >= k || last) break;
+      reach2 *= 2.5f;
+    }
+    write_list<KN_G>(L, k, J.nbr + (int64_t)__float_as_int(q.w) * k);
+  }
 }
 
 // Curvature from the neighbour lists (FP64 covariance, 1/k, centred), one
@@ -830,488 +1256,322 @@ __device__ inline void curvature_block(const float4* __restrict__ p4, int n, int
 // Dynamic LDS of the curvature kernels: CURV_BT rows of curv_stride(k) ints.
 inline size_t curv_lds_bytes(int k) { return sizeof(int) * (size_t)CURV_BT * (size_t)(k | 1); }
 
-__global__ __launch_bounds__(CURV_BT) void curvature_kernel(const float4* __restrict__ p4, int n, int k,
-                                                            const int32_t* __restrict__ idx,
-                                                            float* __restrict__ a_out) {
+__global__ __launch_bounds__(CURV_BT) void curvature_kernel(GridArgs A, int k) {
   extern __shared__ int s_nb[];
-  curvature_block(p4, n, k, idx, a_out, blockIdx.x, s_nb);
+  int b;
+  const GridJob J = job_of(A, b);
+  if (J.a_out) curvature_block(J.p4, J.n, k, J.nbr, J.a_out, b, s_nb);
 }
 
-int grid_max_cells(int n) {
+// ------------------------------------------------------------------- host
+// Clouds of up to SMALL_N points (in a batch SMALL_BATCH_N, where the clouds
+// are built side by side) are built by one block, which takes 11 us at 1 024
+// points, 27 at 8 192 and 47 at 16 384; the six launches of the large build
+// take 32 us at 16 385 and 35 at 36 000, and the gaps between them.
+constexpr int SMALL_N = 8192;
+constexpr int SMALL_BATCH_N = 65535;  // 16-bit cell starts
+
+static int large_cells(int n) {
   int m = 1024;
-  while (m < 2 * n && m < (1 << 24)) m <<= 1;
+  while (m < 4 * n && m < (1 << 24)) m <<= 1;
   return m;
 }
-
-size_t grid_knn_workspace(int n, int k) {
-  const int max_cells = grid_max_cells(n);
-  const int nb = (max_cells + SCAN_B - 1) / SCAN_B;
-  size_t b = 0;
-  auto add = [&](size_t bytes) { b += (bytes + 255) & ~size_t(255); };
-  add(sizeof(GridInfo));
-  add(sizeof(int) * (size_t)n);            // cell_of
-  add(sizeof(int) * (size_t)max_cells);    // counts
-  add(sizeof(int) * (size_t)max_cells);    // cursor
-  add(sizeof(int) * ((size_t)max_cells + 1));  // starts
-  add(sizeof(int) * ((size_t)nb + 1));     // block sums
-  add(sizeof(float4) * (size_t)n);         // sorted points
-  add(sizeof(float4) * (size_t)n);         // packed points
-  add(sizeof(int32_t) * (size_t)n * k);    // neighbour lists
-  add(sizeof(int) * ((size_t)n + 1));      // far-query list
-  add(sizeof(int) * ((size_t)n + 1));      // second far-query list (batches)
-  return b;
-}
+static int small_cells(int n) { return std::min(2 * SM_WORDS, std::max(1024, 4 * n)); }
 
 namespace {
 
-struct GridBufs {
-  GridInfo* gi;
-  int* cell_of;
-  int* counts;
-  int* cursor;
-  int* starts;
-  int* bsum;
-  float4* spts;
-  float4* p4;  // the points in their own order, (x, y, z, 0)
-  int32_t* nbr;
-  int* far;  // [0]: count, [1..n]: sorted positions of the queries left to the far pass
-  int* far2;  // the same for the batch's second hand-over
-};
+size_t up256(size_t b) { return (b + 255) & ~size_t(255); }
 
-GridBufs carve_grid(void* ws, int n, int k) {
-  const int max_cells = grid_max_cells(n);
-  const int nb = (max_cells + SCAN_B - 1) / SCAN_B;
-  char* p = (char*)ws;
+// Workspace of one cloud, carved at ws (nullptr: size only).
+size_t carve_job(char* ws, int n, int k, GridJob* J) {
+  size_t o = 0;
   auto take = [&](size_t bytes) {
-    char* r = p;
-    p += (bytes + 255) & ~size_t(255);
+    char* r = ws + o;
+    o += up256(bytes);
     return (void*)r;
   };
-  GridBufs B;
-  B.gi = (GridInfo*)take(sizeof(GridInfo));
-  B.cell_of = (int*)take(sizeof(int) * (size_t)n);
-  B.counts = (int*)take(sizeof(int) * (size_t)max_cells);
-  B.cursor = (int*)take(sizeof(int) * (size_t)max_cells);
-  B.starts = (int*)take(sizeof(int) * ((size_t)max_cells + 1));
-  B.bsum = (int*)take(sizeof(int) * ((size_t)nb + 1));
-  B.spts = (float4*)take(sizeof(float4) * (size_t)n);
-  B.p4 = (float4*)take(sizeof(float4) * (size_t)n);
-  B.nbr = (int32_t*)take(sizeof(int32_t) * (size_t)n * k);
-  B.far = (int*)take(sizeof(int) * ((size_t)n + 1));
-  B.far2 = (int*)take(sizeof(int) * ((size_t)n + 1));
-  return B;
+  const int mc = large_cells(n);  // never below small_cells of the sizes that use them
+  const int cells = std::max(mc, small_cells(n));
+  GridJob T{};
+  T.gi = (GridInfo*)take(sizeof(GridInfo));
+  T.cell_of = (int*)take(sizeof(int) * (size_t)n);
+  T.rank = (int*)take(sizeof(int) * (size_t)n);
+  T.counts = (int*)take(sizeof(int) * (size_t)cells);
+  T.starts = (int*)take(sizeof(int) * ((size_t)cells + 1));
+  T.part = (int*)take(sizeof(int) * ((size_t)LG_PART + cells / LG_SCAN + 1));
+  T.spts = (float4*)take(sizeof(float4) * (size_t)n);
+  T.scell = (int*)take(sizeof(int) * (size_t)n);
+  T.p4 = (float4*)take(sizeof(float4) * (size_t)n);
+  T.nbr = (int32_t*)take(sizeof(int32_t) * (size_t)n * k);
+  T.blocks = (int*)take(sizeof(int) * ((size_t)n + 1));
+  if (J) {
+    T.n = n;
+    *J = T;
+  }
+  return o;
 }
 
-// Uniform grid of the points, counting-sorted by cell.
-hipError_t build_grid(const float* x, const float* y, const float* z, int n, const GridBufs& B, hipStream_t st) {
-  const int max_cells = grid_max_cells(n);
-  const int nb = (max_cells + SCAN_B - 1) / SCAN_B;
-  const dim3 gn((n + 255) / 256), b256(256);
-  hipLaunchKernelGGL(grid_setup_kernel, dim3(1), dim3(1024), 0, st, x, y, z, n, max_cells, B.gi, B.far);
-  if (hipError_t e = launch_fill_i(B.counts, max_cells, st)) return e;
-  hipLaunchKernelGGL(grid_count_kernel, gn, b256, 0, st, x, y, z, n, B.gi, B.cell_of, B.counts);
-  hipLaunchKernelGGL(grid_refine_kernel, dim3(1), dim3(1024), 0, st, B.counts, n, max_cells, B.gi);
-  if (hipError_t e = launch_fill_i(B.counts, max_cells, st)) return e;
-  if (hipError_t e = launch_fill_i(B.cursor, max_cells, st)) return e;
-  hipLaunchKernelGGL(grid_count_kernel, gn, b256, 0, st, x, y, z, n, B.gi, B.cell_of, B.counts);
-  hipLaunchKernelGGL(scan_local_kernel, dim3(nb), dim3(SCAN_B), 0, st, B.counts, max_cells, B.starts, B.bsum);
-  hipLaunchKernelGGL(scan_blocks_kernel, dim3(1), dim3(64), 0, st, B.bsum, nb);
-  hipLaunchKernelGGL(scan_add_kernel, dim3(nb), dim3(SCAN_B), 0, st, B.starts, max_cells, B.bsum, nb);
-  hipLaunchKernelGGL(grid_scatter_kernel, gn, b256, 0, st, x, y, z, n, B.cell_of, B.starts, B.cursor, B.spts,
-                     B.p4);
+size_t far_bytes(int64_t points) { return up256(sizeof(int2) * (size_t)(points + 2)); }
+
+hipError_t build_large(const GridJob& J, int2* far, hipStream_t st) {
+  const dim3 blocks(LG_BLOCKS), bt(LG_BT);
+  const unsigned ns = (unsigned)((J.max_cells + LG_SCAN - 1) / LG_SCAN);
+  hipLaunchKernelGGL(grid_box_kernel, blocks, bt, 0, st, J, far);
+  hipLaunchKernelGGL(grid_occupancy_kernel, blocks, bt, 0, st, J);
+  hipLaunchKernelGGL(grid_count_kernel, dim3((unsigned)std::min(2048, (J.n + LG_BT - 1) / LG_BT)), bt, 0, st, J);
+  hipLaunchKernelGGL(grid_sums_kernel, dim3(ns), dim3(1024), 0, st, J);
+  hipLaunchKernelGGL(grid_starts_kernel, dim3(ns), dim3(1024), 0, st, J);
+  const int pb = (J.n + LG_BT - 1) / LG_BT;
+  hipLaunchKernelGGL(grid_scatter_kernel, dim3((unsigned)(pb + std::min(256, pb))), bt, 0, st, J, pb);
+  return hipGetLastError();
+}
+
+hipError_t build_one(GridJob& J, int2* far, hipStream_t st) {
+  if (J.n > SMALL_N) {
+    J.max_cells = large_cells(J.n);
+    return build_large(J, far, st);
+  }
+  J.max_cells = small_cells(J.n);
+  hipLaunchKernelGGL(grid_small_kernel, dim3(1), dim3(SM_BT), sizeof(int) * (size_t)((J.max_cells + 1) / 2), st,
+                     GridArgs{J, nullptr, nullptr}, far);
   return hipGetLastError();
 }
 
 }  // namespace
 
+size_t grid_knn_workspace(int n, int k) { return carve_job(nullptr, n, k, nullptr) + far_bytes(n); }
+
 hipError_t launch_grid_knn(const float* x, const float* y, const float* z, int n, int k, float* a_out,
                            int32_t* idx_out, void* ws, hipStream_t st) {
-  const GridBufs B = carve_grid(ws, n, k);
-  if (hipError_t e = build_grid(x, y, z, n, B, st)) return e;
-  int32_t* lists = idx_out ? idx_out : B.nbr;
-  const dim3 gn((n + 255) / 256), b256(256);
-  const dim3 gq((n + GQ_BT - 1) / GQ_BT), bq(GQ_BT);
-  // pass 1: one lane per query up to shell KNN_RCAP; pass 2: one wave per
-  // query left over (a fixed grid of waves loops over the device-side list)
-  const dim3 gf(512);
-  if (k <= 8) {
-    hipLaunchKernelGGL(grid_knn_kernel<8>, gq, bq, 0, st, B.spts, B.starts, B.gi, n, k, KNN_RCAP, B.far, lists);
-    hipLaunchKernelGGL(grid_knn_far_kernel<8>, gf, bq, 0, st, B.spts, B.p4, B.starts, B.gi, k, B.far, lists);
-  } else if (k <= 16) {
-    hipLaunchKernelGGL(grid_knn_kernel<16>, gq, bq, 0, st, B.spts, B.starts, B.gi, n, k, KNN_RCAP, B.far, lists);
-    hipLaunchKernelGGL(grid_knn_far_kernel<16>, gf, bq, 0, st, B.spts, B.p4, B.starts, B.gi, k, B.far, lists);
-  } else if (k <= 24) {
-    hipLaunchKernelGGL(grid_knn_kernel<24>, gq, bq, 0, st, B.spts, B.starts, B.gi, n, k, KNN_RCAP, B.far, lists);
-    hipLaunchKernelGGL(grid_knn_far_kernel<24>, gf, bq, 0, st, B.spts, B.p4, B.starts, B.gi, k, B.far, lists);
-  } else {
-    hipLaunchKernelGGL(grid_knn_kernel<32>, gq, bq, 0, st, B.spts, B.starts, B.gi, n, k, KNN_RCAP, B.far, lists);
-    hipLaunchKernelGGL(grid_knn_far_kernel<32>, gf, bq, 0, st, B.spts, B.p4, B.starts, B.gi, k, B.far, lists);
-  }
+  GridJob J;
+  int2* far = (int2*)((char*)ws + carve_job((char*)ws, n, k, &J));
+  J.x = x, J.y = y, J.z = z, J.a_out = a_out;
+  J.occ = grid_occ(k);
+  if (idx_out) J.nbr = idx_out;
+  if (hipError_t e = build_one(J, far, st)) return e;
+  const GridArgs A{J, nullptr, nullptr};
+  // a few queries per group where there are many: fewer block starts
+  const int rounds = n <= 65536 ? 1 : 4;
+  hipLaunchKernelGGL(knn_kernel, dim3((unsigned)((n + KN_Q * rounds - 1) / (KN_Q * rounds))), dim3(KN_BT), 0, st, A, k,
+                     rounds, far, n + 1);
+  hipLaunchKernelGGL(knn_far_kernel, dim3(512), dim3(KN_BT), 0, st, A, k, far, n + 1);
   if (a_out)
-    hipLaunchKernelGGL(curvature_kernel, gn, dim3(CURV_BT), curv_lds_bytes(k), st, B.p4, n, k, lists, a_out);
+    hipLaunchKernelGGL(curvature_kernel, dim3((unsigned)((n + CURV_BT - 1) / CURV_BT)), dim3(CURV_BT),
+                       curv_lds_bytes(k), st, A, k);
   return hipGetLastError();
-}
-
-// Nearest point of the grid's cloud to each query (any points, inside or
-// outside the grid's box) among the points whose key is <= max_key: the
-// same shell search and (key, index) order as grid_knn_kernel with k = 1,
-// stopped once the unsearched cells lie beyond max_key.  A query with no
-// such point, or with a non-finite coordinate, gets index -1 and key +inf.
-__global__ __launch_bounds__(GQ_BT) void grid_nn_kernel(const float4* __restrict__ spts, const int* __restrict__ starts,
-                                                        const GridInfo* __restrict__ gi, const float* __restrict__ qx,
-                                                        const float* __restrict__ qy, const float* __restrict__ qz,
-                                                        int nq, float max_key, int32_t* __restrict__ nn,
-                                                        float* __restrict__ key) {
-  __shared__ float4 s_buf[SPAN_U * GQ_BT];
-  float4* buf = s_buf + threadIdx.x;
-  const int t = blockIdx.x * GQ_BT + threadIdx.x;
-  if (t >= nq) return;  // no barriers below
-  const GridInfo G = *gi;
-  const float qv[3] = {qx[t], qy[t], qz[t]};
-  float bd = INFINITY;
-  int bi = -1;
-  if (isfinite(qv[0]) && isfinite(qv[1]) && isfinite(qv[2])) {
-    int c[3];
-    for (int a = 0; a < 3; ++a) c[a] = cell_coord(qv[a], G.lo[a], G.h, G.dims[a]);
-    const int rmax = max(G.dims[0], max(G.dims[1], G.dims[2]));
-    for (int r = 0; r <= rmax; ++r) {
-      shell_spans(starts, G, c, r, [&](int p0, int p1) {
-        span_points(spts, p0, p1, buf, [&](const float4& P) {
-          const int j = __float_as_int(P.w);
-          const float ex = __fsub_rn(P.x, qv[0]), ey = __fsub_rn(P.y, qv[1]), ez = __fsub_rn(P.z, qv[2]);
-          const float d2 = __fadd_rn(__fadd_rn(__fmul_rn(ex, ex), __fmul_rn(ey, ey)), __fmul_rn(ez, ez));
-          if (key_less(d2, j, bd, bi)) {
-            bd = d2;
-            bi = j;
-          }
-        });
-      });
-      // distance from the query to any cell outside the searched cube
-      double lb = INFINITY;
-      bool all = true;
-      for (int a = 0; a < 3; ++a) {
-        if (c[a] - r > 0) {
-          lb = fmin(lb, (double)qv[a] - ((double)G.lo[a] + (double)(c[a] - r) * (double)G.h));
-          all = false;
-        }
-        if (c[a] + r < G.dims[a] - 1) {
-          lb = fmin(lb, ((double)G.lo[a] + (double)(c[a] + r + 1) * (double)G.h) - (double)qv[a]);
-          all = false;
-        }
-      }
-      if (all) break;
-      const double lbs = lb - 1e-3 * (double)G.h;
-      // nothing unsearched can beat the current best, or reach max_key
-      if (lbs > 0.0 && fmin((double)bd, (double)max_key) * 1.00001 < lbs * lbs) break;
-    }
-  }
-  if (!(bd <= max_key)) {
-    bd = INFINITY;
-    bi = -1;
-  }
-  nn[t] = bi;
-  key[t] = bd;
-}
-
-// ---------------------------------------------------------------- batches
-// The same exact search for many clouds (one launch per phase for all of
-// them): every cloud has its own grid and workspace region, and blocks are
-// mapped to clouds through a job table and a (cloud, block) list.
-struct GridJob {
-  const float* x;
-  const float* y;
-  const float* z;
-  float* a_out;
-  int n, max_cells;
-  GridInfo* gi;
-  int* cell_of;
-  int* counts;
-  int* cursor;
-  int* starts;
-  float4* spts;
-  float4* p4;
-  int32_t* nbr;
-  int* far;
-  int* far2;
-};
-
-// Job c of the table, with its pointers marked as global memory (gptr).
-__device__ inline GridJob job_at(const GridJob* jobs, int c) {
-  GridJob J = jobs[c];
-  J.x = gptr(J.x), J.y = gptr(J.y), J.z = gptr(J.z), J.a_out = gptr(J.a_out), J.gi = gptr(J.gi);
-  J.cell_of = gptr(J.cell_of), J.counts = gptr(J.counts), J.cursor = gptr(J.cursor), J.starts = gptr(J.starts);
-  J.spts = gptr(J.spts), J.p4 = gptr(J.p4), J.nbr = gptr(J.nbr), J.far = gptr(J.far), J.far2 = gptr(J.far2);
-  return J;
-}
-
-__global__ __launch_bounds__(1024) void grid_setup_batch_kernel(const GridJob* __restrict__ jobs) {
-  const GridJob J = job_at(jobs, blockIdx.x);
-  grid_setup_body(J.x, J.y, J.z, J.n, J.max_cells, J.gi, J.far, J.far2);
-}
-
-__global__ __launch_bounds__(1024) void grid_refine_batch_kernel(const GridJob* __restrict__ jobs) {
-  const GridJob J = job_at(jobs, blockIdx.x);
-  grid_refine_body(J.counts, J.n, J.max_cells, J.gi);
-}
-
-// counts (and, with both, cursor) of every cell set to 0; grid (clouds, splits)
-__global__ __launch_bounds__(1024) void grid_clear_batch_kernel(const GridJob* __restrict__ jobs, int both) {
-  const GridJob J = job_at(jobs, blockIdx.x);
-  for (int c = blockIdx.y * 1024 + threadIdx.x; c < J.max_cells; c += gridDim.y * 1024) {
-    J.counts[c] = 0;
-    if (both) J.cursor[c] = 0;
-  }
-}
-
-__global__ __launch_bounds__(256) void grid_count_batch_kernel(const GridJob* __restrict__ jobs,
-                                                               const int2* __restrict__ bmap) {
-  const int2 cb = bmap[blockIdx.x];
-  const GridJob J = job_at(jobs, cb.x);
-  grid_count_point(J.x, J.y, J.z, J.n, J.gi, J.cell_of, J.counts, cb.y * 256 + threadIdx.x);
-}
-
-// Exclusive scan of one cloud's cell counts into starts[0, max_cells], one
-// block per cloud, 1024 cells per step: wave scans by shuffles, then the
-// wave totals, then the running carry.
-__global__ __launch_bounds__(1024) void grid_scan_batch_kernel(const GridJob* __restrict__ jobs) {
-  __shared__ int s_w[16];
-  __shared__ int s_carry;
-  const GridJob J = job_at(jobs, blockIdx.x);
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  if (threadIdx.x == 0) s_carry = 0;
-  __syncthreads();
-  for (int base = 0; base < J.max_cells; base += 1024) {
-    const int i = base + threadIdx.x;
-    const int v = i < J.max_cells ? J.counts[i] : 0;
-    int x = v;
-    for (int off = 1; off < 64; off <<= 1) {
-      const int o = __shfl_up(x, off, 64);
-      if (lane >= off) x += o;
-    }
-    if (lane == 63) s_w[w] = x;
-    __syncthreads();
-    int before = s_carry;
-    for (int u = 0; u < w; ++u) before += s_w[u];
-    if (i < J.max_cells) J.starts[i] = before + x - v;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      int tot = 0;
-      for (int u = 0; u < 16; ++u) tot += s_w[u];
-      s_carry += tot;
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) J.starts[J.max_cells] = s_carry;
-}
-
-__global__ __launch_bounds__(256) void grid_scatter_batch_kernel(const GridJob* __restrict__ jobs,
-                                                                 const int2* __restrict__ bmap) {
-  const int2 cb = bmap[blockIdx.x];
-  const GridJob J = job_at(jobs, cb.x);
-  grid_scatter_point(J.x, J.y, J.z, J.n, J.cell_of, J.starts, J.cursor, J.spts, J.p4, cb.y * 256 + threadIdx.x);
-}
-
-template <int KC>
-__global__ __launch_bounds__(GQ_BT) void grid_knn_batch_kernel(const GridJob* __restrict__ jobs,
-                                                               const int2* __restrict__ bmap, int k) {
-  __shared__ float4 s_buf[SPAN_U * GQ_BT];
-  __shared__ uint64_t s_cand[KNN_CB * GQ_BT];
-  const int2 cb = bmap[blockIdx.x];
-  const GridJob J = job_at(jobs, cb.x);
-  grid_knn_query<KC>(J.spts, nullptr, J.starts, J.gi, J.n, k, KNN_RCAP, J.far, J.nbr, cb.y * GQ_BT + threadIdx.x,
-                     s_buf + threadIdx.x, s_cand + threadIdx.x, 0);
-}
-
-// The far queries of all clouds as one list: positions [off[c], off[c + 1])
-// are cloud c's far list (far, or far2 with `second`), with off (fq + 2,
-// n_clouds + 1 entries) the exclusive scan of their counts.  One block.
-__global__ __launch_bounds__(1024) void far_scan_batch_kernel(const GridJob* __restrict__ jobs, int n_clouds,
-                                                              int* __restrict__ fq, int second) {
-  __shared__ int s_w[16];
-  __shared__ int s_carry;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  int* off = fq + 2;
-  if (threadIdx.x == 0) s_carry = 0;
-  __syncthreads();
-  for (int base = 0; base < n_clouds; base += 1024) {
-    const int c = base + threadIdx.x;
-    const int v = c < n_clouds ? gptr(second ? jobs[c].far2 : jobs[c].far)[0] : 0;
-    int x = v;
-    for (int d = 1; d < 64; d <<= 1) {
-      const int o = __shfl_up(x, d, 64);
-      if (lane >= d) x += o;
-    }
-    if (lane == 63) s_w[w] = x;
-    __syncthreads();
-    int before = s_carry;
-    for (int u = 0; u < w; ++u) before += s_w[u];
-    if (c < n_clouds) off[c] = before + x - v;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      int tot = 0;
-      for (int u = 0; u < 16; ++u) tot += s_w[u];
-      s_carry += tot;
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) off[n_clouds] = s_carry;
-}
-
-// Cloud of far-list position g: the last c with off[c] <= g (a cloud without
-// far queries shares its offset with the next one, so the last such c is
-// the one whose range holds g), by bisection (off[n_clouds] = total > g).
-__device__ inline int far_cloud_of(const int* __restrict__ off, int n_clouds, int g) {
-  int lo = 0, hi = n_clouds;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (off[mid] <= g)
-      lo = mid;
-    else
-      hi = mid;
-  }
-  return lo;
-}
-
-// The handed-over queries of all clouds, one lane each: lane g of the grid
-// takes positions g, g + grid size, ... of the concatenated lists (far) and
-// resumes the one-lane search at shell r0; a query not finished after shell
-// r0 is handed over again, to far2, so that the few deep searches do not
-// hold up waves of queries that need one shell more.  (A lane per query suits the batch's many handed-over
-// queries; the one-cloud pass keeps a wave per query, which finishes a few
-// of them sooner.)
-template <int KC>
-__global__ __launch_bounds__(GQ_BT) void grid_knn_far_lanes_kernel(const GridJob* __restrict__ jobs, int n_clouds,
-                                                                   const int* __restrict__ fq, int k, int r0) {
-  __shared__ float4 s_buf[SPAN_U * GQ_BT];
-  __shared__ uint64_t s_cand[KNN_CB * GQ_BT];
-  const int* off = fq + 2;
-  const int total = off[n_clouds];
-  for (int g = blockIdx.x * GQ_BT + threadIdx.x; g < total; g += gridDim.x * GQ_BT) {
-    const int c = far_cloud_of(off, n_clouds, g);
-    const GridJob J = job_at(jobs, c);
-    grid_knn_query<KC>(J.spts, J.p4, J.starts, J.gi, J.n, k, r0, J.far2, J.nbr, J.far[1 + (g - off[c])],
-                       s_buf + threadIdx.x, s_cand + threadIdx.x, r0);
-  }
-}
-
-// The queries still open after the lane pass, one wave each (deep searches,
-// which one lane would take long over): wave w of the grid takes positions
-// w, w + number of waves, ... of the concatenated lists (far2), resuming at
-// shell r0.
-template <int KC>
-__global__ __launch_bounds__(GQ_BT) void grid_knn_far_waves_batch_kernel(const GridJob* __restrict__ jobs,
-                                                                         int n_clouds, const int* __restrict__ fq,
-                                                                         int k, int r0) {
-  __shared__ float4 s_buf[SPAN_U * GQ_BT];
-  const int* off = fq + 2;
-  const int total = off[n_clouds];
-  const int n_waves = (gridDim.x * GQ_BT) >> 6;
-  for (int g = (blockIdx.x * GQ_BT + threadIdx.x) >> 6; g < total; g += n_waves) {
-    const int c = far_cloud_of(off, n_clouds, g);
-    const GridJob J = job_at(jobs, c);
-    const GridInfo G = *J.gi;
-    grid_knn_far_query<KC>(J.spts, J.p4, J.starts, G, k, J.far2[1 + (g - off[c])], J.nbr, s_buf + threadIdx.x, r0);
-  }
-}
-
-// Block (cloud, block) of the list: CURV_BT points of one cloud, as
-// curvature_kernel.
-static_assert(CURV_BT == 256, "the (cloud, block) list counts blocks of 256 points");
-__global__ __launch_bounds__(CURV_BT) void curvature_batch_kernel(const GridJob* __restrict__ jobs,
-                                                                  const int2* __restrict__ bmap, int k) {
-  extern __shared__ int s_nb[];
-  const int2 cb = bmap[blockIdx.x];
-  const GridJob J = job_at(jobs, cb.x);
-  if (J.a_out) curvature_block(J.p4, J.n, k, J.nbr, J.a_out, cb.y, s_nb);
-}
-
-// The handed-over queries of a batch: shell KNN_RCAP + 1 with a lane per
-// query (far -> far2), then those still open with a wave per query.  The lane
-// pass gets more blocks than fit at once, so that every CU holds as many
-// waves as its LDS allows while the list lasts.  (Measured on the 512 clouds
-// of the batch workload: a wave per query for all of them took 1.5 times as
-// long, a lane per query for the deeper shells as well 1.2 to 2 times.)
-template <class LanesK, class WavesK>
-void far_passes(LanesK lanes, WavesK waves, const GridJob* d_jobs, int n_clouds, int* d_fq, int k, hipStream_t st) {
-  const dim3 gl(2048), gw(1024), bt(GQ_BT);
-  hipLaunchKernelGGL(far_scan_batch_kernel, dim3(1), dim3(1024), 0, st, d_jobs, n_clouds, d_fq, 0);
-  hipLaunchKernelGGL(lanes, gl, bt, 0, st, d_jobs, n_clouds, (const int*)d_fq, k, KNN_RCAP + 1);
-  hipLaunchKernelGGL(far_scan_batch_kernel, dim3(1), dim3(1024), 0, st, d_jobs, n_clouds, d_fq, 1);
-  hipLaunchKernelGGL(waves, gw, bt, 0, st, d_jobs, n_clouds, (const int*)d_fq, k, KNN_RCAP + 2);
 }
 
 size_t grid_knn_batch_workspace(const int* n, int n_clouds, int k) {
   size_t b = 0;
-  int64_t blocks = 0;
+  int64_t blocks = 0, points = 0;
   for (int c = 0; c < n_clouds; ++c) {
-    b += grid_knn_workspace(n[c], k);
+    b += carve_job(nullptr, n[c], k, nullptr);
     blocks += (n[c] + 255) / 256;
+    points += n[c];
   }
-  b += ((sizeof(GridJob) * (size_t)n_clouds + 255) & ~size_t(255)) + ((sizeof(int2) * (size_t)blocks + 255) & ~size_t(255));
-  b += (sizeof(int) * ((size_t)n_clouds + 3) + 255) & ~size_t(255);  // far list offsets (at + 2)
-  return b;
+  return b + up256(sizeof(GridJob) * (size_t)n_clouds) + up256(sizeof(int2) * (size_t)(blocks + n_clouds)) +
+         far_bytes(points);
 }
 
+// Many clouds: one launch per phase for all of them, through a table of jobs
+// and a list of (cloud, block of 256 points).  Clouds above SMALL_BATCH_N
+// points build their grids one after the other.
 hipError_t launch_grid_knn_batch(const float* const* x, const float* const* y, const float* const* z, const int* n,
                                  float* const* a_out, int32_t* const* idx_out, int n_clouds, int k, void* ws,
                                  hipStream_t st) {
   if (n_clouds < 1) return hipSuccess;
+  // one host table, one copy: the jobs, the (cloud, 0) list of the small
+  // builds, the (cloud, block) list
+  const size_t jobs_bytes = up256(sizeof(GridJob) * (size_t)n_clouds);
   std::vector<GridJob> jobs(n_clouds);
-  std::vector<int2> bmap;
+  std::vector<int2> small, bmap;
   char* p = (char*)ws;
+  int64_t points = 0;
+  int cells = 0;
   for (int c = 0; c < n_clouds; ++c) {
-    const GridBufs B = carve_grid(p, n[c], k);
-    p += grid_knn_workspace(n[c], k);
-    int32_t* lists = (idx_out && idx_out[c]) ? idx_out[c] : B.nbr;
-    jobs[c] = GridJob{x[c], y[c], z[c], a_out ? a_out[c] : nullptr, n[c], grid_max_cells(n[c]), B.gi, B.cell_of,
-                      B.counts, B.cursor, B.starts, B.spts, B.p4, lists, B.far, B.far2};
+    GridJob& J = jobs[c];
+    p += carve_job(p, n[c], k, &J);
+    J.x = x[c], J.y = y[c], J.z = z[c], J.a_out = a_out ? a_out[c] : nullptr;
+    J.occ = grid_occ(k);
+    if (idx_out && idx_out[c]) J.nbr = idx_out[c];
+    if (n[c] <= SMALL_BATCH_N) {
+      J.max_cells = small_cells(n[c]);
+      cells = std::max(cells, J.max_cells);
+      small.push_back(make_int2(c, 0));
+    } else {
+      J.max_cells = large_cells(n[c]);
+    }
     for (int b = 0; b < (n[c] + 255) / 256; ++b) bmap.push_back(make_int2(c, b));
+    points += n[c];
   }
-  GridJob* d_jobs = (GridJob*)p;
-  p += (sizeof(GridJob) * (size_t)n_clouds + 255) & ~size_t(255);
-  int2* d_bmap = (int2*)p;
-  p += (sizeof(int2) * bmap.size() + 255) & ~size_t(255);
-  int* d_fq = (int*)p;
-  hipError_t e = hipMemcpyAsync(d_jobs, jobs.data(), sizeof(GridJob) * jobs.size(), hipMemcpyHostToDevice, st);
+  // the largest first: a build takes as long as its cloud is large
+  std::stable_sort(small.begin(), small.end(), [&](const int2& a, const int2& b) { return n[a.x] > n[b.x]; });
+  std::vector<char> table(jobs_bytes + sizeof(int2) * (small.size() + bmap.size()));
+  std::copy((const char*)jobs.data(), (const char*)(jobs.data() + n_clouds), table.data());
+  std::copy((const char*)small.data(), (const char*)(small.data() + small.size()), table.data() + jobs_bytes);
+  std::copy((const char*)bmap.data(), (const char*)(bmap.data() + bmap.size()),
+            table.data() + jobs_bytes + sizeof(int2) * small.size());
+  const GridJob* d_jobs = (const GridJob*)p;
+  const int2* d_small = (const int2*)(p + jobs_bytes);
+  const int2* d_bmap = d_small + small.size();
+  int2* far = (int2*)(p + jobs_bytes + up256(sizeof(int2) * (small.size() + bmap.size())));
+  hipError_t e = hipMemcpyAsync(p, table.data(), table.size(), hipMemcpyHostToDevice, st);
   if (e != hipSuccess) return e;
-  e = hipMemcpyAsync(d_bmap, bmap.data(), sizeof(int2) * bmap.size(), hipMemcpyHostToDevice, st);
-  if (e != hipSuccess) return e;
-  // the copies read host vectors that go out of scope below
+  // the copy reads a host vector that goes out of scope below
   e = hipStreamSynchronize(st);
   if (e != hipSuccess) return e;
-  const dim3 gc((unsigned)n_clouds), gcs((unsigned)n_clouds, 16), gb((unsigned)bmap.size());
-  hipLaunchKernelGGL(grid_setup_batch_kernel, gc, dim3(1024), 0, st, d_jobs);
-  hipLaunchKernelGGL(grid_clear_batch_kernel, gcs, dim3(1024), 0, st, d_jobs, 0);
-  hipLaunchKernelGGL(grid_count_batch_kernel, gb, dim3(256), 0, st, d_jobs, d_bmap);
-  hipLaunchKernelGGL(grid_refine_batch_kernel, gc, dim3(1024), 0, st, d_jobs);
-  hipLaunchKernelGGL(grid_clear_batch_kernel, gcs, dim3(1024), 0, st, d_jobs, 1);
-  hipLaunchKernelGGL(grid_count_batch_kernel, gb, dim3(256), 0, st, d_jobs, d_bmap);
-  hipLaunchKernelGGL(grid_scan_batch_kernel, gc, dim3(1024), 0, st, d_jobs);
-  hipLaunchKernelGGL(grid_scatter_batch_kernel, gb, dim3(256), 0, st, d_jobs, d_bmap);
-
-  if (k <= 8) {
-    hipLaunchKernelGGL(grid_knn_batch_kernel<8>, gb, dim3(GQ_BT), 0, st, d_jobs, d_bmap, k);
-    far_passes(grid_knn_far_lanes_kernel<8>, grid_knn_far_waves_batch_kernel<8>, d_jobs, n_clouds, d_fq, k, st);
-  } else if (k <= 16) {
-    hipLaunchKernelGGL(grid_knn_batch_kernel<16>, gb, dim3(GQ_BT), 0, st, d_jobs, d_bmap, k);
-    far_passes(grid_knn_far_lanes_kernel<16>, grid_knn_far_waves_batch_kernel<16>, d_jobs, n_clouds, d_fq, k, st);
-  } else if (k <= 24) {
-    hipLaunchKernelGGL(grid_knn_batch_kernel<24>, gb, dim3(GQ_BT), 0, st, d_jobs, d_bmap, k);
-    far_passes(grid_knn_far_lanes_kernel<24>, grid_knn_far_waves_batch_kernel<24>, d_jobs, n_clouds, d_fq, k, st);
-  } else {
-    hipLaunchKernelGGL(grid_knn_batch_kernel<32>, gb, dim3(GQ_BT), 0, st, d_jobs, d_bmap, k);
-    far_passes(grid_knn_far_lanes_kernel<32>, grid_knn_far_waves_batch_kernel<32>, d_jobs, n_clouds, d_fq, k, st);
-  }
-  hipLaunchKernelGGL(curvature_batch_kernel, gb, dim3(CURV_BT), curv_lds_bytes(k), st, d_jobs, d_bmap, k);
+  for (int c = 0; c < n_clouds; ++c)
+    if (n[c] > SMALL_BATCH_N)
+      if ((e = build_large(jobs[c], far, st)) != hipSuccess) return e;
+  // (the far count is cleared by every large build and by cloud 0's small
+  // one; all of them run before the search)
+  if (!small.empty())
+    hipLaunchKernelGGL(grid_small_kernel, dim3((unsigned)small.size()), dim3(SM_BT), sizeof(int) * (size_t)((cells + 1) / 2), st,
+                       GridArgs{GridJob{}, d_jobs, d_small}, far);
+  const GridArgs A{GridJob{}, d_jobs, d_bmap};
+  const dim3 gb((unsigned)bmap.size());
+  hipLaunchKernelGGL(knn_kernel, gb, dim3(KN_BT), 0, st, A, k, 256 / KN_Q, far, (int)points + 1);
+  hipLaunchKernelGGL(knn_far_kernel, dim3(1024), dim3(KN_BT), 0, st, A, k, far, (int)points + 1);
+  hipLaunchKernelGGL(curvature_kernel, gb, dim3(CURV_BT), curv_lds_bytes(k), st, A, k);
   return hipGetLastError();
 }
 
+// ---------------------------------------------------------------- nearest
+// The nearest point kept by a group of GL lanes: each lane's own best key,
+// and the group's after every batch, which bounds the cells still visited.
+template <int GL, bool FUSED>
+struct Nearest {
+  uint64_t best, bound;
+
+  static __device__ uint64_t key_at(const float4& P, const float4& q) {
+    return FUSED ? point_key_fused(P, q) : point_key(P, q);
+  }
+
+  __device__ void add(uint64_t w, bool ok) {
+    if (ok && w < best) best = w;
+  }
+  template <int U>
+  __device__ void room() {}
+  __device__ void lower() {}
+  __device__ void again() {}
+  __device__ void settle() {
+    if constexpr (GL == 64) {
+      best = min(best, other<32>());
+      best = min(best, other<16>());
+    }
+    best = min(best, other<8>());
+    best = min(best, other<4>());
+    best = min(best, other<2>());
+    best = min(best, other<1>());
+    bound = min(bound, best);
+  }
+  template <int OFF>
+  __device__ uint64_t other() const {
+    return (uint64_t)xor_lane_u<OFF>((unsigned)(best >> 32)) << 32 | xor_lane_u<OFF>((unsigned)best);
+  }
+};
+
+constexpr int NN_RMAX = 3;  // cells from its own a group searches for a query before a wave takes it
+
+// Nearest point of the grid's cloud to each query (any points, inside or
+// outside the grid's box) among the points whose key is <= max_key: the same
+// (key, index) order as the neighbour lists, 16 lanes per query.  A query with
+// no such point, or with a non-finite coordinate, gets index -1 and key +inf.
+// Queries not settled within NN_RMAX cells go to the far list.  Bound by the
+// latency of the dependent loads (start of a row, its points): 115 us for
+// 250 000 queries near 307 200 points, where a lane per query took 872 us.
+template <bool FUSED>
+__global__ __launch_bounds__(KN_BT) void nearest_kernel(GridJob J, const float* __restrict__ qx,
+                                                        const float* __restrict__ qy, const float* __restrict__ qz,
+                                                        int nq, float max_key, int32_t* __restrict__ nn,
+                                                        float* __restrict__ key, int2* __restrict__ far) {
+  __shared__ int2 s_seg[KN_Q][KN_G * SEG_PER];
+  const GridInfo G = *J.gi;
+  const int grp = threadIdx.x / KN_G, l = threadIdx.x % KN_G;
+  const int t = blockIdx.x * KN_Q + grp;
+  if (t >= nq) return;  // no block barrier below; a group leaves as a whole
+  const float4 q = make_float4(qx[t], qy[t], qz[t], 0.f);
+  Nearest<KN_G, FUSED> N{KEY_INF, ((uint64_t)__float_as_uint(max_key) << 32) | 0xffffffffu};
+  bool found = true;
+  if (isfinite(q.x) && isfinite(q.y) && isfinite(q.z)) {
+    Place at;
+    cell_of_point(G, q.x, q.y, q.z, at.c);
+    at.set(G, q);
+    // the query's own cell first: in a dense cloud its best key leaves little
+    // of the others
+    for (int inner = -1, R = 0;;) {
+      visit<KN_G, KN_U, 1>(J, G, at, q, R, inner, N, s_seg[grp]);
+      const int want = cells_reached(G, at, N.bound, 1 << 20);
+      found = want <= R || cube_bound(G, at, R) == KEY_INF;
+      if (found || (R > 0 && want > NN_RMAX)) break;
+      inner = R;
+      R = R == 0 ? 1 : want;
+    }
+  }
+  if (l != 0) return;
+  if (!found) {
+    far[1 + atomicAdd(&far[0].x, 1)] = make_int2(0, t);
+    return;
+  }
+  const bool hit = N.best < KEY_INF && key_of(N.best) <= max_key;
+  nn[t] = hit ? (int32_t)(uint32_t)N.best : -1;
+  key[t] = hit ? key_of(N.best) : INFINITY;
+}
+
+// The queries nearest_kernel left, one wave each: 64 points around the place
+// in the sorted array where the query's cell begins give a first bound for a
+// search of the cells within reach or, if these are many, by blocks of cells.
+constexpr int NF_RMAX = 6;
+
+template <bool FUSED>
+__global__ __launch_bounds__(KN_BT) void nearest_far_kernel(GridJob J, const float* __restrict__ qx,
+                                                            const float* __restrict__ qy,
+                                                            const float* __restrict__ qz, float max_key,
+                                                            int32_t* __restrict__ nn, float* __restrict__ key,
+                                                            const int2* __restrict__ far) {
+  __shared__ int2 s_seg[KN_BT / 64][64 * SEG_PER];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int total = far[0].x;
+  const GridInfo G = *J.gi;
+  for (int f = (blockIdx.x * KN_BT + threadIdx.x) >> 6; f < total; f += (gridDim.x * KN_BT) >> 6) {
+    const int t = far[1 + f].y;
+    const float4 q = make_float4(qx[t], qy[t], qz[t], 0.f);
+    Place at;
+    cell_of_point(G, q.x, q.y, q.z, at.c);
+    at.set(G, q);
+    Nearest<64, FUSED> N{KEY_INF, ((uint64_t)__float_as_uint(max_key) << 32) | 0xffffffffu};
+    const int first = max(0, min(J.starts[cell_index(G, at.c)] - 32, J.n - 64));
+    N.add(N.key_at(J.spts[min(first + lane, J.n - 1)], q), true);
+    N.settle();
+    if (cells_reached(G, at, N.bound, 1 << 20) <= NF_RMAX)
+      visit<64, KF_U, KF_ROWS>(J, G, at, q, NF_RMAX, -1, N, s_seg[wave]);
+    else
+      visit_blocks<KF_U>(J, G, at, q, N, s_seg[wave]);
+    if (lane == 0) {
+      const bool hit = N.best < KEY_INF && key_of(N.best) <= max_key;
+      nn[t] = hit ? (int32_t)(uint32_t)N.best : -1;
+      key[t] = hit ? key_of(N.best) : INFINITY;
+    }
+  }
+}
+
+// Workspace: the grid's, and a far list of nq entries.
+size_t grid_nn_workspace(int n, int nq) { return carve_job(nullptr, n, 1, nullptr) + far_bytes(nq); }
+
 hipError_t launch_grid_nn(const float* x, const float* y, const float* z, int n, const float* qx, const float* qy,
-                          const float* qz, int nq, float max_key, int32_t* nn, float* key, void* ws, hipStream_t st) {
-  const GridBufs B = carve_grid(ws, n, 1);
-  if (hipError_t e = build_grid(x, y, z, n, B, st)) return e;
-  hipLaunchKernelGGL(grid_nn_kernel, dim3((nq + GQ_BT - 1) / GQ_BT), dim3(GQ_BT), 0, st, B.spts, B.starts, B.gi, qx,
-                     qy, qz, nq, max_key, nn, key);
+                          const float* qz, int nq, float max_key, bool fused, int32_t* nn, float* key, void* ws,
+                          hipStream_t st) {
+  GridJob J;
+  int2* far = (int2*)((char*)ws + carve_job((char*)ws, n, 1, &J));
+  J.x = x, J.y = y, J.z = z;
+  J.occ = 4.0f;
+  J.reach = std::min(1e30f, 1.002f * std::sqrt(max_key));
+  if (hipError_t e = build_one(J, far, st)) return e;
+  auto search = fused ? nearest_kernel<true> : nearest_kernel<false>;
+  auto search_far = fused ? nearest_far_kernel<true> : nearest_far_kernel<false>;
+  hipLaunchKernelGGL(search, dim3((unsigned)((nq + KN_Q - 1) / KN_Q)), dim3(KN_BT), 0, st, J, qx, qy, qz, nq, max_key,
+                     nn, key, far);
+  hipLaunchKernelGGL(search_far, dim3(2048), dim3(KN_BT), 0, st, J, qx, qy, qz, max_key, nn, key, far);
   return hipGetLastError();
 }
 

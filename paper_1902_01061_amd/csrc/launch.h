@@ -164,7 +164,6 @@ hipError_t launch_fill(double* p, int n, double v, hipStream_t st);
 hipError_t launch_fill_f(float* p, int64_t n, float v, hipStream_t st);
 hipError_t launch_identity_pose(double* pose, hipStream_t st);
 hipError_t launch_fill_i(int* p, int n, hipStream_t st);
-int grid_max_cells(int n);
 size_t grid_knn_workspace(int n, int k);
 // The grid search (launch_grid_knn) for many clouds at once: cloud c has
 // n[c] points at x[c], y[c], z[c] and receives its curvatures in a_out[c]
@@ -180,9 +179,12 @@ hipError_t launch_grid_knn(const float* x, const float* y, const float* z, int n
                            int32_t* idx_out, void* ws, hipStream_t st);
 // Nearest point of the cloud (x, y, z, n) to each query among those with
 // key <= max_key (-1 / +inf if none), same order as the grid kNN (FP32 key,
-// ties by index); ws: grid_knn_workspace(n, 1) bytes.
+// ties by index), or, fused, in that of the key with its squares fused into the
+// sums; ws: grid_nn_workspace(n, nq) bytes.
+size_t grid_nn_workspace(int n, int nq);
 hipError_t launch_grid_nn(const float* x, const float* y, const float* z, int n, const float* qx, const float* qy,
-                          const float* qz, int nq, float max_key, int32_t* nn, float* key, void* ws, hipStream_t st);
+                          const float* qz, int nq, float max_key, bool fused, int32_t* nn, float* key, void* ws,
+                          hipStream_t st);
 // Change flags of the posed template against the reference (see change.hip);
 // ws: change_workspace(M, N) bytes.
 size_t change_workspace(int M, int N);

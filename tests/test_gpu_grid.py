@@ -1,0 +1,124 @@
+"""Edges of the grid search behind the neighbour lists and the change
+detection: the sizes at which the build changes hands (one block or many
+launches), lists that overflow and are cut, and queries far from every point.
+Lists and nearest points are compared exactly with brute force (FP32 keys,
+ties by index)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ref as O
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sg():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1902_01061_amd as sg
+    return sg
+
+
+@pytest.fixture(scope="module")
+def ctx(sg):
+    c = sg.Context(0)
+    yield c
+    c.close()
+
+
+def _surface(n, seed, spread=0.002):
+    rng = np.random.default_rng(seed)
+    u = rng.normal(size=(n, 3))
+    u /= np.linalg.norm(u, axis=1, keepdims=True)
+    return (u * [1.0, 0.7, 0.4] + rng.normal(size=(n, 3)) * spread).astype(np.float32)
+
+
+def _check_lists(P, idx, k, q):
+    assert np.array_equal(idx[q], O.knn_c(P, k, q))
+
+
+@pytest.mark.parametrize("n,k", [(1, 1), (2, 2), (33, 32), (255, 7), (256, 32), (257, 1), (8191, 24), (8192, 32),
+                                 (8193, 32), (65535, 16), (65536, 16)])
+def test_lists_where_the_build_changes(sg, ctx, n, k):
+    P = _surface(n, n)
+    q = np.arange(n) if n <= 257 else np.random.default_rng(1).choice(n, 400, replace=False)
+    q[-1] = n - 1
+    _check_lists(P, ctx.knn(sg.Cloud(P), k).cpu().numpy(), k, q)
+
+
+@pytest.mark.parametrize("sizes", [(65535, 40, 1000), (65536, 40, 65535)])
+def test_batch_lists_where_the_build_changes(sg, ctx, sizes):
+    k = 16
+    clouds = [_surface(n, i) for i, n in enumerate(sizes)]
+    _, idx = ctx.descriptors_batch([sg.Cloud(P) for P in clouds], k, want_idx=True)
+    torch.cuda.synchronize()
+    for P, i in zip(clouds, idx):
+        q = np.random.default_rng(2).choice(len(P), min(len(P), 300), replace=False)
+        _check_lists(P, i.cpu().numpy(), k, q)
+
+
+def _uneven(kind, n):
+    rng = np.random.default_rng(5)
+    if kind == "one point many times":
+        return np.tile(np.float32([[0.3, -0.2, 0.1]]), (n, 1))
+    if kind == "dense spot and wide halo":      # far queries of every depth, cells above any list
+        spot = rng.normal(size=(n - 600, 3)) * 1e-3
+        halo = rng.normal(size=(600, 3)) * np.exp(rng.uniform(-6, 5, size=(600, 1)))
+        return np.concatenate([spot, halo]).astype(np.float32)
+    if kind == "two spots far apart":           # most cells empty
+        return np.concatenate([rng.normal(size=(n - 5, 3)) * 1e-2,
+                               rng.normal(size=(5, 3)) * 1e-2 + [300.0, 200.0, -100.0]]).astype(np.float32)
+    t = np.arange(n)                            # exact ties along a row
+    return np.stack([t, 0 * t, 0 * t], 1).astype(np.float32)
+
+
+@pytest.mark.parametrize("kind", ["one point many times", "dense spot and wide halo", "two spots far apart", "row"])
+@pytest.mark.parametrize("n,k", [(3000, 5), (3000, 32), (20000, 24)])
+def test_lists_of_uneven_clouds(sg, ctx, kind, n, k):
+    P = _uneven(kind, n)
+    q = np.unique(np.concatenate([np.random.default_rng(3).choice(n, 150, replace=False), np.arange(n - 700, n, 5),
+                                  [0, n - 1]]))
+    _check_lists(P, ctx.knn(sg.Cloud(P), k).cpu().numpy(), k, q)
+
+
+def _nearest(Y, X, fused=False):
+    """Index and FP32 key of the nearest point of X for each row of Y; the
+    residual's key has its squares fused into the sums (one rounding each)."""
+    nn, key = np.empty(len(Y), np.int32), np.empty(len(Y), np.float32)
+    for i0 in range(0, len(Y), 256):
+        d = X[None] - Y[i0:i0 + 256, None]
+        if fused:
+            e = d.astype(np.float64) ** 2
+            d2 = e[..., 1].astype(np.float32)
+            for a in (0, 2):
+                d2 = (e[..., a] + d2).astype(np.float32)
+        else:
+            d2 = (d[..., 0] * d[..., 0] + d[..., 1] * d[..., 1]) + d[..., 2] * d[..., 2]
+        nn[i0:i0 + 256] = d2.argmin(1)
+        key[i0:i0 + 256] = d2.min(1)
+    return nn, key
+
+
+@pytest.mark.parametrize("kind", ["surface", "dense spot and wide halo", "two spots far apart"])
+@pytest.mark.parametrize("n", [1, 70, 3000, 17000])
+@pytest.mark.parametrize("tau", [1e-3, 0.1, 3.0, 1e18])
+def test_nearest_points_from_anywhere(sg, ctx, kind, n, tau):
+    """Queries among the points, near them, far outside their box and
+    non-finite, for bounds from a fraction of a cell to everything."""
+    if n < 1000 and kind != "surface":
+        pytest.skip("the uneven clouds need room for their parts")
+    X = _surface(n, 7) if kind == "surface" else _uneven(kind, n)
+    rng = np.random.default_rng(8)
+    Y = np.concatenate([X[rng.integers(0, n, 300)], X[rng.integers(0, n, 300)] + rng.normal(size=(300, 3)) * 0.05,
+                        rng.normal(size=(200, 3)) * [3.0, 5.0, 4.0], rng.normal(size=(60, 3)) * 1e3,
+                        [[np.nan, 0, 0], [0, np.inf, 0]]]).astype(np.float32)
+    a = torch.zeros(len(Y), device="cuda")
+    ax = torch.zeros(n, device="cuda")
+    flags, nn, key = ctx.change_detect(sg.Cloud(Y), a, sg.Cloud(X), ax, sg.pose_identity(), tau)
+    want_nn, want_key = _nearest(Y[:-2], X)
+    hit = want_key <= np.float32(tau) * np.float32(tau)
+    want_nn = np.where(hit, want_nn, -1)
+    assert np.array_equal(nn.cpu().numpy()[:-2], want_nn)
+    assert np.array_equal(key.cpu().numpy()[:-2][hit], want_key[hit])
+    assert (nn.cpu().numpy()[-2:] == -1).all()
