@@ -1454,14 +1454,18 @@ int sgr_residual(sgr_ctx* ctx, const sgr_cloud* tmpl, const sgr_cloud* ref, cons
   if (int e = check_cloud(ref, "reference")) return e;
   HIPCHK(hipSetDevice(ctx->device));
   const int M = (int)tmpl->n, N = (int)ref->n;
-  const int nblk = residual_blocks(M);
-  Carve cv{nullptr};
-  cv.take<double>((size_t)nblk * 2);
-  if (int e = ensure_ws(ctx, cv.off)) return e;
-  Carve w{ctx->ws};
-  double* part = w.take<double>((size_t)nblk * 2);
-  HIPCHK(launch_residual(tmpl->x, tmpl->y, tmpl->z, M, ref->x, ref->y, ref->z, N, (const double*)pose, corr, part,
-                         nblk, rmse_out, (hipStream_t)stream));
+  // The grid's scratch is some 100 bytes per point; where a capture or the
+  // device's memory does not allow it, the search over all of the reference
+  // needs almost none.
+  bool grid = residual_grid(N, corr != nullptr);
+  if (grid && residual_workspace(M, N, true) > ctx->ws_size) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    HIPCHK(hipStreamIsCapturing((hipStream_t)stream, &cap));
+    grid = cap == hipStreamCaptureStatusNone && ensure_ws(ctx, residual_workspace(M, N, true)) == SGR_OK;
+  }
+  if (int e = ensure_ws(ctx, residual_workspace(M, N, grid))) return e;
+  HIPCHK(launch_residual(tmpl->x, tmpl->y, tmpl->z, M, ref->x, ref->y, ref->z, N, (const double*)pose, corr, grid,
+                         ctx->ws, rmse_out, (hipStream_t)stream));
   return SGR_OK;
 }
 

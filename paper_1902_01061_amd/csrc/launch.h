@@ -370,9 +370,13 @@ int force_chunk_gran();
 int force_tile_j();
 hipError_t launch_update(const double* wpart, int nblk, const double* pose_in, double* pose_out, Derived* dv, int t,
                          double G_fixed, int do_update, double* wrench_out, double* stats_row, hipStream_t st);
+// ws: residual_workspace(M, N, grid) bytes; grid (only without corr): nearest
+// points by the grid search, where residual_grid() finds that the faster one.
 hipError_t launch_residual(const float* yx, const float* yy, const float* yz, int M, const float* xx, const float* xy,
-                           const float* xz, int N, const double* pose, const int32_t* corr, double* part, int nblk,
+                           const float* xz, int N, const double* pose, const int32_t* corr, bool grid, void* ws,
                            double* rmse_out, hipStream_t st);
+bool residual_grid(int N, bool has_corr);
+size_t residual_workspace(int M, int N, bool grid);
 int residual_blocks(int M);
 
 }  // namespace sgr

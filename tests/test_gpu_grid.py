@@ -122,3 +122,47 @@ def test_nearest_points_from_anywhere(sg, ctx, kind, n, tau):
     assert np.array_equal(nn.cpu().numpy()[:-2], want_nn)
     assert np.array_equal(key.cpu().numpy()[:-2][hit], want_key[hit])
     assert (nn.cpu().numpy()[-2:] == -1).all()
+
+
+@pytest.mark.parametrize("m", [1, 257, 3000])
+@pytest.mark.parametrize("n", [1023, 1024, 1025, 16385])
+@pytest.mark.parametrize("shift", [0.0, 0.4, 50.0])
+def test_residual_on_both_sides_of_the_switch(sg, ctx, m, n, shift):
+    """References around the size from which the residual searches the grid,
+    near and far from the template.  The FP64 mean over the points brute force
+    picks: T differs by an FP64 rounding (fused multiply-adds), at most 1e-14
+    of the smallest distances here, and so do the sums of up to 3 000 squares:
+    1e-12.  (An FP64 rounding of T changes its FP32 rounding once in 1e8
+    coordinates.)"""
+    X, Y = _surface(n, 11), _surface(m, 12)
+    R = np.linalg.qr(np.random.default_rng(13).normal(size=(3, 3)))[0]
+    R *= np.sign(np.linalg.det(R))
+    s, t = 1.07, np.array([shift, -0.3 * shift, 0.1])
+    got = ctx.residual(sg.Cloud(Y), sg.Cloud(X), sg.pose_from_srt(s, R, t)).item()
+    T = np.empty((m, 3))
+    y = Y.astype(np.float64)
+    for r in range(3):
+        T[:, r] = s * (R[r, 0] * y[:, 0] + R[r, 1] * y[:, 1] + R[r, 2] * y[:, 2]) + t[r]
+    nn, _ = _nearest(T.astype(np.float32), X, fused=True)
+    want = np.sqrt((((T - X[nn].astype(np.float64)) ** 2).sum(1)).mean())
+    assert got == pytest.approx(want, rel=1e-12)
+
+
+def test_residual_in_a_capture_that_cannot_grow_the_scratch(sg):
+    c = sg.Context(0)
+    Y, X = _surface(2000, 21), _surface(20000, 22)
+    ty, tx, p = sg.Cloud(Y), sg.Cloud(X), sg.pose_identity()
+    small = sg.Cloud(Y[:10])
+    c.residual(small, small, p)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        out = c.residual(ty, tx, p)
+    want = None
+    for _ in range(3):
+        g.replay()
+        torch.cuda.synchronize()
+        want = out.item() if want is None else want
+        assert out.item() == want
+    assert c.residual(ty, tx, p).item() == want   # now through the grid, the same bits
+    c.close()
