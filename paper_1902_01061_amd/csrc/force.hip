@@ -720,34 +720,17 @@ static void launch_force_r(const ForceArgs& A, int pm, bool sm, int nblk, bool w
   }
 }
 
-// Resident blocks per CU of the force kernel (cached per instantiation).
-template <int R, int PM, bool SM>
-static int force_occ() {
-  static int occ = 0;
-  if (occ == 0) {
-    int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, force_kernel<R, PM, false, false, SM>, F_BT, 0) !=
-            hipSuccess ||
-        n < 1)
-      n = 1;
-    occ = n;
-  }
-  return occ;
-}
-
-template <int R>
-static int force_occ_r(int pm, bool sm) {
-  if (pm == 1) return sm ? force_occ<R, 1, true>() : force_occ<R, 1, false>();
-  if (pm == 3) return sm ? force_occ<R, 3, true>() : force_occ<R, 3, false>();
-  return sm ? force_occ<R, 0, true>() : force_occ<R, 0, false>();
-}
-
+// Blocks per CU the reference is cut for where no tile choice says otherwise:
+// what the register counts of these kernels gave when the cut was chosen.
+// Constants, because the FP32 sums are those of the chunks: with the
+// occupancy asked of the runtime, a compiler that saves a register changes
+// the forces.
 int force_blocks_per_cu(int R, int pm, bool sm) {
   switch (R) {
-    case 1: return force_occ_r<1>(pm, sm);
-    case 2: return force_occ_r<2>(pm, sm);
-    case 4: return force_occ_r<4>(pm, sm);
-    case 8: return force_occ_r<8>(pm, sm);
+    case 1: return 8;
+    case 2: return sm || pm == 3 ? 8 : 7;
+    case 4: return sm || pm == 3 ? 5 : 4;
+    case 8: return sm || pm != 1 ? 3 : 2;
     default: return 1;
   }
 }

@@ -338,8 +338,8 @@ hipError_t launch_prepare(const float* aX, const float* wX, int64_t N, const flo
 hipError_t launch_pack_ref(const float* x, const float* y, const float* z, const float* aX, const float* wX, int64_t N,
                            const Derived* dv, float4* ref4, float* lw, hipStream_t st);
 hipError_t launch_force(const ForceArgs& A, int R, int pm, bool want_u, bool want_f, hipStream_t st, bool sm);
-// Resident blocks per CU of the force kernel without energy or per-point
-// output (R points per lane, p mode, scalar-load variant).
+// Blocks per CU the force kernel's launch is shaped for (R points per lane, p
+// mode, scalar-load variant).
 int force_blocks_per_cu(int R, int pm, bool sm);
 hipError_t launch_moments_batch(const CloudDesc* clouds, int n_clouds, double* out, hipStream_t st);
 hipError_t launch_prepare_batch(const PrepDesc* d, int B, const PrepParams& P, Derived* outs, hipStream_t st);
