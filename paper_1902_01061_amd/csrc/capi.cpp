@@ -617,6 +617,7 @@ struct SingleWs {
   float* aX;
   float* aY;
   double* mom;  // template [0, 10), reference [10, 20)
+  double* wide; // WIDE_PART doubles
   Derived* dv;
   float4* ref4;
   float* lw;
@@ -656,6 +657,7 @@ int carve_single(sgr_ctx* ctx, int M, int N, const sgr_params* prm, int kmax, Si
     w.aX = c.take<float>(N);
     w.aY = c.take<float>(M);
     w.mom = c.take<double>(20);
+    w.wide = c.take<double>(WIDE_PART);
     w.dv = c.take<Derived>(1);
     w.ref4 = c.take<float4>(pad_n(N));
     w.lw = c.take<float>(pad_n(N));
@@ -681,7 +683,7 @@ int carve_single(sgr_ctx* ctx, int M, int N, const sgr_params* prm, int kmax, Si
 int setup_single(const sgr_cloud* tmpl, const sgr_cloud* ref, const PrepParams& P, bool want_s2, SingleWs& w,
                  hipStream_t st) {
   const int M = (int)tmpl->n, N = (int)ref->n;
-  HIPCHK(launch_prepare(w.aX, ref->m, N, w.aY, tmpl->m, M, w.mom, w.mom + 10, P, w.dv, st));
+  HIPCHK(launch_prepare(w.aX, ref->m, N, w.aY, tmpl->m, M, w.mom, w.mom + 10, P, w.wide, w.dv, st));
   HIPCHK(launch_pack_ref(ref->x, ref->y, ref->z, w.aX, ref->m, N, w.dv, w.ref4, w.lw, st));
   if (!w.ps_S) HIPCHK(launch_sort_perm(w.aY, M, w.perm, w.sws, st));
   HIPCHK(launch_pack_tmpl(tmpl->x, tmpl->y, tmpl->z, w.aY, tmpl->m, M, w.ps_S ? nullptr : w.perm, w.dv, w.tm4, w.tmx,
@@ -787,6 +789,9 @@ struct VecWs {
   double* wpart;
   double* fpart;
   double* mom;
+  double* wide;  // WIDE_PART doubles
+  double* vs;    // scratch of the descriptor statistics
+  unsigned long long* far_mask;
   int K, n_chunks, slots;
   int n_cu;   // compute units (the far-row grid is one round of blocks)
   bool half;  // split-f16 products (decided by setup_vec)
@@ -818,6 +823,7 @@ int carve_vec(sgr_ctx* ctx, int M, int N, int D, bool with_f, bool with_mom, Vec
     Carve c{pass ? ctx->ws : nullptr};
     w.dv = c.take<Derived>(1);
     w.vd = c.take<double>(36);
+    w.vs = c.take<double>(vprep_scratch());
     // rows of K floats (FP32 form) or vforce_half_K(D) halves (split f16)
     const size_t row_words = (size_t)std::max(w.K, vforce_half_K(D) / 2);
     w.At = c.take<float>((size_t)vforce_pad_rows(M) * row_words);
@@ -826,7 +832,9 @@ int carve_vec(sgr_ctx* ctx, int M, int N, int D, bool with_f, bool with_mom, Vec
     w.wpart = c.take<double>((size_t)wslots * WR_STRIDE);
     w.fpart = with_f ? c.take<double>((size_t)w.n_chunks * M * 3) : nullptr;
     w.mom = with_mom ? c.take<double>(20) : nullptr;
+    w.wide = c.take<double>(WIDE_PART);
     w.far_idx = c.take<int>((size_t)M + 1);
+    w.far_mask = c.take<unsigned long long>(vfar_mask_words(M));
     w.far_ref = c.take<double>((size_t)vfar_pad_refs(N) * vfar_stride(D));
     w.far_part = c.take<double>(vfar_part_doubles(M));
     if (pinv) {
@@ -849,9 +857,9 @@ int carve_vec(sgr_ctx* ctx, int M, int N, int D, bool with_f, bool with_mom, Vec
 int setup_vec(const sgr_cloud* tmpl, const float* a_t, const sgr_cloud* ref, const float* a_r, int D,
               const double* mom_t, const double* mom_r, const sgr_params* prm, VecWs& w, hipStream_t st) {
   const int M = (int)tmpl->n, N = (int)ref->n;
-  HIPCHK(launch_prepare(nullptr, ref->m, N, nullptr, tmpl->m, M, mom_t, mom_r, prep_of(prm), w.dv, st));
-  HIPCHK(launch_vprep(a_r, N, a_t, M, D, prm->sigma, w.dv, w.vd, st));
-  HIPCHK(launch_vfar_list(a_t, M, D, w.vd, w.dv, w.far_idx, st));
+  HIPCHK(launch_prepare(nullptr, ref->m, N, nullptr, tmpl->m, M, mom_t, mom_r, prep_of(prm), w.wide, w.dv, st));
+  HIPCHK(launch_vprep(a_r, N, a_t, M, D, prm->sigma, w.dv, w.vd, w.vs, st));
+  HIPCHK(launch_vfar_list(a_t, M, D, w.vd, w.dv, w.far_mask, w.far_idx, st));
   double cmax = 0.0;
   int n_far = 0;
   HIPCHK(hipMemcpyAsync(&cmax, w.vd + 34, sizeof(double), hipMemcpyDeviceToHost, st));
@@ -966,7 +974,7 @@ int setup_unrolled(const sgr_cloud* tmpl, const float* a_t, const sgr_cloud* ref
   // forward poses bit for bit
   PrepParams P = prep_of(prm);
   P.cold_svd = 1;
-  HIPCHK(launch_prepare(a_r, ref->m, U.N, a_t, tmpl->m, U.M, mom_t, mom_r, P, U.dv, st));
+  HIPCHK(launch_prepare(a_r, ref->m, U.N, a_t, tmpl->m, U.M, mom_t, mom_r, P, nullptr, U.dv, st));
   HIPCHK(launch_pack_ref(ref->x, ref->y, ref->z, a_r, ref->m, U.N, U.dv, U.ref4, U.lw, st));
   HIPCHK(launch_sort_perm(a_t, U.M, U.perm, U.sws, st));
   HIPCHK(launch_pack_tmpl(tmpl->x, tmpl->y, tmpl->z, a_t, tmpl->m, U.M, U.perm, U.dv, U.tm4, U.tmx, st));
@@ -1079,11 +1087,18 @@ int sgr_descriptors(sgr_ctx* ctx, const sgr_cloud* c, int k, float* a_out, doubl
   if (!a_out && !moments_out) return fail(SGR_EINVAL, "nothing to compute");
   HIPCHK(hipSetDevice(ctx->device));
   hipStream_t st = (hipStream_t)stream;
+  double* part = nullptr;
   if (a_out) {
-    if (int e = ensure_ws(ctx, grid_knn_workspace((int)c->n, k))) return e;
-    HIPCHK(launch_grid_knn(c->x, c->y, c->z, (int)c->n, k, a_out, nullptr, ctx->ws, st));
+    Carve cv{nullptr};
+    cv.take<char>(grid_knn_workspace((int)c->n, k));
+    cv.take<double>(WIDE_PART);
+    if (int e = ensure_ws(ctx, cv.off)) return e;
+    Carve w{ctx->ws};
+    char* gws = w.take<char>(grid_knn_workspace((int)c->n, k));
+    part = w.take<double>(WIDE_PART);
+    HIPCHK(launch_grid_knn(c->x, c->y, c->z, (int)c->n, k, a_out, nullptr, gws, st));
   }
-  if (moments_out) HIPCHK(launch_moments(c->x, c->y, c->z, c->n, moments_out, st));
+  if (moments_out) HIPCHK(launch_moments(c->x, c->y, c->z, c->n, part, moments_out, st));
   return SGR_OK;
 }
 
@@ -1149,7 +1164,7 @@ static int step_impl(sgr_ctx* ctx, const sgr_cloud* tmpl, const float* a_t, cons
   float4* tm4 = w.take<float4>(M);
   float2* tmx = w.take<float2>(M);
 
-  HIPCHK(launch_prepare(a_r, ref->m, N, a_t, tmpl->m, M, mom_t, mom_r, prep_of(prm), dv, st));
+  HIPCHK(launch_prepare(a_r, ref->m, N, a_t, tmpl->m, M, mom_t, mom_r, prep_of(prm), nullptr, dv, st));
   HIPCHK(launch_pack_ref(ref->x, ref->y, ref->z, a_r, ref->m, N, dv, ref4, lw, st));
   HIPCHK(launch_sort_perm(a_t, M, perm, sws, st));
   HIPCHK(launch_pack_tmpl(tmpl->x, tmpl->y, tmpl->z, a_t, tmpl->m, M, perm, dv, tm4, tmx, st));
@@ -1221,8 +1236,8 @@ int sgr_register(sgr_ctx* ctx, const sgr_cloud* tmpl, const sgr_cloud* ref, cons
     if (int e = carve_single(ctx, M, N, prm, prm->k, w, false, use_loop, 1)) return e;
     HIPCHK(launch_grid_knn(ref->x, ref->y, ref->z, N, prm->k, w.aX, nullptr, w.gws, st));
     HIPCHK(launch_grid_knn(tmpl->x, tmpl->y, tmpl->z, M, prm->k, w.aY, nullptr, w.gws, st));
-    HIPCHK(launch_moments(ref->x, ref->y, ref->z, N, w.mom + 10, st));
-    HIPCHK(launch_moments(tmpl->x, tmpl->y, tmpl->z, M, w.mom, st));
+    HIPCHK(launch_moments(ref->x, ref->y, ref->z, N, w.wide, w.mom + 10, st));
+    HIPCHK(launch_moments(tmpl->x, tmpl->y, tmpl->z, M, w.wide, w.mom, st));
     if (int e = setup_single(tmpl, ref, prep_of(prm), stats != nullptr, w, st)) return e;
     if (int e = run_single_loop(ctx, ctx->gc, tmpl, ref, prm, w, inout, stats, 0, prm->E, 0, st)) return e;
     int32_t status = 0;
@@ -1287,8 +1302,8 @@ int sgr_register_pyramid(sgr_ctx* ctx, const sgr_cloud* tmpl, const sgr_cloud* r
     SingleWs w;
     if (int e = carve_single(ctx, M, N, prm, kmax, w, radius, use_loop, n_levels)) return e;
     if ((int)ctx->gcp.size() < n_levels) ctx->gcp.resize(n_levels);
-    HIPCHK(launch_moments(ref->x, ref->y, ref->z, N, w.mom + 10, st));
-    HIPCHK(launch_moments(tmpl->x, tmpl->y, tmpl->z, M, w.mom, st));
+    HIPCHK(launch_moments(ref->x, ref->y, ref->z, N, w.wide, w.mom + 10, st));
+    HIPCHK(launch_moments(tmpl->x, tmpl->y, tmpl->z, M, w.wide, w.mom, st));
     std::vector<int32_t> status(n_levels, 0);
     int t0 = 0;
     for (int l = 0; l < n_levels; ++l) {
@@ -1389,8 +1404,8 @@ int sgr_register_vec(sgr_ctx* ctx, const sgr_cloud* tmpl, const float* a_t, cons
   for (const bool use_loop : {true, false}) {
     VecWs w;
     if (int e = carve_vec(ctx, M, N, D, false, true, w, pinv, use_loop)) return e;
-    HIPCHK(launch_moments(ref->x, ref->y, ref->z, N, w.mom + 10, st));
-    HIPCHK(launch_moments(tmpl->x, tmpl->y, tmpl->z, M, w.mom, st));
+    HIPCHK(launch_moments(ref->x, ref->y, ref->z, N, w.wide, w.mom + 10, st));
+    HIPCHK(launch_moments(tmpl->x, tmpl->y, tmpl->z, M, w.wide, w.mom, st));
     if (int e = setup_vec(tmpl, a_t, ref, a_r, D, w.mom, w.mom + 10, prm, w, st)) return e;
     if (pinv) {
       // the pair sums once: one pass of the vector kernel writing them per chunk
@@ -1536,7 +1551,7 @@ int sgr_autotune(sgr_ctx* ctx, const sgr_cloud* tmpl, const float* a_t, const sg
   float2* tmx = w.take<float2>(M);
   const size_t wp_off = w.off;
   HIPCHK(launch_identity_pose(pose, st));
-  HIPCHK(launch_prepare(a_r, ref->m, N, a_t, tmpl->m, M, mom_t, mom_r, prep_of(prm), dv, st));
+  HIPCHK(launch_prepare(a_r, ref->m, N, a_t, tmpl->m, M, mom_t, mom_r, prep_of(prm), nullptr, dv, st));
   HIPCHK(launch_pack_ref(ref->x, ref->y, ref->z, a_r, ref->m, N, dv, ref4, lw, st));
   HIPCHK(launch_sort_perm(a_t, M, perm, sws, st));
   HIPCHK(launch_pack_tmpl(tmpl->x, tmpl->y, tmpl->z, a_t, tmpl->m, M, perm, dv, tm4, tmx, st));
@@ -1676,9 +1691,9 @@ int sgr_force_fwd(sgr_ctx* ctx, const sgr_cloud* tmpl, const float* a_t, const s
   char* sws = w.take<char>(sort_perm_workspace(M, 1));
   float4* tm4 = w.take<float4>(M);
   float2* tmx = w.take<float2>(M);
-  HIPCHK(launch_moments(tmpl->x, tmpl->y, tmpl->z, M, mom_t, st));
+  HIPCHK(launch_moments(tmpl->x, tmpl->y, tmpl->z, M, nullptr, mom_t, st));
   HIPCHK(launch_identity_pose(pose, st));
-  HIPCHK(launch_prepare(a_r, ref->m, N, a_t, tmpl->m, M, mom_t, mom_r, prep_of(prm), dv, st));
+  HIPCHK(launch_prepare(a_r, ref->m, N, a_t, tmpl->m, M, mom_t, mom_r, prep_of(prm), nullptr, dv, st));
   HIPCHK(launch_pack_ref(ref->x, ref->y, ref->z, a_r, ref->m, N, dv, ref4, lw, st));
   HIPCHK(launch_sort_perm(a_t, M, perm, sws, st));
   HIPCHK(launch_pack_tmpl(tmpl->x, tmpl->y, tmpl->z, a_t, tmpl->m, M, perm, dv, tm4, tmx, st));
@@ -1736,8 +1751,8 @@ int sgr_force_bwd(sgr_ctx* ctx, const sgr_cloud* tmpl, const float* a_t, const s
   double* gw0 = w.take<double>(16);
   if (!grad_f) HIPCHK(launch_fill_f(gf0, (int64_t)M * 3, 0.f, st));
   if (!grad_wrench) HIPCHK(launch_fill(gw0, 16, 0.0, st));
-  HIPCHK(launch_moments(tmpl->x, tmpl->y, tmpl->z, M, mom_t, st));
-  HIPCHK(launch_prepare(a_r, ref->m, N, a_t, tmpl->m, M, mom_t, mom_r, prep_of(prm), dv, st));
+  HIPCHK(launch_moments(tmpl->x, tmpl->y, tmpl->z, M, nullptr, mom_t, st));
+  HIPCHK(launch_prepare(a_r, ref->m, N, a_t, tmpl->m, M, mom_t, mom_r, prep_of(prm), nullptr, dv, st));
   HIPCHK(launch_pack_ref(ref->x, ref->y, ref->z, a_r, ref->m, N, dv, ref4, lw, st));
   AdjArgs A{tmpl->x, tmpl->y, tmpl->z, a_t, tmpl->m, ref4, lw, dv, M, N, T.chunk_len, T.n_chunks, T.nblk,
             pm == 1, G, f, grad_f ? grad_f : gf0, grad_wrench ? grad_wrench : gw0, lam, ypart, spart,
@@ -1818,7 +1833,7 @@ int sgr_plan_create(sgr_ctx* ctx, const sgr_cloud* tmpl, const float* a_t, const
   pl->tm4 = w.take<float4>(M);
   pl->tmx = w.take<float2>(M);
   hipStream_t st = (hipStream_t)stream;
-  hipError_t e1 = launch_prepare(a_r, ref->m, N, a_t, tmpl->m, M, mom_t, mom_r, prep_of(prm), pl->dv, st);
+  hipError_t e1 = launch_prepare(a_r, ref->m, N, a_t, tmpl->m, M, mom_t, mom_r, prep_of(prm), nullptr, pl->dv, st);
   hipError_t e2 = e1 == hipSuccess ? launch_pack_ref(ref->x, ref->y, ref->z, a_r, ref->m, N, pl->dv, pl->ref4, pl->lw, st)
                                    : e1;
   if (e2 == hipSuccess) e2 = launch_sort_perm(a_t, M, pl->perm, sws, st);
@@ -2032,8 +2047,8 @@ int sgr_unrolled_bwd(sgr_ctx* ctx, const sgr_cloud* tmpl, const float* a_t, cons
       HIPCHK(launch_update_bwd(Pt, W, g0, U.dv, g1, gW, st));
       // force field at the posed template: per-point gradient and (sigma, eps)
       HIPCHK(launch_pose_points(tmpl->x, tmpl->y, tmpl->z, M, Pt, Yx, Yy, Yz, st));
-      HIPCHK(launch_moments(Yx, Yy, Yz, M, mom_y, st));
-      HIPCHK(launch_prepare(a_r, ref->m, N, a_t, tmpl->m, M, mom_y, mom_r, prep_of(prm), dva, st));
+      HIPCHK(launch_moments(Yx, Yy, Yz, M, nullptr, mom_y, st));
+      HIPCHK(launch_prepare(a_r, ref->m, N, a_t, tmpl->m, M, mom_y, mom_r, prep_of(prm), nullptr, dva, st));
       AdjArgs AA{Yx, Yy, Yz, a_t, tmpl->m, U.ref4, U.lw, dva, M, N, TA.chunk_len, TA.n_chunks, TA.nblk,
                  U.pm == 1, G_host(prm, t), f, gf0, gW, lam, ypart, spart, gy, nullptr, gse_t};
       HIPCHK(launch_adjoint(AA, TA.R, fsum, st));

@@ -406,6 +406,42 @@ __device__ inline void block_sum(double (&v)[NV], double* lds) {
   __syncthreads();
 }
 
+// Elements t, t + 1024, ... below n in that order, as thread t of a block of
+// 1024 visits them, U loads in flight: use(load(i)) for each.
+template <int U, class Load, class Use>
+__device__ inline void strided(int64_t t, int64_t n, Load&& load, Use&& use) {
+  for (int64_t i = t; i < n; i += 1024 * U) {
+    decltype(load(i)) r[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) r[u] = load(min(i + 1024 * u, n - 1));
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (i + 1024 * u < n) use(r[u]);
+  }
+}
+
+// block_sum<NV, 1024> taken apart, for a reduction whose 16 waves are 16
+// blocks: wave w leaves its sums in part[w NV ..], and any wave adds them up
+// (lane k: component k).  The additions are those of block_sum.
+template <int NV>
+__device__ inline void wave_part(const double (&v)[NV], double* part, int w) {
+  constexpr int P = NV <= 1 ? 1 : (NV <= 2 ? 2 : (NV <= 4 ? 4 : (NV <= 8 ? 8 : (NV <= 16 ? 16 : 32))));
+  double p[P];
+#pragma unroll
+  for (int k = 0; k < P; ++k) p[k] = k < NV ? v[k < NV ? k : 0] : 0.0;
+  wave_sum_many<P>(p);
+  const int lane = threadIdx.x & 63, comp = lane / (64 / P);
+  if (lane % (64 / P) == 0 && comp < NV) part[w * NV + comp] = p[0];
+}
+__device__ inline double part_sum(const double* part, int nv, int k) {
+  double p[16], s = 0.0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) p[w] = part[w * nv + k];
+#pragma unroll
+  for (int w = 0; w < 16; ++w) s += p[w];
+  return s;
+}
+
 // Smallest and largest value over the threads of a block of BT threads
 // (NaN is ignored; every thread receives both).  lds: 2 * BT / 64 doubles of
 // scratch, free on entry (a barrier precedes its use).

@@ -34,59 +34,86 @@ __device__ inline double G_at(const Derived& D, int t) {
   return 0.1 * D.G1 + 0.9 * D.G1 / (1.0 + exp(-(((double)t - 1.0) - 0.5 * D.E)));
 }
 
-// Per-registration set-up: statistics of the reference curvatures, masses
-// and the constants of the force law.  One block, fixed-order reductions.
-__device__ inline void prepare_body(const float* __restrict__ aX, const float* __restrict__ wX, int64_t N,
-                                    const float* __restrict__ aY, const float* __restrict__ mY, int64_t M,
-                                    const double* __restrict__ mom_t, const double* __restrict__ mom_r,
-                                    const PrepParams& P, Derived* __restrict__ out, double* lds, double* red_max,
-                                    double* abar_p) {
-  double& abar_s = *abar_p;
-  // aX == nullptr (and aY == nullptr): no scalar curvature (a caller that
-  // weights pairs by other descriptors, or by the masses alone); the
-  // curvature statistics are then 0 and sigma comes from the caller.
-  double s[3] = {0, 0, 0};
-  for (int64_t j = threadIdx.x; j < N; j += 1024) {
-    s[0] += aX ? (double)aX[j] : 0.0;
-    s[1] += wX ? (double)wX[j] : 1.0;
-  }
-  for (int64_t i = threadIdx.x; i < M; i += 1024) s[2] += mY ? (double)mY[i] : 1.0;
-  block_sum<3, 1024>(s, lds);
-  if (threadIdx.x == 0) abar_s = s[0] / (double)N;
-  __syncthreads();
-  const double abar = abar_s;
-  double v[1] = {0};
-  for (int64_t j = threadIdx.x; j < N && aX; j += 1024) {
-    const double d = (double)aX[j] - abar;
-    v[0] += d * d;
-  }
-  block_sum<1, 1024>(v, lds);
-  // largest |a - abar| over both clouds and largest log2 weight: bound of the
-  // expanded similarity exponent (checked below once sigma is known)
-  // and the range of the reference curvatures
-  double mx[4] = {0.0, -INFINITY, -INFINITY, -INFINITY};
-  for (int64_t j = threadIdx.x; j < N; j += 1024) {
-    const double a = aX ? (double)aX[j] : 0.0;
-    mx[0] = fmax(mx[0], fabs(a - abar));
-    double l = wX ? log2((double)wX[j]) : 0.0;
-    if (P.g_mode == 1) l += log2(a / abar);
-    mx[1] = fmax(mx[1], l);
-    mx[2] = fmax(mx[2], a);
-    mx[3] = fmax(mx[3], -a);
-  }
-  for (int64_t i = threadIdx.x; i < M && aY; i += 1024) mx[0] = fmax(mx[0], fabs((double)aY[i] - abar));
-  for (int c = 0; c < 4; ++c) {
-    double m = mx[c];
-    for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
-    if ((threadIdx.x & 63) == 0) red_max[threadIdx.x >> 6] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      for (int w = 1; w < 16; ++w) m = fmax(m, red_max[w]);
-      mx[c] = m;
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x != 0) return;
+// Inputs of the per-registration set-up.
+struct PrepIn {
+  const float* aX;
+  const float* wX;
+  int64_t N;
+  const float* aY;
+  const float* mY;
+  int64_t M;
+  const double* mom_t;
+  const double* mom_r;
+};
+
+// An array, or a constant (0 or 1) where there is none: a load without a
+// branch, so that many can be in flight.
+__device__ const float OR_CONST[2] = {0.f, 1.f};
+struct OrConst {
+  const float* p;
+  int64_t step;
+  __device__ OrConst(const float* a, int c) : p(a ? a : OR_CONST + c), step(a ? 1 : 0) {}
+  __device__ float operator()(int64_t i) const { return p[i * step]; }
+};
+
+// Thread t's share of the sums: reference curvatures and masses, template
+// masses.  aX == nullptr (and aY == nullptr): no scalar curvature (a caller
+// that weights pairs by other descriptors, or by the masses alone); the
+// curvature statistics are then 0 and sigma comes from the caller.
+template <int U>
+__device__ inline void prep_sums(const PrepIn& I, int64_t t, double (&s)[3]) {
+  s[0] = s[1] = s[2] = 0.0;
+  const OrConst aX(I.aX, 0), wX(I.wX, 1);
+  strided<U>(t, I.N, [&](int64_t j) { return make_float2(aX(j), wX(j)); },
+             [&](const float2& p) {
+               s[0] += (double)p.x;
+               s[1] += (double)p.y;
+             });
+  strided<U>(t, I.M, OrConst(I.mY, 1), [&](float m) { s[2] += (double)m; });
+}
+
+// Its share of sum (a - abar)^2 (v) and of four maxima (mx): |a - abar| over
+// both clouds and log2 weight (bound of the expanded similarity exponent,
+// checked once sigma is known), and the range of the reference curvatures.
+template <int U>
+__device__ inline void prep_spread(const PrepIn& I, int g_mode, int64_t t, double abar, double& v, double (&mx)[4]) {
+  v = 0.0;
+  mx[0] = 0.0;
+  mx[1] = mx[2] = mx[3] = -INFINITY;
+  const OrConst aX(I.aX, 0), wX(I.wX, 1);
+  strided<U>(t, I.N, [&](int64_t j) { return make_float2(aX(j), wX(j)); },
+             [&](const float2& p) {
+               const double a = (double)p.x, d = a - abar;
+               if (I.aX) v += d * d;
+               mx[0] = fmax(mx[0], fabs(d));
+               if (I.wX) {
+                 double l = log2((double)p.y);
+                 if (g_mode == 1) l += log2(a / abar);
+                 mx[1] = fmax(mx[1], l);
+               }
+               mx[2] = fmax(mx[2], a);
+               mx[3] = fmax(mx[3], -a);
+             });
+  if (I.aY)
+    strided<U>(t, I.M, [&](int64_t i) { return I.aY[i]; },
+               [&](float a) { mx[0] = fmax(mx[0], fabs((double)a - abar)); });
+}
+
+__device__ inline double wave_max(double m) {
+  for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
+  return m;
+}
+
+// The constants, from the sums s, the spread v and the maxima mx.
+__device__ inline void prep_store(const PrepIn& I, const PrepParams& P, const double s[3], double v, double mx[4],
+                                  Derived* __restrict__ out) {
+  const int64_t N = I.N, M = I.M;
+  const float* aX = I.aX;
+  const double* mom_t = I.mom_t;
+  const double* mom_r = I.mom_r;
+  const double abar = s[0] / (double)N;
+  // without masses the largest weight is that of the largest curvature
+  if (!I.wX) mx[1] = P.g_mode == 1 ? fmax(-INFINITY, log2(mx[2] / abar)) : 0.0;
   Derived D;
   int32_t st = 0;
   for (int c = 0; c < 3; ++c) D.xbar[c] = mom_r[c];
@@ -96,7 +123,7 @@ __device__ inline void prepare_body(const float* __restrict__ aX, const float* _
   for (int c = 0; c < 6; ++c) D.SigY0[c] = mom_t[3 + c];
   D.lamY0 = mom_t[9];
   D.abar = abar;
-  const double sd = sqrt(v[0] / (double)N);
+  const double sd = sqrt(v / (double)N);
   D.sigma = (P.sigma > 0 ? P.sigma : sd) * P.sigma_scale;
   D.Z = s[1];
   D.Mtot = s[2];
@@ -131,25 +158,73 @@ __device__ inline void prepare_body(const float* __restrict__ aX, const float* _
   *out = D;
 }
 
-__global__ __launch_bounds__(1024) void prepare_kernel(const float* __restrict__ aX, const float* __restrict__ wX,
-                                                       int64_t N, const float* __restrict__ aY,
-                                                       const float* __restrict__ mY, int64_t M,
-                                                       const double* __restrict__ mom_t, const double* __restrict__ mom_r,
-                                                       PrepParams P, Derived* __restrict__ out) {
+// Per-registration set-up in one block, fixed-order reductions; bound by the
+// latency of each thread's loads, eight in flight.
+__device__ inline void prepare_body(const PrepIn& I, const PrepParams& P, Derived* __restrict__ out, double* lds,
+                                    double* red_max, double* abar_p) {
+  double s[3];
+  prep_sums<8>(I, threadIdx.x, s);
+  block_sum<3, 1024>(s, lds);
+  if (threadIdx.x == 0) *abar_p = s[0] / (double)I.N;
+  __syncthreads();
+  double v[1], mx[4];
+  prep_spread<8>(I, P.g_mode, threadIdx.x, *abar_p, v[0], mx);
+  block_sum<1, 1024>(v, lds);
+  for (int c = 0; c < 4; ++c) {
+    const double m = wave_max(mx[c]);
+    if ((threadIdx.x & 63) == 0) red_max[(threadIdx.x >> 6) * 4 + c] = m;
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  for (int c = 0; c < 4; ++c) {
+    mx[c] = red_max[c];
+    for (int w = 1; w < 16; ++w) mx[c] = fmax(mx[c], red_max[4 * w + c]);
+  }
+  prep_store(I, P, s, v[0], mx, out);
+}
+
+__global__ __launch_bounds__(1024) void prepare_kernel(PrepIn I, PrepParams P, Derived* __restrict__ out) {
   __shared__ double lds[16 * 3];
-  __shared__ double red_max[16];
+  __shared__ double red_max[16 * 4];
   __shared__ double abar_s;
-  prepare_body(aX, wX, N, aY, mY, M, mom_t, mom_r, P, out, lds, red_max, &abar_s);
+  prepare_body(I, P, out, lds, red_max, &abar_s);
+}
+
+// The same with the block's 16 waves as 16 blocks on as many CUs (the same
+// additions in the same order): part [0, 48) the sums, [48, 64) the spread,
+// [64, 128) the maxima.
+__global__ __launch_bounds__(64) void prepare_wide1_kernel(PrepIn I, double* __restrict__ part) {
+  double s[3];
+  prep_sums<24>(I, blockIdx.x * 64 + threadIdx.x, s);
+  wave_part<3>(s, part, blockIdx.x);
+}
+__global__ __launch_bounds__(64) void prepare_wide2_kernel(PrepIn I, int g_mode, double* __restrict__ part) {
+  const double abar = lane_value(part_sum(part, 3, 0), 0) / (double)I.N;
+  double v[1], mx[4];
+  prep_spread<24>(I, g_mode, blockIdx.x * 64 + threadIdx.x, abar, v[0], mx);
+  wave_part<1>(v, part + 48, blockIdx.x);
+  for (int c = 0; c < 4; ++c) {
+    const double m = wave_max(mx[c]);
+    if (threadIdx.x == 0) part[64 + 4 * blockIdx.x + c] = m;
+  }
+}
+__global__ __launch_bounds__(64) void prepare_wide3_kernel(PrepIn I, PrepParams P, const double* __restrict__ part,
+                                                           Derived* __restrict__ out) {
+  const double sum = threadIdx.x < 3 ? part_sum(part, 3, threadIdx.x) : 0.0;
+  double s[3], mx[4];
+  for (int k = 0; k < 3; ++k) s[k] = lane_value(sum, k);
+  for (int c = 0; c < 4; ++c) mx[c] = wave_max(part[64 + 4 * (threadIdx.x & 15) + c]);
+  if (threadIdx.x == 0) prep_store(I, P, s, part_sum(part + 48, 1, 0), mx, out);
 }
 
 // One block per registration of a batch.
 __global__ __launch_bounds__(1024) void prepare_batch_kernel(const PrepDesc* __restrict__ d, PrepParams P,
                                                              Derived* __restrict__ outs) {
   __shared__ double lds[16 * 3];
-  __shared__ double red_max[16];
+  __shared__ double red_max[16 * 4];
   __shared__ double abar_s;
   const PrepDesc g = prep_at(d, blockIdx.x);
-  prepare_body(g.aX, g.wX, g.N, g.aY, g.mY, g.M, g.mom_t, g.mom_r, P, outs + blockIdx.x, lds, red_max, &abar_s);
+  prepare_body(PrepIn{g.aX, g.wX, g.N, g.aY, g.mY, g.M, g.mom_t, g.mom_r}, P, outs + blockIdx.x, lds, red_max, &abar_s);
 }
 
 // Template in the order the force kernel visits it: position ip holds the
@@ -653,8 +728,17 @@ __global__ __launch_bounds__(256) void reduce_f_kernel(const double* __restrict_
 }
 
 hipError_t launch_prepare(const float* aX, const float* wX, int64_t N, const float* aY, const float* mY, int64_t M,
-                          const double* mom_t, const double* mom_r, const PrepParams& P, Derived* out, hipStream_t st) {
-  hipLaunchKernelGGL(prepare_kernel, dim3(1), dim3(1024), 0, st, aX, wX, N, aY, mY, M, mom_t, mom_r, P, out);
+                          const double* mom_t, const double* mom_r, const PrepParams& P, double* part, Derived* out,
+                          hipStream_t st) {
+  const PrepIn I{aX, wX, N, aY, mY, M, mom_t, mom_r};
+  if (part && std::max(N, M) > WIDE_N) {
+    const dim3 waves(16), bt(64);
+    hipLaunchKernelGGL(prepare_wide1_kernel, waves, bt, 0, st, I, part);
+    hipLaunchKernelGGL(prepare_wide2_kernel, waves, bt, 0, st, I, P.g_mode, part);
+    hipLaunchKernelGGL(prepare_wide3_kernel, dim3(1), bt, 0, st, I, P, part, out);
+  } else {
+    hipLaunchKernelGGL(prepare_kernel, dim3(1), dim3(1024), 0, st, I, P, out);
+  }
   return hipGetLastError();
 }
 

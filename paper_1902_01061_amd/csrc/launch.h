@@ -192,7 +192,15 @@ hipError_t launch_change(const float* yx, const float* yy, const float* yz, cons
                          const float* xy, const float* xz, const float* aX, int N, const double* pose, float tau2,
                          double shape_thr, uint8_t* flags, int32_t* nn, float* key, void* ws, hipStream_t st);
 
-hipError_t launch_moments(const float* x, const float* y, const float* z, int64_t n, double* out, hipStream_t st);
+// Clouds of more points are reduced by 16 waves on as many CUs instead of one
+// block's, if the caller has WIDE_PART doubles of scratch (part, or nullptr).
+// Moments: 16 us in three launches against 22 in one block at 36 000 points
+// (7 at 1 024), 53 against 150 at 307 200; the constants of a 32 400 x 36 000
+// registration 29 against 36 us, of a 250 000 x 307 200 one 105 against 497.
+constexpr int64_t WIDE_N = 16384;
+constexpr int WIDE_PART = 160;
+hipError_t launch_moments(const float* x, const float* y, const float* z, int64_t n, double* part, double* out,
+                          hipStream_t st);
 // Force with vector descriptors (p = 1, g = s) on the matrix cores.
 struct VForceArgs {
   const void* At;       // template augmented rows [Mpad]: K floats, or K halves (split f16)
@@ -223,8 +231,10 @@ __host__ __device__ inline int vfar_stride(int D) { return vfar_db(D) + 6; }
 size_t vfar_part_doubles(int M);
 int vfar_pad_refs(int N);
 void vfar_prepare(int D);  // host queries of the far-row launch, outside stream capture
-hipError_t launch_vfar_list(const float* aY, int M, int D, const double* vd, const Derived* dv, int* far_idx,
-                            hipStream_t st);
+// mask: vfar_mask_words(M) words of scratch.
+size_t vfar_mask_words(int M);
+hipError_t launch_vfar_list(const float* aY, int M, int D, const double* vd, const Derived* dv,
+                            unsigned long long* mask, int* far_idx, hipStream_t st);
 hipError_t launch_vfar_ref(const float* aX, const float* wX, int N, int D, const double* vd, const float4* ref4,
                            double* refd, hipStream_t st);
 hipError_t launch_vfar(const VForceArgs& A, const float* aY, int D, const double* vd, const double* refd,
@@ -242,7 +252,8 @@ int vforce_chunks(int M, int N, int n_cu);
 // largest |a - abar|^2 / sigma^2 over the reference and the template rows
 // that enter the contraction (for vforce_half_ok), and over the reference
 hipError_t launch_vprep(const float* aX, int64_t N, const float* aY, int64_t M, int D, double sigma, Derived* dv,
-                        double* vd, hipStream_t st);
+                        double* vd, double* vs, hipStream_t st);
+size_t vprep_scratch();  // doubles of vs
 bool vforce_half_ok(double cmax);
 // Rows: vforce_K(D) floats each (half = false) or vforce_half_K(D) halves
 // each (half = true).
@@ -334,7 +345,8 @@ size_t radius_desc_workspace(int n);
 hipError_t launch_radius_desc(const float* x, const float* y, const float* z, int n, const double* mom, double scale2,
                               float r2_in, float* a_out, int32_t* cnt_out, void* ws, hipStream_t st);
 hipError_t launch_prepare(const float* aX, const float* wX, int64_t N, const float* aY, const float* mY, int64_t M,
-                          const double* mom_t, const double* mom_r, const PrepParams& P, Derived* out, hipStream_t st);
+                          const double* mom_t, const double* mom_r, const PrepParams& P, double* part, Derived* out,
+                          hipStream_t st);
 hipError_t launch_pack_ref(const float* x, const float* y, const float* z, const float* aX, const float* wX, int64_t N,
                            const Derived* dv, float4* ref4, float* lw, hipStream_t st);
 hipError_t launch_force(const ForceArgs& A, int R, int pm, bool want_u, bool want_f, hipStream_t st, bool sm);

@@ -69,7 +69,7 @@ constexpr double LOG2E = 1.4426950408889634;
 constexpr double VF_FAR2 = 64.0;  // |c|^2 beyond which a template row is a far row (8 spreads)
 
 // |c_r|^2 = |a_r - abar|^2 / sigma^2 of descriptor row r, in FP64 (the same
-// expression decides far rows in vfar_list_kernel and vpack_kernel).
+// expression decides far rows in vfar_mask_kernel and vpack_kernel).
 __device__ inline double std_norm2(const float* __restrict__ a, int64_t r, int D, const double* __restrict__ vd) {
   const double isig = 1.0 / vd[32];
   double n2 = 0.0;
@@ -86,74 +86,154 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 // that the 64 lanes of one read (16 columns x 4 k) hit 64 distinct banks.
 __host__ __device__ constexpr int bt_stride(int K) { return ((K / 4) & 1) ? K : K + 4; }
 
-// abar, sigma and kappa of the vector descriptors; writes sigma into the
+// abar, sigma and kappa of the vector descriptors; sigma also goes into the
 // Derived of the registration (its other fields come from the scalar
-// set-up, called without curvatures).
-__global__ __launch_bounds__(1024) void vprep_kernel(const float* __restrict__ aX, int64_t N,
-                                                     const float* __restrict__ aY, int64_t M, int D, double sigma_in,
-                                                     Derived* __restrict__ dv, double* __restrict__ vd) {
-  __shared__ double lds[16 * 32];
+// set-up, called without curvatures).  Three launches, each as wide as its
+// order allows: the 16 waves of a block of 1024 as 16 blocks per group of
+// four components for the means, as 16 blocks for sigma (one chain of
+// additions per thread, over the components within a row), and a thread per
+// row for the largest norms.  Bound by the latency of the rows' loads; one
+// block for all three took 463 us at 36 000 references, 32 400 templates and
+// D = 16, where these take about 40.
+// vs: [0, 512) per-wave sums of the components, [512, 528) of the squares.
+struct VStat {
+  const float* aX;
+  int64_t N;
+  const float* aY;
+  int64_t M;
+  int D;
+  double sigma_in;
+  Derived* dv;
+  double* vd;
+  double* vs;
+};
+
+// Components [c, c + 4) of row r (the last one again beyond D); V4: D is a
+// multiple of four and the rows are aligned to 16 bytes.
+template <bool V4>
+__device__ inline float4 row4(const float* __restrict__ a, int64_t r, int D, int c) {
+  const float* p = a + r * D;
+  if constexpr (V4) return *reinterpret_cast<const float4*>(p + c);
+  return make_float4(p[c], p[min(c + 1, D - 1)], p[min(c + 2, D - 1)], p[min(c + 3, D - 1)]);
+}
+
+template <bool V4>
+__global__ __launch_bounds__(64) void vmean_kernel(VStat A) {
+  const int c0 = 4 * blockIdx.y;
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
+  strided<12>(blockIdx.x * 64 + threadIdx.x, A.N, [&](int64_t j) { return row4<V4>(A.aX, j, A.D, c0); },
+              [&](const float4& p) {
+                s[0] += (double)p.x;
+                s[1] += (double)p.y;
+                s[2] += (double)p.z;
+                s[3] += (double)p.w;
+              });
+  double p[4] = {s[0], s[1], s[2], s[3]};
+  wave_sum_many<4>(p);
+  const int c = c0 + threadIdx.x / 16;
+  if (threadIdx.x % 16 == 0) A.vs[blockIdx.x * 32 + c] = c < A.D ? p[0] : 0.0;
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 2) A.vd[34 + threadIdx.x] = 0.0;  // the maxima of vnorm_kernel
+}
+
+// mean[0, 32) in LDS (zero beyond D).
+__device__ inline void vmeans(const VStat& A, double* mean) {
+  if (threadIdx.x < 32) mean[threadIdx.x] = (int)threadIdx.x < A.D ? part_sum(A.vs, 32, threadIdx.x) / (double)A.N : 0.0;
+  __syncthreads();
+}
+
+template <bool V4>
+__global__ __launch_bounds__(64) void vsigma_kernel(VStat A) {
   __shared__ double mean[32];
-  __shared__ double sig_s;
-  double s[32];
-  for (int c = 0; c < 32; ++c) s[c] = 0.0;
-  for (int64_t j = threadIdx.x; j < N; j += 1024) {
+  vmeans(A, mean);
+  constexpr int U = 16;  // groups of four components in flight
+  const int G = (A.D + 3) / 4;
+  double v = 0.0;
+  int64_t j = blockIdx.x * 64 + threadIdx.x, jl = j;
+  int g = 0, gl = 0;  // (jl, gl) loads ahead of (j, g)
+  while (j < A.N) {
+    float4 r[U];
 #pragma unroll
-    for (int c = 0; c < 32; ++c)
-      if (c < D) s[c] += (double)aX[j * D + c];
+    for (int u = 0; u < U; ++u) {
+      r[u] = row4<V4>(A.aX, min(jl, A.N - 1), A.D, 4 * gl);
+      if (++gl == G) {
+        gl = 0;
+        jl += 1024;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (j < A.N) {
+        const float q[4] = {r[u].x, r[u].y, r[u].z, r[u].w};
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          if (V4 || 4 * g + c < A.D) {
+            const double d = (double)q[c] - mean[4 * g + c];
+            v += d * d;
+          }
+      }
+      if (++g == G) {
+        g = 0;
+        j += 1024;
+      }
+    }
   }
-  block_sum<32, 1024>(s, lds);
-  if (threadIdx.x == 0)
-    for (int c = 0; c < 32; ++c) mean[c] = c < D ? s[c] / (double)N : 0.0;
-  __syncthreads();
-  double v[1] = {0.0};
-  for (int64_t j = threadIdx.x; j < N; j += 1024)
-    for (int c = 0; c < D; ++c) {
-      const double d = (double)aX[j * D + c] - mean[c];
-      v[0] += d * d;
+  double p[1] = {v};
+  wave_part<1>(p, A.vs + 512, blockIdx.x);
+}
+
+// Largest |a - abar|^2 / sigma^2 (NaN if any is; kept as the bits of
+// non-negative doubles, which order like their values with NaN above) over the
+// reference (vd[35]), and over the reference and the template rows that enter
+// the contraction (vd[34]: far rows do not): the host picks the f16 form only
+// if every augmented entry fits its range.
+template <bool V4>
+__global__ __launch_bounds__(256) void vnorm_kernel(VStat A) {
+  __shared__ double mean[32];
+  __shared__ unsigned long long top[2];
+  if (threadIdx.x < 2) top[threadIdx.x] = 0;
+  vmeans(A, mean);
+  const double sigma = A.sigma_in > 0 ? A.sigma_in : sqrt(part_sum(A.vs + 512, 1, 0) / (double)A.N);
+  if (blockIdx.x == 0) {
+    if (threadIdx.x < 32) A.vd[threadIdx.x] = mean[threadIdx.x];
+    if (threadIdx.x == 0) {
+      const double kappa = LOG2E / (sigma * sigma);
+      A.vd[32] = sigma;
+      A.vd[33] = kappa;
+      A.dv->sigma = sigma;
+      if (!(sigma > 0) || !isfinite(kappa)) A.dv->status |= ST_DEGENERATE;
     }
-  block_sum<1, 1024>(v, lds);
-  if (threadIdx.x == 0) sig_s = sigma_in > 0 ? sigma_in : sqrt(v[0] / (double)N);
-  __syncthreads();
-  const double sigma = sig_s;
-  // largest |a - abar|^2 / sigma^2 (NaN-propagating) over the reference
-  // (mr), and over the reference and the template rows that enter the
-  // contraction (mx: far rows do not): the host picks the f16 form only if
-  // every augmented entry fits its range
-  double mx = 0.0, mr = 0.0;
-  for (int64_t r = threadIdx.x; r < N + M; r += 1024) {
-    const float* a = r < N ? aX + r * D : aY + (r - N) * D;
+  }
+  const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  unsigned long long mx = 0, mr = 0;
+  if (r < A.N + A.M) {
+    const float* a = r < A.N ? A.aX : A.aY;
+    const int64_t row = r < A.N ? r : r - A.N;
     double n2 = 0.0;
-    for (int c = 0; c < D; ++c) {
-      const double e = ((double)a[c] - mean[c]) / sigma;
-      n2 += e * e;
+    for (int g = 0; 4 * g < A.D; ++g) {
+      const float4 p = row4<V4>(a, row, A.D, 4 * g);
+      const float q[4] = {p.x, p.y, p.z, p.w};
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (V4 || 4 * g + c < A.D) {
+          const double e = ((double)q[c] - mean[4 * g + c]) / sigma;
+          n2 += e * e;
+        }
     }
-    if (r < N) mr = (n2 > mr || n2 != n2) ? n2 : mr;
-    if (r < N || !(n2 > VF_FAR2)) mx = (n2 > mx || n2 != n2) ? n2 : mx;
+    const unsigned long long bits = n2 != n2 ? 0x7ff8000000000000ull : (unsigned long long)__double_as_longlong(n2);
+    if (r < A.N) mr = bits;
+    if (r < A.N || !(n2 > VF_FAR2)) mx = bits;
   }
   for (int off = 32; off > 0; off >>= 1) {
-    const double o = __shfl_xor(mx, off, 64);
-    mx = (o > mx || o != o) ? o : mx;
-    const double q = __shfl_xor(mr, off, 64);
-    mr = (q > mr || q != q) ? q : mr;
+    mx = max(mx, (unsigned long long)__shfl_xor(mx, off, 64));
+    mr = max(mr, (unsigned long long)__shfl_xor(mr, off, 64));
   }
   if ((threadIdx.x & 63) == 0) {
-    lds[threadIdx.x >> 6] = mx;
-    lds[16 + (threadIdx.x >> 6)] = mr;
+    atomicMax(&top[0], mx);
+    atomicMax(&top[1], mr);
   }
   __syncthreads();
-  if (threadIdx.x != 0) return;
-  for (int w = 1; w < 16; ++w) {
-    mx = (lds[w] > mx || lds[w] != lds[w]) ? lds[w] : mx;
-    mr = (lds[16 + w] > mr || lds[16 + w] != lds[16 + w]) ? lds[16 + w] : mr;
-  }
-  for (int c = 0; c < 32; ++c) vd[c] = mean[c];
-  vd[32] = sigma;
-  vd[33] = LOG2E / (sigma * sigma);
-  vd[34] = mx;
-  vd[35] = mr;
-  dv->sigma = sigma;
-  if (!(sigma > 0) || !isfinite(vd[33])) dv->status |= ST_DEGENERATE;
+  if (threadIdx.x < 2 && top[threadIdx.x])
+    atomicMax(reinterpret_cast<unsigned long long*>(A.vd + 34 + threadIdx.x), top[threadIdx.x]);
 }
 
 // Augmented rows from the standardised descriptors c = (a - abar) / sigma:
@@ -466,36 +546,38 @@ __device__ inline bool far_reachable(double n2, const double* __restrict__ vd, c
 }
 
 // The far rows that can carry a force, in increasing order: far_idx[0..n)
-// and n in far_idx[M].  One block; thread t scans a contiguous range of rows,
-// so that an exclusive scan of the per-thread counts places every index
-// deterministically.
-__global__ __launch_bounds__(1024) void vfar_list_kernel(const float* __restrict__ aY, int M, int D,
-                                                         const double* __restrict__ vd,
-                                                         const Derived* __restrict__ dv, int* __restrict__ far_idx) {
+// and n in far_idx[M].  A bit per row first, then one block places the rows
+// of the bits: thread t those of a contiguous range of words, from an
+// exclusive scan of the threads' counts.
+__global__ __launch_bounds__(256) void vfar_mask_kernel(const float* __restrict__ aY, int M, int D,
+                                                        const double* __restrict__ vd,
+                                                        const Derived* __restrict__ dv,
+                                                        unsigned long long* __restrict__ mask) {
+  const int r = blockIdx.x * 256 + threadIdx.x;
+  const double n2 = std_norm2(aY, min(r, M - 1), D, vd);
+  const unsigned long long m = __ballot(r < M && n2 > VF_FAR2 && far_reachable(n2, vd, dv));
+  if ((threadIdx.x & 63) == 0) mask[r >> 6] = m;
+}
+
+__global__ __launch_bounds__(1024) void vfar_list_kernel(const unsigned long long* __restrict__ mask, int words, int M,
+                                                         int* __restrict__ far_idx) {
   __shared__ int cnt[1024];
-  const int per = (M + 1023) / 1024;
-  const int r0 = min(M, (int)threadIdx.x * per), r1 = min(M, r0 + per);
-  auto is_far = [&](int r) {
-    const double n2 = std_norm2(aY, r, D, vd);
-    return n2 > VF_FAR2 && far_reachable(n2, vd, dv);
-  };
+  const int t = threadIdx.x, per = (words + 1023) / 1024;
+  const int w0 = min(words, t * per), w1 = min(words, w0 + per);
   int c = 0;
-  for (int r = r0; r < r1; ++r) c += is_far(r);
-  cnt[threadIdx.x] = c;
+  for (int w = w0; w < w1; ++w) c += __popcll(mask[w]);
+  cnt[t] = c;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int acc = 0;
-    for (int t = 0; t < 1024; ++t) {
-      const int v = cnt[t];
-      cnt[t] = acc;
-      acc += v;
-    }
-    far_idx[M] = acc;
+  for (int off = 1; off < 1024; off <<= 1) {
+    const int o = t >= off ? cnt[t - off] : 0;
+    __syncthreads();
+    cnt[t] += o;
+    __syncthreads();
   }
-  __syncthreads();
-  int o = cnt[threadIdx.x];
-  for (int r = r0; r < r1; ++r)
-    if (is_far(r)) far_idx[o++] = r;
+  if (t == 1023) far_idx[M] = cnt[t];
+  int o = cnt[t] - c;
+  for (int w = w0; w < w1 && c; ++w)
+    for (unsigned long long m = mask[w]; m; m &= m - 1) far_idx[o++] = 64 * w + __builtin_ctzll(m);
 }
 
 // Far-row evaluation.  The pair exponent t_ij = lw_j - log2(e) |c_i - c_j|^2
@@ -818,10 +900,23 @@ int vforce_chunks(int M, int N, int n_cu) {
   return std::max(1, std::min(nc, n_t));
 }
 
-hipError_t launch_vprep(const float* aX, int64_t N, const float* aY, int64_t M, int D, double sigma, Derived* dv,
-                        double* vd, hipStream_t st) {
-  hipLaunchKernelGGL(vprep_kernel, dim3(1), dim3(1024), 0, st, aX, N, aY, M, D, sigma, dv, vd);
+size_t vprep_scratch() { return 528; }
+size_t vfar_mask_words(int M) { return 4 * (((size_t)M + 255) / 256); }
+
+template <bool V4>
+static hipError_t launch_vstat(const VStat& A, hipStream_t st) {
+  hipLaunchKernelGGL(vmean_kernel<V4>, dim3(16, (unsigned)((A.D + 3) / 4)), dim3(64), 0, st, A);
+  hipLaunchKernelGGL(vsigma_kernel<V4>, dim3(16), dim3(64), 0, st, A);
+  hipLaunchKernelGGL(vnorm_kernel<V4>, dim3((unsigned)((A.N + A.M + 255) / 256)), dim3(256), 0, st, A);
   return hipGetLastError();
+}
+
+hipError_t launch_vprep(const float* aX, int64_t N, const float* aY, int64_t M, int D, double sigma, Derived* dv,
+                        double* vd, double* vs, hipStream_t st) {
+  const VStat A{aX, N, aY, M, D, sigma, dv, vd, vs};
+  // whole groups of four components, read at once where they are aligned
+  return D % 4 == 0 && (((uintptr_t)aX | (uintptr_t)aY) & 15) == 0 ? launch_vstat<true>(A, st)
+                                                                   : launch_vstat<false>(A, st);
 }
 
 hipError_t launch_vpack(const float* X, const float* Y, const float* Z, const float* aX, const float* wX, int N,
@@ -856,9 +951,10 @@ hipError_t launch_vforce(const VForceArgs& A, bool wu, bool wf, hipStream_t st) 
   }
 }
 
-hipError_t launch_vfar_list(const float* aY, int M, int D, const double* vd, const Derived* dv, int* far_idx,
-                            hipStream_t st) {
-  hipLaunchKernelGGL(vfar_list_kernel, dim3(1), dim3(1024), 0, st, aY, M, D, vd, dv, far_idx);
+hipError_t launch_vfar_list(const float* aY, int M, int D, const double* vd, const Derived* dv,
+                            unsigned long long* mask, int* far_idx, hipStream_t st) {
+  hipLaunchKernelGGL(vfar_mask_kernel, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, st, aY, M, D, vd, dv, mask);
+  hipLaunchKernelGGL(vfar_list_kernel, dim3(1), dim3(1024), 0, st, mask, (M + 63) / 64, M, far_idx);
   return hipGetLastError();
 }
 
