@@ -33,6 +33,7 @@ static int fail(int code, const std::string& msg) {
 
 struct GraphCache {
   std::vector<uint8_t> key;
+  std::vector<uint8_t> seen;  // key of the last call that ran without a graph
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
 };
@@ -213,11 +214,18 @@ hipError_t run_force(ForceArgs A, const Tiles& T, const FLaunch& L, int pm, bool
 // The packed reference is padded to whole tiles with zero-weight points.
 size_t pad_n(int64_t N) { return (size_t)((N + 255) / 256) * 256; }
 
-// Capture `loop` (which launches on the given stream) into the cache unless
-// the cached graph was made for the same key, then launch it on `st`.
+// Runs `loop` (which launches on the given stream): from the cached graph if
+// that was made for the same key, else directly, and as a new graph once a
+// key comes the second time in a row.  A capture costs more than it saves on
+// one run: 100 iterations at 1 024 points take 1 593 us with a capture, 1 331
+// launched directly and 1 266 from a graph that exists.
 template <class F>
 int run_graph(sgr_ctx* ctx, GraphCache& gc, const std::vector<uint8_t>& key, F&& loop, hipStream_t st) {
   if (!gc.exec || key != gc.key) {
+    if (key != gc.seen) {
+      gc.seen = key;
+      return loop(st);
+    }
     if (gc.exec) (void)hipGraphExecDestroy(gc.exec);
     if (gc.graph) (void)hipGraphDestroy(gc.graph);
     gc.exec = nullptr;
