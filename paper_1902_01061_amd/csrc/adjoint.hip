@@ -24,28 +24,44 @@ constexpr int A_BT = 256;
 constexpr int A_TJ = 256;
 constexpr int A_GRAN = 16;  // balanced reference chunks are cut at multiples of this
 
-// lambda_i for every template point; also the sum of f (for the K term).
-__global__ __launch_bounds__(A_BT) void adj_lambda_kernel(AdjArgs A) {
-  const int i = blockIdx.x * A_BT + threadIdx.x;
-  if (i >= A.M) return;
-  const Derived& D = *A.dv;
+// Centroid of the template, from its 16 partial sums; ybar: 3 doubles of LDS.
+__device__ inline void adj_centroid(const AdjArgs& A, double* ybar) {
+  if (threadIdx.x < 3) ybar[threadIdx.x] = part_sum(A.cpart, 3, threadIdx.x) / (double)A.M;
+  __syncthreads();
+}
+
+// lambda_i of a template point.
+__device__ inline void adj_lambda(const AdjArgs& A, const double* ybar, int i, float lam[3]) {
   const double m = A.mY ? (double)A.mY[i] : 1.0;
-  const double e[3] = {(double)A.y0x[i] - D.ybar0[0], (double)A.y0y[i] - D.ybar0[1], (double)A.y0z[i] - D.ybar0[2]};
+  const double e[3] = {(double)A.y0x[i] - ybar[0], (double)A.y0y[i] - ybar[1], (double)A.y0z[i] - ybar[2]};
   for (int a = 0; a < 3; ++a) {
     double l = (double)A.gf[3 * i + a] + m * A.gw[WR_F + a];
     for (int b = 0; b < 3; ++b) l += A.gw[WR_K + 3 * a + b] * e[b];
-    A.lam[3 * i + a] = (float)l;
+    lam[a] = (float)l;
   }
 }
 
+// The pair sums.  The first block adds up the saved forces instead (for the
+// centring term of K), in the order of a block of 1024; the others form the
+// lambda of their own points.
 template <int R, bool P1>
 __global__ __launch_bounds__(A_BT) void adj_pair_kernel(AdjArgs A) {
   __shared__ float4 s_ref[A_TJ];
   __shared__ float s_lw[A_TJ];
   __shared__ double s_red[(A_BT / 64) * 2];
+  __shared__ double s_sum[16 * 3];
+  if (blockIdx.x == 0) {
+    for (int t = threadIdx.x; t < 1024; t += A_BT)
+      points_part(t, A.M, [&](int64_t i) { return make_float3(A.f[3 * i], A.f[3 * i + 1], A.f[3 * i + 2]); }, s_sum);
+    __syncthreads();
+    if (threadIdx.x < 3) A.fsum[threadIdx.x] = part_sum(s_sum, 3, threadIdx.x);
+    return;
+  }
+  const int blk = blockIdx.x - 1;
   const int n_iblk = (A.M + A_BT * R - 1) / (A_BT * R);
-  const int iblk = blockIdx.x % n_iblk;
-  const int chunk = blockIdx.x / n_iblk;
+  const int iblk = blk % n_iblk;
+  const int chunk = blk / n_iblk;
+  adj_centroid(A, s_sum);
   const Derived& D = *A.dv;
   const float eps2 = (float)D.eps2, hp = (float)D.hp;
 
@@ -60,9 +76,11 @@ __global__ __launch_bounds__(A_BT) void adj_pair_kernel(AdjArgs A) {
       yy[r] = (float)((double)A.y0y[i] - D.xbar[1]);
       yz[r] = (float)((double)A.y0z[i] - D.xbar[2]);
       bi[r] = (float)(((double)A.aY[i] - D.abar) * D.bscale);
-      lx[r] = A.lam[3 * i];
-      ly[r] = A.lam[3 * i + 1];
-      lz[r] = A.lam[3 * i + 2];
+      float l[3];
+      adj_lambda(A, s_sum, i, l);
+      lx[r] = l[0];
+      ly[r] = l[1];
+      lz[r] = l[2];
     } else {
       yx[r] = yy[r] = yz[r] = bi[r] = lx[r] = ly[r] = lz[r] = 0.f;
     }
@@ -156,47 +174,21 @@ __global__ __launch_bounds__(A_BT) void adj_pair_kernel(AdjArgs A) {
   }
   block_sum<2, A_BT>(red, s_red);
   if (threadIdx.x == 0) {
-    A.spart[2 * blockIdx.x] = red[0];
-    A.spart[2 * blockIdx.x + 1] = red[1];
+    A.spart[2 * blk] = red[0];
+    A.spart[2 * blk + 1] = red[1];
   }
 }
 
-// Sum of the saved forces (for the centring term of K), one block.
-__global__ __launch_bounds__(1024) void adj_fsum_kernel(const float* __restrict__ f, int M, double* __restrict__ out) {
-  __shared__ double lds[16 * 3];
-  double s[3] = {0, 0, 0};
-  for (int i = threadIdx.x; i < M; i += 1024) {
-    s[0] += f[3 * i];
-    s[1] += f[3 * i + 1];
-    s[2] += f[3 * i + 2];
-  }
-  block_sum<3, 1024>(s, lds);
-  if (threadIdx.x == 0)
-    for (int c = 0; c < 3; ++c) out[c] = s[c];
-}
-
-__global__ __launch_bounds__(A_BT) void adj_final_kernel(AdjArgs A, const double* __restrict__ fsum) {
-  const int i = blockIdx.x * A_BT + threadIdx.x;
-  if (i < A.M) {
-    const Derived& D = *A.dv;
-    double S[4] = {0, 0, 0, 0};
-    for (int c = 0; c < A.n_chunks; ++c) {
-      const double* p = A.ypart + ((int64_t)c * A.M + i) * 4;
-      for (int e = 0; e < 4; ++e) S[e] += p[e];
-    }
-    const double kap = -(A.G / D.Z) * D.coefL;
-    const double l[3] = {A.lam[3 * i], A.lam[3 * i + 1], A.lam[3 * i + 2]};
-    const double f[3] = {A.f[3 * i], A.f[3 * i + 1], A.f[3 * i + 2]};
-    const double fb[3] = {fsum[0] / (double)A.M, fsum[1] / (double)A.M, fsum[2] / (double)A.M};
-    for (int c = 0; c < 3; ++c) {
-      double g = kap * (l[c] * S[0] + 2.0 * D.hp * S[1 + c]);
-      for (int a = 0; a < 3; ++a) g += A.gw[WR_K + 3 * a + c] * (f[a] - fb[a]);
-      A.grad_y[3 * i + c] = (float)g;
-    }
-    if (A.grad_m) A.grad_m[i] = (float)(A.gw[WR_F] * f[0] + A.gw[WR_F + 1] * f[1] + A.gw[WR_F + 2] * f[2]);
-  }
-  if (blockIdx.x == 0 && A.grad_se) {
-    __shared__ double lds[4 * 2];
+// Gradients from the chunks' sums, bound by the latency of their loads (eight
+// chunks in flight), and the sums of the pose gradient over the same points.
+// The first block forms the (sigma, eps) gradient instead.
+__global__ __launch_bounds__(A_BT) void adj_final_kernel(AdjArgs A) {
+  __shared__ double lds[(A_BT / 64) * 12];
+  __shared__ double ybar[3];
+  const Derived& D = *A.dv;
+  const double kap = -(A.G / D.Z) * D.coefL;
+  if (blockIdx.x == 0) {
+    if (!A.grad_se) return;
     double v[2] = {0, 0};
     for (int b = threadIdx.x; b < A.nblk; b += A_BT) {
       v[0] += A.spart[2 * b];
@@ -204,42 +196,71 @@ __global__ __launch_bounds__(A_BT) void adj_final_kernel(AdjArgs A, const double
     }
     block_sum<2, A_BT>(v, lds);
     if (threadIdx.x == 0) {
-      const Derived& D = *A.dv;
       // c (a_i - a_j)^2 / sigma^2 = c ln2 db^2; d s / d sigma = s 2 (a_i - a_j)^2 / sigma^3
-      const double kap = -(A.G / D.Z) * D.coefL;
-      A.grad_se[0] = kap * (2.0 / D.sigma) * 0.6931471805599453 * v[0];
-      A.grad_se[1] = kap * 2.0 * D.hp * sqrt(D.eps2) * v[1];
+      double g[2] = {kap * (2.0 / D.sigma) * 0.6931471805599453 * v[0], kap * 2.0 * D.hp * sqrt(D.eps2) * v[1]};
+      for (int e = 0; e < 2; ++e) {
+        asm volatile("" : "+v"(g[e]));  // rounded before it is added
+        A.grad_se[e] = A.se_add ? A.grad_se[e] + g[e] : g[e];
+      }
+    }
+    return;
+  }
+  adj_centroid(A, ybar);
+  double pv[12];
+  for (int e = 0; e < 12; ++e) pv[e] = 0.0;
+  for (int i = (blockIdx.x - 1) * A_BT + threadIdx.x; i < A.M; i += (gridDim.x - 1) * A_BT) {
+    constexpr int U = 8;
+    double S[4] = {0, 0, 0, 0};
+    for (int c = 0; c < A.n_chunks; c += U) {
+      double2 p[U][2];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const double2* q =
+            reinterpret_cast<const double2*>(A.ypart + ((int64_t)min(c + u, A.n_chunks - 1) * A.M + i) * 4);
+        p[u][0] = q[0];
+        p[u][1] = q[1];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (c + u < A.n_chunks) {
+          S[0] += p[u][0].x;
+          S[1] += p[u][0].y;
+          S[2] += p[u][1].x;
+          S[3] += p[u][1].y;
+        }
+    }
+    float lam[3];
+    adj_lambda(A, ybar, i, lam);
+    const double l[3] = {lam[0], lam[1], lam[2]};
+    const double f[3] = {A.f[3 * i], A.f[3 * i + 1], A.f[3 * i + 2]};
+    const double fb[3] = {A.fsum[0] / (double)A.M, A.fsum[1] / (double)A.M, A.fsum[2] / (double)A.M};
+    float gy[3];
+    for (int c = 0; c < 3; ++c) {
+      double g = kap * (l[c] * S[0] + 2.0 * D.hp * S[1 + c]);
+      for (int a = 0; a < 3; ++a) g += A.gw[WR_K + 3 * a + c] * (f[a] - fb[a]);
+      gy[c] = (float)g;
+      if (A.grad_y) A.grad_y[3 * i + c] = gy[c];
+    }
+    if (A.grad_m) A.grad_m[i] = (float)(A.gw[WR_F] * f[0] + A.gw[WR_F + 1] * f[1] + A.gw[WR_F + 2] * f[2]);
+    if (A.pg) {
+      const double p[3] = {(double)A.p0.x[i], (double)A.p0.y[i], (double)A.p0.z[i]};
+      for (int r = 0; r < 3; ++r) {
+        for (int q = 0; q < 3; ++q) pv[3 * r + q] += (double)gy[r] * p[q];
+        pv[9 + r] += (double)gy[r];
+      }
     }
   }
-}
-
-// Resident blocks per CU of the pair kernel (cached per instantiation).
-template <int R, bool P1>
-static int adj_occ() {
-  static int occ = 0;
-  if (occ == 0) {
-    int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, adj_pair_kernel<R, P1>, A_BT, 0) != hipSuccess || n < 1)
-      n = 1;
-    occ = n;
-  }
-  return occ;
-}
-
-int adj_blocks_per_cu(int R, bool p1) {
-  if (R == 1) return p1 ? adj_occ<1, true>() : adj_occ<1, false>();
-  if (R == 2) return p1 ? adj_occ<2, true>() : adj_occ<2, false>();
-  return p1 ? adj_occ<4, true>() : adj_occ<4, false>();
+  if (!A.pg) return;
+  block_sum<12, A_BT>(pv, lds);
+  if (threadIdx.x == 0)
+    for (int e = 0; e < 12; ++e) A.pg[(int64_t)(blockIdx.x - 1) * 12 + e] = pv[e];
 }
 
 int adj_chunk_gran() { return A_GRAN; }
 
-hipError_t launch_adjoint(const AdjArgs& A, int R, double* fsum_tmp, hipStream_t st) {
-  const int gi = (A.M + A_BT - 1) / A_BT;
-  hipLaunchKernelGGL(adj_lambda_kernel, dim3(gi), dim3(A_BT), 0, st, A);
-  hipLaunchKernelGGL(adj_fsum_kernel, dim3(1), dim3(1024), 0, st, A.f, A.M, fsum_tmp);
+hipError_t launch_adjoint(const AdjArgs& A, int R, hipStream_t st) {
   const int n_iblk = (A.M + A_BT * R - 1) / (A_BT * R);
-  const dim3 grid(n_iblk * A.n_chunks);
+  const dim3 grid(n_iblk * A.n_chunks + 1);
   if (A.p1) {
     if (R == 1)
       hipLaunchKernelGGL((adj_pair_kernel<1, true>), grid, dim3(A_BT), 0, st, A);
@@ -255,7 +276,8 @@ hipError_t launch_adjoint(const AdjArgs& A, int R, double* fsum_tmp, hipStream_t
     else
       hipLaunchKernelGGL((adj_pair_kernel<4, false>), grid, dim3(A_BT), 0, st, A);
   }
-  hipLaunchKernelGGL(adj_final_kernel, dim3(gi), dim3(A_BT), 0, st, A, (const double*)fsum_tmp);
+  const int blocks = A.pg ? pose_grad_blocks(A.M) : (A.M + A_BT - 1) / A_BT;
+  hipLaunchKernelGGL(adj_final_kernel, dim3(blocks + 1), dim3(A_BT), 0, st, A);
   return hipGetLastError();
 }
 

@@ -997,8 +997,11 @@ int unrolled_force(const sgr_cloud* tmpl, const float* a_t, const Unrolled& U, i
   ForceArgs A{tmpl->x, tmpl->y, tmpl->z, a_t, tmpl->m, U.ref4, U.lw, pose_in, U.dv, U.M, U.N,
               U.T.chunk_len, U.T.n_chunks, t, 0.0, U.wpart, wf ? U.fpart : nullptr, U.perm, U.tm4, U.tmx};
   HIPCHK(run_force(A, U.T, U.L, U.pm, false, wf, st));
-  if (wf) HIPCHK(launch_reduce_f(U.fpart, U.L.n_chunks, U.M, U.perm, f_out, st));
-  HIPCHK(launch_update(U.wpart, U.L.slots, pose_in, pose_out, U.dv, t, 0.0, pose_out ? 1 : 0, W_out, nullptr, st));
+  if (wf)
+    HIPCHK(launch_finish(U.fpart, U.L.n_chunks, U.M, U.perm, f_out, U.wpart, U.L.slots, pose_in, pose_out, U.dv, t, 0.0,
+                         pose_out ? 1 : 0, W_out, st));
+  else
+    HIPCHK(launch_update(U.wpart, U.L.slots, pose_in, pose_out, U.dv, t, 0.0, pose_out ? 1 : 0, W_out, nullptr, st));
   return SGR_OK;
 }
 
@@ -1186,8 +1189,11 @@ static int step_impl(sgr_ctx* ctx, const sgr_cloud* tmpl, const float* a_t, cons
     HIPCHK(run_force(A, T, L, pmode_of(prm->p), wrench_out != nullptr, f_out != nullptr, st));
     used = L.slots;
   }
-  if (f_out) HIPCHK(launch_reduce_f(fpart, nch, M, perm, f_out, st));
-  HIPCHK(launch_update(wpart, used, (const double*)in, (double*)out, dv, t, 0.0, 1, wrench_out, nullptr, st));
+  if (f_out)
+    HIPCHK(launch_finish(fpart, nch, M, perm, f_out, wpart, used, (const double*)in, (double*)out, dv, t, 0.0, 1,
+                         wrench_out, st));
+  else
+    HIPCHK(launch_update(wpart, used, (const double*)in, (double*)out, dv, t, 0.0, 1, wrench_out, nullptr, st));
   return SGR_OK;
 }
 
@@ -1392,8 +1398,11 @@ int sgr_step_vec(sgr_ctx* ctx, const sgr_cloud* tmpl, const float* a_t, const sg
   int used = w.slots;
   HIPCHK(run_vforce(vargs(tmpl, ref, w, (const double*)in, t), a_t, D, w, wrench_out != nullptr,
                     f_out != nullptr, &used, st));
-  if (f_out) HIPCHK(launch_reduce_f(w.fpart, w.n_chunks, M, nullptr, f_out, st));
-  HIPCHK(launch_update(w.wpart, used, (const double*)in, (double*)out, w.dv, t, 0.0, 1, wrench_out, nullptr, st));
+  if (f_out)
+    HIPCHK(launch_finish(w.fpart, w.n_chunks, M, nullptr, f_out, w.wpart, used, (const double*)in, (double*)out, w.dv,
+                         t, 0.0, 1, wrench_out, st));
+  else
+    HIPCHK(launch_update(w.wpart, used, (const double*)in, (double*)out, w.dv, t, 0.0, 1, wrench_out, nullptr, st));
   return SGR_OK;
 }
 
@@ -1715,8 +1724,11 @@ int sgr_force_fwd(sgr_ctx* ctx, const sgr_cloud* tmpl, const float* a_t, const s
     HIPCHK(run_force(A, T, L, pm, wrench_out != nullptr, f_out != nullptr, st));
     used = L.slots;
   }
-  if (f_out) HIPCHK(launch_reduce_f(fpart, nch, M, perm, f_out, st));
-  if (wrench_out) HIPCHK(launch_update(wpart, used, pose, nullptr, dv, 0, G, 0, wrench_out, nullptr, st));
+  if (f_out)
+    HIPCHK(launch_finish(fpart, nch, M, perm, f_out, wrench_out ? wpart : nullptr, used, pose, nullptr, dv, 0, G, 0,
+                         wrench_out, st));
+  else
+    HIPCHK(launch_update(wpart, used, pose, nullptr, dv, 0, G, 0, wrench_out, nullptr, st));
   return SGR_OK;
 }
 
@@ -1735,37 +1747,36 @@ int sgr_force_bwd(sgr_ctx* ctx, const sgr_cloud* tmpl, const float* a_t, const s
   const int pm = pmode_of(prm->p);
   const Tiles T = adj_shape(ctx, M, N, ctx->tiles.pick(M, N, pm).R, pm == 1);
   Carve cv{nullptr};
-  cv.take<double>(16);
+  cv.take<double>(48);
   cv.take<double>(16);
   cv.take<Derived>(1);
   cv.take<float4>(pad_n(N));
   cv.take<float>(pad_n(N));
-  cv.take<float>((size_t)M * 3);
   cv.take<double>((size_t)T.n_chunks * M * 4);
   cv.take<double>((size_t)T.nblk * 2);
   cv.take<float>((size_t)M * 3);
   cv.take<double>(16);
   if (int e = ensure_ws(ctx, cv.off)) return e;
   Carve w{ctx->ws};
-  double* mom_t = w.take<double>(16);
+  double* cpart = w.take<double>(48);
   double* fsum = w.take<double>(16);
   Derived* dv = w.take<Derived>(1);
   float4* ref4 = w.take<float4>(pad_n(N));
   float* lw = w.take<float>(pad_n(N));
-  float* lam = w.take<float>((size_t)M * 3);
   double* ypart = w.take<double>((size_t)T.n_chunks * M * 4);
   double* spart = w.take<double>((size_t)T.nblk * 2);
   float* gf0 = w.take<float>((size_t)M * 3);
   double* gw0 = w.take<double>(16);
   if (!grad_f) HIPCHK(launch_fill_f(gf0, (int64_t)M * 3, 0.f, st));
   if (!grad_wrench) HIPCHK(launch_fill(gw0, 16, 0.0, st));
-  HIPCHK(launch_moments(tmpl->x, tmpl->y, tmpl->z, M, nullptr, mom_t, st));
-  HIPCHK(launch_prepare(a_r, ref->m, N, a_t, tmpl->m, M, mom_t, mom_r, prep_of(prm), nullptr, dv, st));
-  HIPCHK(launch_pack_ref(ref->x, ref->y, ref->z, a_r, ref->m, N, dv, ref4, lw, st));
+  // of the template's moments the gradient needs only the centroid
+  HIPCHK(launch_prepare(a_r, ref->m, N, a_t, tmpl->m, M, nullptr, mom_r, prep_of(prm), nullptr, dv, st));
+  HIPCHK(launch_pack_ref_sums(ref->x, ref->y, ref->z, a_r, ref->m, N, dv, ref4, lw,
+                              Points{tmpl->x, tmpl->y, tmpl->z, M}, cpart, st));
   AdjArgs A{tmpl->x, tmpl->y, tmpl->z, a_t, tmpl->m, ref4, lw, dv, M, N, T.chunk_len, T.n_chunks, T.nblk,
-            pm == 1, G, f, grad_f ? grad_f : gf0, grad_wrench ? grad_wrench : gw0, lam, ypart, spart,
-            grad_y, grad_m, grad_se};
-  HIPCHK(launch_adjoint(A, T.R, fsum, st));
+            pm == 1, G, f, grad_f ? grad_f : gf0, grad_wrench ? grad_wrench : gw0, cpart, fsum, ypart, spart,
+            grad_y, grad_m, grad_se, false, Points{}, nullptr};
+  HIPCHK(launch_adjoint(A, T.R, st));
   return SGR_OK;
 }
 
@@ -1885,8 +1896,10 @@ int sgr_plan_force(sgr_plan* pl, int t, double G, const sgr_pose* pose, double* 
     HIPCHK(run_force(A, pl->T, L, pl->pm, wrench_out != nullptr, f_out != nullptr, st));
     used = L.slots;
   }
-  if (f_out) HIPCHK(launch_reduce_f(pl->fpart, pl->nch, (int)pl->tmpl.n, pl->perm, f_out, st));
-  if (wrench_out)
+  if (f_out)
+    HIPCHK(launch_finish(pl->fpart, pl->nch, (int)pl->tmpl.n, pl->perm, f_out, wrench_out ? pl->wpart : nullptr, used,
+                         (const double*)pose, nullptr, pl->dv, t, G, 0, wrench_out, st));
+  else if (wrench_out)
     HIPCHK(launch_update(pl->wpart, used, (const double*)pose, nullptr, pl->dv, t, G, 0, wrench_out, nullptr, st));
   return SGR_OK;
 }
@@ -2000,73 +2013,77 @@ int sgr_unrolled_bwd(sgr_ctx* ctx, const sgr_cloud* tmpl, const float* a_t, cons
   const Tiles TA = adj_shape(ctx, M, N, U.T.R, U.pm == 1);
   const int nseg = (E + K - 1) / K;
   const int npg = pose_grad_blocks(M);
-  auto carve_rest = [&](Carve& c, double** seg, double** W, double** g0, double** g1, double** gW, double** gse_t,
-                        double** mom_y, Derived** dva, double** fsum, double** pg, float** Y, float** f, float** gf0,
-                        float** gy, float** lam, double** ypart, double** spart) {
+  // The forces of a segment are kept while its poses are recomputed, unless
+  // that takes more than KEEP_BYTES: then they are evaluated again.
+  constexpr size_t KEEP_BYTES = size_t(256) << 20;
+  const int S = std::min(K, E);  // iterations of a segment
+  const bool keep = (size_t)S * M * 3 * sizeof(float) <= KEEP_BYTES;
+  struct Rest {
+    double *seg, *W, *g[2], *gW, *cpart, *fsum, *pg, *ypart, *spart;
+    float *Y, *f, *gf0;
+  } r;
+  auto carve_rest = [&](Carve& c) {
     carve_unrolled(c, U, true);
-    *seg = c.take<double>((size_t)(K + 1) * 13);
-    *W = c.take<double>(16);
-    *g0 = c.take<double>(16);
-    *g1 = c.take<double>(16);
-    *gW = c.take<double>(16);
-    *gse_t = c.take<double>(2);
-    *mom_y = c.take<double>(16);
-    *dva = c.take<Derived>(1);
-    *fsum = c.take<double>(16);
-    *pg = c.take<double>((size_t)npg * 12);
-    *Y = c.take<float>((size_t)M * 3);
-    *f = c.take<float>((size_t)M * 3);
-    *gf0 = c.take<float>((size_t)M * 3);
-    *gy = c.take<float>((size_t)M * 3);
-    *lam = c.take<float>((size_t)M * 3);
-    *ypart = c.take<double>((size_t)TA.n_chunks * M * 4);
-    *spart = c.take<double>((size_t)TA.nblk * 2);
+    r.seg = c.take<double>((size_t)(S + 1) * 13);
+    r.W = c.take<double>((size_t)S * 16);
+    r.g[0] = c.take<double>(16);
+    r.g[1] = c.take<double>(16);
+    r.gW = c.take<double>(16);
+    r.cpart = c.take<double>(48);
+    r.fsum = c.take<double>(16);
+    r.pg = c.take<double>((size_t)npg * 12);
+    r.Y = c.take<float>((size_t)M * 3);
+    r.f = c.take<float>((size_t)(keep ? S : 1) * M * 3);
+    r.gf0 = c.take<float>((size_t)M * 3);
+    r.ypart = c.take<double>((size_t)TA.n_chunks * M * 4);
+    r.spart = c.take<double>((size_t)TA.nblk * 2);
   };
-  double *seg, *W, *g0, *g1, *gW, *gse_t, *mom_y, *fsum, *pg, *ypart, *spart;
-  Derived* dva;
-  float *Y, *f, *gf0, *gy, *lam;
   {
     Carve cv{nullptr};
-    carve_rest(cv, &seg, &W, &g0, &g1, &gW, &gse_t, &mom_y, &dva, &fsum, &pg, &Y, &f, &gf0, &gy, &lam, &ypart, &spart);
+    carve_rest(cv);
     if (int e = ensure_ws(ctx, cv.off)) return e;
   }
   Carve w{ctx->ws};
-  carve_rest(w, &seg, &W, &g0, &g1, &gW, &gse_t, &mom_y, &dva, &fsum, &pg, &Y, &f, &gf0, &gy, &lam, &ypart, &spart);
+  carve_rest(w);
   if (int e = setup_unrolled(tmpl, a_t, ref, a_r, mom_t, mom_r, prm, U, st)) return e;
-  HIPCHK(launch_fill_f(gf0, (int64_t)M * 3, 0.f, st));
+  HIPCHK(launch_fill_f(r.gf0, (int64_t)M * 3, 0.f, st));
   HIPCHK(launch_fill(grad_se, 2, 0.0, st));
-  HIPCHK(hipMemcpyAsync(g0, grad_final, 13 * sizeof(double), hipMemcpyDeviceToDevice, st));
-  float* Yx = Y;
-  float* Yy = Y + M;
-  float* Yz = Y + 2 * (size_t)M;
+  HIPCHK(hipMemcpyAsync(r.g[0], grad_final, 13 * sizeof(double), hipMemcpyDeviceToDevice, st));
+  const Points P0{tmpl->x, tmpl->y, tmpl->z, M};
+  float* Yx = r.Y;
+  float* Yy = r.Y + M;
+  float* Yz = r.Y + 2 * (size_t)M;
   for (int sgi = nseg - 1; sgi >= 0; --sgi) {
     const int t0 = sgi * K, t1 = std::min(E, t0 + K);
+    auto pose_at = [&](int t) { return r.seg + (size_t)(t - t0) * 13; };
+    auto W_at = [&](int t) { return r.W + (size_t)(t - t0) * 16; };
+    auto f_at = [&](int t) { return keep ? r.f + (size_t)(t - t0) * M * 3 : r.f; };
     // poses of this segment, recomputed from its checkpoint
-    HIPCHK(hipMemcpyAsync(seg, ckpt + (size_t)sgi * 13, 13 * sizeof(double), hipMemcpyDeviceToDevice, st));
+    HIPCHK(hipMemcpyAsync(r.seg, ckpt + (size_t)sgi * 13, 13 * sizeof(double), hipMemcpyDeviceToDevice, st));
     for (int t = t0; t < t1 - 1; ++t)
-      if (int e = unrolled_force(tmpl, a_t, U, t, seg + (size_t)(t - t0) * 13, seg + (size_t)(t - t0 + 1) * 13,
-                                 nullptr, nullptr, st))
+      if (int e = unrolled_force(tmpl, a_t, U, t, pose_at(t), pose_at(t + 1), keep ? W_at(t) : nullptr,
+                                 keep ? f_at(t) : nullptr, st))
         return e;
     for (int t = t1 - 1; t >= t0; --t) {
-      const double* Pt = seg + (size_t)(t - t0) * 13;
       // forward quantities of iteration t: per-point forces and the wrench
-      if (int e = unrolled_force(tmpl, a_t, U, t, Pt, nullptr, W, f, st)) return e;
-      // update: cotangent of the pose it starts from and of (F, K)
-      HIPCHK(launch_update_bwd(Pt, W, g0, U.dv, g1, gW, st));
-      // force field at the posed template: per-point gradient and (sigma, eps)
-      HIPCHK(launch_pose_points(tmpl->x, tmpl->y, tmpl->z, M, Pt, Yx, Yy, Yz, st));
-      HIPCHK(launch_moments(Yx, Yy, Yz, M, nullptr, mom_y, st));
-      HIPCHK(launch_prepare(a_r, ref->m, N, a_t, tmpl->m, M, mom_y, mom_r, prep_of(prm), nullptr, dva, st));
-      AdjArgs AA{Yx, Yy, Yz, a_t, tmpl->m, U.ref4, U.lw, dva, M, N, TA.chunk_len, TA.n_chunks, TA.nblk,
-                 U.pm == 1, G_host(prm, t), f, gf0, gW, lam, ypart, spart, gy, nullptr, gse_t};
-      HIPCHK(launch_adjoint(AA, TA.R, fsum, st));
-      HIPCHK(launch_axpy(gse_t, 2, grad_se, st));
-      // y_i = s R y0_i + t: per-point gradient onto the pose
-      HIPCHK(launch_pose_grad(gy, tmpl->x, tmpl->y, tmpl->z, M, Pt, pg, g1, st));
-      std::swap(g0, g1);
+      if (!keep || t == t1 - 1)
+        if (int e = unrolled_force(tmpl, a_t, U, t, pose_at(t), nullptr, W_at(t), f_at(t), st)) return e;
+      // update: cotangent of the pose it starts from and of (F, K), after
+      // that of the pose through the points of the iteration before
+      HIPCHK(launch_update_bwd(UpdateBwd{pose_at(t), W_at(t), r.g[0], U.dv, r.g[1], r.gW, t < t1 - 1 ? r.pg : nullptr,
+                                         pose_at(t + 1), P0, Yx, Yy, Yz, r.cpart},
+                               st));
+      // force field at the posed template: per-point gradient, taken to the
+      // pose (y_i = s R y0_i + t), and (sigma, eps)
+      AdjArgs AA{Yx, Yy, Yz, a_t, tmpl->m, U.ref4, U.lw, U.dv, M, N, TA.chunk_len, TA.n_chunks, TA.nblk,
+                 U.pm == 1, G_host(prm, t), f_at(t), r.gf0, r.gW, r.cpart, r.fsum, r.ypart, r.spart, nullptr, nullptr,
+                 grad_se, true, P0, r.pg};
+      HIPCHK(launch_adjoint(AA, TA.R, st));
+      std::swap(r.g[0], r.g[1]);
     }
+    HIPCHK(launch_pose_grad(r.pg, M, pose_at(t0), r.g[0], st));
   }
-  HIPCHK(hipMemcpyAsync(grad_pose0, g0, 13 * sizeof(double), hipMemcpyDeviceToDevice, st));
+  HIPCHK(hipMemcpyAsync(grad_pose0, r.g[0], 13 * sizeof(double), hipMemcpyDeviceToDevice, st));
   return SGR_OK;
 }
 

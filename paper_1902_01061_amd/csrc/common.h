@@ -442,6 +442,20 @@ __device__ inline double part_sum(const double* part, int nv, int k) {
   return s;
 }
 
+// Share of virtual thread t (of 1024) in the sum of n points point(i), each a
+// float3: its wave's sums go to part[3 (t / 64) ..].  Four blocks of 256
+// threads, or one that takes the four quarters in turn, make up the 1024.
+template <class Point>
+__device__ inline void points_part(int t, int64_t n, Point&& point, double* part) {
+  double s[3] = {0.0, 0.0, 0.0};
+  strided<8>(t, n, point, [&](const float3& p) {
+    s[0] += p.x;
+    s[1] += p.y;
+    s[2] += p.z;
+  });
+  wave_part<3>(s, part, t >> 6);
+}
+
 // Smallest and largest value over the threads of a block of BT threads
 // (NaN is ignored; every thread receives both).  lds: 2 * BT / 64 doubles of
 // scratch, free on entry (a barrier precedes its use).

@@ -119,9 +119,10 @@ __device__ inline void prep_store(const PrepIn& I, const PrepParams& P, const do
   for (int c = 0; c < 3; ++c) D.xbar[c] = mom_r[c];
   D.lamX = mom_r[9];
   D.L = sqrt(D.lamX);
-  for (int c = 0; c < 3; ++c) D.ybar0[c] = mom_t[c];
-  for (int c = 0; c < 6; ++c) D.SigY0[c] = mom_t[3 + c];
-  D.lamY0 = mom_t[9];
+  // no template moments: a caller that only evaluates the force field
+  for (int c = 0; c < 3; ++c) D.ybar0[c] = mom_t ? mom_t[c] : 0.0;
+  for (int c = 0; c < 6; ++c) D.SigY0[c] = mom_t ? mom_t[3 + c] : 0.0;
+  D.lamY0 = mom_t ? mom_t[9] : 0.0;
   D.abar = abar;
   const double sd = sqrt(v / (double)N);
   D.sigma = (P.sigma > 0 ? P.sigma : sd) * P.sigma_scale;
@@ -282,8 +283,12 @@ __global__ __launch_bounds__(256) void pack_ref_kernel(const float* __restrict__
                                                        const float* __restrict__ Zc, const float* __restrict__ aX,
                                                        const float* __restrict__ wX, int64_t N,
                                                        const Derived* __restrict__ dv, float4* __restrict__ ref4,
-                                                       float* __restrict__ lw) {
-  pack_ref_body(X, Y, Zc, aX, wX, N, dv, ref4, lw, (int64_t)blockIdx.x * 256 + threadIdx.x);
+                                                       float* __restrict__ lw, Points C, double* __restrict__ cpart) {
+  const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (j < ((N + 255) & ~int64_t(255)))
+    pack_ref_body(X, Y, Zc, aX, wX, N, dv, ref4, lw, j);
+  else  // four more blocks
+    points_part((int)(j - ((N + 255) & ~int64_t(255))), C.n, [&](int64_t i) { return make_float3(C.x[i], C.y[i], C.z[i]); }, cpart);
 }
 
 __global__ __launch_bounds__(256) void pack_batch_kernel(const PrepDesc* __restrict__ d, const int* __restrict__ blk2reg,
@@ -715,18 +720,6 @@ __global__ __launch_bounds__(F_BT) void force_batch_kernel(BatchArgs B) {
   }
 }
 
-// f_out[perm[ip]] = sum over chunks of the per-chunk forces of visiting
-// position ip (fixed order); perm may be null (identity).
-__global__ __launch_bounds__(256) void reduce_f_kernel(const double* __restrict__ fpart, int n_chunks, int M,
-                                                       const int* __restrict__ perm, float* __restrict__ f_out) {
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= (int64_t)M * 3) return;
-  double s = 0.0;
-  for (int c = 0; c < n_chunks; ++c) s += fpart[(int64_t)c * M * 3 + e];
-  const int64_t ip = e / 3;
-  f_out[(perm ? (int64_t)perm[ip] : ip) * 3 + (e - ip * 3)] = (float)s;
-}
-
 hipError_t launch_prepare(const float* aX, const float* wX, int64_t N, const float* aY, const float* mY, int64_t M,
                           const double* mom_t, const double* mom_r, const PrepParams& P, double* part, Derived* out,
                           hipStream_t st) {
@@ -768,8 +761,14 @@ hipError_t launch_pack_batch(const PrepDesc* d, const int* blk2reg, int n_blocks
 
 hipError_t launch_pack_ref(const float* x, const float* y, const float* z, const float* aX, const float* wX, int64_t N,
                            const Derived* dv, float4* ref4, float* lw, hipStream_t st) {
-  hipLaunchKernelGGL(pack_ref_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, st, x, y, z, aX, wX, N, dv, ref4,
-                     lw);
+  return launch_pack_ref_sums(x, y, z, aX, wX, N, dv, ref4, lw, Points{}, nullptr, st);
+}
+
+hipError_t launch_pack_ref_sums(const float* x, const float* y, const float* z, const float* aX, const float* wX,
+                                int64_t N, const Derived* dv, float4* ref4, float* lw, const Points& C, double* cpart,
+                                hipStream_t st) {
+  hipLaunchKernelGGL(pack_ref_kernel, dim3((unsigned)((N + 255) / 256 + (cpart ? 4 : 0))), dim3(256), 0, st, x, y, z,
+                     aX, wX, N, dv, ref4, lw, C, cpart);
   return hipGetLastError();
 }
 
@@ -859,13 +858,6 @@ hipError_t launch_force_batch(const BatchArgs& B, int R, int pm, bool want_u, in
   }
 #undef SGR_FB_R
 #undef SGR_FB
-  return hipGetLastError();
-}
-
-hipError_t launch_reduce_f(const double* fpart, int n_chunks, int M, const int* perm, float* f_out, hipStream_t st) {
-  const int64_t n = (int64_t)M * 3;
-  hipLaunchKernelGGL(reduce_f_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, fpart, n_chunks, M, perm,
-                     f_out);
   return hipGetLastError();
 }
 

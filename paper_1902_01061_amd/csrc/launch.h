@@ -118,6 +118,13 @@ struct BatchArgs {
   double* wpart;
 };
 
+struct Points {
+  const float* x;
+  const float* y;
+  const float* z;
+  int n;
+};
+
 struct AdjArgs {
   const float* y0x;
   const float* y0y;
@@ -134,32 +141,46 @@ struct AdjArgs {
   const float* f;       // forces of the forward pass [M][3]
   const float* gf;      // upstream gradient of f [M][3]
   const double* gw;     // upstream gradient of the wrench (F[3], K[9])
-  float* lam;           // [M][3] workspace
+  const double* cpart;  // centroid of the template: 16 partial sums of 3 (points_part)
+  double* fsum;         // [3] workspace: sum of f
   double* ypart;        // [n_chunks][M][4] workspace
   double* spart;        // [nblk][2] workspace
   float* grad_y;        // [M][3]
   float* grad_m;        // [M] or nullptr
   double* grad_se;      // [2] (sigma, eps) or nullptr
+  bool se_add;          // grad_se is added to
+  Points p0;            // with pg: template before the pose
+  double* pg;           // [pose_grad_blocks(M)][12] sums of grad_y p0^T and grad_y, or nullptr
 };
 
-hipError_t launch_adjoint(const AdjArgs& A, int R, double* fsum_tmp, hipStream_t st);
-// Resident blocks per CU of the adjoint pair kernel; granularity of its
-// balanced reference chunks (AdjArgs.chunk_len = 0).
-int adj_blocks_per_cu(int R, bool p1);
+hipError_t launch_adjoint(const AdjArgs& A, int R, hipStream_t st);
+// Granularity of the adjoint kernel's balanced reference chunks.
 int adj_chunk_gran();
 // Adjoint of one rigid update: gpose_in[13] and gW[16] from gpose_out[13]
-// (pose_in the pose the update started from, W its wrench).
-hipError_t launch_update_bwd(const double* pose_in, const double* W, const double* gpose_out, const Derived* dv,
-                             double* gpose_in, double* gW, hipStream_t st);
-// o = s R p + t for the template points (FP32 out).
-hipError_t launch_pose_points(const float* x, const float* y, const float* z, int M, const double* pose, float* ox,
-                              float* oy, float* oz, hipStream_t st);
-// gpose += pose cotangent of the per-point gradient gy [M][3] of y = s R p + t;
-// part needs pose_grad_blocks(M) * 12 doubles.
+// (pose_in the pose the update started from, W its wrench), and beside it the
+// template at pose_in, o = s R p + t (FP32), with the sums of its centroid
+// (cpart: 48 doubles).  With pg, the pose gradient of the later iteration
+// (started from pose_next) is first added to gpose_out.
+struct UpdateBwd {
+  const double* pose_in;
+  const double* W;
+  double* gpose_out;
+  const Derived* dv;
+  double* gpose_in;
+  double* gW;
+  const double* pg;
+  const double* pose_next;
+  Points p;
+  float* ox;
+  float* oy;
+  float* oz;
+  double* cpart;
+};
+hipError_t launch_update_bwd(const UpdateBwd& A, hipStream_t st);
+// gpose += pose cotangent of the per-point gradient of y = s R p + t, from
+// its sums part [pose_grad_blocks(M)][12].
 int pose_grad_blocks(int M);
-hipError_t launch_pose_grad(const float* gy, const float* x, const float* y, const float* z, int M, const double* pose,
-                            double* part, double* gpose, hipStream_t st);
-hipError_t launch_axpy(const double* x, int n, double* y, hipStream_t st);
+hipError_t launch_pose_grad(const double* part, int M, const double* pose, double* gpose, hipStream_t st);
 hipError_t launch_fill(double* p, int n, double v, hipStream_t st);
 hipError_t launch_fill_f(float* p, int64_t n, float v, hipStream_t st);
 hipError_t launch_identity_pose(double* pose, hipStream_t st);
@@ -349,6 +370,10 @@ hipError_t launch_prepare(const float* aX, const float* wX, int64_t N, const flo
                           hipStream_t st);
 hipError_t launch_pack_ref(const float* x, const float* y, const float* z, const float* aX, const float* wX, int64_t N,
                            const Derived* dv, float4* ref4, float* lw, hipStream_t st);
+// The same with the centroid sums of another cloud (cpart: 48 doubles).
+hipError_t launch_pack_ref_sums(const float* x, const float* y, const float* z, const float* aX, const float* wX,
+                                int64_t N, const Derived* dv, float4* ref4, float* lw, const Points& C, double* cpart,
+                                hipStream_t st);
 hipError_t launch_force(const ForceArgs& A, int R, int pm, bool want_u, bool want_f, hipStream_t st, bool sm);
 // Blocks per CU the force kernel's launch is shaped for (R points per lane, p
 // mode, scalar-load variant).
@@ -376,7 +401,11 @@ hipError_t launch_sort_perm_batch(const RegDesc* regs, int B, const int* off, in
 hipError_t launch_force_mixed(const ForceArgs& A, bool want_f, hipStream_t st);
 int mixed_points_per_block();
 // f_out[perm[ip]] (perm nullable) = sum over chunks of fpart[chunk][ip] (visiting order).
-hipError_t launch_reduce_f(const double* fpart, int n_chunks, int M, const int* perm, float* f_out, hipStream_t st);
+// f_out[perm[ip]] = the per-chunk forces of position ip added up (perm may be
+// nullptr), and beside it the update of launch_update (wpart nullptr: none).
+hipError_t launch_finish(const double* fpart, int n_chunks, int M, const int* perm, float* f_out, const double* wpart,
+                         int nblk, const double* pose_in, double* pose_out, Derived* dv, int t, double G_fixed,
+                         int do_update, double* wrench_out, hipStream_t st);
 int force_points_per_block(int R);
 int force_chunk_gran();
 int force_tile_j();

@@ -142,6 +142,9 @@ hipError_t launch_update(const double* wpart, int nblk, const double* pose_in, d
 }
 
 
+__host__ __device__ inline int grad_blocks(int M) { return M < 256 * 256 ? (M + 255) / 256 : 256; }
+int pose_grad_blocks(int M) { return grad_blocks(M); }
+
 // ---------------------------------------------------------------- adjoint
 // Reverse-mode derivative of one rigid update (Sec. III-B, eqs. 5.5, 6, 8,
 // 9 as in pose_update) with respect to the pose it starts from and the
@@ -153,14 +156,11 @@ hipError_t launch_update(const double* wpart, int nblk, const double* pose_in, d
 // scale c s = sqrt(lambda_X / lambda_Y0) does not depend on the pose, and
 // the Newton-Schulz step Ro = Rn (3I - Rn^T Rn) / 2 is differentiated as
 // written.  Assumes the forward update was applied (status 0).
-// One wave (its launch): the bound lets the single thread keep its FP64
-// state in registers (the default bound of 1 024 threads spilled it).
-__global__ __launch_bounds__(64) void update_bwd_kernel(const double* __restrict__ pose_in,
-                                                        const double* __restrict__ W,
-                                                        const double* __restrict__ gpose_out,
-                                                        const Derived* __restrict__ dv, double* __restrict__ gpose_in,
-                                                        double* __restrict__ gW) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// A call, so that which products are fused into sums does not depend on what
+// surrounds it: the unrolled gradients cancel so far that a rounding of FP64
+// here shows in their eighth digit.
+__device__ __attribute__((noinline)) void update_bwd(const double* pose_in, const double* W, const double* gpose_out, const Derived* dv,
+                                  double* gpose_in, double* gW) {
   const Derived& D = *dv;
   const double s = pose_in[0];
   double R[9], tv[3];
@@ -302,49 +302,11 @@ __global__ __launch_bounds__(64) void update_bwd_kernel(const double* __restrict
   for (int e = 12; e < WR_STRIDE; ++e) gW[e] = 0.0;
 }
 
-// World coordinates of the posed template, s R y0 + t (FP64, rounded once).
-__global__ __launch_bounds__(256) void pose_points_kernel(const float* __restrict__ x, const float* __restrict__ y,
-                                                          const float* __restrict__ z, int M,
-                                                          const double* __restrict__ pose, float* __restrict__ ox,
-                                                          float* __restrict__ oy, float* __restrict__ oz) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= M) return;
-  const double s = pose[0];
-  const double p[3] = {(double)x[i], (double)y[i], (double)z[i]};
-  double o[3];
-  for (int r = 0; r < 3; ++r) o[r] = s * (pose[1 + 3 * r] * p[0] + pose[2 + 3 * r] * p[1] + pose[3 + 3 * r] * p[2]) + pose[10 + r];
-  ox[i] = (float)o[0];
-  oy[i] = (float)o[1];
-  oz[i] = (float)o[2];
-}
-
-// Per-block sums of gy_i y0_i^T (9) and gy_i (3) over the template points.
-__global__ __launch_bounds__(256) void pose_grad_partial_kernel(const float* __restrict__ gy, const float* __restrict__ x,
-                                                                const float* __restrict__ y,
-                                                                const float* __restrict__ z, int M,
-                                                                double* __restrict__ part) {
-  __shared__ double lds[4 * 12];
-  double v[12];
-  for (int e = 0; e < 12; ++e) v[e] = 0.0;
-  for (int i = blockIdx.x * 256 + threadIdx.x; i < M; i += gridDim.x * 256) {
-    const double g[3] = {(double)gy[3 * i], (double)gy[3 * i + 1], (double)gy[3 * i + 2]};
-    const double p[3] = {(double)x[i], (double)y[i], (double)z[i]};
-    for (int r = 0; r < 3; ++r) {
-      for (int q = 0; q < 3; ++q) v[3 * r + q] += g[r] * p[q];
-      v[9 + r] += g[r];
-    }
-  }
-  block_sum<12, 256>(v, lds);
-  if (threadIdx.x == 0)
-    for (int e = 0; e < 12; ++e) part[(int64_t)blockIdx.x * 12 + e] = v[e];
-}
-
 // gpose += the pose cotangent of y_i = s R y0_i + t: sbar += <A, R>,
-// Rbar += s A, tbar += g, with A = sum_i gy_i y0_i^T, g = sum_i gy_i.
-__global__ __launch_bounds__(256) void pose_grad_final_kernel(const double* __restrict__ part, int nb,
-                                                              const double* __restrict__ pose,
-                                                              double* __restrict__ gpose) {
-  __shared__ double lds[4 * 12];
+// Rbar += s A, tbar += g, with A = sum_i gy_i y0_i^T, g = sum_i gy_i from
+// their nb partial sums (one block of 256).
+__device__ inline void pose_grad(const double* __restrict__ part, int nb, const double* __restrict__ pose,
+                                 double* __restrict__ gpose, double* lds) {
   double v[12];
   for (int e = 0; e < 12; ++e) v[e] = 0.0;
   for (int b = threadIdx.x; b < nb; b += 256)
@@ -358,35 +320,93 @@ __global__ __launch_bounds__(256) void pose_grad_final_kernel(const double* __re
   for (int e = 0; e < 3; ++e) gpose[10 + e] += v[9 + e];
 }
 
-__global__ void axpy_kernel(const double* __restrict__ x, int n, double* __restrict__ y) {
-  if (threadIdx.x < n) y[threadIdx.x] += x[threadIdx.x];
+__global__ __launch_bounds__(256) void pose_grad_kernel(const double* part, int nb, const double* pose,
+                                                        double* gpose) {
+  __shared__ double lds[4 * 12];
+  pose_grad(part, nb, pose, gpose, lds);
 }
 
-hipError_t launch_update_bwd(const double* pose_in, const double* W, const double* gpose_out, const Derived* dv,
-                             double* gpose_in, double* gW, hipStream_t st) {
-  hipLaunchKernelGGL(update_bwd_kernel, dim3(1), dim3(64), 0, st, pose_in, W, gpose_out, dv, gpose_in, gW);
+// What an iteration's adjoint needs before the pair sums, side by side: block
+// 0 adds the pose gradient of the later iteration and differentiates the
+// update (one thread, FP64: a bound of 256 threads leaves it its registers),
+// four blocks pose the template and sum its centroid.  Bound by block 0's
+// chain: 10 us, where the launches it replaces took 45 (moments and
+// constants of the posed template among them, of which only the centroid
+// is not known already).
+__global__ __launch_bounds__(256) void update_bwd_kernel(UpdateBwd A) {
+  __shared__ double lds[4 * 12];
+  if (blockIdx.x == 0) {
+    if (A.pg) pose_grad(A.pg, grad_blocks(A.p.n), A.pose_next, A.gpose_out, lds);
+    if (threadIdx.x == 0) update_bwd(A.pose_in, A.W, A.gpose_out, A.dv, A.gpose_in, A.gW);
+    return;
+  }
+  const double* pose = A.pose_in;
+  const double s = pose[0];
+  points_part((blockIdx.x - 1) * 256 + threadIdx.x, A.p.n,
+              [&](int64_t i) {
+                const double p[3] = {(double)A.p.x[i], (double)A.p.y[i], (double)A.p.z[i]};
+                double o[3];
+                for (int r = 0; r < 3; ++r)
+                  o[r] = s * (pose[1 + 3 * r] * p[0] + pose[2 + 3 * r] * p[1] + pose[3 + 3 * r] * p[2]) + pose[10 + r];
+                const float3 q = make_float3((float)o[0], (float)o[1], (float)o[2]);
+                A.ox[i] = q.x;  // (the last point again for a thread beyond it)
+                A.oy[i] = q.y;
+                A.oz[i] = q.z;
+                return q;
+              },
+              A.cpart);
+}
+
+// Per-point forces from their chunks, and the update (block 0) beside it.
+// Bound by the latency of the chunk loads, 16 in flight, and by the update's
+// chain beside them: 8.8 us at 8 192 points and 64 chunks, where the two took
+// 18.8 (one load at a time) and 7.4 us one after the other.
+__global__ __launch_bounds__(512) void finish_kernel(const double* __restrict__ fpart, int n_chunks, int M,
+                                                     const int* __restrict__ perm, float* __restrict__ f_out,
+                                                     const double* __restrict__ wpart, int nblk, const double* pose_in,
+                                                     double* pose_out, Derived* __restrict__ dv, int t, double G_fixed,
+                                                     int do_update, double* __restrict__ wrench_out) {
+  __shared__ double lds[512 / 4];
+  if (blockIdx.x == 0) {
+    if (!wpart) return;
+    UpdateIn u;
+    if (threadIdx.x == 0) update_load(dv, pose_in, t, G_fixed, u);
+    double W[13];
+    sum_partials<512, 16>(wpart, nblk, lds, W);
+    if (threadIdx.x == 0) update_apply(W, u, pose_out, dv, do_update, wrench_out, nullptr);
+    return;
+  }
+  const int64_t e = (int64_t)(blockIdx.x - 1) * 512 + threadIdx.x, n = (int64_t)M * 3;
+  if (e >= n) return;
+  constexpr int U = 16;
+  double s = 0.0;
+  for (int c = 0; c < n_chunks; c += U) {
+    double v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = fpart[(int64_t)min(c + u, n_chunks - 1) * n + e];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (c + u < n_chunks) s += v[u];
+  }
+  const int64_t ip = e / 3;
+  f_out[(perm ? (int64_t)perm[ip] : ip) * 3 + (e - ip * 3)] = (float)s;
+}
+
+hipError_t launch_finish(const double* fpart, int n_chunks, int M, const int* perm, float* f_out, const double* wpart,
+                         int nblk, const double* pose_in, double* pose_out, Derived* dv, int t, double G_fixed,
+                         int do_update, double* wrench_out, hipStream_t st) {
+  hipLaunchKernelGGL(finish_kernel, dim3((unsigned)(((int64_t)M * 3 + 511) / 512 + 1)), dim3(512), 0, st, fpart,
+                     n_chunks, M, perm, f_out, wpart, nblk, pose_in, pose_out, dv, t, G_fixed, do_update, wrench_out);
   return hipGetLastError();
 }
 
-hipError_t launch_pose_points(const float* x, const float* y, const float* z, int M, const double* pose, float* ox,
-                              float* oy, float* oz, hipStream_t st) {
-  hipLaunchKernelGGL(pose_points_kernel, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, st, x, y, z, M, pose, ox, oy,
-                     oz);
+hipError_t launch_update_bwd(const UpdateBwd& A, hipStream_t st) {
+  hipLaunchKernelGGL(update_bwd_kernel, dim3(5), dim3(256), 0, st, A);
   return hipGetLastError();
 }
 
-int pose_grad_blocks(int M) { return std::min(256, (M + 255) / 256); }
-
-hipError_t launch_pose_grad(const float* gy, const float* x, const float* y, const float* z, int M, const double* pose,
-                            double* part, double* gpose, hipStream_t st) {
-  const int nb = pose_grad_blocks(M);
-  hipLaunchKernelGGL(pose_grad_partial_kernel, dim3(nb), dim3(256), 0, st, gy, x, y, z, M, part);
-  hipLaunchKernelGGL(pose_grad_final_kernel, dim3(1), dim3(256), 0, st, (const double*)part, nb, pose, gpose);
-  return hipGetLastError();
-}
-
-hipError_t launch_axpy(const double* x, int n, double* y, hipStream_t st) {
-  hipLaunchKernelGGL(axpy_kernel, dim3(1), dim3(64), 0, st, x, n, y);
+hipError_t launch_pose_grad(const double* part, int M, const double* pose, double* gpose, hipStream_t st) {
+  hipLaunchKernelGGL(pose_grad_kernel, dim3(1), dim3(256), 0, st, part, pose_grad_blocks(M), pose, gpose);
   return hipGetLastError();
 }
 
