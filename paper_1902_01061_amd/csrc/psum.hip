@@ -31,6 +31,10 @@ namespace {
 
 constexpr int PS_BT = 256;
 constexpr int PS_NQ = 5;  // S0, S1 (3), S2
+// Reference points whose weights are formed before any of them is added: the
+// exponentials' latency stays off the sums, which are added in the same order
+// whatever U.
+constexpr int PS_U = 4;
 
 // Sums of R template points per lane (positions ip0 + r * PS_BT) over the
 // reference points [j0, j1) of one LDS tile after the other, written to
@@ -41,9 +45,10 @@ constexpr int PS_NQ = 5;  // S0, S1 (3), S2
 // into chunks beyond FP64 rounding.
 template <int R, bool Q>
 __device__ inline void psum_block(const float4* __restrict__ tm4, int M, const float4* __restrict__ ref4,
-                                  const float* __restrict__ lw, int j0, int j1, int ip0, float4* s_x, float* s_l,
-                                  float* s_q, double* __restrict__ out) {
+                                  const float* __restrict__ lw, int j0, int j1, int ip0, float4* s_x, float2* s_l,
+                                  double* __restrict__ out) {
   constexpr int NQ = Q ? PS_NQ : PS_NQ - 1;
+  constexpr int U = PS_U;
   float bi[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) bi[r] = ip0 + r * PS_BT < M ? tm4[ip0 + r * PS_BT].w : 0.f;
@@ -63,32 +68,40 @@ __device__ inline void psum_block(const float4* __restrict__ tm4, int M, const f
         l = lw[j];
       }
       s_x[threadIdx.x] = X;
-      s_l[threadIdx.x] = l;
-      if constexpr (Q) s_q[threadIdx.x] = __builtin_fmaf(X.x, X.x, __builtin_fmaf(X.y, X.y, X.z * X.z));
+      s_l[threadIdx.x] = make_float2(l, __builtin_fmaf(X.x, X.x, __builtin_fmaf(X.y, X.y, X.z * X.z)));
     }
     __syncthreads();
+    // whole groups of U: points beyond the range have zero weight
     const int n = min(PS_BT, j1 - base);
     float a[R][NQ];
 #pragma unroll
     for (int r = 0; r < R; ++r)
 #pragma unroll
       for (int q = 0; q < NQ; ++q) a[r][q] = 0.f;
-#pragma unroll 2
-    for (int jj = 0; jj < n; ++jj) {
-      const float4 X = s_x[jj];
-      const float l = s_l[jj];
-      float xq = 0.f;
-      if constexpr (Q) xq = s_q[jj];
+    for (int jj = 0; jj < n; jj += U) {
+      float4 X[U];
+      float c[U][R];
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const float d = bi[r] - X.w;
-        const float c = __builtin_amdgcn_exp2f(__builtin_fmaf(-d, d, l));
-        a[r][0] += c;
-        a[r][1] = __builtin_fmaf(c, X.x, a[r][1]);
-        a[r][2] = __builtin_fmaf(c, X.y, a[r][2]);
-        a[r][3] = __builtin_fmaf(c, X.z, a[r][3]);
-        if constexpr (Q) a[r][4] = __builtin_fmaf(c, xq, a[r][4]);
+      for (int u = 0; u < U; ++u) {
+        X[u] = s_x[jj + u];
+        const float2 l = s_l[jj + u];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const float d = bi[r] - X[u].w;
+          c[u][r] = __builtin_amdgcn_exp2f(__builtin_fmaf(-d, d, l.x));
+        }
+        if constexpr (Q) X[u].w = l.y;
       }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          a[r][0] += c[u][r];
+          a[r][1] = __builtin_fmaf(c[u][r], X[u].x, a[r][1]);
+          a[r][2] = __builtin_fmaf(c[u][r], X[u].y, a[r][2]);
+          a[r][3] = __builtin_fmaf(c[u][r], X[u].z, a[r][3]);
+          if constexpr (Q) a[r][4] = __builtin_fmaf(c[u][r], X[u].w, a[r][4]);
+        }
     }
 #pragma unroll
     for (int r = 0; r < R; ++r)
@@ -114,11 +127,11 @@ __global__ __launch_bounds__(PS_BT) void psum_kernel(const float4* __restrict__ 
                                                      const float4* __restrict__ ref4, const float* __restrict__ lw,
                                                      int N, int chunk_len, double* __restrict__ part) {
   __shared__ float4 s_x[PS_BT];
-  __shared__ float s_l[PS_BT], s_q[Q ? PS_BT : 1];
+  __shared__ float2 s_l[PS_BT];
   const int n_iblk = (M + PS_BT * PS_R - 1) / (PS_BT * PS_R);
   const int iblk = blockIdx.x % n_iblk, chunk = blockIdx.x / n_iblk;
   const int j0 = chunk * chunk_len, j1 = min(N, j0 + chunk_len);
-  psum_block<PS_R, Q>(tm4, M, ref4, lw, j0, j1, iblk * PS_BT * PS_R + threadIdx.x, s_x, s_l, s_q,
+  psum_block<PS_R, Q>(tm4, M, ref4, lw, j0, j1, iblk * PS_BT * PS_R + threadIdx.x, s_x, s_l,
                       part + (int64_t)chunk * M * PS_NQ);
 }
 
@@ -126,20 +139,35 @@ __global__ __launch_bounds__(PS_BT) void psum_kernel(const float4* __restrict__ 
 // points, reference chunk) of a list in decreasing cost, so that the long
 // items start first and the short ones fill the end of the launch.  A
 // registration with one chunk writes its sums at once.
-constexpr int PS_RB = 2;
+constexpr int PS_RB = 3;
 
 __global__ __launch_bounds__(PS_BT) void psum_batch_kernel(const PsumReg* __restrict__ regs,
                                                            const int4* __restrict__ items, int chunk_len,
                                                            const float4* __restrict__ ref4,
                                                            const float* __restrict__ lw) {
   __shared__ float4 s_x[PS_BT];
-  __shared__ float s_l[PS_BT], s_q[PS_BT];
+  __shared__ float2 s_l[PS_BT];
   const int4 it = items[blockIdx.x];
   const PsumReg g = regs[it.x];
   const int j0 = it.z * chunk_len, j1 = min(g.N, j0 + chunk_len);
   double* out = g.n_chunks == 1 ? g.S : g.part + (int64_t)it.z * g.M * PS_NQ;
   psum_block<PS_RB, true>(gptr(g.tm4), g.M, ref4 + g.ref_off, lw + g.ref_off, j0, j1,
-                          it.y * PS_BT * PS_RB + threadIdx.x, s_x, s_l, s_q, gptr(out));
+                          it.y * PS_BT * PS_RB + threadIdx.x, s_x, s_l, gptr(out));
+}
+
+// One sum over the chunks, in chunk order, eight loads in flight.
+__device__ inline double chunk_sum(const double* __restrict__ p, int64_t stride, int n) {
+  constexpr int U = 8;
+  double s = 0.0;
+  for (int c = 0; c < n; c += U) {
+    double v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = p[min(c + u, n - 1) * stride];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (c + u < n) s += v[u];
+  }
+  return s;
 }
 
 // Chunk sums of the registrations with several chunks, in chunk order; the
@@ -150,9 +178,7 @@ __global__ __launch_bounds__(256) void psum_reduce_batch_kernel(const PsumReg* _
   const double* __restrict__ part = gptr(g.part);
   const int64_t ne = (int64_t)g.M * PS_NQ;
   for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < ne; e += (int64_t)gridDim.x * 256) {
-    double s = 0.0;
-    for (int c = 0; c < g.n_chunks; ++c) s += part[(int64_t)c * ne + e];
-    gptr(g.S)[e] = s;
+    gptr(g.S)[e] = chunk_sum(part + e, ne, g.n_chunks);
   }
 }
 
@@ -160,9 +186,7 @@ __global__ __launch_bounds__(256) void psum_reduce_kernel(const double* __restri
                                                           double* __restrict__ S) {
   const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (e >= (int64_t)M * PS_NQ) return;
-  double s = 0.0;
-  for (int c = 0; c < n_chunks; ++c) s += part[(int64_t)c * M * PS_NQ + e];
-  S[e] = s;
+  S[e] = chunk_sum(part + e, (int64_t)M * PS_NQ, n_chunks);
 }
 
 // Wrench terms of template point ip (visiting order) of one registration:
@@ -495,17 +519,26 @@ __global__ __launch_bounds__(LP_BT) void pinv_loop_batch_kernel(const LoopReg* _
 
 }  // namespace
 
-// Reference chunks of psum_kernel: about 4 blocks per CU, and up to 24 while
-// every block keeps at least 4e6 pairs (more rounds of shorter chunks even
-// out the end of a large launch; on a small pair each block's fixed start
-// and end would dominate).
+// Reference chunks of psum_kernel, of whole tiles: the cut that costs least by
+// the tiles of the CU that has most (14 us each, and a quarter of one for a
+// block's start and end) and the chunks' sums to be added (40 bytes a point at
+// 4 TB/s), among those that give a CU 3 to 24 blocks where there are enough
+// tiles for that.  32 400 x 36 000: 24 chunks, 3 blocks of 6 tiles per CU,
+// 268 us; 29 chunks, 4 blocks of 5, took 284.
 int pinv_chunks(int M, int N, int n_cu) {
   const int n_iblk = (M + PS_BT * PS_R - 1) / (PS_BT * PS_R);
   const int n_t = (N + PS_BT - 1) / PS_BT;
-  const int64_t lo = int64_t(4) * n_cu, hi = int64_t(24) * n_cu;
-  const int64_t target = std::min(hi, std::max(lo, (int64_t)M * N / 4000000));
-  const int nc = (int)((target + n_iblk - 1) / n_iblk);
-  return std::max(1, std::min(nc, n_t));
+  int best = 0;
+  double best_us = 0.0;
+  for (int t = 1; t <= n_t; ++t) {
+    const int nc = (n_t + t - 1) / t;
+    const int64_t per_cu = ((int64_t)n_iblk * nc + n_cu - 1) / n_cu;
+    if (per_cu > 24 && t < n_t) continue;
+    if (per_cu < 3 && best > 0) break;
+    const double us = 14.0 * (double)per_cu * (t + 0.25) + 1e-5 * (double)nc * M;
+    if (best == 0 || us < best_us) best = nc, best_us = us;
+  }
+  return best;
 }
 
 int pinv_blocks(int M) { return (M + PS_BT - 1) / PS_BT; }
