@@ -637,6 +637,7 @@ struct SingleWs {
   int* sync;         // the loop's ticket (64 ints), then its exchange words
   double* pose0;     // poses before each level's loop
   int loop_ppt, loop_nb;  // the one-launch loop's shape (0 blocks: not used)
+  ForceLoop floop;        // that of the all-pairs force
   int* perm;
   char* sws;
   float4* tm4;
@@ -658,6 +659,11 @@ int carve_single(sgr_ctx* ctx, int M, int N, const sgr_params* prm, int kmax, Si
   w.ps_chunks = pinv ? pinv_chunks(M, N, ctx->n_cu) : 0;
   w.loop_ppt = pinv ? loop_points(M, 1) : 0;
   w.loop_nb = pinv && use_loop ? loop_blocks(M, w.loop_ppt) : 0;
+  // the all-pairs force of a small pair: one point a lane, FP32, p = 1
+  w.floop = ForceLoop{};
+  if (!pinv && use_loop && pm == 1 && !is_mixed(prm) && w.T.R == 1 && !w.T.sm)
+    w.floop = force_loop_shape(M, N, force_shape(ctx, M, N, w.T, pm).n_chunks);
+  const bool loops = pinv || w.floop.blocks > 0;
   size_t gbytes = kmax > 0 ? std::max(grid_knn_workspace(N, kmax), grid_knn_workspace(M, kmax)) : 0;
   if (radius) gbytes = std::max({gbytes, radius_desc_workspace(N), radius_desc_workspace(M)});
   for (int pass = 0; pass < 2; ++pass) {
@@ -677,11 +683,13 @@ int carve_single(sgr_ctx* ctx, int M, int N, const sgr_params* prm, int kmax, Si
     w.tmx = c.take<float2>(M);
     w.ps_part = pinv ? c.take<double>((size_t)w.ps_chunks * M * 5) : nullptr;
     w.ps_S = pinv ? c.take<double>((size_t)M * 5) : nullptr;
-    w.sync = pinv ? c.take<int>(64 + 2 * loop_words(w.loop_nb)) : nullptr;
-    w.pose0 = pinv ? c.take<double>((size_t)13 * n_levels) : nullptr;
+    w.sync = loops ? c.take<int>(64 + 2 * loop_words(std::max(w.loop_nb, w.floop.blocks))) : nullptr;
+    w.pose0 = loops ? c.take<double>((size_t)13 * n_levels) : nullptr;
     if (!pass)
       if (int e = ensure_ws(ctx, c.off)) return e;
   }
+  w.floop.ref4 = w.ref4;
+  w.floop.lw = w.lw;
   return SGR_OK;
 }
 
@@ -723,6 +731,14 @@ int run_single_loop(sgr_ctx* ctx, GraphCache& gc, const sgr_cloud* tmpl, const s
     return run_loop(ctx, LoopReg{w.tm4, w.tmx, w.ps_S, (double*)inout, w.pose0 + 13 * (size_t)level, w.dv, stats,
                                  nullptr, nullptr, M, w.loop_nb},
                     w.loop_ppt, w.sync, t0, t1, st);
+  if (w.floop.blocks > 0 && !stats && t1 - t0 > 1) {
+    const int nb = w.floop.blocks;
+    LoopReg g{w.tm4, w.tmx, nullptr, (double*)inout, w.pose0 + 13 * (size_t)level, w.dv, nullptr, nullptr, nullptr, M, nb};
+    g.xch = reinterpret_cast<unsigned long long*>(w.sync + 64);
+    HIPCHK(launch_fill_i(w.sync, 64 + 2 * (int)loop_words(nb), st));
+    HIPCHK(launch_force_loop(g, w.floop, w.sync, t0, t1, ctx->loop_spins, st));
+    return SGR_OK;
+  }
   const int pm = pmode_of(prm->p);
   auto loop = [&](hipStream_t s) -> int {
     for (int t = t0; t < t1; ++t) {

@@ -341,6 +341,18 @@ struct LoopReg {
   unsigned long long* xch;     // loop_words(nb) words
   int M, nb;
 };
+// All iterations of a small p = 1 registration's all-pairs force in one launch
+// (without statistics): a LoopReg whose S is not read, and the force launch
+// whose chunks it keeps.
+struct ForceLoop {
+  const float4* ref4;
+  const float* lw;
+  int N, n_iblk, n_chunks, gran;
+  int groups, share, blocks;  // shares of the reference, points of the largest, blocks (0: not for this pair)
+};
+ForceLoop force_loop_shape(int M, int N, int n_chunks);
+hipError_t launch_force_loop(const LoopReg& g, const ForceLoop& F, int* ticket, int t0, int t1, int spins,
+                             hipStream_t st);
 int loop_points(int64_t M_total, int n_regs);
 int loop_blocks(int M, int ppt);
 size_t loop_words(int nb);

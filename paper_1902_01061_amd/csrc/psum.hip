@@ -325,8 +325,11 @@ constexpr int LP_BT = 512;
 constexpr int LP_WAVES = LP_BT / 64;
 constexpr int LP_WORDS = 26;  // two tagged words per wrench component
 
-template <int PPT>
-__device__ inline void loop_body(const LoopReg& g, int sub, int t0, int t1, int spins) {
+// The iterations of one block: add(sR, cv, b, wu, v) adds the wrench terms of
+// the thread's points, posed with s R, cv about the centroid b, to v[0, 13)
+// (the energy only with wu), without the factors of G.
+template <class Add>
+__device__ inline void loop_run(const LoopReg& g, int sub, int t0, int t1, int spins, Add&& add) {
   __shared__ double s_part[LP_WAVES][16];
   __shared__ double s_x[LP_MAX_BLOCKS][13];
   __shared__ double s_pose[12];  // s R (9), cv (3)
@@ -335,33 +338,6 @@ __device__ inline void loop_body(const LoopReg& g, int sub, int t0, int t1, int 
   __shared__ int s_dead;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const Derived& D = *g.dv;
-  // this thread's points: coordinates, g S0 and g S1, mass (the offsets from
-  // the centroid are formed again in every iteration, which leaves the update
-  // its registers with 8 points)
-  float x0[PPT], y0[PPT], z0[PPT], mi[PPT];
-  double A0[PPT], Ax[PPT], Ay[PPT], Az[PPT];
-  const int p0 = sub * LP_BT * PPT + tid;
-#pragma unroll
-  for (int u = 0; u < PPT; ++u) {
-    const int ip = p0 + u * LP_BT;
-    x0[u] = y0[u] = z0[u] = mi[u] = 0.f;
-    A0[u] = Ax[u] = Ay[u] = Az[u] = 0.0;
-    if (ip < g.M) {
-      const float4 T = g.tm4[ip];
-      const float2 X = g.tmx[ip];
-      const double* S = g.S + (int64_t)ip * PS_NQ;
-      const double gi = D.g_mode == 1.0 ? (double)X.x / D.abar : 1.0;
-      x0[u] = T.x;
-      y0[u] = T.y;
-      z0[u] = T.z;
-      A0[u] = gi * S[0];
-      Ax[u] = gi * S[1];
-      Ay[u] = gi * S[2];
-      Az[u] = gi * S[3];
-      mi[u] = X.y;
-    }
-  }
-  const double eps2 = D.eps2;
   // s R and cv of the pose in s_u (thread 0)
   auto share_pose = [&]() {
     double sR[9];
@@ -397,42 +373,12 @@ __device__ inline void loop_body(const LoopReg& g, int sub, int t0, int t1, int 
 #pragma unroll
     for (int e = 0; e < 16; ++e) v[e] = 0.0;
     double sR[9], cv[3];
-    const double b0 = D.ybar0[0], b1 = D.ybar0[1], b2 = D.ybar0[2];
+    const double b[3] = {D.ybar0[0], D.ybar0[1], D.ybar0[2]};
 #pragma unroll
     for (int e = 0; e < 9; ++e) sR[e] = s_pose[e];
 #pragma unroll
     for (int r = 0; r < 3; ++r) cv[r] = s_pose[9 + r];
-#pragma unroll
-    for (int k = 0; k < PPT; ++k) {
-      asm volatile("" : "+v"(x0[k]), "+v"(y0[k]), "+v"(z0[k]));  // kept as floats, not hoisted as doubles
-      const double ex = (double)x0[k] - b0, ey = (double)y0[k] - b1, ez = (double)z0[k] - b2;
-      const double px = (double)(float)(sR[0] * ex + sR[1] * ey + sR[2] * ez + cv[0]);
-      const double py = (double)(float)(sR[3] * ex + sR[4] * ey + sR[5] * ez + cv[1]);
-      const double pz = (double)(float)(sR[6] * ex + sR[7] * ey + sR[8] * ez + cv[2]);
-      const double fx = px * A0[k] - Ax[k], fy = py * A0[k] - Ay[k], fz = pz * A0[k] - Az[k];
-      const double cx = px - cv[0], cy = py - cv[1], cz = pz - cv[2];
-      const double m = (double)mi[k];
-      v[WR_F + 0] += m * fx;
-      v[WR_F + 1] += m * fy;
-      v[WR_F + 2] += m * fz;
-      v[WR_K + 0] += fx * cx;
-      v[WR_K + 1] += fx * cy;
-      v[WR_K + 2] += fx * cz;
-      v[WR_K + 3] += fy * cx;
-      v[WR_K + 4] += fy * cy;
-      v[WR_K + 5] += fy * cz;
-      v[WR_K + 6] += fz * cx;
-      v[WR_K + 7] += fz * cy;
-      v[WR_K + 8] += fz * cz;
-      if (wu) {
-        const int ip = p0 + k * LP_BT;
-        if (ip < g.M) {
-          const double gi = D.g_mode == 1.0 ? (double)g.tmx[ip].x / D.abar : 1.0;
-          v[WR_U] += (px * px + py * py + pz * pz + eps2) * A0[k] - 2.0 * (px * Ax[k] + py * Ay[k] + pz * Az[k]) +
-                     gi * g.S[(int64_t)ip * PS_NQ + 4];
-        }
-      }
-    }
+    add(sR, cv, b, wu, v);
     wave_sum_many<16>(v);
     if ((lane & 3) == 0) s_part[wave][lane >> 2] = v[0];
     __syncthreads();
@@ -494,6 +440,73 @@ __device__ inline void loop_body(const LoopReg& g, int sub, int t0, int t1, int 
 }
 
 template <int PPT>
+__device__ inline void loop_body(const LoopReg& g, int sub, int t0, int t1, int spins) {
+  const int tid = threadIdx.x;
+  const Derived& D = *g.dv;
+  // this thread's points: coordinates, g S0 and g S1, mass (the offsets from
+  // the centroid are formed again in every iteration, which leaves the update
+  // its registers with 8 points)
+  float x0[PPT], y0[PPT], z0[PPT], mi[PPT];
+  double A0[PPT], Ax[PPT], Ay[PPT], Az[PPT];
+  const int p0 = sub * LP_BT * PPT + tid;
+#pragma unroll
+  for (int u = 0; u < PPT; ++u) {
+    const int ip = p0 + u * LP_BT;
+    x0[u] = y0[u] = z0[u] = mi[u] = 0.f;
+    A0[u] = Ax[u] = Ay[u] = Az[u] = 0.0;
+    if (ip < g.M) {
+      const float4 T = g.tm4[ip];
+      const float2 X = g.tmx[ip];
+      const double* S = g.S + (int64_t)ip * PS_NQ;
+      const double gi = D.g_mode == 1.0 ? (double)X.x / D.abar : 1.0;
+      x0[u] = T.x;
+      y0[u] = T.y;
+      z0[u] = T.z;
+      A0[u] = gi * S[0];
+      Ax[u] = gi * S[1];
+      Ay[u] = gi * S[2];
+      Az[u] = gi * S[3];
+      mi[u] = X.y;
+    }
+  }
+  const double eps2 = D.eps2;
+  loop_run(g, sub, t0, t1, spins, [&](const double (&sR)[9], const double (&cv)[3], const double (&b)[3], bool wu,
+                                      double (&v)[16]) {
+#pragma unroll
+    for (int k = 0; k < PPT; ++k) {
+      asm volatile("" : "+v"(x0[k]), "+v"(y0[k]), "+v"(z0[k]));  // kept as floats, not hoisted as doubles
+      const double ex = (double)x0[k] - b[0], ey = (double)y0[k] - b[1], ez = (double)z0[k] - b[2];
+      const double px = (double)(float)(sR[0] * ex + sR[1] * ey + sR[2] * ez + cv[0]);
+      const double py = (double)(float)(sR[3] * ex + sR[4] * ey + sR[5] * ez + cv[1]);
+      const double pz = (double)(float)(sR[6] * ex + sR[7] * ey + sR[8] * ez + cv[2]);
+      const double fx = px * A0[k] - Ax[k], fy = py * A0[k] - Ay[k], fz = pz * A0[k] - Az[k];
+      const double cx = px - cv[0], cy = py - cv[1], cz = pz - cv[2];
+      const double m = (double)mi[k];
+      v[WR_F + 0] += m * fx;
+      v[WR_F + 1] += m * fy;
+      v[WR_F + 2] += m * fz;
+      v[WR_K + 0] += fx * cx;
+      v[WR_K + 1] += fx * cy;
+      v[WR_K + 2] += fx * cz;
+      v[WR_K + 3] += fy * cx;
+      v[WR_K + 4] += fy * cy;
+      v[WR_K + 5] += fy * cz;
+      v[WR_K + 6] += fz * cx;
+      v[WR_K + 7] += fz * cy;
+      v[WR_K + 8] += fz * cz;
+      if (wu) {
+        const int ip = p0 + k * LP_BT;
+        if (ip < g.M) {
+          const double gi = D.g_mode == 1.0 ? (double)g.tmx[ip].x / D.abar : 1.0;
+          v[WR_U] += (px * px + py * py + pz * pz + eps2) * A0[k] - 2.0 * (px * Ax[k] + py * Ay[k] + pz * Az[k]) +
+                     gi * g.S[(int64_t)ip * PS_NQ + 4];
+        }
+      }
+    }
+  });
+}
+
+template <int PPT>
 __global__ __launch_bounds__(LP_BT) void pinv_loop_kernel(LoopReg g, int* __restrict__ ticket, int t0, int t1,
                                                           int spins) {
   __shared__ int s_id;
@@ -515,6 +528,131 @@ __global__ __launch_bounds__(LP_BT) void pinv_loop_batch_kernel(const LoopReg* _
   g.tm4 = gptr(g.tm4), g.tmx = gptr(g.tmx), g.S = gptr(g.S), g.pose = gptr(g.pose), g.dv = gptr(g.dv);
   g.pose0 = gptr(g.pose0), g.stats = gptr(g.stats), g.energy = gptr(g.energy), g.xch = gptr(g.xch);
   loop_body<PPT>(g, rb.y, t0, t1, spins);
+}
+
+// ------------------------------------------ iteration loop of small forces
+// The p = 1 force of a small pair, every pair evaluated in every iteration, all
+// iterations in one launch.  With the per-iteration kernels 1 024 points took
+// 10.8 us an iteration (force_kernel 5.5, update_kernel 5.3), of which the
+// pairs are below 1 us; here they take 7.5, bound by the chain of sums,
+// exchange and update.  The reference chunks
+// are force_kernel's, and the FP32 sums of a point over a chunk's tiles are
+// formed in its order with its exponent, so they have its bits; the FP64 sums
+// over chunks and points differ by their rounding.  A block of LP_BT threads
+// has 256 template points twice, each half of it every other chunk of the
+// block's share, which stays in LDS (exponents centred for the block's points)
+// with the point's constants in registers.
+constexpr int FL_PTS = 256;  // force_kernel's block and tile
+constexpr int FL_PAD = 1;     // points of zero weight behind a block's share
+
+__global__ __launch_bounds__(LP_BT) void force_loop_kernel(LoopReg g, ForceLoop F, int* __restrict__ ticket, int t0,
+                                                           int t1, int spins) {
+  extern __shared__ float4 s_ref[];                      // [F.share + FL_PAD]
+  float* s_lw = reinterpret_cast<float*>(s_ref + F.share + FL_PAD);
+  __shared__ double s_red[2 * LP_BT / 64];
+  __shared__ int s_id;
+  if (threadIdx.x == 0) s_id = g.nb > 1 ? atomicAdd(ticket, 1) : 0;
+  __syncthreads();
+  const int sub = s_id, tid = threadIdx.x;
+  const Derived& D = *g.dv;
+  const int iblk = sub % F.n_iblk, grp = sub / F.n_iblk;
+  const int64_t n_sub = (F.N + F.gran - 1) / F.gran;
+  auto chunk0 = [&](int c) { return min(F.N, (int)(c * n_sub / F.n_chunks) * F.gran); };
+  const int c0 = (int)((int64_t)grp * F.n_chunks / F.groups), c1 = (int)((int64_t)(grp + 1) * F.n_chunks / F.groups);
+  const int J0 = chunk0(c0), J1 = chunk0(c1);
+  const int ip = iblk * FL_PTS + tid % FL_PTS;
+  const bool on = ip < g.M;
+  const float4 T = on ? g.tm4[ip] : make_float4(0.f, 0.f, 0.f, 0.f);
+  const float2 TX = on ? g.tmx[ip] : make_float2(0.f, 0.f);
+  const float bi = T.w;
+  float lo = on ? bi : INFINITY, hi = on ? bi : -INFINITY, beta = 0.f;
+  block_range<LP_BT>(lo, hi, s_red);
+  const bool expd = expanded_centre(lo, hi, D, false, beta);
+  const float al = 2.f * (bi - beta);
+  const double dl = (double)(bi - beta);
+  const double gi = D.g_mode == 1.0 ? (double)TX.x / D.abar : 1.0;
+  const double gs = gi * (expd ? exp2(-dl * dl) : 1.0), mi = (double)TX.y;
+  // the chunks' first points within the share (a 64-bit division each)
+  int* s_c = reinterpret_cast<int*>(s_lw + F.share + FL_PAD);  // [F.share / F.gran + 1]
+  for (int c = tid; c <= c1 - c0; c += LP_BT) s_c[c] = chunk0(c0 + c) - J0;
+  for (int j = J0 + tid; j < J1 + FL_PAD; j += LP_BT) {
+    float4 X = make_float4(0.f, 0.f, 0.f, 0.f);  // behind the share: zero weight
+    float l = -INFINITY;
+    if (j < J1) {
+      X = F.ref4[j];
+      l = F.lw[j];
+    }
+    if (expd) {
+      float d = X.w - beta;
+      if (fabsf(d) > 1e18f) d = copysignf(1e18f, d);
+      X.w = d;
+      l = __builtin_fmaf(-d, d, l);
+    }
+    s_ref[j - J0] = X;
+    s_lw[j - J0] = l;
+  }
+  __syncthreads();
+  loop_run(g, sub, t0, t1, spins, [&](const double (&sR)[9], const double (&cv)[3], const double (&b)[3], bool,
+                                      double (&v)[16]) {
+    if (!on) return;  // a block's expanded exponent may overflow for others' b
+    double S0 = 0.0, Sx = 0.0, Sy = 0.0, Sz = 0.0;
+    for (int c = tid / FL_PTS; c < c1 - c0; c += LP_BT / FL_PTS) {
+      const int j1 = s_c[c + 1];
+      for (int base = s_c[c]; base < j1; base += FL_PTS) {
+        const int tn = min(FL_PTS, j1 - base);
+        const float4* X = s_ref + base;
+        const float* L = s_lw + base;
+        float a0 = 0.f, ax = 0.f, ay = 0.f, az = 0.f;
+        if (expd) {
+          // in pairs, as force_kernel adds them; an odd last point (the
+          // reference's) with the zero weight behind it
+#pragma unroll 4
+          for (int jj = 0; jj < tn; jj += 2) {
+            const float4 X0 = X[jj], X1 = X[jj + 1];
+            const float w0 = __builtin_amdgcn_exp2f(__builtin_fmaf(al, X0.w, L[jj]));
+            const float w1 = __builtin_amdgcn_exp2f(__builtin_fmaf(al, X1.w, L[jj + 1]));
+            a0 += w0 + w1;
+            ax = __builtin_fmaf(w0, X0.x, __builtin_fmaf(w1, X1.x, ax));
+            ay = __builtin_fmaf(w0, X0.y, __builtin_fmaf(w1, X1.y, ay));
+            az = __builtin_fmaf(w0, X0.z, __builtin_fmaf(w1, X1.z, az));
+          }
+        } else {
+#pragma unroll 4
+          for (int jj = 0; jj < tn; ++jj) {
+            const float4 P = X[jj];
+            const float db = bi - P.w;
+            const float w = __builtin_amdgcn_exp2f(__builtin_fmaf(-db, db, L[jj]));
+            a0 += w;
+            ax = __builtin_fmaf(w, P.x, ax);
+            ay = __builtin_fmaf(w, P.y, ay);
+            az = __builtin_fmaf(w, P.z, az);
+          }
+        }
+        S0 += (double)a0;
+        Sx += (double)ax;
+        Sy += (double)ay;
+        Sz += (double)az;
+      }
+    }
+    const double ex = (double)T.x - b[0], ey = (double)T.y - b[1], ez = (double)T.z - b[2];
+    const double px = (double)(float)(sR[0] * ex + sR[1] * ey + sR[2] * ez + cv[0]);
+    const double py = (double)(float)(sR[3] * ex + sR[4] * ey + sR[5] * ez + cv[1]);
+    const double pz = (double)(float)(sR[6] * ex + sR[7] * ey + sR[8] * ez + cv[2]);
+    const double fx = gs * (px * S0 - Sx), fy = gs * (py * S0 - Sy), fz = gs * (pz * S0 - Sz);
+    const double cx = px - cv[0], cy = py - cv[1], cz = pz - cv[2];
+    v[WR_F + 0] = mi * fx;
+    v[WR_F + 1] = mi * fy;
+    v[WR_F + 2] = mi * fz;
+    v[WR_K + 0] = fx * cx;
+    v[WR_K + 1] = fx * cy;
+    v[WR_K + 2] = fx * cz;
+    v[WR_K + 3] = fy * cx;
+    v[WR_K + 4] = fy * cy;
+    v[WR_K + 5] = fy * cz;
+    v[WR_K + 6] = fz * cx;
+    v[WR_K + 7] = fz * cy;
+    v[WR_K + 8] = fz * cz;
+  });
 }
 
 }  // namespace
@@ -633,6 +771,39 @@ int loop_blocks(int M, int ppt) {
 }
 
 size_t loop_words(int nb) { return nb > 1 ? (size_t)2 * nb * LP_WORDS : 0; }
+
+// The loop's shape for a force launch of n_chunks reference chunks with one
+// point a lane; blocks 0: it stays with the per-iteration kernels.  The loop
+// has 64 CUs, so its pairs take four times as long: a block's share of the
+// reference is limited to FL_SHARE points.  An iteration in the loop and with
+// the per-iteration kernels, by the share: 64 points 7.5 and 10.8 us, 256
+// 11.8 and 13.6, 512 17.5 and 19.1, 1 024 24.7 and 20.2.
+constexpr int FL_SHARE = 512;
+
+ForceLoop force_loop_shape(int M, int N, int n_chunks) {
+  ForceLoop F{};
+  F.N = N;
+  F.gran = force_chunk_gran();
+  F.n_chunks = n_chunks;
+  F.n_iblk = (M + FL_PTS - 1) / FL_PTS;
+  if (force_points_per_block(1) != FL_PTS || force_tile_j() != FL_PTS || F.n_iblk > LP_MAX_BLOCKS) return F;
+  F.groups = std::min(n_chunks, LP_MAX_BLOCKS / F.n_iblk);
+  const int64_t n_sub = (N + F.gran - 1) / F.gran;
+  for (int q = 0; q < F.groups; ++q) {
+    const int64_t c0 = (int64_t)q * n_chunks / F.groups, c1 = (int64_t)(q + 1) * n_chunks / F.groups;
+    F.share = std::max(F.share, (int)(c1 * n_sub / n_chunks - c0 * n_sub / n_chunks) * F.gran);
+  }
+  F.blocks = F.share <= FL_SHARE ? F.n_iblk * F.groups : 0;
+  return F;
+}
+
+hipError_t launch_force_loop(const LoopReg& g, const ForceLoop& F, int* ticket, int t0, int t1, int spins,
+                             hipStream_t st) {
+  const size_t lds = (size_t)(F.share + FL_PAD) * (sizeof(float4) + sizeof(float)) +
+                     (size_t)(F.share / F.gran + 2) * sizeof(int);
+  hipLaunchKernelGGL(force_loop_kernel, dim3((unsigned)g.nb), dim3(LP_BT), lds, st, g, F, ticket, t0, t1, spins);
+  return hipGetLastError();
+}
 
 hipError_t launch_pinv_loop(const LoopReg& g, int ppt, int* ticket, int t0, int t1, int spins, hipStream_t st) {
   const dim3 grid((unsigned)g.nb), block(LP_BT);
