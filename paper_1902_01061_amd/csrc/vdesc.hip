@@ -19,28 +19,55 @@ namespace {
 
 constexpr int HN_BT = 64;
 
-__global__ __launch_bounds__(256) void normals_kernel(const float* __restrict__ X, const float* __restrict__ Y,
-                                                      const float* __restrict__ Zc, int n, int k,
-                                                      const int32_t* __restrict__ idx, double* __restrict__ nrm) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
+// f(j) for point i's neighbours in list order (itself where the list ends),
+// the coordinates of NB_U of them in flight.
+constexpr int NB_U = 8;
+
+template <class F>
+__device__ inline void each_neighbour(const float* __restrict__ X, const float* __restrict__ Y,
+                                      const float* __restrict__ Zc, int i, int k, const int32_t* __restrict__ nb,
+                                      F&& f) {
+  for (int s = 0; s < k; s += NB_U) {
+    int j[NB_U];
+    float p[NB_U][3];
+#pragma unroll
+    for (int u = 0; u < NB_U; ++u) {
+      j[u] = nb[min(s + u, k - 1)];
+      if (j[u] < 0) j[u] = i;
+    }
+#pragma unroll
+    for (int u = 0; u < NB_U; ++u) {
+      p[u][0] = X[j[u]];
+      p[u][1] = Y[j[u]];
+      p[u][2] = Zc[j[u]];
+    }
+#pragma unroll
+    for (int u = 0; u < NB_U; ++u)
+      if (s + u < k) f(p[u]);
+  }
+}
+
+// Bound by the latency of two rounds of dependent loads (list, coordinates)
+// and of the FP64 eigenvector: one wave per block spreads 36 000 points over
+// all CUs (29 us at k = 24; 37 in blocks of 256 with one load at a time).
+__global__ __launch_bounds__(HN_BT) void normals_kernel(const float* __restrict__ X, const float* __restrict__ Y,
+                                                        const float* __restrict__ Zc, int n, int k,
+                                                        const int32_t* __restrict__ idx, double* __restrict__ nrm) {
+  const int i = blockIdx.x * HN_BT + threadIdx.x;
   if (i >= n) return;
   const int32_t* nb = idx + (int64_t)i * k;
   double m[3] = {0, 0, 0};
-  for (int s = 0; s < k; ++s) {
-    const int j = nb[s] >= 0 ? nb[s] : i;
-    m[0] += (double)X[j];
-    m[1] += (double)Y[j];
-    m[2] += (double)Zc[j];
-  }
+  each_neighbour(X, Y, Zc, i, k, nb, [&](const float (&p)[3]) {
+    for (int c = 0; c < 3; ++c) m[c] += (double)p[c];
+  });
   const double invk = 1.0 / (double)k;
   for (int c = 0; c < 3; ++c) m[c] *= invk;
   double C[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-  for (int s = 0; s < k; ++s) {
-    const int j = nb[s] >= 0 ? nb[s] : i;
-    const double e[3] = {(double)X[j] - m[0], (double)Y[j] - m[1], (double)Zc[j] - m[2]};
+  each_neighbour(X, Y, Zc, i, k, nb, [&](const float (&p)[3]) {
+    const double e[3] = {(double)p[0] - m[0], (double)p[1] - m[1], (double)p[2] - m[2]};
     for (int r = 0; r < 3; ++r)
       for (int c = 0; c < 3; ++c) C[r * 3 + c] += e[r] * e[c];
-  }
+  });
   for (int e = 0; e < 9; ++e) C[e] *= invk;
   double sv[3], u[3][3], v[3][3];
   svd3(C, sv, u, v);
@@ -226,7 +253,8 @@ hipError_t launch_normal_hist(const float* x, const float* y, const float* z, in
   p += ((size_t)n * 24 + 255) & ~(size_t)255;
   hipError_t e = launch_grid_knn(x, y, z, n, k, nullptr, idx, p, st);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(normals_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, x, y, z, n, k, idx, nrm);
+  hipLaunchKernelGGL(normals_kernel, dim3((unsigned)((n + HN_BT - 1) / HN_BT)), dim3(HN_BT), 0, st, x, y, z, n, k, idx,
+                     nrm);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(hist_kernel, dim3((unsigned)((n + HN_BT - 1) / HN_BT)), dim3(HN_BT), 0, st, n, k, D, idx, nrm,

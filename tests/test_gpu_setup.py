@@ -116,3 +116,13 @@ def test_far_rows_in_any_word(sg, ctx, m):
         h = m // 2 + 7
         np.testing.assert_allclose(f, np.concatenate([force(0, h), force(h, m)]), rtol=2e-5,
                                    atol=2e-5 * np.abs(f).max())
+
+
+@pytest.mark.parametrize("n,k", [(9, 9), (63, 8), (64, 24), (65, 7), (129, 17)])
+def test_normal_histograms_at_block_edges(sg, ctx, n, k):
+    """FP32 rounding of the oracle's FP64 histograms: 3e-8 for weights up to
+    one, where the normals are determined."""
+    rng = np.random.default_rng(n)
+    P = np.stack([rng.uniform(-1, 1, n), rng.uniform(-1, 1, n), 0.05 * rng.normal(size=n)], 1).astype(np.float32)
+    h = ctx.descriptors_hn(sg.Cloud(P), k, 5).cpu().numpy()
+    np.testing.assert_allclose(h, O.normal_histograms(P, k, 5)[0], rtol=0, atol=6e-8)
