@@ -406,6 +406,31 @@ __device__ inline void block_sum(double (&v)[NV], double* lds) {
   __syncthreads();
 }
 
+// The same sums with a butterfly for each value, the result valid in thread 0.
+// The r-form force kernel keeps it: with block_sum its pair loop is the same instructions in
+// other registers and took 25.3 instead of 24.0 ms on 250 000 x 307 200.
+template <int NV, int BT>
+__device__ inline void block_sum_each(double (&v)[NV], double* lds) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+#pragma unroll
+  for (int k = 0; k < NV; ++k)
+    for (int off = 32; off > 0; off >>= 1) v[k] += __shfl_xor(v[k], off, 64);
+  if (lane == 0) {
+#pragma unroll
+    for (int k = 0; k < NV; ++k) lds[w * NV + k] = v[k];
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      double s = 0.0;
+      for (int ww = 0; ww < BT / 64; ++ww) s += lds[ww * NV + k];
+      v[k] = s;
+    }
+  }
+  __syncthreads();
+}
+
 // Elements t, t + 1024, ... below n in that order, as thread t of a block of
 // 1024 visits them, U loads in flight: use(load(i)) for each.
 template <int U, class Load, class Use>

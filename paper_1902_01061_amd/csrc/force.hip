@@ -669,7 +669,10 @@ __device__ inline void force_block(const ForceArgs& A, int iblk, int j0, int j1,
       fp[2] = fz;
     }
   }
-  block_sum<13, F_BT>(w, s_red);
+  if constexpr (MOM)
+    block_sum<13, F_BT>(w, s_red);
+  else
+    block_sum_each<13, F_BT>(w, s_red);
   if (threadIdx.x == 0) {
     double* o = A.wpart + (int64_t)slot * WR_STRIDE;
 #pragma unroll
