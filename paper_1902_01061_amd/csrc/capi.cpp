@@ -33,7 +33,8 @@ static int fail(int code, const std::string& msg) {
 
 struct GraphCache {
   std::vector<uint8_t> key;
-  std::vector<uint8_t> seen;  // key of the last call that ran without a graph
+  std::vector<uint8_t> seen;  // key of the last calls that ran without a graph
+  int times = 0;              // how many they were in a row
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
 };
@@ -215,17 +216,16 @@ hipError_t run_force(ForceArgs A, const Tiles& T, const FLaunch& L, int pm, bool
 size_t pad_n(int64_t N) { return (size_t)((N + 255) / 256) * 256; }
 
 // Runs `loop` (which launches on the given stream): from the cached graph if
-// that was made for the same key, else directly, and as a new graph once a
-// key comes the second time in a row.  A capture costs more than it saves on
-// one run: 100 iterations at 1 024 points take 1 593 us with a capture, 1 331
-// launched directly and 1 266 from a graph that exists.
+// that was made for the same key, else directly, and as a new graph when a
+// key comes the fourth time in a row.  A capture costs what four runs from
+// its graph save: 100 iterations at 1 024 points take 1 593 us with a capture,
+// 1 331 launched directly and 1 266 from a graph that exists.
 template <class F>
 int run_graph(sgr_ctx* ctx, GraphCache& gc, const std::vector<uint8_t>& key, F&& loop, hipStream_t st) {
   if (!gc.exec || key != gc.key) {
-    if (key != gc.seen) {
-      gc.seen = key;
-      return loop(st);
-    }
+    gc.times = key == gc.seen ? gc.times + 1 : 1;
+    gc.seen = key;
+    if (gc.times < 4) return loop(st);
     if (gc.exec) (void)hipGraphExecDestroy(gc.exec);
     if (gc.graph) (void)hipGraphDestroy(gc.graph);
     gc.exec = nullptr;

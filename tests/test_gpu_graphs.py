@@ -1,4 +1,4 @@
-"""The first call with new inputs runs its iterations directly, the second in
+"""The first calls with new inputs run their iterations directly, the fourth in
 a row captures them, later ones replay: all give the same bits, also when two
 inputs alternate and when the inputs change behind the same addresses."""
 import numpy as np
@@ -49,10 +49,10 @@ def test_direct_captured_and_replayed_runs_agree(sg, kind):
             other.close()
 
     want = [fresh(0), fresh(1)]
-    for i in (0, 0, 0, 0, 1, 0, 1, 1, 1, 0, 0):
+    for i in (0, 0, 0, 0, 0, 1, 0, 1, 1, 1, 1, 1, 0, 0):
         assert torch.equal(run(i), want[i]), i
     pairs[0][0].soa.copy_(_cloud(sg, pairs[0][0].n, 99).soa)      # the same addresses, other points
     want[0] = fresh(0)
-    for _ in range(3):
+    for _ in range(6):
         assert torch.equal(run(0), want[0])
     ctx.close()
