@@ -51,7 +51,7 @@ struct sgr_ctx {
   std::vector<GraphCache> gcp;  // pyramidal schedule, one per level
   GraphCache gcv;  // vector descriptors
   TileTable tiles;
-  int loop_spins = 2000000;  // polls before the one-launch loop gives up (about 2 s)
+  int loop_spins = 200000;  // polls before the one-launch loop gives up (about 0.2 s)
 };
 
 namespace {
