@@ -38,18 +38,10 @@
 #include <vector>
 
 #include "common.h"
+#include "grid_geom.h"
 #include "launch.h"
 
 namespace sgr {
-
-struct GridInfo {
-  float lo[3];
-  float h;
-  double inv_h;
-  int dims[3];
-  int ncells;
-  double ext[3];  // bounding-box extents (for re-sizing the cells)
-};
 
 // Workspace and arrays of one cloud's search.
 struct GridJob {
@@ -106,94 +98,11 @@ __device__ inline GridJob job_at(const GridArgs& A, int c) {
 }
 
 // ------------------------------------------------------------------- grid
-// Cell counts per axis for cell size h, grown by 10 % steps until the grid
-// has at most max_cells cells.
-__device__ inline void grid_dims(GridInfo& G, double h, int max_cells) {
-  int d[3];
-  for (int it = 0; it < 400; ++it) {
-    const double ih = 1.0 / h;
-    long long tot = 1;
-    for (int a = 0; a < 3; ++a) {
-      d[a] = (int)fmin(1024.0, floor(G.ext[a] * ih) + 1.0);
-      tot *= d[a];
-    }
-    if (tot <= max_cells) break;
-    h *= 1.1;
-  }
-  G.h = (float)h;
-  G.inv_h = 1.0 / (double)G.h;
-  for (int a = 0; a < 3; ++a) G.dims[a] = d[a];
-  G.ncells = d[0] * d[1] * d[2];
-}
-
-// Trial grid from the box of the finite points (lo > hi: none): about two
-// points per cell of the bounding volume; flat or linear clouds fall back to
-// their non-degenerate extents.
-__device__ inline GridInfo grid_trial(const float box[6], int n, int max_cells) {
-  GridInfo G;
-  double e[3];
-  for (int a = 0; a < 3; ++a) {
-    const bool any = box[a] <= box[3 + a];  // some finite point
-    G.lo[a] = any ? box[a] : 0.f;
-    e[a] = any ? (double)box[3 + a] - (double)box[a] : 0.0;
-    G.ext[a] = e[a];
-  }
-  const double hi = fmax(e[0], fmax(e[1], e[2])), lo = fmin(e[0], fmin(e[1], e[2]));
-  const double mid = fmax(fmin(e[0], e[1]), fmin(fmax(e[0], e[1]), e[2]));
-  const double rho = 2.0;
-  double h;
-  if (lo > 1e-6 * hi)
-    h = cbrt(hi * mid * lo * rho / n);
-  else if (mid > 1e-6 * hi)
-    h = sqrt(hi * mid * rho / n);
-  else
-    h = hi * rho / n;
-  if (!(h > 0) || !isfinite(h)) h = 1.0;
-  grid_dims(G, h, max_cells);
-  return G;
-}
-
-// Final cell size from the trial grid's occupancy mu, the mean over the
-// points of their cell's count.  Scans are surfaces, whose counts go with the
-// side squared; a cloud with fewer points per cell than wanted is taken as a
-// volume.
-// A search for points within `reach` settles every query in its 27 cells
-// when they are that large.
-__device__ inline void grid_resize(GridInfo& G, double mu, const GridJob& J) {
-  const double f = (double)J.occ / mu;
-  grid_dims(G, (double)G.h * (f < 1.0 ? sqrt(f) : cbrt(f)), J.max_cells);
-  if (G.h < J.reach && J.reach <= 2.f * G.h) grid_dims(G, (double)J.reach, J.max_cells);
-}
-
 // Wanted occupancy for k neighbours.  Counted over surfaces of even
 // density, a query of occupancy 0.45 k finds twice k points within the distance its 27 cells
 // cover, among five times k candidates, and one in fifty finds fewer than k;
 // at 0.3 k it is one in four, at 0.7 k the candidates are nine times k.
 inline float grid_occ(int k) { return std::max(2.0f, 0.5f * (float)k); }
-
-// Cell coordinates and cell faces are computed in FP64 so that rounding
-// cannot move a point across a face by more than a negligible fraction of a
-// cell, whatever the offset of the cloud from the origin.
-__device__ inline int cell_coord(float p, float lo, double inv_h, int dim) {
-  const double u = floor(((double)p - (double)lo) * inv_h);
-  return u < 0.0 ? 0 : (u >= (double)dim ? dim - 1 : (int)u);
-}
-
-__device__ inline int cell_index(const GridInfo& G, const int c[3]) {
-  return (c[2] * G.dims[1] + c[1]) * G.dims[0] + c[0];
-}
-__device__ inline void cell_of_point(const GridInfo& G, float x, float y, float z, int c[3]) {
-  c[0] = cell_coord(x, G.lo[0], G.inv_h, G.dims[0]);
-  c[1] = cell_coord(y, G.lo[1], G.inv_h, G.dims[1]);
-  c[2] = cell_coord(z, G.lo[2], G.inv_h, G.dims[2]);
-}
-__device__ inline int cell_index(const GridInfo& G, float x, float y, float z) {
-  int c[3];
-  cell_of_point(G, x, y, z, c);
-  return cell_index(G, c);
-}
-// At most 1024 cells per axis.
-__device__ inline int pack_cell(const int c[3]) { return c[0] | c[1] << 10 | c[2] << 20; }
 
 // Box of the finite points among the block's (points base + tid, stride):
 // an infinite coordinate would make the grid one row of cells.
@@ -251,10 +160,6 @@ __device__ inline int block_scan(int v, int& total, int* lds) {
   return before + x - v;
 }
 
-// Blocks of BLK^3 cells, listed where they hold points: what a query far from
-// everything looks at instead of the cells between.
-constexpr int BLK = 8;
-
 // Lists block number b of the grid (wave-uniform) if it holds points; lane l
 // looks at one of its BLK^2 rows of cells.  start(c): first point of cell c.
 template <class Start>
@@ -270,10 +175,6 @@ __device__ inline void list_block(const GridInfo& G, int b, int* blocks, Start&&
   }
   if (__any(any) && lane == 0) blocks[1 + atomicAdd(blocks, 1)] = pack_cell(bc);
 }
-__device__ inline int block_count(const GridInfo& G) {
-  return ((G.dims[0] + BLK - 1) / BLK) * ((G.dims[1] + BLK - 1) / BLK) * ((G.dims[2] + BLK - 1) / BLK);
-}
-
 // Whole grid of one cloud in one block, its cells in LDS as 16-bit halves (so
 // n <= 65 535): one launch and no global atomics where the points are few
 // (the phases of the large build are launches of 3 to 5 us each, whatever the
@@ -318,7 +219,7 @@ __global__ __launch_bounds__(SM_BT) void grid_small_kernel(GridArgs A, int2* __r
     }
     block_sum<1, SM_BT>(sq, s_red);
     if (tid == 0) {
-      grid_resize(s_g, sq[0] / (double)J.n, J);
+      grid_resize(s_g, sq[0] / (double)J.n, J.occ, J.reach, J.max_cells);
       *J.gi = s_g;
     }
     __syncthreads();
@@ -470,7 +371,7 @@ __global__ __launch_bounds__(LG_BT) void grid_count_kernel(GridJob J) {
       sq += s_box[2 * w + 1];
     }
     GridInfo G = grid_trial(box, J.n, J.max_cells);
-    if (pts > 0.f) grid_resize(G, (double)sq / (double)pts, J);
+    if (pts > 0.f) grid_resize(G, (double)sq / (double)pts, J.occ, J.reach, J.max_cells);
     s_g = G;
     if (blockIdx.x == 0) *J.gi = G;
   }
@@ -555,8 +456,6 @@ __global__ __launch_bounds__(LG_BT) void grid_scatter_kernel(GridJob J, int poin
 }
 
 // ----------------------------------------------------------------- search
-__device__ inline float key_of(uint64_t w) { return __uint_as_float((uint32_t)(w >> 32)); }
-
 // Keys are (float32 distance bits << 32 | index): for distances >= 0 the bit
 // pattern orders like the value, so one unsigned compare gives the (distance,
 // index) order.
@@ -572,45 +471,6 @@ __device__ inline uint64_t point_key_fused(const float4& P, const float4& q) {
   const float d2 = __builtin_fmaf(ez, ez, __builtin_fmaf(ex, ex, __fmul_rn(ey, ey)));
   return ((uint64_t)__float_as_uint(d2) << 32) | (uint32_t)__float_as_int(P.w);
 }
-constexpr uint64_t KEY_INF = 0x7f800000ull << 32;  // no key of a finite distance reaches it
-
-// A query's place in the grid: its cell and its position in it in cell units,
-// formed in FP64 (in [0, 1) inside the grid; beyond it for a query outside,
-// whose cell is the nearest).  Distances in cell units below are floats with
-// a margin of 1e-3 of a cell, which covers their rounding and that of the
-// cells, and 2e-5 relative for the float32 key.
-struct Place {
-  int c[3];
-  float fr[3];
-
-  __device__ void set(const GridInfo& G, const float4& q) {
-    const float qv[3] = {q.x, q.y, q.z};
-#pragma unroll
-    for (int a = 0; a < 3; ++a) fr[a] = (float)(((double)qv[a] - (double)G.lo[a]) * G.inv_h - (double)c[a]);
-  }
-  // distance to the slab of cells d beyond the query's along axis a
-  __device__ float gap(int a, int d) const {
-    return fmaxf(0.f, fmaxf((float)d - fr[a], fr[a] - (float)(d + 1)) - 1e-3f);
-  }
-};
-
-// Whole cells in a distance along a row, which has at most 1024.
-__device__ inline int cell_step(float d) { return (int)floorf(fminf(4096.f, fmaxf(-4096.f, d))); }
-
-// Keys below this bound belong to points nearer than every cell outside the
-// cube of radius r around the query's; KEY_INF when no cell lies outside it.
-__device__ inline uint64_t cube_bound(const GridInfo& G, const Place& at, int r) {
-  float lb = INFINITY;
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    if (at.c[a] - r > 0) lb = fminf(lb, at.fr[a] + (float)r);
-    if (at.c[a] + r < G.dims[a] - 1) lb = fminf(lb, 1.f - at.fr[a] + (float)r);
-  }
-  if (lb == INFINITY) return KEY_INF;
-  const float d = fmaxf(0.f, lb - 1e-3f) * G.h;
-  return (uint64_t)__float_as_uint(d * d * (1.f - 2e-5f)) << 32;
-}
-
 // LDS written by some lanes of a wave is read by others of the same wave.
 __device__ inline void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -889,22 +749,15 @@ __device__ inline int visit(const GridJob& J, const GridInfo& G, const Place& at
       if (dy >= side) dy -= side, ++dz;
       dz -= R;
       dy -= R;
-      const int cz = at.c[2] + dz, cy = at.c[1] + dy, cx = at.c[0];
-      if (i < rows && cz >= 0 && cz < G.dims[2] && cy >= 0 && cy < G.dims[1]) {
-        const float gy = at.gap(1, dy), gz = at.gap(2, dz);
-        const float left = reach2 - (gy * gy + gz * gz);
-        if (!(left < 0.f)) {
-          // cells of the row within sqrt(left) of the query
-          const float reach = sqrtf(left) * 1.0001f + 2e-3f;
-          const int xl = max(max(0, cx - R), min(cx, cx + cell_step(at.fr[0] - reach)));
-          const int xr = min(min(G.dims[0] - 1, cx + R), max(cx, cx + cell_step(at.fr[0] + reach)));
-          const int* st = J.starts + (cz * G.dims[1] + cy) * G.dims[0];
-          if (max(abs(dy), abs(dz)) > inner) {
-            a[v] = make_int2(st[xl], st[xr + 1]);
-          } else {
-            if (xl < cx - inner) a[v] = make_int2(st[xl], st[cx - inner]);
-            if (xr > cx + inner) b[v] = make_int2(st[cx + inner + 1], st[xr + 1]);
-          }
+      int xl, xr;
+      if (i < rows && row_cells(G, at, R, dy, dz, reach2, xl, xr)) {
+        const int cx = at.c[0];
+        const int* st = J.starts + ((at.c[2] + dz) * G.dims[1] + at.c[1] + dy) * G.dims[0];
+        if (max(abs(dy), abs(dz)) > inner) {
+          a[v] = make_int2(st[xl], st[xr + 1]);
+        } else {
+          if (xl < cx - inner) a[v] = make_int2(st[xl], st[cx - inner]);
+          if (xr > cx + inner) b[v] = make_int2(st[cx + inner + 1], st[xr + 1]);
         }
       }
     }
@@ -912,20 +765,6 @@ __device__ inline int visit(const GridJob& J, const GridInfo& G, const Place& at
     for (int v = 0; v < RU; ++v) seen += take_spans<GL, U>(J, a[v], b[v], q, L, s_seg);
   }
   return group_sum<GL>(seen);
-}
-
-// Radius of the smallest cube of cells around the query's outside of which no
-// key below the bound lies.
-__device__ inline int cells_reached(const GridInfo& G, const Place& at, uint64_t bound, int rmax) {
-  const float u = sqrtf(key_of(bound)) * (float)G.inv_h * 1.0001f + 2e-3f;
-  if (!(u < 1e9f)) return rmax;
-  float r = 0.f;
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    if (at.c[a] > 0) r = fmaxf(r, -floorf(at.fr[a] - u));
-    if (at.c[a] < G.dims[a] - 1) r = fmaxf(r, floorf(at.fr[a] + u));
-  }
-  return r < (float)rmax ? (int)r : rmax;
 }
 
 // Every key below the sink's bound, by the listed blocks of cells: a wave
@@ -936,41 +775,24 @@ __device__ inline void visit_blocks(const GridJob& J, const GridInfo& G, const P
                                     int2* s_seg) {
   const int lane = threadIdx.x & 63;
   const float inv_h2 = (float)G.inv_h * (float)G.inv_h * (1.f + 2e-5f);
-  // squared distance (cell units, never too large) to block bc
-  auto block_gap = [&](int pb) {
+  auto gap_of = [&](int pb) {
     const int bc[3] = {pb & 1023, (pb >> 10) & 1023, pb >> 20};
-    float g2 = 0.f;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const float d = (float)(bc[a] * BLK - at.c[a]);
-      const float g = fmaxf(0.f, fmaxf(d - at.fr[a], at.fr[a] - (d + (float)BLK)) - 1e-3f);
-      g2 += g * g;
-    }
-    return g2;
+    return block_gap(at, bc);
   };
   auto visit_block = [&](int pb) {
-    const int dy = (pb >> 10 & 1023) * BLK + lane % BLK - at.c[1], dz = (pb >> 20) * BLK + lane / BLK - at.c[2];
-    const int cy = at.c[1] + dy, cz = at.c[2] + dz, x0 = (pb & 1023) * BLK;
+    const int bc[3] = {pb & 1023, (pb >> 10) & 1023, pb >> 20};
     int2 a = make_int2(0, 0);
-    if (cy < G.dims[1] && cz < G.dims[2]) {
-      const float gy = at.gap(1, dy), gz = at.gap(2, dz);
-      const float left = key_of(L.bound) * inv_h2 - (gy * gy + gz * gz);
-      if (!(left < 0.f)) {
-        const float reach = sqrtf(left) * 1.0001f + 2e-3f;
-        const int xl = max(x0, at.c[0] + cell_step(at.fr[0] - reach));
-        const int xr = min(min(G.dims[0], x0 + BLK) - 1, at.c[0] + cell_step(at.fr[0] + reach));
-        if (xl <= xr) {
-          const int* st = J.starts + (cz * G.dims[1] + cy) * G.dims[0];
-          a = make_int2(st[xl], st[xr + 1]);
-        }
-      }
+    int cy, cz, xl, xr;
+    if (block_row_cells(G, at, bc, lane, key_of(L.bound) * inv_h2, cy, cz, xl, xr)) {
+      const int* st = J.starts + (cz * G.dims[1] + cy) * G.dims[0];
+      a = make_int2(st[xl], st[xr + 1]);
     }
     take_spans<64, U>(J, a, make_int2(0, 0), q, L, s_seg);
   };
   const int nb = J.blocks[0];
   uint64_t best = ~0ull;
   for (int i = lane; i < nb; i += 64)
-    best = min(best, (uint64_t)__float_as_uint(block_gap(J.blocks[1 + i])) << 32 | (unsigned)i);
+    best = min(best, (uint64_t)__float_as_uint(gap_of(J.blocks[1 + i])) << 32 | (unsigned)i);
   for (int off = 32; off > 0; off >>= 1) best = min(best, (uint64_t)__shfl_xor((unsigned long long)best, off, 64));
   const int first = nb > 0 ? (int)(unsigned)best : -1;
   if (first < 0) return;
@@ -979,7 +801,7 @@ __device__ inline void visit_blocks(const GridJob& J, const GridInfo& G, const P
   for (int i0 = 0; i0 < nb; i0 += 64) {
     const int i = i0 + lane;
     const int pb = J.blocks[1 + min(i, nb - 1)];
-    const float g2 = block_gap(pb);
+    const float g2 = gap_of(pb);
     bool want = i < nb && i != first;
     for (;;) {
       const uint64_t m = __ballot(want && !(g2 > key_of(L.bound) * inv_h2));
