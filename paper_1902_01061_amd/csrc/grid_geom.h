@@ -76,7 +76,9 @@ SGR_HD void grid_resize(GridInfo& G, double mu, float occ, float reach, int max_
 
 // Cell coordinates and cell faces are computed in FP64 so that rounding
 // cannot move a point across a face by more than a negligible fraction of a
-// cell, whatever the offset of the cloud from the origin.
+// cell, whatever the offset of the cloud from the origin.  The last cell of an
+// axis holds every point beyond it: a cloud longer than 1024 cells of the
+// wanted size keeps that many, and its last cell is as deep as the rest of it.
 SGR_HD int cell_coord(float p, float lo, double inv_h, int dim) {
   const double u = floor(((double)p - (double)lo) * inv_h);
   return u < 0.0 ? 0 : (u >= (double)dim ? dim - 1 : (int)u);
@@ -105,22 +107,36 @@ SGR_HD float key_of(uint64_t w) { return __builtin_bit_cast(float, (uint32_t)(w 
 constexpr uint64_t KEY_INF = 0x7f800000ull << 32;  // no key of a finite distance reaches it
 
 // A query's place in the grid: its cell and its position in it in cell units,
-// formed in FP64 (in [0, 1) inside the grid; beyond it for a query outside,
-// whose cell is the nearest).  Distances in cell units below are floats with
-// a margin of 1e-3 of a cell, which covers their rounding and that of the
-// cells, and 2e-5 relative for the float32 key.
+// formed in FP64 (in [0, 1) inside the grid, from 0 up in the last cell; beyond
+// it for a query outside, whose cell is the nearest).  Distances in cell units
+// below are floats with a margin of 1e-3 of a cell, which covers their rounding
+// and that of the cells, and 2e-5 relative for the float32 key.
 struct Place {
   int c[3];
   float fr[3];
+  float up[3];  // fr as seen from the upper faces of cells: the last cell has none below the points
 
   SGR_HD void set(const GridInfo& G, const float4& q) {
     const float qv[3] = {q.x, q.y, q.z};
 #pragma unroll
-    for (int a = 0; a < 3; ++a) fr[a] = (float)(((double)qv[a] - (double)G.lo[a]) * G.inv_h - (double)c[a]);
+    for (int a = 0; a < 3; ++a) {
+      fr[a] = (float)(((double)qv[a] - (double)G.lo[a]) * G.inv_h - (double)c[a]);
+      up[a] = fminf(fr[a], 1.f);
+    }
   }
-  // distance to the slab of cells d beyond the query's along axis a
-  SGR_HD float gap(int a, int d) const {
-    return fmaxf(0.f, fmaxf((float)d - fr[a], fr[a] - (float)(d + 1)) - 1e-3f);
+  // After set(), for a query that may lie above the points' box (and the cells):
+  // as far above its cell as above these.
+  SGR_HD void set_above(const GridInfo& G, const float4& q) {
+    const float qv[3] = {q.x, q.y, q.z};
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const double above = ((double)qv[a] - (double)G.lo[a]) * G.inv_h - fmax((double)G.dims[a], G.ext[a] * G.inv_h);
+      if (above > 0.0) up[a] = 1.f + (float)above;
+    }
+  }
+  // distance to the slabs of cells [d, d + n) beyond the query's along axis a
+  SGR_HD float gap(int a, int d, int n = 1) const {
+    return fmaxf(0.f, fmaxf((float)d - fr[a], up[a] - (float)(d + n)) - 1e-3f);
   }
 };
 
@@ -184,8 +200,7 @@ SGR_HDI float block_gap(const Place& at, const int bc[3]) {
   float g2 = 0.f;
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    const float d = (float)(bc[a] * BLK - at.c[a]);
-    const float g = fmaxf(0.f, fmaxf(d - at.fr[a], at.fr[a] - (d + (float)BLK)) - 1e-3f);
+    const float g = at.gap(a, bc[a] * BLK - at.c[a], BLK);
     g2 += g * g;
   }
   return g2;
@@ -203,7 +218,7 @@ SGR_HDI bool block_row_cells(const GridInfo& G, const Place& at, const int bc[3]
   const float left = reach2 - (gy * gy + gz * gz);
   if (left < 0.f) return false;
   const float reach = sqrtf(left) * 1.0001f + 2e-3f;
-  xl = max2(x0, at.c[0] + cell_step(at.fr[0] - reach));
+  xl = max2(x0, at.c[0] + cell_step(at.up[0] - reach));
   xr = min2(min2(G.dims[0], x0 + BLK) - 1, at.c[0] + cell_step(at.fr[0] + reach));
   return xl <= xr;
 }

@@ -1361,6 +1361,7 @@ __global__ __launch_bounds__(KN_BT) void nearest_far_kernel(GridJob J, const flo
     Place at;
     cell_of_point(G, q.x, q.y, q.z, at.c);
     at.set(G, q);
+    at.set_above(G, q);
     Nearest<64, FUSED> N{KEY_INF, ((uint64_t)__float_as_uint(max_key) << 32) | 0xffffffffu};
     const int first = max(0, min(J.starts[cell_index(G, at.c)] - 32, J.n - 64));
     N.add(N.key_at(J.spts[min(first + lane, J.n - 1)], q), true);

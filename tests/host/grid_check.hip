@@ -193,6 +193,7 @@ static int nearest(const Grid& g, const float4& q, float max_key) {
     R = R == 0 ? 1 : want;
   }
   if (!found) {
+    s.at.set_above(g.G, q);
     const int n = (int)g.pts.size(), first = std::max(0, std::min(g.starts[cell_index(g.G, s.at.c)] - 32, n - 64));
     s.list.clear();
     s.bound = top;

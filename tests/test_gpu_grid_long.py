@@ -1,0 +1,77 @@
+"""Neighbour lists, nearest points and residuals of clouds longer than the
+grid's 1 024 cells along an axis, whose last cell there holds everything beyond:
+a stray point on each of the six sides, and a pipe and a strip along each axis,
+exactly as brute force gives them (FP32 keys, ties by index)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ref as O
+from test_gpu_grid import _nearest, _surface
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sg():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1902_01061_amd as sg
+    return sg
+
+
+@pytest.fixture(scope="module")
+def ctx(sg):
+    c = sg.Context(0)
+    yield c
+    c.close()
+
+
+def _cloud(kind, axis, side, n):
+    rng = np.random.default_rng(2)
+    if kind == "stray point":
+        P = _surface(n, 1)
+        P[17] = 0
+        P[17, axis] = side * 500
+        return P
+    if kind == "pipe":                 # 1 000 long, radius 0.5
+        f = rng.uniform(0, 2 * np.pi, n)
+        P = np.stack([rng.uniform(0, 1000, n), 0.5 * np.cos(f), 0.5 * np.sin(f)], 1)
+    else:                              # a strip 300 x 1
+        P = np.stack([rng.uniform(0, 300, n), rng.uniform(0, 1, n), rng.normal(size=n) * 1e-3], 1)
+    return np.roll(P, axis, axis=1).astype(np.float32)
+
+
+LONG = [("stray point", a, s) for a in range(3) for s in (1, -1)] + [(k, a, 1) for k in ("pipe", "strip") for a in range(3)]
+
+
+@pytest.mark.parametrize("kind,axis,side", LONG)
+@pytest.mark.parametrize("n", [6000, 20000])      # a grid built by one block, and by many
+def test_lists(sg, ctx, kind, axis, side, n):
+    P, k = _cloud(kind, axis, side, n), 16
+    q = np.unique(np.r_[np.arange(0, n, n // 400), 17])
+    assert np.array_equal(ctx.knn(sg.Cloud(P), k).cpu().numpy()[q], O.knn_c(P, k, q))
+    _, idx = ctx.descriptors_batch([sg.Cloud(P)], k, want_idx=True)
+    assert np.array_equal(idx[0].cpu().numpy()[q], O.knn_c(P, k, q))
+
+
+@pytest.mark.parametrize("kind,axis,side", LONG)
+@pytest.mark.parametrize("n", [6000, 20000])
+def test_nearest_points_and_residual(sg, ctx, kind, axis, side, n):
+    """The residual is the FP64 mean over the points that brute force picks:
+    1e-12 for sums of 700 squares of identically posed points."""
+    X = _cloud(kind, axis, side, n)
+    rng = np.random.default_rng(3)
+    near = X[::n // 500]
+    Y = np.concatenate([near + rng.normal(size=near.shape) * 0.01, near[::5] * 1.02,
+                        rng.normal(size=(100, 3)) * 400]).astype(np.float32)
+    zero = torch.zeros(len(Y), device="cuda"), torch.zeros(n, device="cuda")
+    want, keys = _nearest(Y, X)
+    for tau in (0.05, 1e18):
+        _, nn, key = ctx.change_detect(sg.Cloud(Y), zero[0], sg.Cloud(X), zero[1], sg.pose_identity(), tau)
+        hit = keys <= np.float32(tau) * np.float32(tau)
+        assert np.array_equal(nn.cpu().numpy(), np.where(hit, want, -1))
+        assert np.array_equal(key.cpu().numpy()[hit], keys[hit])
+    nn, _ = _nearest(Y, X, fused=True)
+    rmse = np.sqrt(((Y.astype(np.float64) - X[nn].astype(np.float64)) ** 2).sum(1).mean())
+    assert ctx.residual(sg.Cloud(Y), sg.Cloud(X), sg.pose_identity()).item() == pytest.approx(rmse, rel=1e-12)

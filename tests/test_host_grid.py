@@ -54,6 +54,50 @@ def _surface(n, seed):
     return (u * [1.0, 0.7, 0.4] + rng.normal(size=(n, 3)) * 0.002).astype(np.float32)
 
 
+def _long(kind, n, axis, seed):
+    """A pipe 1 000 long of radius 0.5, or a strip 300 x 1, along an axis."""
+    rng = np.random.default_rng(seed)
+    if kind == "pipe":
+        f = rng.uniform(0, 2 * np.pi, n)
+        P = np.stack([rng.uniform(0, 1000, n), 0.5 * np.cos(f), 0.5 * np.sin(f)], 1)
+    else:
+        P = np.stack([rng.uniform(0, 300, n), rng.uniform(0, 1, n), rng.normal(size=n) * 1e-3], 1)
+    return np.roll(P, axis, axis=1).astype(np.float32)
+
+
+def _cloud(kind, axis, side):
+    if kind == "stray point":
+        P = _surface(20000, 1)
+        P[17] = 0
+        P[17, axis] = side * 500
+        return P
+    return _long(kind, 6000, axis, 2)
+
+
+# An axis of more than 1 024 cells of the wanted size keeps 1 024: its last cell
+# holds everything beyond.
+LONG = [("stray point", a, s) for a in range(3) for s in (1, -1)] + \
+       [(kind, a, 1) for kind in ("pipe", "strip") for a in range(3)]
+
+
+@pytest.mark.parametrize("kind,axis,side", LONG)
+def test_lists_of_clouds_longer_than_the_grid(search, kind, axis, side):
+    P = _cloud(kind, axis, side)
+    k, step = 16, len(P) // 250
+    assert np.array_equal(search("knn", P, k, step).reshape(-1, k), _lists(P, k, step))
+
+
+@pytest.mark.parametrize("kind,axis,side", LONG)
+@pytest.mark.parametrize("tau", [0.05, 1e18])
+def test_nearest_points_of_clouds_longer_than_the_grid(search, kind, axis, side, tau):
+    P = _cloud(kind, axis, side)
+    rng = np.random.default_rng(3)
+    near = P[::len(P) // 200]
+    Q = np.concatenate([near + rng.normal(size=near.shape) * 0.01, near[::5] * 1.02,
+                        rng.normal(size=(40, 3)) * 400]).astype(np.float32)
+    assert np.array_equal(search("nn", P, len(Q), tau, Q), _nearest(P, Q, tau))
+
+
 @pytest.mark.parametrize("n", [1, 40, 3000, 9000])
 def test_ordinary_clouds(search, n):
     P = _surface(n, n)
