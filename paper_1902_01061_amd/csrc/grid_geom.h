@@ -16,9 +16,11 @@ struct GridInfo {
 };
 
 // Cell counts per axis for cell size h, grown by 10 % steps until the grid
-// has at most max_cells cells.
+// has at most max_cells cells.  No cell is so small that its square, or a key
+// of that size, underflows in FP32.
 SGR_HD void grid_dims(GridInfo& G, double h, int max_cells) {
   int d[3];
+  h = fmax(h, 1e-18);
   for (int it = 0; it < 400; ++it) {
     const double ih = 1.0 / h;
     long long tot = 1;
@@ -184,6 +186,20 @@ SGR_HD int cells_reached(const GridInfo& G, const Place& at, uint64_t bound, int
     if (at.c[a] < G.dims[a] - 1) r = fmaxf(r, floorf(at.fr[a] + u));
   }
   return r < (float)rmax ? (int)r : rmax;
+}
+
+// A search around a query that is widened until it has found enough: all keys
+// below reach2, which starts above 0 (the square of a cell may have underflowed)
+// and grows 2.5 times a turn, so that it ends at the latest when it reaches the
+// whole grid (last).  Returns the radius of its cube of cells.
+SGR_HD float widen_first(uint64_t edge) { return fmaxf(2.f * key_of(edge), 1.1754944e-38f); }
+constexpr float WIDEN = 2.5f;
+SGR_HD int widen(const GridInfo& G, const Place& at, float reach2, int rmax, uint64_t& bound, bool& last) {
+  bound = (uint64_t)__builtin_bit_cast(uint32_t, reach2) << 32;
+  const int R = cells_reached(G, at, bound, rmax);
+  last = R >= rmax;
+  if (last) bound = KEY_INF;
+  return R;
 }
 
 // Blocks of BLK^3 cells, listed where they hold points: what a query far from

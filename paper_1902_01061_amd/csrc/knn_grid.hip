@@ -969,15 +969,12 @@ __global__ __launch_bounds__(KN_BT) void knn_far_kernel(GridArgs A, int k, const
     // fewer than k keys below the cube's bound: all keys below twice that
     // distance squared, then five times, ...
     QueryList L{sh.g.key + grp * KN_STRIDE, 0, k, 0};
-    float reach2 = 2.f * key_of(cube_bound(G, at, 1));
-    for (;;) {
+    for (float reach2 = widen_first(cube_bound(G, at, 1));; reach2 *= WIDEN) {
+      bool last;
       L.cnt = 0;
-      L.bound = min(KEY_INF, (uint64_t)__float_as_uint(reach2) << 32);
-      const int R = cells_reached(G, at, L.bound, rmax);
-      const bool last = L.bound == KEY_INF;
+      const int R = widen(G, at, reach2, rmax, L.bound, last);
       visit<KN_G, KN_U, 2>(J, G, at, q, R, -1, L, sh.g.seg[grp]);
       if (L.cnt >= k || last) break;
-      reach2 *= 2.5f;
     }
     write_list<KN_G>(L, k, J.nbr + (int64_t)__float_as_int(q.w) * k);
   }

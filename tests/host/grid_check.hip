@@ -149,12 +149,12 @@ static std::vector<uint64_t> knn(const Grid& g, int t, int k) {
   if (edge == KEY_INF || (dense ? under : (int)s.list.size()) >= k) return s.list;
   const int rmax = rmax_of(g.G);
   if (s.seen >= k) {
-    float reach2 = 2.f * key_of(edge);
-    for (int round = 0; round < 1000; ++round, reach2 *= 2.5f) {
+    float reach2 = widen_first(edge);
+    for (int round = 0; round < 1000; ++round, reach2 *= WIDEN) {
+      bool last;
       s.list.clear();
-      s.bound = std::min(KEY_INF, (uint64_t)__builtin_bit_cast(uint32_t, reach2) << 32);
-      const bool last = s.bound == KEY_INF;
-      s.visit(cells_reached(g.G, s.at, s.bound, rmax), -1);
+      const int R = widen(g.G, s.at, reach2, rmax, s.bound, last);
+      s.visit(R, -1);
       if ((int)s.list.size() >= k || last) return s.list;
     }
     std::fprintf(stderr, "no end\n");

@@ -1,7 +1,8 @@
 """Neighbour lists, nearest points and residuals of clouds longer than the
 grid's 1 024 cells along an axis, whose last cell there holds everything beyond:
 a stray point on each of the six sides, and a pipe and a strip along each axis,
-exactly as brute force gives them (FP32 keys, ties by index)."""
+exactly as brute force gives them (FP32 keys, ties by index).  Also clouds so
+small that the squares of their cells underflow."""
 import numpy as np
 import pytest
 import torch
@@ -75,3 +76,12 @@ def test_nearest_points_and_residual(sg, ctx, kind, axis, side, n):
     nn, _ = _nearest(Y, X, fused=True)
     rmse = np.sqrt(((Y.astype(np.float64) - X[nn].astype(np.float64)) ** 2).sum(1).mean())
     assert ctx.residual(sg.Cloud(Y), sg.Cloud(X), sg.pose_identity()).item() == pytest.approx(rmse, rel=1e-12)
+
+
+@pytest.mark.parametrize("scale", [1e-38, 1e-24, 1e-22, 1e-20, 1e-17])
+@pytest.mark.parametrize("n", [3000, 20000])
+def test_lists_of_clouds_whose_squares_underflow(sg, ctx, scale, n):
+    """Cell sides whose FP32 square underflows; many keys are 0 (ties by index)."""
+    P, k = np.concatenate([_surface(n, 5), np.float32([[3, 0, 0], [0, 30, 0]])]) * np.float32(scale), 16
+    q = np.r_[np.arange(0, n, n // 300), n, n + 1]
+    assert np.array_equal(ctx.knn(sg.Cloud(P), k).cpu().numpy()[q], O.knn_c(P, k, q))

@@ -36,8 +36,14 @@ def _keys(P, q):
 
 
 def _lists(P, k, step):
+    """-1 where fewer than k points have a finite key."""
+    out = []
     with np.errstate(over="ignore"):
-        return np.array([np.argsort(_keys(P, q), kind="stable")[:k] for q in P[::step]], np.int32)
+        for q in P[::step]:
+            d = _keys(P, q)
+            i = np.argsort(d, kind="stable")[:k]
+            out.append(np.where(np.isfinite(d[i]), i, -1))
+    return np.array(out, np.int32)
 
 
 def _nearest(P, Q, tau):
@@ -107,3 +113,16 @@ def test_ordinary_clouds(search, n):
     Q = np.concatenate([P[::step] + rng.normal(size=P[::step].shape) * 0.05, rng.normal(size=(60, 3)) * 4]).astype(np.float32)
     for tau in (1e-3, 0.3, 1e18):
         assert np.array_equal(search("nn", P, len(Q), tau, Q), _nearest(P, Q, tau))
+
+
+@pytest.mark.parametrize("scale", [1e-38, 1e-30, 1e-24, 1e-22, 1e-20, 1e-18, 1e-16, 1e-10, 1e10, 1e17, 1e18, 1e25, 1e35])
+def test_clouds_of_any_scale(search, scale):
+    """Keys that underflow (many are 0, and ties go by index) and overflow."""
+    P = np.concatenate([_surface(3000, 5), np.float32([[3, 0, 0], [0, 30, 0], [0, 0, -300]])]) * np.float32(scale)
+    for k in (5, 24):
+        assert np.array_equal(search("knn", P, k, 10).reshape(-1, k), _lists(P, k, 10))
+    rng = np.random.default_rng(6)
+    with np.errstate(over="ignore"):
+        Q = np.concatenate([P[::10] * np.float32(1.01), rng.normal(size=(60, 3)).astype(np.float32) * np.float32(scale)])
+    Q = Q[np.isfinite(Q).all(1)]
+    assert np.array_equal(search("nn", P, len(Q), 1.8e19, Q), _nearest(P, Q, 1.8e19))
