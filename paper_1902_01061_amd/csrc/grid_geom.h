@@ -142,6 +142,11 @@ struct Place {
   }
 };
 
+// What is left of a squared distance once that to a row is taken off, as a
+// distance along the row with its margin.  Not a number where both overflowed
+// (a query 1e19 cells away): the whole row then.
+SGR_HD float row_reach(float left) { return left < 1e30f ? sqrtf(left) * 1.0001f + 2e-3f : INFINITY; }
+
 // Whole cells in a distance along a row, which has at most 1024.
 SGR_HD int cell_step(float d) { return (int)floorf(fminf(4096.f, fmaxf(-4096.f, d))); }
 
@@ -154,7 +159,7 @@ SGR_HDI bool row_cells(const GridInfo& G, const Place& at, int R, int dy, int dz
   const float left = reach2 - (gy * gy + gz * gz);
   if (left < 0.f) return false;
   // cells of the row within sqrt(left) of the query
-  const float reach = sqrtf(left) * 1.0001f + 2e-3f;
+  const float reach = row_reach(left);
   xl = max2(max2(0, cx - R), min2(cx, cx + cell_step(at.fr[0] - reach)));
   xr = min2(min2(G.dims[0] - 1, cx + R), max2(cx, cx + cell_step(at.fr[0] + reach)));
   return true;
@@ -233,7 +238,7 @@ SGR_HDI bool block_row_cells(const GridInfo& G, const Place& at, const int bc[3]
   const float gy = at.gap(1, cy - at.c[1]), gz = at.gap(2, cz - at.c[2]);
   const float left = reach2 - (gy * gy + gz * gz);
   if (left < 0.f) return false;
-  const float reach = sqrtf(left) * 1.0001f + 2e-3f;
+  const float reach = row_reach(left);
   xl = max2(x0, at.c[0] + cell_step(at.up[0] - reach));
   xr = min2(min2(G.dims[0], x0 + BLK) - 1, at.c[0] + cell_step(at.fr[0] + reach));
   return xl <= xr;

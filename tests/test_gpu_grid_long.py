@@ -85,3 +85,14 @@ def test_lists_of_clouds_whose_squares_underflow(sg, ctx, scale, n):
     P, k = np.concatenate([_surface(n, 5), np.float32([[3, 0, 0], [0, 30, 0]])]) * np.float32(scale), 16
     q = np.r_[np.arange(0, n, n // 300), n, n + 1]
     assert np.array_equal(ctx.knn(sg.Cloud(P), k).cpu().numpy()[q], O.knn_c(P, k, q))
+
+
+@pytest.mark.parametrize("e", [16, 18.6, 18.9])
+def test_nearest_points_of_queries_far_away(sg, ctx, e):
+    """So many cells away that the square of the distance in cells overflows."""
+    X = _surface(3000, 5)
+    u = np.random.default_rng(7).normal(size=(100, 3))
+    Y = (u / np.linalg.norm(u, axis=1, keepdims=True) * 10.0 ** e).astype(np.float32)
+    _, nn, _ = ctx.change_detect(sg.Cloud(Y), torch.zeros(100, device="cuda"), sg.Cloud(X),
+                                 torch.zeros(3000, device="cuda"), sg.pose_identity(), 1.5e19)
+    assert np.array_equal(nn.cpu().numpy(), _nearest(Y, X)[0])

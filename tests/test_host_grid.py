@@ -126,3 +126,15 @@ def test_clouds_of_any_scale(search, scale):
         Q = np.concatenate([P[::10] * np.float32(1.01), rng.normal(size=(60, 3)).astype(np.float32) * np.float32(scale)])
     Q = Q[np.isfinite(Q).all(1)]
     assert np.array_equal(search("nn", P, len(Q), 1.8e19, Q), _nearest(P, Q, 1.8e19))
+
+
+@pytest.mark.parametrize("e", [3, 8, 16, 18, 18.6, 18.9, 19, 20, 38])
+def test_nearest_points_of_queries_far_away(search, e):
+    """Up to where every key overflows (no nearest point)."""
+    P = _surface(3000, 5)
+    u = np.random.default_rng(7).normal(size=(100, 3))
+    Q = (u / np.linalg.norm(u, axis=1, keepdims=True) * 10.0 ** e).astype(np.float32)
+    with np.errstate(over="ignore"):
+        keys = [_keys(P, q) for q in Q]
+    want = [d.argmin() if np.isfinite(d.min()) else -1 for d in keys]
+    assert np.array_equal(search("nn", P, len(Q), np.inf, Q), want)
