@@ -635,7 +635,7 @@ struct SingleWs {
   double* ps_S;
   int ps_chunks;
   int* sync;         // the loop's ticket (64 ints), then its exchange words
-  double* pose0;     // poses before each level's loop
+  double* pose0;     // pose before the first loop
   int loop_ppt, loop_nb;  // the one-launch loop's shape (0 blocks: not used)
   ForceLoop floop;        // that of the all-pairs force
   int* perm;
@@ -649,7 +649,7 @@ struct SingleWs {
 // kmax: largest k of a nearest-neighbour search the call makes (0: none).
 // use_loop: flags bit 3 may run its iterations in one launch.
 int carve_single(sgr_ctx* ctx, int M, int N, const sgr_params* prm, int kmax, SingleWs& w, bool radius,
-                 bool use_loop, int n_levels) {
+                 bool use_loop) {
   const int pm = pmode_of(prm->p);
   const bool pinv = (prm->flags & FLAG_PINV) != 0;
   w.T = ctx->tiles.pick(M, N, pm);
@@ -684,7 +684,7 @@ int carve_single(sgr_ctx* ctx, int M, int N, const sgr_params* prm, int kmax, Si
     w.ps_part = pinv ? c.take<double>((size_t)w.ps_chunks * M * 5) : nullptr;
     w.ps_S = pinv ? c.take<double>((size_t)M * 5) : nullptr;
     w.sync = loops ? c.take<int>(64 + 2 * loop_words(std::max(w.loop_nb, w.floop.blocks))) : nullptr;
-    w.pose0 = loops ? c.take<double>((size_t)13 * n_levels) : nullptr;
+    w.pose0 = loops ? c.take<double>(13) : nullptr;
     if (!pass)
       if (int e = ensure_ws(ctx, c.off)) return e;
   }
@@ -722,18 +722,19 @@ int run_loop(sgr_ctx* ctx, LoopReg g, int ppt, int* sync, int t0, int t1, hipStr
 // G follows eq. 12 over prm->E.  The energy U is accumulated only where it is
 // read, in the per-iteration stats; with stats, the last of the E
 // iterations of a mixed-precision registration uses the FP32 kernel so that
-// its energy is the FP32 one.
+// its energy is the FP32 one.  pose0 (nullable) receives the pose as it was if
+// the iterations run in one launch.
 int run_single_loop(sgr_ctx* ctx, GraphCache& gc, const sgr_cloud* tmpl, const sgr_cloud* ref,
                     const sgr_params* prm, const SingleWs& w, sgr_pose* inout, double* stats, int t0, int t1,
-                    int level, hipStream_t st) {
+                    double* pose0, hipStream_t st) {
   const int M = (int)tmpl->n, N = (int)ref->n;
   if (w.loop_nb > 0)
-    return run_loop(ctx, LoopReg{w.tm4, w.tmx, w.ps_S, (double*)inout, w.pose0 + 13 * (size_t)level, w.dv, stats,
+    return run_loop(ctx, LoopReg{w.tm4, w.tmx, w.ps_S, (double*)inout, pose0, w.dv, stats,
                                  nullptr, nullptr, M, w.loop_nb},
                     w.loop_ppt, w.sync, t0, t1, st);
   if (w.floop.blocks > 0 && !stats && t1 - t0 > 1) {
     const int nb = w.floop.blocks;
-    LoopReg g{w.tm4, w.tmx, nullptr, (double*)inout, w.pose0 + 13 * (size_t)level, w.dv, nullptr, nullptr, nullptr, M, nb};
+    LoopReg g{w.tm4, w.tmx, nullptr, (double*)inout, pose0, w.dv, nullptr, nullptr, nullptr, M, nb};
     g.xch = reinterpret_cast<unsigned long long*>(w.sync + 64);
     HIPCHK(launch_fill_i(w.sync, 64 + 2 * (int)loop_words(nb), st));
     HIPCHK(launch_force_loop(g, w.floop, w.sync, t0, t1, ctx->loop_spins, st));
@@ -1263,13 +1264,13 @@ int sgr_register(sgr_ctx* ctx, const sgr_cloud* tmpl, const sgr_cloud* ref, cons
   const int M = (int)tmpl->n, N = (int)ref->n;
   for (const bool use_loop : {true, false}) {
     SingleWs w;
-    if (int e = carve_single(ctx, M, N, prm, prm->k, w, false, use_loop, 1)) return e;
+    if (int e = carve_single(ctx, M, N, prm, prm->k, w, false, use_loop)) return e;
     HIPCHK(launch_grid_knn(ref->x, ref->y, ref->z, N, prm->k, w.aX, nullptr, w.gws, st));
     HIPCHK(launch_grid_knn(tmpl->x, tmpl->y, tmpl->z, M, prm->k, w.aY, nullptr, w.gws, st));
     HIPCHK(launch_moments(ref->x, ref->y, ref->z, N, w.wide, w.mom + 10, st));
     HIPCHK(launch_moments(tmpl->x, tmpl->y, tmpl->z, M, w.wide, w.mom, st));
     if (int e = setup_single(tmpl, ref, prep_of(prm), stats != nullptr, w, st)) return e;
-    if (int e = run_single_loop(ctx, ctx->gc, tmpl, ref, prm, w, inout, stats, 0, prm->E, 0, st)) return e;
+    if (int e = run_single_loop(ctx, ctx->gc, tmpl, ref, prm, w, inout, stats, 0, prm->E, w.pose0, st)) return e;
     int32_t status = 0;
     HIPCHK(hipMemcpyAsync(&status, &w.dv->status, sizeof(int32_t), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
@@ -1330,10 +1331,14 @@ int sgr_register_pyramid(sgr_ctx* ctx, const sgr_cloud* tmpl, const sgr_cloud* r
   const int M = (int)tmpl->n, N = (int)ref->n;
   for (const bool use_loop : {true, false}) {
     SingleWs w;
-    if (int e = carve_single(ctx, M, N, prm, kmax, w, radius, use_loop, n_levels)) return e;
+    if (int e = carve_single(ctx, M, N, prm, kmax, w, radius, use_loop)) return e;
     if ((int)ctx->gcp.size() < n_levels) ctx->gcp.resize(n_levels);
     HIPCHK(launch_moments(ref->x, ref->y, ref->z, N, w.wide, w.mom + 10, st));
     HIPCHK(launch_moments(tmpl->x, tmpl->y, tmpl->z, M, w.wide, w.mom, st));
+    // for a restart after a stall: a level may run without the loop and
+    // advance the pose before another level's loop stalls
+    if (w.loop_nb > 0 || w.floop.blocks > 0)
+      HIPCHK(hipMemcpyAsync(w.pose0, inout, sizeof(sgr_pose), hipMemcpyDeviceToDevice, st));
     std::vector<int32_t> status(n_levels, 0);
     int t0 = 0;
     for (int l = 0; l < n_levels; ++l) {
@@ -1349,7 +1354,7 @@ int sgr_register_pyramid(sgr_ctx* ctx, const sgr_cloud* tmpl, const sgr_cloud* r
       PrepParams P = prep_of(prm);
       P.sigma_scale = v.sigma_scale;
       if (int e = setup_single(tmpl, ref, P, stats != nullptr, w, st)) return e;
-      if (int e = run_single_loop(ctx, ctx->gcp[l], tmpl, ref, prm, w, inout, stats, t0, t0 + v.iters, l, st)) return e;
+      if (int e = run_single_loop(ctx, ctx->gcp[l], tmpl, ref, prm, w, inout, stats, t0, t0 + v.iters, nullptr, st)) return e;
       HIPCHK(hipMemcpyAsync(&status[l], &w.dv->status, sizeof(int32_t), hipMemcpyDeviceToHost, st));
       t0 += v.iters;
     }
