@@ -14,6 +14,7 @@
 
 #include "../../include/sgreg.h"
 #include "launch.h"
+#include "reuse.h"
 #include "tiles.h"
 
 using namespace sgr;
@@ -32,9 +33,7 @@ static int fail(int code, const std::string& msg) {
   } while (0)
 
 struct GraphCache {
-  std::vector<uint8_t> key;
-  std::vector<uint8_t> seen;  // key of the last calls that ran without a graph
-  int times = 0;              // how many they were in a row
+  CaptureRule rule;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
 };
@@ -215,17 +214,14 @@ hipError_t run_force(ForceArgs A, const Tiles& T, const FLaunch& L, int pm, bool
 // The packed reference is padded to whole tiles with zero-weight points.
 size_t pad_n(int64_t N) { return (size_t)((N + 255) / 256) * 256; }
 
-// Runs `loop` (which launches on the given stream): from the cached graph if
-// that was made for the same key, else directly, and as a new graph when a
-// key comes the fourth time in a row.  A capture costs what four runs from
-// its graph save: 100 iterations at 1 024 points take 1 593 us with a capture,
-// 1 331 launched directly and 1 266 from a graph that exists.
+// Runs `loop` (which launches on the given stream) directly, as a new graph, or
+// from the cached graph, as the cache's rule says.
 template <class F>
 int run_graph(sgr_ctx* ctx, GraphCache& gc, const std::vector<uint8_t>& key, F&& loop, hipStream_t st) {
-  if (!gc.exec || key != gc.key) {
-    gc.times = key == gc.seen ? gc.times + 1 : 1;
-    gc.seen = key;
-    if (gc.times < 4) return loop(st);
+  const CaptureRule::Act act = gc.rule.next(key);
+  if (act == CaptureRule::DIRECT) return loop(st);
+  if (act == CaptureRule::CAPTURE) {
+    gc.rule.dropped();
     if (gc.exec) (void)hipGraphExecDestroy(gc.exec);
     if (gc.graph) (void)hipGraphDestroy(gc.graph);
     gc.exec = nullptr;
@@ -247,7 +243,7 @@ int run_graph(sgr_ctx* ctx, GraphCache& gc, const std::vector<uint8_t>& key, F&&
     }
     gc.graph = g;
     gc.exec = ex;
-    gc.key = key;
+    gc.rule.captured(key);
   }
   HIPCHK(hipGraphLaunch(gc.exec, st));
   return SGR_OK;
