@@ -127,7 +127,12 @@ typedef struct {
 } sgr_params;
 
 /* Context on HIP device `device`: owns the workspace, captured graphs and the
- * tile table.  The only memory the library allocates. */
+ * tile table.  The only memory the library allocates.
+ * Registrations that run all iterations in one launch have blocks that wait
+ * for each other.  If they are not resident together (other work fills the
+ * card), they give up after a number of polls, 200 000 or the whole number in
+ * the environment variable SGR_LOOP_SPINS when the context is made (any other
+ * text is ignored); the call then starts again with a launch per iteration. */
 int sgr_create(sgr_ctx** ctx, int device);
 int sgr_destroy(sgr_ctx* ctx);
 const char* sgr_last_error(void);

@@ -50,7 +50,7 @@ struct sgr_ctx {
   std::vector<GraphCache> gcp;  // pyramidal schedule, one per level
   GraphCache gcv;  // vector descriptors
   TileTable tiles;
-  int loop_spins = 200000;  // polls before the one-launch loop gives up (about 0.2 s)
+  LoopRule loop;
 };
 
 namespace {
@@ -574,7 +574,7 @@ int run_batch(sgr_ctx* ctx, const BatchIn& in, const sgr_params* prm, double* po
   };
   if (loop) {
     HIPCHK(launch_fill_i(d_sync, (int)sync_ints, st));
-    HIPCHK(launch_pinv_loop_batch(d_lregs, d_lblk, (int)lblk.size(), ppt, d_sync, 0, prm->E, ctx->loop_spins, st));
+    HIPCHK(launch_pinv_loop_batch(d_lregs, d_lblk, (int)lblk.size(), ppt, d_sync, 0, prm->E, ctx->loop.spins, st));
   } else if ((prm->flags & 1) || prm->E < 2) {
     if (int e = iterations(st)) return e;
   } else {
@@ -709,7 +709,7 @@ int setup_single(const sgr_cloud* tmpl, const sgr_cloud* ref, const PrepParams& 
 int run_loop(sgr_ctx* ctx, LoopReg g, int ppt, int* sync, int t0, int t1, hipStream_t st) {
   g.xch = reinterpret_cast<unsigned long long*>(sync + 64);
   HIPCHK(launch_fill_i(sync, 64 + 2 * (int)loop_words(g.nb), st));
-  HIPCHK(launch_pinv_loop(g, ppt, sync, t0, t1, ctx->loop_spins, st));
+  HIPCHK(launch_pinv_loop(g, ppt, sync, t0, t1, ctx->loop.spins, st));
   return SGR_OK;
 }
 
@@ -733,7 +733,7 @@ int run_single_loop(sgr_ctx* ctx, GraphCache& gc, const sgr_cloud* tmpl, const s
     LoopReg g{w.tm4, w.tmx, nullptr, (double*)inout, pose0, w.dv, nullptr, nullptr, nullptr, M, nb};
     g.xch = reinterpret_cast<unsigned long long*>(w.sync + 64);
     HIPCHK(launch_fill_i(w.sync, 64 + 2 * (int)loop_words(nb), st));
-    HIPCHK(launch_force_loop(g, w.floop, w.sync, t0, t1, ctx->loop_spins, st));
+    HIPCHK(launch_force_loop(g, w.floop, w.sync, t0, t1, ctx->loop.spins, st));
     return SGR_OK;
   }
   const int pm = pmode_of(prm->p);
@@ -1077,7 +1077,7 @@ int sgr_create(sgr_ctx** out, int device) {
     return fail(SGR_EHIP, "stream creation failed");
   }
   c->tiles.init(c->n_cu);
-  if (const char* v = std::getenv("SGR_LOOP_SPINS")) c->loop_spins = std::max(1, std::atoi(v));
+  c->loop.spins = LoopRule::limit(std::getenv("SGR_LOOP_SPINS"));
   if (int e = scratch_init(device)) {
     (void)hipStreamDestroy(c->cap);
     delete c;

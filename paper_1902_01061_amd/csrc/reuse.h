@@ -2,7 +2,9 @@
 // (host only; the results do not depend on it beyond rounding).
 #pragma once
 #include <stdint.h>
+#include <stdlib.h>
 
+#include <climits>
 #include <vector>
 
 namespace sgr {
@@ -36,6 +38,21 @@ struct CaptureRule {
     times = 0;
   }
   void dropped() { key.clear(); }
+};
+
+// Registrations whose iterations run in one launch, with blocks that wait for
+// each other.
+struct LoopRule {
+  static constexpr int SPINS = 200000;  // polls before a loop gives up (0.2 s at an estimated 1 us each)
+  int spins = SPINS;
+
+  // The limit from a text: a whole number from 1 up, else (or nullptr) SPINS.
+  static int limit(const char* text) {
+    if (!text || *text < '0' || *text > '9') return SPINS;
+    char* end = nullptr;
+    const long v = strtol(text, &end, 10);
+    return *end == 0 && v >= 1 && v <= INT_MAX ? (int)v : SPINS;
+  }
 };
 
 }  // namespace sgr

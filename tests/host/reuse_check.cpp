@@ -1,18 +1,26 @@
-// Host harness for the capture rule: reads a line of keys (letters), prints what
-// each call does, d(irect), c(apture) or r(eplay).
+// Host harness for csrc/reuse.h.
+//   reuse_check capture KEYS   what a call with each key (letter) does:
+//                              d(irect), c(apture) or r(eplay)
+//   reuse_check limit [TEXT]   the poll limit from the text
 #include <cstdio>
+#include <cstring>
 
 #include "../../paper_1902_01061_amd/csrc/reuse.h"
 
-int main() {
-  sgr::CaptureRule rule;
-  for (int c = std::getchar(); c > ' '; c = std::getchar()) {
-    const std::vector<uint8_t> key(3, (uint8_t)c);
-    const auto act = rule.next(key);
-    if (act == sgr::CaptureRule::CAPTURE) {
-      rule.dropped();
-      rule.captured(key);
+int main(int argc, char** argv) {
+  const char* text = argc > 2 ? argv[2] : nullptr;
+  if (!std::strcmp(argv[1], "limit")) {
+    std::printf("%d", sgr::LoopRule::limit(text));
+  } else {
+    sgr::CaptureRule rule;
+    for (; *text; ++text) {
+      const std::vector<uint8_t> key(3, (uint8_t)*text);
+      const auto act = rule.next(key);
+      if (act == sgr::CaptureRule::CAPTURE) {
+        rule.dropped();
+        rule.captured(key);
+      }
+      std::putchar("dcr"[act]);
     }
-    std::putchar("dcr"[act]);
   }
 }

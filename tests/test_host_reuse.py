@@ -1,4 +1,5 @@
-"""When calls run directly, capture a graph or replay it (csrc/reuse.h)."""
+"""When calls run directly, capture a graph or replay it, and the poll limit of
+the one-launch loop (csrc/reuse.h)."""
 import os
 import shutil
 import subprocess
@@ -16,7 +17,7 @@ def reuse(tmp_path_factory):
     exe = str(tmp_path_factory.mktemp("reuse") / "reuse_check")
     subprocess.run([cxx, "-std=c++17", "-O1", "-Wall", "-Werror", os.path.join(HERE, "host", "reuse_check.cpp"), "-o",
                     exe], check=True)
-    return lambda keys: subprocess.run([exe], input=keys + "\n", capture_output=True, text=True, check=True).stdout
+    return lambda *a: subprocess.run([exe, *a], capture_output=True, text=True, check=True).stdout
 
 
 @pytest.mark.parametrize("keys,acts", [
@@ -29,4 +30,11 @@ def reuse(tmp_path_factory):
     ("AAABAAAA", "ddddddd" + "c"),
 ])
 def test_capture_rule(reuse, keys, acts):
-    assert reuse(keys) == acts
+    assert reuse("capture", keys) == acts
+
+
+@pytest.mark.parametrize("text,limit", [(None, 200000), ("1", 1), ("5000", 5000), ("", 200000), ("abc", 200000),
+                                        ("0", 200000), ("-3", 200000), ("12x", 200000), ("1e6", 200000),
+                                        ("99999999999", 200000), ("99999999999999999999", 200000), (" 7", 200000)])
+def test_poll_limit(reuse, text, limit):
+    assert int(reuse("limit", *([] if text is None else [text]))) == limit
