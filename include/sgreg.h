@@ -132,7 +132,8 @@ typedef struct {
  * for each other.  If they are not resident together (other work fills the
  * card), they give up after a number of polls, 200 000 or the whole number in
  * the environment variable SGR_LOOP_SPINS when the context is made (any other
- * text is ignored); the call then starts again with a launch per iteration. */
+ * text is ignored); the call then starts again with a launch per iteration, as
+ * do the context's next 255 registrations. */
 int sgr_create(sgr_ctx** ctx, int device);
 int sgr_destroy(sgr_ctx* ctx);
 const char* sgr_last_error(void);

@@ -259,7 +259,7 @@ void key_add(std::vector<uint8_t>& k, const T* p, size_t n) {
 // descriptors, set-up, then E iterations of (persistent force, update).
 struct BatchIn {
   int B;
-  bool use_loop = true;                  // flags bit 3: one launch for all iterations (false: after a stall)
+  bool use_loop;                         // flags bit 3: one launch for all iterations
   std::vector<const sgr_cloud*> tm, rf;  // per registration
   std::vector<int> tm_cloud, rf_cloud;   // index of each registration's clouds in `clouds`
   std::vector<const sgr_cloud*> clouds;  // distinct clouds (descriptors computed once each)
@@ -599,6 +599,7 @@ int run_batch(sgr_ctx* ctx, const BatchIn& in, const sgr_params* prm, double* po
     // again, with one launch per iteration
     if (!R0_multistart)
       HIPCHK(hipMemcpyAsync(poses, d_pose0, sizeof(double) * 13 * B, hipMemcpyDeviceToDevice, st));
+    ctx->loop.stalled();
     BatchIn again = in;
     again.use_loop = false;
     return run_batch(ctx, again, prm, poses, R0_multistart, energy_out, stats, best_out, st);
@@ -1258,7 +1259,7 @@ int sgr_register(sgr_ctx* ctx, const sgr_cloud* tmpl, const sgr_cloud* ref, cons
   HIPCHK(hipSetDevice(ctx->device));
   hipStream_t st = (hipStream_t)stream;
   const int M = (int)tmpl->n, N = (int)ref->n;
-  for (const bool use_loop : {true, false}) {
+  for (const bool use_loop : {ctx->loop.use(), false}) {
     SingleWs w;
     if (int e = carve_single(ctx, M, N, prm, prm->k, w, false, use_loop)) return e;
     HIPCHK(launch_grid_knn(ref->x, ref->y, ref->z, N, prm->k, w.aX, nullptr, w.gws, st));
@@ -1271,6 +1272,7 @@ int sgr_register(sgr_ctx* ctx, const sgr_cloud* tmpl, const sgr_cloud* ref, cons
     HIPCHK(hipMemcpyAsync(&status, &w.dv->status, sizeof(int32_t), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     if (status & ST_STALLED) {
+      ctx->loop.stalled();
       // the loop's blocks were not resident together: from the initial pose
       // again, with one launch per iteration
       HIPCHK(hipMemcpyAsync(inout, w.pose0, sizeof(sgr_pose), hipMemcpyDeviceToDevice, st));
@@ -1325,7 +1327,7 @@ int sgr_register_pyramid(sgr_ctx* ctx, const sgr_cloud* tmpl, const sgr_cloud* r
   HIPCHK(hipSetDevice(ctx->device));
   hipStream_t st = (hipStream_t)stream;
   const int M = (int)tmpl->n, N = (int)ref->n;
-  for (const bool use_loop : {true, false}) {
+  for (const bool use_loop : {ctx->loop.use(), false}) {
     SingleWs w;
     if (int e = carve_single(ctx, M, N, prm, kmax, w, radius, use_loop)) return e;
     if ((int)ctx->gcp.size() < n_levels) ctx->gcp.resize(n_levels);
@@ -1358,6 +1360,7 @@ int sgr_register_pyramid(sgr_ctx* ctx, const sgr_cloud* tmpl, const sgr_cloud* r
     int32_t any = 0;
     for (int l = 0; l < n_levels; ++l) any |= status[l];
     if (any & ST_STALLED) {
+      ctx->loop.stalled();
       HIPCHK(hipMemcpyAsync(inout, w.pose0, sizeof(sgr_pose), hipMemcpyDeviceToDevice, st));
       continue;
     }
@@ -1435,7 +1438,7 @@ int sgr_register_vec(sgr_ctx* ctx, const sgr_cloud* tmpl, const float* a_t, cons
   hipStream_t st = (hipStream_t)stream;
   const int M = (int)tmpl->n, N = (int)ref->n;
   const bool pinv = (prm->flags & FLAG_PINV) != 0;
-  for (const bool use_loop : {true, false}) {
+  for (const bool use_loop : {ctx->loop.use(), false}) {
     VecWs w;
     if (int e = carve_vec(ctx, M, N, D, false, true, w, pinv, use_loop)) return e;
     HIPCHK(launch_moments(ref->x, ref->y, ref->z, N, w.wide, w.mom + 10, st));
@@ -1486,6 +1489,7 @@ int sgr_register_vec(sgr_ctx* ctx, const sgr_cloud* tmpl, const float* a_t, cons
     HIPCHK(hipMemcpyAsync(&status, &w.dv->status, sizeof(int32_t), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     if (status & ST_STALLED) {
+      ctx->loop.stalled();
       HIPCHK(hipMemcpyAsync(inout, w.pose0, sizeof(sgr_pose), hipMemcpyDeviceToDevice, st));
       continue;
     }
@@ -1950,6 +1954,7 @@ int sgr_register_batch(sgr_ctx* ctx, int B, const sgr_cloud* tmpls, const sgr_cl
   if (prm->k < 1 || prm->k > 32) return fail(SGR_EINVAL, "k must be in [1, 32]");
   BatchIn in;
   in.B = B;
+  in.use_loop = ctx->loop.use();
   for (int r = 0; r < B; ++r) {
     if (int e = check_cloud(&tmpls[r], "template")) return e;
     if (int e = check_cloud(&refs[r], "reference")) return e;
@@ -1979,6 +1984,7 @@ int sgr_multistart(sgr_ctx* ctx, const sgr_cloud* tmpl, const sgr_cloud* ref, co
   if (tmpl->n < prm->k || ref->n < prm->k) return fail(SGR_EINVAL, "a cloud has fewer points than k");
   BatchIn in;
   in.B = S;
+  in.use_loop = ctx->loop.use();
   in.clouds = {tmpl, ref};
   for (int s = 0; s < S; ++s) {
     in.tm.push_back(tmpl);

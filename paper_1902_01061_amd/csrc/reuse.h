@@ -40,11 +40,23 @@ struct CaptureRule {
   void dropped() { key.clear(); }
 };
 
-// Registrations whose iterations run in one launch, with blocks that wait for
-// each other.
+// Whether a registration may run its iterations in one launch, whose blocks
+// wait for each other.  When they were not resident together, the call has
+// waited its poll limit for nothing and done its work twice; what keeps them
+// apart (another context's work on the same card) is likely to last, so the
+// next registrations do without.
 struct LoopRule {
   static constexpr int SPINS = 200000;  // polls before a loop gives up (0.2 s at an estimated 1 us each)
+  static constexpr int REST = 255;
   int spins = SPINS;
+  int rest = 0;  // registrations still to do without
+
+  bool use() {
+    if (rest == 0) return true;
+    --rest;
+    return false;
+  }
+  void stalled() { rest = REST; }
 
   // The limit from a text: a whole number from 1 up, else (or nullptr) SPINS.
   static int limit(const char* text) {

@@ -1,5 +1,5 @@
-"""When calls run directly, capture a graph or replay it, and the poll limit of
-the one-launch loop (csrc/reuse.h)."""
+"""When calls run directly, capture a graph or replay it, and when registrations
+do without the one-launch loop (csrc/reuse.h)."""
 import os
 import shutil
 import subprocess
@@ -31,6 +31,12 @@ def reuse(tmp_path_factory):
 ])
 def test_capture_rule(reuse, keys, acts):
     assert reuse("capture", keys) == acts
+
+
+def test_loop_rule(reuse):
+    """One stall, 255 calls without the loop, then the loop again."""
+    assert reuse("loop", "....") == "llll"
+    assert reuse("loop", "." + "s" * 258) == "ll" + "i" * 255 + "li"
 
 
 @pytest.mark.parametrize("text,limit", [(None, 200000), ("1", 1), ("5000", 5000), ("", 200000), ("abc", 200000),
