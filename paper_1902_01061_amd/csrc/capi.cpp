@@ -83,6 +83,18 @@ int ensure_ws(sgr_ctx* ctx, size_t bytes) {
   return SGR_OK;
 }
 
+// For scratch that a call can do without: whether there are `bytes`, or could be
+// had.  None is taken while the stream is captured.
+bool spare_ws(sgr_ctx* ctx, size_t bytes, hipStream_t st) {
+  if (bytes <= ctx->ws_size) return true;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return cap == hipStreamCaptureStatusNone && ensure_ws(ctx, bytes) == SGR_OK;
+}
+
 int check_cloud(const sgr_cloud* c, const char* what) {
   if (!c) return fail(SGR_EINVAL, std::string(what) + ": NULL cloud");
   if (!c->x || !c->y || !c->z) return fail(SGR_EINVAL, std::string(what) + ": NULL coordinate array");
@@ -1510,12 +1522,8 @@ int sgr_residual(sgr_ctx* ctx, const sgr_cloud* tmpl, const sgr_cloud* ref, cons
   // The grid's scratch is some 100 bytes per point; where a capture or the
   // device's memory does not allow it, the search over all of the reference
   // needs almost none.
-  bool grid = residual_grid(N, corr != nullptr);
-  if (grid && residual_workspace(M, N, true) > ctx->ws_size) {
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    HIPCHK(hipStreamIsCapturing((hipStream_t)stream, &cap));
-    grid = cap == hipStreamCaptureStatusNone && ensure_ws(ctx, residual_workspace(M, N, true)) == SGR_OK;
-  }
+  const bool grid = residual_grid(N, corr != nullptr) &&
+                    spare_ws(ctx, residual_workspace(M, N, true), (hipStream_t)stream);
   if (int e = ensure_ws(ctx, residual_workspace(M, N, grid))) return e;
   HIPCHK(launch_residual(tmpl->x, tmpl->y, tmpl->z, M, ref->x, ref->y, ref->z, N, (const double*)pose, corr, grid,
                          ctx->ws, rmse_out, (hipStream_t)stream));
@@ -2037,10 +2045,11 @@ int sgr_unrolled_bwd(sgr_ctx* ctx, const sgr_cloud* tmpl, const float* a_t, cons
   const int nseg = (E + K - 1) / K;
   const int npg = pose_grad_blocks(M);
   // The forces of a segment are kept while its poses are recomputed, unless
-  // that takes more than KEEP_BYTES: then they are evaluated again.
+  // that takes more than KEEP_BYTES or there is no room: then they are evaluated
+  // again.
   constexpr size_t KEEP_BYTES = size_t(256) << 20;
   const int S = std::min(K, E);  // iterations of a segment
-  const bool keep = (size_t)S * M * 3 * sizeof(float) <= KEEP_BYTES;
+  bool keep = (size_t)S * M * 3 * sizeof(float) <= KEEP_BYTES;
   struct Rest {
     double *seg, *W, *g[2], *gW, *cpart, *fsum, *pg, *ypart, *spart;
     float *Y, *f, *gf0;
@@ -2062,9 +2071,13 @@ int sgr_unrolled_bwd(sgr_ctx* ctx, const sgr_cloud* tmpl, const float* a_t, cons
     r.spart = c.take<double>((size_t)TA.nblk * 2);
   };
   {
-    Carve cv{nullptr};
+    Carve cv{nullptr}, least{nullptr};
     carve_rest(cv);
-    if (int e = ensure_ws(ctx, cv.off)) return e;
+    if (!spare_ws(ctx, cv.off, st)) {
+      keep = false;
+      carve_rest(least);
+      if (int e = ensure_ws(ctx, least.off)) return e;
+    }
   }
   Carve w{ctx->ws};
   carve_rest(w);
