@@ -352,8 +352,8 @@ int sgr_plan_force(sgr_plan* plan, int t, double G, const sgr_pose* pose, double
  * the distance-law mode of p (1, 3 or other): R template points per lane
  * (1, 2, 4 or 8), a target of blocks_per_cu blocks of 256 threads per
  * compute unit (each template block's reference range is cut into equal
- * chunks at multiples of 64 points to reach it; without an entry the
- * target is one wave of resident blocks, from the kernel's occupancy) and
+ * chunks at multiples of 16 points to reach it; without an entry the
+ * target is a constant of R, p and the variant, 2 to 8 blocks) and
  * the variant (0: reference tiles staged in LDS; 1: read through scalar
  * loads).  Affects plans and calls created afterwards.  R = 0 removes the
  * entry. */
@@ -361,7 +361,7 @@ int sgr_set_tiles(sgr_ctx* ctx, int64_t M, int64_t N, double p, int R, int block
 
 /* Autotuner: times the pair-force kernel for every launch shape (R in
  * {1, 2, 4, 8}, LDS or scalar-load variant, 1 to 4 blocks per CU and 1 to 8
- * waves of resident blocks, at most 64 blocks per CU) on this pair, `reps`
+ * times the default, at most 64 blocks per CU) on this pair, `reps`
  * launches each, and stores the fastest in the
  * tile table for the (M, N, p) bucket.  best (host int[3], nullable): R,
  * blocks_per_cu, variant; best_ms (host, nullable): its time per launch.

@@ -178,7 +178,8 @@ Tiles tiles_for(const sgr_ctx* ctx, int M, int N, const sgr_params* p) {
 // Shape of one FP32 force launch for a single registration: every template
 // block gets n_chunks reference chunks cut at multiples of force_chunk_gran()
 // points, with n_chunks chosen so that the launch is about T.bpc blocks per
-// CU (by default one wave of resident blocks, from the kernel's occupancy).
+// CU (without a tile entry force_blocks_per_cu(), constants, so that the FP32
+// sums of the chunks do not change with a build's registers).
 // Whole-tile chunks would leave the last wave of blocks partly empty
 // whenever the work is not a multiple of the resident block count, and a
 // small pair (a few thousand points) would occupy a few CUs only.
@@ -203,8 +204,7 @@ FLaunch force_shape(const sgr_ctx* ctx, int M, int N, const Tiles& T, int pm) {
 // two blocks per CU (fewer for a small pair: chunks of at least 16 points).
 // Every chunk writes 32 bytes per template point of partial sums, so more,
 // shorter chunks cost traffic as well as per-block overhead.
-Tiles adj_shape(const sgr_ctx* ctx, int M, int N, int R, bool p1) {
-  (void)p1;
+Tiles adj_shape(const sgr_ctx* ctx, int M, int N, int R) {
   if (R > 4) R = 4;
   Tiles T{};
   T.R = R;
@@ -1560,8 +1560,8 @@ int sgr_autotune(sgr_ctx* ctx, const sgr_cloud* tmpl, const float* a_t, const sg
   const auto key = std::make_tuple(log2_bucket(M), log2_bucket(N), pm);
   // Candidates: template points per lane, the reference load variant, and
   // the blocks per CU of the launch: 1 to 4 (long reference chunks, a few
-  // resident blocks), and 1 to 8 waves of resident blocks (from the kernel's
-  // occupancy, at most 64 blocks per CU).  Several waves of shorter chunks
+  // resident blocks), and 1 to 8 times force_blocks_per_cu(), which is about
+  // one wave of resident blocks (at most 64 blocks per CU).  Several waves of shorter chunks
   // even out the end of a large launch: the SIMDs serve the oldest wave
   // first, so the blocks of a CU do not finish together, and a block's fixed
   // start and end cost little beside a long pair loop.
@@ -1609,9 +1609,9 @@ int sgr_autotune(sgr_ctx* ctx, const sgr_cloud* tmpl, const float* a_t, const sg
   for (int v : {0, 1})
     for (int R : cand_R)
       for (int c = 0; c < 4 + kMaxWaves; ++c) {
-        const int occ = force_blocks_per_cu(R, pm, v != 0);
-        const int bpc = c < 4 ? c + 1 : (c - 3) * occ;
-        if (c < 4 && bpc >= occ) continue;  // covered by the occupancy targets
+        const int def = force_blocks_per_cu(R, pm, v != 0);
+        const int bpc = c < 4 ? c + 1 : (c - 3) * def;
+        if (c < 4 && bpc >= def) continue;  // covered by the multiples of the default
         if (bpc > 64) continue;
         Tiles T = TileTable::make(M, N, R, 8 * ctx->n_cu, v);
         T.bpc = bpc;
@@ -1774,7 +1774,7 @@ int sgr_force_bwd(sgr_ctx* ctx, const sgr_cloud* tmpl, const float* a_t, const s
   hipStream_t st = (hipStream_t)stream;
   const int M = (int)tmpl->n, N = (int)ref->n;
   const int pm = pmode_of(prm->p);
-  const Tiles T = adj_shape(ctx, M, N, ctx->tiles.pick(M, N, pm).R, pm == 1);
+  const Tiles T = adj_shape(ctx, M, N, ctx->tiles.pick(M, N, pm).R);
   Carve cv{nullptr};
   cv.take<double>(48);
   cv.take<double>(16);
@@ -2041,7 +2041,7 @@ int sgr_unrolled_bwd(sgr_ctx* ctx, const sgr_cloud* tmpl, const float* a_t, cons
   unrolled_shape(ctx, tmpl, ref, prm, U);
   const int M = U.M, N = U.N, E = prm->E;
   // the adjoint kernels use tile-multiple chunks (at most 4 points per lane)
-  const Tiles TA = adj_shape(ctx, M, N, U.T.R, U.pm == 1);
+  const Tiles TA = adj_shape(ctx, M, N, U.T.R);
   const int nseg = (E + K - 1) / K;
   const int npg = pose_grad_blocks(M);
   // The forces of a segment are kept while its poses are recomputed, unless

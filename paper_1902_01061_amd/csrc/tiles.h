@@ -1,8 +1,8 @@
 // Launch shape of the pair-force kernel: template points per lane (R),
 // template blocks, reference chunks.  The defaults are R = 2 (R = 1 for
-// small templates) and, for the FP32 force kernel, one wave of resident
-// blocks; the tile-multiple chunking here (8 blocks per CU) serves the
-// mixed-precision and adjoint kernels.  The autotuner can override R, the
+// small templates) and, for the FP32 force kernel, the blocks per CU of
+// force_blocks_per_cu(); the tile-multiple chunking here (8 blocks per CU)
+// serves the mixed-precision kernel.  The autotuner can override R, the
 // blocks per CU and the load variant per (M, N, p-mode) bucket.
 #pragma once
 #include <stdint.h>
@@ -15,7 +15,7 @@ namespace sgr {
 struct Tiles {
   int R;
   int sm;   // 1: reference read through scalar loads instead of LDS
-  int bpc;  // FP32 force kernel: blocks per CU (0: one wave of resident blocks)
+  int bpc;  // FP32 force kernel: blocks per CU (0: force_blocks_per_cu())
   int n_iblk;
   int n_chunks;
   int chunk_len;
