@@ -12,29 +12,34 @@ struct GridInfo {
   double inv_h;
   int dims[3];
   int ncells;
+  int sh[2];      // where the second and third coordinate of a packed cell begin
   double ext[3];  // bounding-box extents (for re-sizing the cells)
 };
 
 // Cell counts per axis for cell size h, grown by 10 % steps until the grid
-// has at most max_cells cells.  No cell is so small that its square, or a key
-// of that size, underflows in FP32.
+// has at most max_cells (up to 2^24) cells: a long cloud may have nearly all of
+// them along one axis.  No cell is so small that its square, or a key of that
+// size, underflows in FP32.
 SGR_HD void grid_dims(GridInfo& G, double h, int max_cells) {
   int d[3];
   h = fmax(h, 1e-18);
   for (int it = 0; it < 400; ++it) {
     const double ih = 1.0 / h;
-    long long tot = 1;
+    double tot = 1.0;
     for (int a = 0; a < 3; ++a) {
-      d[a] = (int)fmin(1024.0, floor(G.ext[a] * ih) + 1.0);
-      tot *= d[a];
+      const double c = fmin(16777216.0, floor(G.ext[a] * ih) + 1.0);
+      d[a] = (int)c;
+      tot *= c;
     }
-    if (tot <= max_cells) break;
+    if (tot <= (double)max_cells) break;
     h *= 1.1;
   }
   G.h = (float)h;
   G.inv_h = 1.0 / (double)G.h;
   for (int a = 0; a < 3; ++a) G.dims[a] = d[a];
   G.ncells = d[0] * d[1] * d[2];
+  G.sh[0] = d[0] > 1 ? 32 - __builtin_clz(d[0] - 1) : 0;
+  G.sh[1] = G.sh[0] + (d[1] > 1 ? 32 - __builtin_clz(d[1] - 1) : 0);
 }
 
 // Trial grid from the box of the finite points (lo > hi: none): about two
@@ -79,8 +84,8 @@ SGR_HD void grid_resize(GridInfo& G, double mu, float occ, float reach, int max_
 // Cell coordinates and cell faces are computed in FP64 so that rounding
 // cannot move a point across a face by more than a negligible fraction of a
 // cell, whatever the offset of the cloud from the origin.  The last cell of an
-// axis holds every point beyond it: a cloud longer than 1024 cells of the
-// wanted size keeps that many, and its last cell is as deep as the rest of it.
+// axis holds every point beyond it: with many cells, whose size is rounded to
+// FP32, the points may reach a little further.
 SGR_HD int cell_coord(float p, float lo, double inv_h, int dim) {
   const double u = floor(((double)p - (double)lo) * inv_h);
   return u < 0.0 ? 0 : (u >= (double)dim ? dim - 1 : (int)u);
@@ -99,8 +104,13 @@ SGR_HD int cell_index(const GridInfo& G, float x, float y, float z) {
   cell_of_point(G, x, y, z, c);
   return cell_index(G, c);
 }
-// At most 1024 cells per axis.
-SGR_HD int pack_cell(const int c[3]) { return c[0] | c[1] << 10 | c[2] << 20; }
+// A cell's coordinates (or a block of cells') in one word of at most 27 bits.
+SGR_HD int pack_cell(const GridInfo& G, const int c[3]) { return c[0] | c[1] << G.sh[0] | c[2] << G.sh[1]; }
+SGR_HD void unpack_cell(const GridInfo& G, int p, int c[3]) {
+  c[0] = p & ((1 << G.sh[0]) - 1);
+  c[1] = (p & ((1 << G.sh[1]) - 1)) >> G.sh[0];
+  c[2] = p >> G.sh[1];
+}
 
 SGR_HDI int min2(int a, int b) { return a < b ? a : b; }
 SGR_HDI int max2(int a, int b) { return a > b ? a : b; }
@@ -147,8 +157,17 @@ struct Place {
 // (a query 1e19 cells away): the whole row then.
 SGR_HD float row_reach(float left) { return left < 1e30f ? sqrtf(left) * 1.0001f + 2e-3f : INFINITY; }
 
-// Whole cells in a distance along a row, which has at most 1024.
-SGR_HD int cell_step(float d) { return (int)floorf(fminf(4096.f, fmaxf(-4096.f, d))); }
+// Whole cells in a distance along a row, which has at most 2^24.
+SGR_HD int cell_step(float d) { return (int)floorf(fminf(3e7f, fmaxf(-3e7f, d))); }
+
+// First of the grid's slabs of cells within R of the query's along an axis,
+// counted from the query's, and their number (of a large cube, which may lie
+// outside the grid nearly everywhere).
+SGR_HDI int slabs(int c, int dim, int R, int& n) {
+  const int first = max2(-R, -c);
+  n = min2(R, dim - 1 - c) - first + 1;
+  return first;
+}
 
 // Cells [xl, xr] of the row of cells (dy, dz) from the query's, within R cells
 // of it and within sqrt(reach2) of the query (cell units); false: none.

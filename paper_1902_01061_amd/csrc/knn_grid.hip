@@ -173,7 +173,7 @@ __device__ inline void list_block(const GridInfo& G, int b, int* blocks, Start&&
     const int row = (cz * G.dims[1] + cy) * G.dims[0];
     any = start(row + min(G.dims[0], bc[0] * BLK + BLK)) > start(row + bc[0] * BLK);
   }
-  if (__any(any) && lane == 0) blocks[1 + atomicAdd(blocks, 1)] = pack_cell(bc);
+  if (__any(any) && lane == 0) blocks[1 + atomicAdd(blocks, 1)] = pack_cell(G, bc);
 }
 // Whole grid of one cloud in one block, its cells in LDS as 16-bit halves (so
 // n <= 65 535): one launch and no global atomics where the points are few
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(SM_BT) void grid_small_kernel(GridArgs A, int2* __r
     const int c = cell_index(G, cc);
     const int pos = half_of(atomicAdd(&s_cnt[c >> 1], c & 1 ? 1 << 16 : 1), c);
     J.spts[pos] = make_float4(x, y, z, __int_as_float(i));
-    J.scell[pos] = pack_cell(cc);
+    J.scell[pos] = pack_cell(G, cc);
     J.p4[i] = make_float4(x, y, z, 0.f);
   }
 }
@@ -390,7 +390,7 @@ __global__ __launch_bounds__(LG_BT) void grid_count_kernel(GridJob J) {
     if (cell_run(c, first, len) && i < J.n) r = atomicAdd(&J.counts[c], len);
     r = __shfl(r, first, 64) + lane - first;
     if (i < J.n) {
-      J.cell_of[i] = pack_cell(cc);
+      J.cell_of[i] = pack_cell(G, cc);
       J.rank[i] = r;
     }
   }
@@ -447,9 +447,11 @@ __global__ __launch_bounds__(LG_BT) void grid_scatter_kernel(GridJob J, int poin
   const int i = blockIdx.x * LG_BT + threadIdx.x;
   if (i >= J.n) return;
   const float x = J.x[i], y = J.y[i], z = J.z[i];
+  const GridInfo G = *J.gi;
   const int pc = J.cell_of[i];
-  const int cc[3] = {pc & 1023, (pc >> 10) & 1023, pc >> 20};
-  const int pos = J.starts[cell_index(*J.gi, cc)] + J.rank[i];
+  int cc[3];
+  unpack_cell(G, pc, cc);
+  const int pos = J.starts[cell_index(G, cc)] + J.rank[i];
   J.spts[pos] = make_float4(x, y, z, __int_as_float(i));
   J.scell[pos] = pc;
   J.p4[i] = make_float4(x, y, z, 0.f);
@@ -683,7 +685,8 @@ __device__ inline int group_scan(int v, int& total) {
 // U times before it uses the first.
 //
 // RU rows per lane are looked up at once (the two loads of a row are the
-// longest wait of a search with many rows).  Returns the number of points in
+// longest wait of a search with many rows).  LARGE: of the cube only the rows
+// inside the grid are enumerated.  Returns the number of points in
 // the spans (of the group).
 constexpr int SEG_PER = 4;
 
@@ -728,12 +731,17 @@ __device__ inline int take_spans(const GridJob& J, int2 a, int2 b, const float4&
   return points;
 }
 
-template <int GL, int U, int RU, class Sink>
+template <int GL, int U, int RU, bool LARGE, class Sink>
 __device__ inline int visit(const GridJob& J, const GridInfo& G, const Place& at, const float4& q, int R, int inner,
                             Sink& L, int2* s_seg) {
   const int l = threadIdx.x % GL;
-  const int side = 2 * R + 1, rows = side * side;
-  const float inv_side = 1.f / (float)side;
+  int ny = 2 * R + 1, nz = ny, y0 = -R, z0 = -R;
+  if constexpr (LARGE) {
+    y0 = slabs(at.c[1], G.dims[1], R, ny);
+    z0 = slabs(at.c[2], G.dims[2], R, nz);
+  }
+  const int rows = ny * nz;
+  const float inv_ny = 1.f / (float)ny;
   const float inv_h = (float)G.inv_h;
   int seen = 0;
   for (int r0 = 0; r0 < rows; r0 += GL * RU) {
@@ -743,12 +751,12 @@ __device__ inline int visit(const GridJob& J, const GridInfo& G, const Place& at
     for (int v = 0; v < RU; ++v) {
       a[v] = b[v] = make_int2(0, 0);
       const int i = r0 + v * GL + l;
-      int dz = (int)(((float)i + 0.5f) * inv_side);
-      int dy = i - dz * side;
-      if (dy < 0) dy += side, --dz;
-      if (dy >= side) dy -= side, ++dz;
-      dz -= R;
-      dy -= R;
+      int dz = (int)(((float)i + 0.5f) * inv_ny);
+      int dy = i - dz * ny;
+      if (dy < 0) dy += ny, --dz;
+      if (dy >= ny) dy -= ny, ++dz;
+      dz += z0;
+      dy += y0;
       int xl, xr;
       if (i < rows && row_cells(G, at, R, dy, dz, reach2, xl, xr)) {
         const int cx = at.c[0];
@@ -776,11 +784,13 @@ __device__ inline void visit_blocks(const GridJob& J, const GridInfo& G, const P
   const int lane = threadIdx.x & 63;
   const float inv_h2 = (float)G.inv_h * (float)G.inv_h * (1.f + 2e-5f);
   auto gap_of = [&](int pb) {
-    const int bc[3] = {pb & 1023, (pb >> 10) & 1023, pb >> 20};
+    int bc[3];
+    unpack_cell(G, pb, bc);
     return block_gap(at, bc);
   };
   auto visit_block = [&](int pb) {
-    const int bc[3] = {pb & 1023, (pb >> 10) & 1023, pb >> 20};
+    int bc[3];
+    unpack_cell(G, pb, bc);
     int2 a = make_int2(0, 0);
     int cy, cz, xl, xr;
     if (block_row_cells(G, at, bc, lane, key_of(L.bound) * inv_h2, cy, cz, xl, xr)) {
@@ -827,7 +837,7 @@ __device__ inline void visit_reach(const GridJob& J, const GridInfo& G, const Pl
   for (int inner = -1, R = 3; R <= RMAX; R = 2 * R + 2) {
     R = min(R, cells_reached(G, at, L.bound, rmax));
     if (R <= inner) return;
-    visit<64, U, KF_ROWS>(J, G, at, q, R, inner, L, s_seg);
+    visit<64, U, KF_ROWS, false>(J, G, at, q, R, inner, L, s_seg);
     L.lower();
     inner = R;
   }
@@ -854,6 +864,15 @@ __device__ inline void write_list(List& L, int k, int32_t* __restrict__ out) {
   for (int e = L.cnt + (int)(threadIdx.x % GL); e < k; e += GL) out[e] = -1;
 }
 
+// The grid of a block's job, its whole numbers in scalar registers (loaded through
+// a pointer from a table they are not known to be the same in every lane).
+__device__ inline GridInfo block_grid(const GridInfo* gi) {
+  GridInfo G = *gi;
+  for (int a = 0; a < 3; ++a) G.dims[a] = __builtin_amdgcn_readfirstlane(G.dims[a]);
+  for (int a = 0; a < 2; ++a) G.sh[a] = __builtin_amdgcn_readfirstlane(G.sh[a]);
+  return G;
+}
+
 // Lists of the queries knn_kernel leaves, counts first: near[0].x of the
 // queries with k points in their 27 cells, near[0].y of the others, which are
 // listed from the end of the same array (size entries).
@@ -871,7 +890,7 @@ __global__ __launch_bounds__(KN_BT, 4) void knn_kernel(GridArgs A, int k, int ro
   __shared__ int2 s_seg[KN_Q][KN_G * SEG_PER];
   int block, cloud;
   const GridJob J = job_of(A, block, &cloud);
-  const GridInfo G = *J.gi;
+  const GridInfo G = block_grid(J.gi);
   const int grp = threadIdx.x / KN_G, l = threadIdx.x % KN_G;
   for (int round = 0; round < rounds; ++round) {
     const int t = (block * rounds + round) * KN_Q + grp;
@@ -884,8 +903,8 @@ __global__ __launch_bounds__(KN_BT, 4) void knn_kernel(GridArgs A, int k, int ro
       for (int e = l; e < k; e += KN_G) out[e] = -1;
       continue;
     }
-    const int pc = J.scell[t];
-    Place at{{pc & 1023, (pc >> 10) & 1023, pc >> 20}, {}};
+    Place at;
+    unpack_cell(G, J.scell[t], at.c);
     at.set(G, q);
     const int own = cell_index(G, at.c);
     const bool dense = J.starts[own + 1] - J.starts[own] >= k;
@@ -893,11 +912,11 @@ __global__ __launch_bounds__(KN_BT, 4) void knn_kernel(GridArgs A, int k, int ro
     // the 27 cells, for keys below the edge; a dense query's own cell first,
     // for any keys, whose k-th limits the rest
     QueryList L{s_key + grp * KN_STRIDE, 0, k, dense ? KEY_INF : edge};
-    int seen = visit<KN_G, KN_U, 1>(J, G, at, q, dense ? 0 : 1, -1, L, s_seg[grp]);
+    int seen = visit<KN_G, KN_U, 1, false>(J, G, at, q, dense ? 0 : 1, -1, L, s_seg[grp]);
     if (dense) {
       L.trim();
       L.bound = min(L.bound, edge);
-      seen += visit<KN_G, KN_U, 1>(J, G, at, q, 1, 0, L, s_seg[grp]);
+      seen += visit<KN_G, KN_U, 1, false>(J, G, at, q, 1, 0, L, s_seg[grp]);
     }
     // keys of a dense query's own cell may lie beyond the edge
     bool found = edge == KEY_INF || (dense ? L.count_under(edge) : L.cnt) >= k;
@@ -940,8 +959,8 @@ __global__ __launch_bounds__(KN_BT) void knn_far_kernel(GridArgs A, int k, const
     const GridJob J = job_at(A, ct.x);
     const GridInfo G = *J.gi;
     const float4 q = J.spts[ct.y];
-    const int pc = J.scell[ct.y];
-    Place at{{pc & 1023, (pc >> 10) & 1023, pc >> 20}, {}};
+    Place at;
+    unpack_cell(G, J.scell[ct.y], at.c);
     at.set(G, q);
     KeyList<64, KF_CAP> L{sh.w.key + wave * KF_CAP, 0, k, KEY_INF};
     {
@@ -962,8 +981,8 @@ __global__ __launch_bounds__(KN_BT) void knn_far_kernel(GridArgs A, int k, const
     const GridJob J = job_at(A, ct.x);
     const GridInfo G = *J.gi;
     const float4 q = J.spts[ct.y];
-    const int pc = J.scell[ct.y];
-    Place at{{pc & 1023, (pc >> 10) & 1023, pc >> 20}, {}};
+    Place at;
+    unpack_cell(G, J.scell[ct.y], at.c);
     at.set(G, q);
     const int rmax = max(G.dims[0], max(G.dims[1], G.dims[2]));
     // fewer than k keys below the cube's bound: all keys below twice that
@@ -973,7 +992,7 @@ __global__ __launch_bounds__(KN_BT) void knn_far_kernel(GridArgs A, int k, const
       bool last;
       L.cnt = 0;
       const int R = widen(G, at, reach2, rmax, L.bound, last);
-      visit<KN_G, KN_U, 2>(J, G, at, q, R, -1, L, sh.g.seg[grp]);
+      visit<KN_G, KN_U, 2, true>(J, G, at, q, R, -1, L, sh.g.seg[grp]);
       if (L.cnt >= k || last) break;
     }
     write_list<KN_G>(L, k, J.nbr + (int64_t)__float_as_int(q.w) * k);
@@ -1319,7 +1338,7 @@ __global__ __launch_bounds__(KN_BT) void nearest_kernel(GridJob J, const float* 
     // the query's own cell first: in a dense cloud its best key leaves little
     // of the others
     for (int inner = -1, R = 0;;) {
-      visit<KN_G, KN_U, 1>(J, G, at, q, R, inner, N, s_seg[grp]);
+      visit<KN_G, KN_U, 1, false>(J, G, at, q, R, inner, N, s_seg[grp]);
       const int want = cells_reached(G, at, N.bound, 1 << 20);
       found = want <= R || cube_bound(G, at, R) == KEY_INF;
       if (found || (R > 0 && want > NN_RMAX)) break;
@@ -1364,7 +1383,7 @@ __global__ __launch_bounds__(KN_BT) void nearest_far_kernel(GridJob J, const flo
     N.add(N.key_at(J.spts[min(first + lane, J.n - 1)], q), true);
     N.settle();
     if (cells_reached(G, at, N.bound, 1 << 20) <= NF_RMAX)
-      visit<64, KF_U, KF_ROWS>(J, G, at, q, NF_RMAX, -1, N, s_seg[wave]);
+      visit<64, KF_U, KF_ROWS, false>(J, G, at, q, NF_RMAX, -1, N, s_seg[wave]);
     else
       visit_blocks<KF_U>(J, G, at, q, N, s_seg[wave]);
     if (lane == 0) {

@@ -48,7 +48,7 @@ struct Grid {
       cell_of_point(G, p[3 * i], p[3 * i + 1], p[3 * i + 2], c);
       const int j = at[cell_index(G, c)]++;
       pts[j] = make_float4(p[3 * i], p[3 * i + 1], p[3 * i + 2], __builtin_bit_cast(float, i));
-      cell[j] = pack_cell(c);
+      cell[j] = pack_cell(G, c);
     }
     const int b0 = (G.dims[0] + BLK - 1) / BLK, b1 = (G.dims[1] + BLK - 1) / BLK;
     for (int b = 0; b < block_count(G); ++b) {
@@ -59,7 +59,7 @@ struct Grid {
           const int row = (z * G.dims[1] + y) * G.dims[0];
           any |= starts[row + std::min(G.dims[0], bc[0] * BLK + BLK)] > starts[row + bc[0] * BLK];
         }
-      if (any) blocks.push_back(pack_cell(bc));
+      if (any) blocks.push_back(pack_cell(G, bc));
     }
   }
 };
@@ -94,8 +94,10 @@ struct Search {
   }
   void visit(int R, int inner) {
     const float inv_h = (float)g.G.inv_h;
-    for (int dz = -R; dz <= R; ++dz)
-      for (int dy = -R; dy <= R; ++dy) {
+    int ny, nz;
+    const int y0 = slabs(at.c[1], g.G.dims[1], R, ny), z0 = slabs(at.c[2], g.G.dims[2], R, nz);
+    for (int dz = z0; dz < z0 + nz; ++dz)
+      for (int dy = y0; dy < y0 + ny; ++dy) {
         int xl, xr;
         if (!row_cells(g.G, at, R, dy, dz, key_of(bound) * (inv_h * inv_h) * (1.f + 2e-5f), xl, xr)) continue;
         const int cx = at.c[0];
@@ -112,13 +114,15 @@ struct Search {
     const float inv_h2 = (float)g.G.inv_h * (float)g.G.inv_h * (1.f + 2e-5f);
     std::vector<std::pair<float, int>> order;
     for (int pb : g.blocks) {
-      const int bc[3] = {pb & 1023, (pb >> 10) & 1023, pb >> 20};
+      int bc[3];
+      unpack_cell(g.G, pb, bc);
       order.push_back({block_gap(at, bc), pb});
     }
     std::sort(order.begin(), order.end());
     for (auto& [g2, pb] : order) {
       if (g2 > key_of(bound) * inv_h2) continue;
-      const int bc[3] = {pb & 1023, (pb >> 10) & 1023, pb >> 20};
+      int bc[3];
+      unpack_cell(g.G, pb, bc);
       for (int r = 0; r < BLK * BLK; ++r) {
         int cy, cz, xl, xr;
         if (!block_row_cells(g.G, at, bc, r, key_of(bound) * inv_h2, cy, cz, xl, xr)) continue;
@@ -133,8 +137,8 @@ static int rmax_of(const GridInfo& G) { return std::max(G.dims[0], std::max(G.di
 
 // knn_kernel and knn_far_kernel for the point at place t of the sorted array.
 static std::vector<uint64_t> knn(const Grid& g, int t, int k) {
-  const int pc = g.cell[t];
-  Search s{g, g.pts[t], {{pc & 1023, (pc >> 10) & 1023, pc >> 20}, {}}, k, 0, {}};
+  Search s{g, g.pts[t], {}, k, 0, {}};
+  unpack_cell(g.G, g.cell[t], s.at.c);
   s.at.set(g.G, s.q);
   const int own = cell_index(g.G, s.at.c);
   const bool dense = g.starts[own + 1] - g.starts[own] >= k;

@@ -1,7 +1,7 @@
-"""Neighbour lists, nearest points and residuals of clouds longer than the
-grid's 1 024 cells along an axis, whose last cell there holds everything beyond:
-a stray point on each of the six sides, and a pipe and a strip along each axis,
-exactly as brute force gives them (FP32 keys, ties by index).  Also clouds so
+"""Neighbour lists, nearest points and residuals of clouds whose grid has nearly
+all of its cells along one axis, or could: a stray point on each of the six
+sides, a pipe, a strip and a thin long slab along each axis, exactly as brute
+force gives them (FP32 keys, ties by index).  Also clouds so
 small that the squares of their cells underflow."""
 import numpy as np
 import pytest
@@ -38,12 +38,14 @@ def _cloud(kind, axis, side, n):
     if kind == "pipe":                 # 1 000 long, radius 0.5
         f = rng.uniform(0, 2 * np.pi, n)
         P = np.stack([rng.uniform(0, 1000, n), 0.5 * np.cos(f), 0.5 * np.sin(f)], 1)
+    elif kind == "slab":               # 8 x 0.008 x 250, normal: dense in the middle
+        P = rng.normal(size=(n, 3)) * [30, 1, 1e-3]
     else:                              # a strip 300 x 1
         P = np.stack([rng.uniform(0, 300, n), rng.uniform(0, 1, n), rng.normal(size=n) * 1e-3], 1)
     return np.roll(P, axis, axis=1).astype(np.float32)
 
 
-LONG = [("stray point", a, s) for a in range(3) for s in (1, -1)] + [(k, a, 1) for k in ("pipe", "strip") for a in range(3)]
+LONG = [("stray point", a, s) for a in range(3) for s in (1, -1)] + [(k, a, 1) for k in ("pipe", "strip", "slab") for a in range(3)]
 
 
 @pytest.mark.parametrize("kind,axis,side", LONG)

@@ -80,8 +80,7 @@ def _cloud(kind, axis, side):
     return _long(kind, 6000, axis, 2)
 
 
-# An axis of more than 1 024 cells of the wanted size keeps 1 024: its last cell
-# holds everything beyond.
+# Grids with nearly all of their cells along one axis.
 LONG = [("stray point", a, s) for a in range(3) for s in (1, -1)] + \
        [(kind, a, 1) for kind in ("pipe", "strip") for a in range(3)]
 
