@@ -97,6 +97,18 @@ __device__ inline GridJob job_at(const GridArgs& A, int c) {
   return J;
 }
 
+// The grid of a block's job in scalar registers (loaded through a pointer it is
+// not known to be the same in every lane).
+__device__ inline GridInfo block_grid(const GridInfo* gi) {
+  static_assert(sizeof(GridInfo) % 4 == 0, "whole words");
+  union {
+    GridInfo G;
+    int w[sizeof(GridInfo) / 4];
+  } u{*gi};
+  for (int e = 0; e < (int)(sizeof(GridInfo) / 4); ++e) u.w[e] = __builtin_amdgcn_readfirstlane(u.w[e]);
+  return u.G;
+}
+
 // ------------------------------------------------------------------- grid
 // Wanted occupancy for k neighbours.  Counted over surfaces of even
 // density, a query of occupancy 0.45 k finds twice k points within the distance its 27 cells
@@ -560,6 +572,7 @@ struct KeyList {
       if (l + u * GL < cnt) f(mine[u], rk[u]);
   }
 
+  static constexpr int LONG = 0;  // points of a span that is read as a whole (0: none)
   static __device__ uint64_t key_at(const float4& P, const float4& q) { return point_key(P, q); }
 
   __device__ void trim() {
@@ -690,17 +703,52 @@ __device__ inline int group_scan(int v, int& total) {
 // the spans (of the group).
 constexpr int SEG_PER = 4;
 
+// The points of the lanes' long spans a, one span after the other, which are
+// emptied: in a crowded cell (far outliers make the cells large) a segment of 8
+// at a time costs more than its points.  30 000 points in one cell, nearest to
+// 30 000 queries: 1.73 ms by segments, 0.6 so (1.05 by a search over all).
+template <int GL, class Sink>
+__device__ inline bool take_long(const GridJob& J, int2& a, const float4& q, Sink& L) {
+  constexpr int U = Sink::LONG / GL;
+  const int lane = threadIdx.x & 63, l = threadIdx.x % GL;
+  bool any = false;
+  for (;;) {
+    const unsigned m = (unsigned)(__ballot(a.y - a.x >= Sink::LONG) >> (lane & 48)) & 0xffffu;
+    static_assert(GL == 16, "a group's bits of the wave's");
+    if (m == 0) return any;
+    any = true;
+    const int src = (lane & 48) + __builtin_ctz(m);
+    const int x = __shfl(a.x, src, 64), y = __shfl(a.y, src, 64);
+    for (int j = x; j < y; j += GL * U) {
+      float4 P[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) P[u] = J.spts[min(j + u * GL + l, y - 1)];
+#pragma unroll
+      for (int u = 0; u < U; ++u) L.add(Sink::key_at(P[u], q), true);  // (the last point again beyond the span)
+    }
+    if (lane == src) a = make_int2(0, 0);
+  }
+}
+
 // The points of every lane's spans a and b; returns how many the lane's were.
 template <int GL, int U, class Sink>
 __device__ inline int take_spans(const GridJob& J, int2 a, int2 b, const float4& q, Sink& L, int2* s_seg) {
   const int l = threadIdx.x % GL;
   const int points = a.y - a.x + b.y - b.x;
+  bool any = false;
+  if constexpr (Sink::LONG > 0) {
+    if (__any(points >= Sink::LONG)) {
+      any = take_long<GL>(J, a, q, L);
+      any |= take_long<GL>(J, b, q, L);
+    }
+  }
   int todo = ((a.y - a.x + 7) >> 3) + ((b.y - b.x + 7) >> 3);
   for (;;) {
     const int take = min(todo, SEG_PER);
     int total;
     const int at0 = group_scan<GL>(take, total);
     if (total == 0) break;
+    any = true;
     wave_sync();
     for (int u = 0; u < take; ++u) {
       if (a.x >= a.y) {
@@ -725,9 +773,10 @@ __device__ inline int take_spans(const GridJob& J, int2 a, int2 b, const float4&
       L.template room<U>();
 #pragma unroll
       for (int u = 0; u < U; ++u) L.add(Sink::key_at(P[u], q), ok[u]);
-      L.settle();
+      if constexpr (Sink::LONG == 0) L.settle();
     }
   }
+  if (Sink::LONG > 0 && any) L.settle();
   return points;
 }
 
@@ -862,15 +911,6 @@ __device__ inline void write_list(List& L, int k, int32_t* __restrict__ out) {
     if (r < k) out[r] = (int32_t)(uint32_t)w;
   });
   for (int e = L.cnt + (int)(threadIdx.x % GL); e < k; e += GL) out[e] = -1;
-}
-
-// The grid of a block's job, its whole numbers in scalar registers (loaded through
-// a pointer from a table they are not known to be the same in every lane).
-__device__ inline GridInfo block_grid(const GridInfo* gi) {
-  GridInfo G = *gi;
-  for (int a = 0; a < 3; ++a) G.dims[a] = __builtin_amdgcn_readfirstlane(G.dims[a]);
-  for (int a = 0; a < 2; ++a) G.sh[a] = __builtin_amdgcn_readfirstlane(G.sh[a]);
-  return G;
 }
 
 // Lists of the queries knn_kernel leaves, counts first: near[0].x of the
@@ -1281,6 +1321,7 @@ template <int GL, bool FUSED>
 struct Nearest {
   uint64_t best, bound;
 
+  static constexpr int LONG = GL == 16 ? 32 : 0;  // (the same point twice does no harm)
   static __device__ uint64_t key_at(const float4& P, const float4& q) {
     return FUSED ? point_key_fused(P, q) : point_key(P, q);
   }
@@ -1319,12 +1360,12 @@ constexpr int NN_RMAX = 3;  // cells from its own a group searches for a query b
 // latency of the dependent loads (start of a row, its points): 115 us for
 // 250 000 queries near 307 200 points, where a lane per query took 872 us.
 template <bool FUSED>
-__global__ __launch_bounds__(KN_BT) void nearest_kernel(GridJob J, const float* __restrict__ qx,
+__global__ __launch_bounds__(KN_BT, 7) void nearest_kernel(GridJob J, const float* __restrict__ qx,
                                                         const float* __restrict__ qy, const float* __restrict__ qz,
                                                         int nq, float max_key, int32_t* __restrict__ nn,
                                                         float* __restrict__ key, int2* __restrict__ far) {
   __shared__ int2 s_seg[KN_Q][KN_G * SEG_PER];
-  const GridInfo G = *J.gi;
+  const GridInfo G = block_grid(J.gi);
   const int grp = threadIdx.x / KN_G, l = threadIdx.x % KN_G;
   const int t = blockIdx.x * KN_Q + grp;
   if (t >= nq) return;  // no block barrier below; a group leaves as a whole
@@ -1370,7 +1411,7 @@ __global__ __launch_bounds__(KN_BT) void nearest_far_kernel(GridJob J, const flo
   __shared__ int2 s_seg[KN_BT / 64][64 * SEG_PER];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int total = far[0].x;
-  const GridInfo G = *J.gi;
+  const GridInfo G = block_grid(J.gi);
   for (int f = (blockIdx.x * KN_BT + threadIdx.x) >> 6; f < total; f += (gridDim.x * KN_BT) >> 6) {
     const int t = far[1 + f].y;
     const float4 q = make_float4(qx[t], qy[t], qz[t], 0.f);

@@ -72,7 +72,7 @@ def test_nearest_points_and_residual(sg, ctx, kind, axis, side, n):
     want, keys = _nearest(Y, X)
     for tau in (0.05, 1e18):
         _, nn, key = ctx.change_detect(sg.Cloud(Y), zero[0], sg.Cloud(X), zero[1], sg.pose_identity(), tau)
-        hit = keys <= np.float32(tau) * np.float32(tau)
+        hit = keys <= np.float32(tau * tau)
         assert np.array_equal(nn.cpu().numpy(), np.where(hit, want, -1))
         assert np.array_equal(key.cpu().numpy()[hit], keys[hit])
     nn, _ = _nearest(Y, X, fused=True)
@@ -98,3 +98,20 @@ def test_nearest_points_of_queries_far_away(sg, ctx, e):
     _, nn, _ = ctx.change_detect(sg.Cloud(Y), torch.zeros(100, device="cuda"), sg.Cloud(X),
                                  torch.zeros(3000, device="cuda"), sg.pose_identity(), 1.5e19)
     assert np.array_equal(nn.cpu().numpy(), _nearest(Y, X)[0])
+
+
+@pytest.mark.parametrize("crowd", [1, 8, 31, 32, 33, 63, 64, 65, 97, 1500])
+def test_nearest_points_in_a_crowded_cell(sg, ctx, crowd):
+    """Cells around the number of points from which a row of them is read as a
+    whole, exact ties among them."""
+    rng = np.random.default_rng(crowd)
+    X = np.concatenate([np.round(rng.normal(size=(crowd, 3)) * 3) * 1e-3, [[100, 0, 0], [0, -80, 0], [0, 0, 60]],
+                        rng.normal(size=(crowd // 2, 3)) * 1e-3 + [0, 0, 60]])
+    X = X[rng.permutation(len(X))].astype(np.float32)
+    Y = np.concatenate([X, np.round(rng.normal(size=(200, 3)) * 8) * 5e-4, rng.normal(size=(50, 3)) * 50,
+                        rng.normal(size=(50, 3)) * 1e-3 + [0, 0, 60]]).astype(np.float32)
+    want, keys = _nearest(Y, X)
+    for tau in (0.002, 1e18):
+        _, nn, _ = ctx.change_detect(sg.Cloud(Y), torch.zeros(len(Y), device="cuda"), sg.Cloud(X),
+                                     torch.zeros(len(X), device="cuda"), sg.pose_identity(), tau)
+        assert np.array_equal(nn.cpu().numpy(), np.where(keys <= np.float32(tau * tau), want, -1))
