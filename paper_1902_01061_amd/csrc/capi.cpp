@@ -644,7 +644,7 @@ struct SingleWs {
   double* ps_S;
   int ps_chunks;
   int* sync;         // the loop's ticket (64 ints), then its exchange words
-  double* pose0;     // pose before the first loop
+  double* pose0;     // pose before the first loop, and (a pyramid) before each level's
   int loop_ppt, loop_nb;  // the one-launch loop's shape (0 blocks: not used)
   ForceLoop floop;        // that of the all-pairs force
   int* perm;
@@ -693,7 +693,7 @@ int carve_single(sgr_ctx* ctx, int M, int N, const sgr_params* prm, int kmax, Si
     w.ps_part = pinv ? c.take<double>((size_t)w.ps_chunks * M * 5) : nullptr;
     w.ps_S = pinv ? c.take<double>((size_t)M * 5) : nullptr;
     w.sync = loops ? c.take<int>(64 + 2 * loop_words(std::max(w.loop_nb, w.floop.blocks))) : nullptr;
-    w.pose0 = loops ? c.take<double>(13) : nullptr;
+    w.pose0 = loops ? c.take<double>(26) : nullptr;
     if (!pass)
       if (int e = ensure_ws(ctx, c.off)) return e;
   }
@@ -731,8 +731,8 @@ int run_loop(sgr_ctx* ctx, LoopReg g, int ppt, int* sync, int t0, int t1, hipStr
 // G follows eq. 12 over prm->E.  The energy U is accumulated only where it is
 // read, in the per-iteration stats; with stats, the last of the E
 // iterations of a mixed-precision registration uses the FP32 kernel so that
-// its energy is the FP32 one.  pose0 (nullable) receives the pose as it was if
-// the iterations run in one launch.
+// its energy is the FP32 one.  pose0 receives the pose as it was if the
+// iterations run in one launch.
 int run_single_loop(sgr_ctx* ctx, GraphCache& gc, const sgr_cloud* tmpl, const sgr_cloud* ref,
                     const sgr_params* prm, const SingleWs& w, sgr_pose* inout, double* stats, int t0, int t1,
                     double* pose0, hipStream_t st) {
@@ -1364,7 +1364,7 @@ int sgr_register_pyramid(sgr_ctx* ctx, const sgr_cloud* tmpl, const sgr_cloud* r
       PrepParams P = prep_of(prm);
       P.sigma_scale = v.sigma_scale;
       if (int e = setup_single(tmpl, ref, P, stats != nullptr, w, st)) return e;
-      if (int e = run_single_loop(ctx, ctx->gcp[l], tmpl, ref, prm, w, inout, stats, t0, t0 + v.iters, nullptr, st)) return e;
+      if (int e = run_single_loop(ctx, ctx->gcp[l], tmpl, ref, prm, w, inout, stats, t0, t0 + v.iters, w.pose0 + 13, st)) return e;
       HIPCHK(hipMemcpyAsync(&status[l], &w.dv->status, sizeof(int32_t), hipMemcpyDeviceToHost, st));
       t0 += v.iters;
     }

@@ -334,7 +334,7 @@ struct LoopReg {
   const float2* tmx;
   const double* S;
   double* pose;                // in place
-  double* pose0;               // receives the pose as it was, or nullptr
+  double* pose0;               // receives the pose as it was
   Derived* dv;
   double* stats;               // [E][STATS_STRIDE] or nullptr
   double* energy;              // energy of the last iteration, or nullptr

@@ -359,7 +359,7 @@ __device__ inline void loop_run(const LoopReg& g, int sub, int t0, int t1, int s
     update_load(g.dv, g.pose, t0, 1.0, u);
     s_u = u;
     share_pose();
-    if (sub == 0 && g.pose0)
+    if (sub == 0)
       for (int e = 0; e < 13; ++e) g.pose0[e] = u.P[e];
   }
   if (tid == 64) {
