@@ -205,8 +205,10 @@ int sgr_step_static(sgr_ctx* ctx, const sgr_cloud* tmpl, const float* a_t, const
  * place: the shape-weighted force (eqs. 3, 5, 10, 11), translation (eq.
  * 5.5), rotation (eq. 6), scale (eq. 8), update (eq. 9), G from eq. 12.  stats (nullable, device float64 [E][32]): per iteration G_t,
  * F[3], K[9], U, the pose after the update (13), the scale factor c and the
- * status word.  Synchronises the stream at the end to read the device
- * status word; SGR_ENUMERIC if an update went non-finite or rank deficient
+ * status word.  With stats the all-pairs force at p = 1 adds its FP32 terms in
+ * other groups than without (about 1e-10 in the pose after a few iterations);
+ * flags bit 3 and the other FP32 laws give the same bits either way.  Synchronises
+ * the stream at the end to read the device status word; SGR_ENUMERIC if an update went non-finite or rank deficient
  * (the pose is then frozen at the last good value). */
 int sgr_register(sgr_ctx* ctx, const sgr_cloud* tmpl, const sgr_cloud* ref, const sgr_params* prm,
                  sgr_pose* inout, double* stats, sgr_stream_t stream);

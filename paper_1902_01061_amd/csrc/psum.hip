@@ -319,8 +319,9 @@ __global__ __launch_bounds__(PS_BT) void pinv_batch_kernel(const RegDesc* __rest
 // LP_MAX_BLOCKS of a registration wait for each other, a quarter of the
 // chip's CUs.  Should they still not be resident together (a stream
 // confined to a few CUs), the poll gives up after `spins` tries, every wave
-// ends, ST_STALLED is set with the pose untouched, and the caller runs the
-// per-iteration kernels instead.
+// ends, ST_STALLED is set, and the caller runs the per-iteration kernels
+// instead, from the pose saved in pose0 (a block that has all partials of the
+// last iteration may have stored its result).
 constexpr int LP_BT = 512;
 constexpr int LP_WAVES = LP_BT / 64;
 constexpr int LP_WORDS = 26;  // two tagged words per wrench component
