@@ -1400,10 +1400,12 @@ __global__ __launch_bounds__(KN_BT, 7) void nearest_kernel(GridJob J, const floa
 // The queries nearest_kernel left, one wave each: 64 points around the place
 // in the sorted array where the query's cell begins give a first bound for a
 // search of the cells within reach or, if these are many, by blocks of cells.
+// Five waves per SIMD: with four, 3.45 instead of 3.31 ms for 250 000 queries off
+// a surface of 307 200 points.
 constexpr int NF_RMAX = 6;
 
 template <bool FUSED>
-__global__ __launch_bounds__(KN_BT) void nearest_far_kernel(GridJob J, const float* __restrict__ qx,
+__global__ __launch_bounds__(KN_BT, 5) void nearest_far_kernel(GridJob J, const float* __restrict__ qx,
                                                             const float* __restrict__ qy,
                                                             const float* __restrict__ qz, float max_key,
                                                             int32_t* __restrict__ nn, float* __restrict__ key,
@@ -1424,7 +1426,7 @@ __global__ __launch_bounds__(KN_BT) void nearest_far_kernel(GridJob J, const flo
     N.add(N.key_at(J.spts[min(first + lane, J.n - 1)], q), true);
     N.settle();
     if (cells_reached(G, at, N.bound, 1 << 20) <= NF_RMAX)
-      visit<64, KF_U, KF_ROWS, false>(J, G, at, q, NF_RMAX, -1, N, s_seg[wave]);
+      visit<64, KF_U, 1, false>(J, G, at, q, NF_RMAX, -1, N, s_seg[wave]);
     else
       visit_blocks<KF_U>(J, G, at, q, N, s_seg[wave]);
     if (lane == 0) {
